@@ -665,6 +665,36 @@ __global__ __launch_bounds__(kBlock) void k_sq_partials(const float* __restrict_
     if (h == 0) part[blk] = r;
 }
 
+// Lane t's share of the partials' tree: partials t, t+256, ... added in that order from +0.  One
+// workgroup does this while the GPU waits, so what counts is the number of round trips to memory:
+// 32 loads are issued ahead of their adds while that many are left (without the clamp of the
+// last round: it kept the loads from going out together), then 8.
+__device__ __forceinline__ float lane_partials(const float* __restrict__ part, uint64_t nblk)
+{
+    float s = 0.0f;
+    uint64_t k0 = threadIdx.x;
+    for (uint64_t left = nblk; left >= 32 * kBlock; left -= 32 * kBlock, k0 += 32 * kBlock) {
+        float v[32];
+#pragma unroll
+        for (int j = 0; j < 32; ++j) v[j] = part[k0 + j * kBlock];
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < 32; ++j) s = s + v[j];
+    }
+    for (; k0 < nblk; k0 += 8 * kBlock) {
+        float v[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const uint64_t k = k0 + (uint64_t)j * kBlock;
+            v[j] = part[k < nblk ? k : nblk - 1];
+        }
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+            if (k0 + (uint64_t)j * kBlock < nblk) s = s + v[j];
+    }
+    return s;
+}
+
 __global__ __launch_bounds__(kBlock) void k_sq_final(const float* __restrict__ part, uint64_t nblk,
                                                      float* __restrict__ out)
 {
@@ -1012,66 +1042,103 @@ hipError_t launch_dropout_mask(hipStream_t s, uint64_t* state, uint8_t* mask, ui
 // stride halving over 256 lanes; block partials combined the same way, lane t first adding
 // partials t, t+256, ...).  mean = T(y) / M, var = T((y - mean)^2) / M.
 //
-// First stage: one WAVE per block of one channel; hardware lane h plays tree lanes h, h+64,
-// h+128, h+192 (strides 128 and 64 are adds between its own registers, 32..1 wave shuffles).
-// Second stage: one workgroup per channel with an LDS stage.  No atomics.
+// One WAVE per block of one channel; hardware lane h plays tree lanes h, h+64, h+128, h+192
+// (strides 128 and 64 are adds between its own registers, 32..1 wave shuffles).  No atomics.
 // ---------------------------------------------------------------------------
-template <bool SQDEV>
-__global__ __launch_bounds__(kBlock) void k_bn_partials(const float* __restrict__ x, uint32_t C, uint32_t HW,
-                                                        uint32_t M, uint32_t nblk,
-                                                        const float* __restrict__ mean,
-                                                        float* __restrict__ part)
+struct BnGeom {
+    uint32_t C, HW, M, nblk;
+    uint64_t magic;                                     // m / HW = (m * magic) >> shift for m < 2^31
+    uint32_t shift;
+    uint32_t step_img, step_pos;                        // 256 = step_img * HW + step_pos
+};
+
+// How four consecutive terms lie in memory.
+constexpr uint32_t kBnLongHW = 1024;
+enum { kBnVector = 0, kBnLong = 1, kBnWrap = 2, kBnAny = 3 };
+// kBnVector: HW is a multiple of 4, so they are one 16-byte vector of one image.
+// kBnLong:   any HW >= kBnLongHW: one vector too, except where an image (or the channel) ends
+//            inside the wave's 256 terms; there four single loads.
+// kBnWrap:   4 <= HW, any remainder: the image can end once inside them; four single loads
+//            (neighbouring lanes share the lines, so the L1 serves three of the four).
+// kBnAny:    HW < 4.
+
+// The 16 vectors of lane h of block `blk`, [tree lane h + 64 j][q].  Where a term lies beyond M
+// some value of the channel is loaded instead; bn_block_sum drops it.
+// A lane's vectors are 256 terms apart, so (image, position) is divided out once and then
+// stepped: a division per vector was most of the kernel's instructions.  OFF is the type of a
+// byte offset into x (32 bits where x is small enough: one scalar base, one register per lane).
+template <int MODE, typename OFF>
+__device__ __forceinline__ void bn_load(const float* __restrict__ x, const BnGeom& g, uint32_t ch, uint32_t blk,
+                                        uint32_t h, f4 (&t)[4][4])
 {
-    const uint32_t h = threadIdx.x & 63;
-    const uint32_t blk = blockIdx.x * 4 + (threadIdx.x >> 6);
-    const uint32_t ch = blockIdx.y;
-    if (blk >= nblk) return;                            // whole wave leaves together
-    const float center = SQDEV ? mean[ch] : 0.0f;
-    const uint32_t base = blk * 4096;
-    f4 t[4][4];                                         // [tree lane h + 64 j][q]: four consecutive terms
+    const char* xb = reinterpret_cast<const char*>(x);
+    const OFF image = (OFF)4 * g.C * g.HW;              // bytes between images
+    const OFF wrap = image - (OFF)4 * g.HW;             // what an image's end adds to the offset
+    const OFF first = (OFF)4 * ch * g.HW;               // the channel's first value: always readable
+    const OFF step = image * g.step_img + 4u * g.step_pos;
+    uint32_t m = blk * 4096u + 4u * h;
+    uint32_t img = (uint32_t)(((uint64_t)m * g.magic) >> g.shift);
+    uint32_t pos = m - img * g.HW;
+    OFF off = first + image * img + (OFF)4 * pos;
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
+    for (int i = 0; i < 16; ++i) {
+        f4& e = t[i & 3][i >> 2];
+        auto singles = [&] {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const uint32_t m0 = base + 4u * (256 * q + 64 * j + h);
-            const uint32_t img = m0 / HW, pos = m0 - img * HW;
-            f4 e;
-            if (m0 + 3 < M && pos + 3 < HW) {           // four terms of one image, all present
-                // plain (cacheable) load: the second pass reads the same values again
-                e = *reinterpret_cast<const f4_dword_aligned*>(x + ((uint64_t)img * C + ch) * HW + pos);
-                if constexpr (SQDEV) {
-                    const f4 d = e - center;
-                    e = d * d;
+            for (int c = 0; c < 4; ++c) {
+                OFF o;
+                if constexpr (MODE != kBnAny) {
+                    o = off + 4u * c + (pos + c >= g.HW ? wrap : (OFF)0);
+                } else {
+                    const uint32_t im = (uint32_t)(((uint64_t)(m + c) * g.magic) >> g.shift);
+                    o = first + image * im + (OFF)4 * (m + c - im * g.HW);
                 }
-            } else {
-                float el[4];
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    const uint32_t m = m0 + c;
-                    float term = 0.0f;                  // terms beyond M count as +0
-                    if (m < M) {
-                        const uint32_t im = m / HW;
-                        const float y = x[((uint64_t)im * C + ch) * HW + (m - im * HW)];
-                        if constexpr (SQDEV) {
-                            const float d = y - center;
-                            term = d * d;
-                        } else {
-                            term = y;
-                        }
-                    }
-                    el[c] = term;
-                }
-                e = f4{el[0], el[1], el[2], el[3]};
+                e[c] = *reinterpret_cast<const float*>(xb + (m + c < g.M ? o : first));
             }
-            t[j][q] = e;
+        };
+        if constexpr (MODE == kBnVector) {              // M is a multiple of 4 too
+            e = *reinterpret_cast<const f4_dword_aligned*>(xb + (m < g.M ? off : first));
+        } else if constexpr (MODE == kBnLong) {
+            if (blk * 4096u + 256u * i >= g.M) e = f4{0.0f, 0.0f, 0.0f, 0.0f};
+            else if (__any(pos + 3 >= g.HW || m + 3 >= g.M)) singles();
+            else e = *reinterpret_cast<const f4_dword_aligned*>(xb + off);
+        } else {
+            // the whole wave is beyond M: no loads (four of them cost more than this branch: 8.0 -> 7.1 us
+            // on 32x2048x7x7; the one load of kBnVector does not: 10.8 -> 11.5 us on 32x512x28x28)
+            if (blk * 4096u + 256u * i < g.M) singles();
+            else e = f4{0.0f, 0.0f, 0.0f, 0.0f};
         }
+        m += 256;
+        pos += g.step_pos;
+        off += step;
+        if (pos >= g.HW) {
+            pos -= g.HW;
+            off += wrap;
+        }
+    }
+}
+
+// The block's partial sum (valid in lane 0): of the terms, or of their squared distance to
+// `mean`; terms beyond M count as +0.
+template <bool SQDEV, bool FULL>
+__device__ __forceinline__ float bn_block_sum_of(const f4 (&t)[4][4], uint32_t blk, uint32_t h, uint32_t M, float mean)
+{
     float s[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         float a = 0.0f;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const f4 e = t[j][q];
+            f4 e = t[j][q];
+            if constexpr (SQDEV) {
+                const f4 d = e - mean;
+                e = d * d;
+            }
+            if constexpr (!FULL) {
+                const uint32_t m = blk * 4096u + 4u * (256 * q + 64 * j + h);
+#pragma unroll
+                for (int c = 0; c < 4; ++c) e[c] = m + c < M ? e[c] : 0.0f;
+            }
             a = a + e.x;
             a = a + e.y;
             a = a + e.z;
@@ -1084,7 +1151,143 @@ __global__ __launch_bounds__(kBlock) void k_bn_partials(const float* __restrict_
     float r = r0 + r1;                                  // stride 64
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) r = r + __shfl_down(r, d, 64);
-    if (h == 0) part[(uint64_t)ch * nblk + blk] = r;
+    return r;
+}
+
+template <bool SQDEV>
+__device__ __forceinline__ float bn_block_sum(const f4 (&t)[4][4], uint32_t blk, uint32_t h, uint32_t M, float mean)
+{
+    return (uint64_t)blk * 4096 + 4096 <= M ? bn_block_sum_of<SQDEV, true>(t, blk, h, M, mean)
+                                            : bn_block_sum_of<SQDEV, false>(t, blk, h, M, mean);
+}
+
+// A channel of at most kBnWaves + kBnExtra blocks: one workgroup, everything in one launch, x
+// read once.  Each wave keeps one block in registers (64 per lane) and, in the EXTRA form, the
+// first waves park a second one in LDS; the second pass costs no memory traffic.  The block
+// partials meet in LDS, where every wave sums them for itself: at most 64 partials are lanes
+// 0..63 of the tree, and its strides 128 and 64 only add +0.  With one block per channel a
+// workgroup takes one channel per wave instead and needs no LDS.
+// Bound by the launch and one round trip to memory for small layers, by HBM for large ones.
+// Measured against two passes of two launches each: 32x2048x7x7 27.2 -> 7.1 us, 32x512x28x28
+// 23.8 -> 11.0 us, 32x256x56x56 (25 blocks, parked) 46.7 -> 19.9 us = 5.2 TB/s.
+constexpr uint32_t kBnWaves = 16;                       // 1024 lanes: the registers of a CU hold 16 blocks
+constexpr uint32_t kBnExtra = 9;                        // 16 KiB each: what fits in 160 KiB beside the partials
+constexpr uint32_t kBnSingles = 4;                      // channels per workgroup when a channel is one block
+enum { kBnSingle = 0, kBnRegs = 1, kBnParked = 2 };
+
+template <int MODE, typename OFF, int FORM>
+__global__ __launch_bounds__(FORM == kBnSingle ? 64 * kBnSingles : 64 * kBnWaves)
+void k_bn_channel(const float* __restrict__ x, const BnGeom g, float fM, float* __restrict__ mean, float* __restrict__ var)
+{
+    extern __shared__ __align__(16) float park[];       // kBnParked: [extra block][vector][lane]
+    __shared__ float part[2][kBnWaves + kBnExtra];
+    const uint32_t h = threadIdx.x & 63;
+    const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t ch = FORM == kBnSingle ? blockIdx.x * kBnSingles + w : blockIdx.x;
+    const uint32_t blk = FORM == kBnSingle ? 0 : w;
+    if (FORM == kBnSingle && ch >= g.C) return;         // whole wave; no barrier in this form
+    const uint32_t blk2 = kBnWaves + w;
+    const bool two = FORM == kBnParked && blk2 < g.nblk;
+    f4* mine = reinterpret_cast<f4*>(park) + (w * 16) * 64 + h;
+    f4 t[4][4];
+    if (two) {                                          // what a lane parks only that lane reads back
+        bn_load<MODE, OFF>(x, g, ch, blk2, h, t);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) mine[64 * i] = t[i & 3][i >> 2];
+        const float s = bn_block_sum<false>(t, blk2, h, g.M, 0.0f);
+        if (h == 0) part[0][blk2] = s;
+    }
+    bn_load<MODE, OFF>(x, g, ch, blk, h, t);
+    __builtin_amdgcn_sched_barrier(0);
+    auto combine = [&](float s, int pass) {
+        if constexpr (FORM == kBnSingle) {
+            return __shfl(s, 0, 64) / fM;
+        } else {
+            if (h == 0) part[pass][w] = s;
+            __syncthreads();
+            float r = h < g.nblk ? 0.0f + part[pass][h] : 0.0f;
+#pragma unroll
+            for (int d = 32; d >= 1; d >>= 1) r = r + __shfl_down(r, d, 64);
+            return __shfl(r, 0, 64) / fM;
+        }
+    };
+    const float mu = combine(bn_block_sum<false>(t, blk, h, g.M, 0.0f), 0);
+    const float s = bn_block_sum<true>(t, blk, h, g.M, mu);
+    if (two) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) t[i & 3][i >> 2] = mine[64 * i];
+        const float s2 = bn_block_sum<true>(t, blk2, h, g.M, mu);
+        if (h == 0) part[1][blk2] = s2;
+    }
+    const float va = combine(s, 1);
+    if (h == 0 && (FORM == kBnSingle || w == 0)) {
+        mean[ch] = mu;
+        var[ch] = va;
+    }
+}
+
+// Longer channels read x twice (second pass over blocks in reverse: what the first read last may
+// still be in the L2s).
+//
+// Up to 256 blocks (WIDE): the four waves of a workgroup take the blocks b, b + W/4,
+// b + W/2 and b + 3W/4, W being the number of blocks rounded up to a power of two, so the first
+// two levels of the partials' tree (strides W/2 and W/4) happen in the workgroup: W/4 sums per
+// channel are left, few enough for both passes' to fit in the workspace side by side and for one
+// wave to add up.  Every wave of the second pass forms the mean for itself while its terms are on
+// their way; three launches.  32x64x112x112 (98 blocks): 47.8 -> 37.4 us, two reads of 103 MB at
+// 6.5 TB/s each and 6 us of launches (a read that hits the Infinity Cache is no faster: 15 us).
+// Beyond that: one partial per block, and a launch after each pass that combines them.
+template <bool SQDEV, bool WIDE, int MODE, typename OFF>
+__global__ __launch_bounds__(kBlock) void k_bn_partials(const float* __restrict__ x, const BnGeom g, float fM,
+                                                        float* __restrict__ mean, float* __restrict__ part)
+{
+    const uint32_t h = threadIdx.x & 63;
+    const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t bx = SQDEV ? gridDim.x - 1 - blockIdx.x : blockIdx.x;
+    const uint32_t ch = SQDEV ? gridDim.y - 1 - blockIdx.y : blockIdx.y;
+    const uint32_t blk = WIDE ? bx + w * gridDim.x : bx * 4 + w;
+    if (!WIDE && blk >= g.nblk) return;                 // whole wave leaves together
+    f4 t[4][4];
+    if (blk < g.nblk) bn_load<MODE, OFF>(x, g, ch, blk, h, t);
+    __builtin_amdgcn_sched_barrier(0);
+    float center = 0.0f;
+    if constexpr (SQDEV) {
+        if constexpr (WIDE) {
+            float r = h < gridDim.x ? part[(uint64_t)ch * gridDim.x + h] : 0.0f;
+#pragma unroll
+            for (int d = 32; d >= 1; d >>= 1) r = r + __shfl_down(r, d, 64);
+            center = __shfl(r, 0, 64) / fM;
+            if (bx == 0 && threadIdx.x == 0) mean[ch] = center;
+        } else {
+            center = mean[ch];
+        }
+    }
+    if constexpr (WIDE) {
+        __shared__ float sums[4];
+        const float r = blk < g.nblk ? bn_block_sum<SQDEV>(t, blk, h, g.M, center) : 0.0f;
+        if (h == 0) sums[w] = r;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            float* out = part + (SQDEV ? (uint64_t)g.C * gridDim.x : 0);
+            out[(uint64_t)ch * gridDim.x + bx] = (sums[0] + sums[2]) + (sums[1] + sums[3]);
+        }
+    } else {
+        const float r = bn_block_sum<SQDEV>(t, blk, h, g.M, center);
+        if (h == 0) part[(uint64_t)ch * g.nblk + blk] = r;
+    }
+}
+
+// out[ch] = the tree over the last `n` <= 64 sums of channel ch / M; one wave per channel.
+__global__ __launch_bounds__(kBlock) void k_bn_final_wave(const float* __restrict__ part, uint32_t n, uint32_t C,
+                                                          float fM, float* __restrict__ out)
+{
+    const uint32_t h = threadIdx.x & 63;
+    const uint32_t ch = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (ch >= C) return;
+    float r = h < n ? part[(uint64_t)ch * n + h] : 0.0f;
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) r = r + __shfl_down(r, d, 64);
+    if (h == 0) out[ch] = r / fM;
 }
 
 __global__ __launch_bounds__(kBlock) void k_bn_final(const float* __restrict__ part, uint32_t nblk, float fM,
@@ -1092,24 +1295,66 @@ __global__ __launch_bounds__(kBlock) void k_bn_final(const float* __restrict__ p
 {
     __shared__ float lds[kBlock];
     const float* pc = part + (uint64_t)blockIdx.x * nblk;
-    float s = 0.0f;
-    for (uint32_t k = threadIdx.x; k < nblk; k += kBlock) s = s + pc[k];      // partials t, t+256, ... in order
-    s = tree256(s, lds);
+    const float s = tree256(lane_partials(pc, nblk), lds);
     if (threadIdx.x == 0) out[blockIdx.x] = s / fM;
+}
+
+template <int MODE, typename OFF>
+static void launch_bn(hipStream_t s, const float* x, const BnGeom& g, float* mean, float* var, float* part)
+{
+    const float fM = (float)g.M;
+    if (g.nblk == 1) {
+        hipLaunchKernelGGL((k_bn_channel<MODE, OFF, kBnSingle>), dim3((g.C + kBnSingles - 1) / kBnSingles),
+                           dim3(64 * kBnSingles), 0, s, x, g, fM, mean, var);
+    } else if (g.nblk <= kBnWaves) {
+        hipLaunchKernelGGL((k_bn_channel<MODE, OFF, kBnRegs>), dim3(g.C), dim3(64 * g.nblk), 0, s, x, g, fM, mean, var);
+    } else if (g.nblk <= kBnWaves + kBnExtra) {
+        hipLaunchKernelGGL((k_bn_channel<MODE, OFF, kBnParked>), dim3(g.C), dim3(64 * kBnWaves),
+                           (g.nblk - kBnWaves) * 4096 * sizeof(float), s, x, g, fM, mean, var);
+    } else if (g.nblk <= 256) {
+        uint32_t n = 8;                                 // sums per channel: a quarter of the blocks' power of two
+        while (4 * n < g.nblk) n *= 2;
+        const dim3 grid(n, g.C);
+        hipLaunchKernelGGL((k_bn_partials<false, true, MODE, OFF>), grid, dim3(kBlock), 0, s, x, g, fM, mean, part);
+        hipLaunchKernelGGL((k_bn_partials<true, true, MODE, OFF>), grid, dim3(kBlock), 0, s, x, g, fM, mean, part);
+        hipLaunchKernelGGL(k_bn_final_wave, dim3((g.C + 3) / 4), dim3(kBlock), 0, s, part + (uint64_t)g.C * n, n, g.C,
+                           fM, var);
+    } else {
+        const dim3 grid((g.nblk + 3) / 4, g.C);
+        hipLaunchKernelGGL((k_bn_partials<false, false, MODE, OFF>), grid, dim3(kBlock), 0, s, x, g, fM, mean, part);
+        hipLaunchKernelGGL(k_bn_final, dim3(g.C), dim3(kBlock), 0, s, part, g.nblk, fM, mean);
+        hipLaunchKernelGGL((k_bn_partials<true, false, MODE, OFF>), grid, dim3(kBlock), 0, s, x, g, fM, mean, part);
+        hipLaunchKernelGGL(k_bn_final, dim3(g.C), dim3(kBlock), 0, s, part, g.nblk, fM, var);
+    }
 }
 
 hipError_t launch_bn_batch_stats(hipStream_t s, const float* x, uint32_t B, uint32_t C, uint32_t HW,
                                  float* mean, float* var, float* part)
 {
-    const uint32_t M = B * HW;
-    const uint32_t nblk = (M + 4095) / 4096;
     if (C == 0) return hipSuccess;
-    const dim3 grid((nblk + 3) / 4, C);
-    const float fM = (float)M;
-    if (nblk) hipLaunchKernelGGL(k_bn_partials<false>, grid, dim3(kBlock), 0, s, x, C, HW, M, nblk, mean, part);
-    hipLaunchKernelGGL(k_bn_final, dim3(C), dim3(kBlock), 0, s, part, nblk, fM, mean);
-    if (nblk) hipLaunchKernelGGL(k_bn_partials<true>, grid, dim3(kBlock), 0, s, x, C, HW, M, nblk, mean, part);
-    hipLaunchKernelGGL(k_bn_final, dim3(C), dim3(kBlock), 0, s, part, nblk, fM, var);
+    BnGeom g;
+    g.C = C;
+    g.HW = HW;
+    g.M = B * HW;
+    g.nblk = (g.M + 4095) / 4096;
+    // 2^l >= HW: magic * HW exceeds 2^(31+l) by at most HW <= 2^l, which m < 2^31 cannot carry into the quotient
+    uint32_t l = 0;
+    while ((1ull << l) < HW) ++l;
+    g.magic = (1ull << (31 + l)) / HW + 1;
+    g.shift = 31 + l;
+    g.step_img = 256 / HW;
+    g.step_pos = 256 % HW;
+    const bool small = (uint64_t)B * C * HW * sizeof(float) <= 0xFFFFFFFFull;
+#define ES_BN(MODE)                                                              \
+    do {                                                                         \
+        if (small) launch_bn<MODE, uint32_t>(s, x, g, mean, var, part);          \
+        else launch_bn<MODE, uint64_t>(s, x, g, mean, var, part);                \
+    } while (0)
+    if (HW % 4 == 0) ES_BN(kBnVector);
+    else if (HW >= kBnLongHW) ES_BN(kBnLong);
+    else if (HW >= 4) ES_BN(kBnWrap);
+    else ES_BN(kBnAny);
+#undef ES_BN
     return hipGetLastError();
 }
 
