@@ -668,7 +668,8 @@ __global__ __launch_bounds__(kBlock) void k_sq_partials(const float* __restrict_
 // Lane t's share of the partials' tree: partials t, t+256, ... added in that order from +0.  One
 // workgroup does this while the GPU waits, so what counts is the number of round trips to memory:
 // 32 loads are issued ahead of their adds while that many are left (without the clamp of the
-// last round: it kept the loads from going out together), then 8.
+// last round: it kept the loads from going out together), then 8.  The norm of 355 M values
+// (86,627 partials) went from 232 to 222 us, of 109 M from 73.6 to 71.0 us.
 __device__ __forceinline__ float lane_partials(const float* __restrict__ part, uint64_t nblk)
 {
     float s = 0.0f;
@@ -699,20 +700,7 @@ __global__ __launch_bounds__(kBlock) void k_sq_final(const float* __restrict__ p
                                                      float* __restrict__ out)
 {
     __shared__ float lds[kBlock];
-    float s = 0.0f;
-    // lane t adds partials t, t+256, ... in that order; eight loads are issued ahead of the adds
-    for (uint64_t k0 = threadIdx.x; k0 < nblk; k0 += 8 * kBlock) {
-        float v[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const uint64_t k = k0 + (uint64_t)j * kBlock;
-            v[j] = part[k < nblk ? k : nblk - 1];
-        }
-#pragma unroll
-        for (int j = 0; j < 8; ++j)
-            if (k0 + (uint64_t)j * kBlock < nblk) s = s + v[j];
-    }
-    s = tree256(s, lds);
+    const float s = tree256(lane_partials(part, nblk), lds);
     if (threadIdx.x == 0) {
         out[0] = s;
         out[1] = sqrtf(s);
