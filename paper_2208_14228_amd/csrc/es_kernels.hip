@@ -1079,10 +1079,11 @@ __global__ void k_philox_advance(uint64_t* state, uint64_t blocks)
 
 // A short mask: one workgroup draws all of it and then advances the offset it has read, so the
 // second launch (which every other workgroup of a longer mask has to have read the state before)
-// goes away: a 1003-byte mask and an EST switch 10.8 -> 8.0 us.  Up to two rounds of a full
-// workgroup (32 KiB, about 1 us each); beyond, one CU takes longer than the launch it saves.
+// goes away: a 1003-byte mask and an EST switch 10.8 -> 8.0 us.  Up to 16 KiB, 16 bytes for each of
+// its lanes: 3.35 us on the GPU against 4.2 for the pair; with a second round 24 KiB take 4.04 us and
+// 32 KiB 4.9, and the pair is as fast or faster.
 constexpr uint32_t kMaskGroup = 1024;
-constexpr uint64_t kShortMask = 2 * 16 * kMaskGroup;
+constexpr uint64_t kShortMask = 16 * kMaskGroup;
 
 __global__ __launch_bounds__(kMaskGroup) void k_dropout_mask_short(uint64_t* __restrict__ state,
                                                                    uint8_t* __restrict__ mask, uint64_t n,
@@ -1092,12 +1093,11 @@ __global__ __launch_bounds__(kMaskGroup) void k_dropout_mask_short(uint64_t* __r
     const uint64_t offset = uniform64(state[1]);
     __syncthreads();                                    // every wave has its copy of the state
     if (threadIdx.x == 0) state[1] = offset + (n + 3) / 4;
-    for (uint64_t t = threadIdx.x; 16 * t < n; t += kMaskGroup) {
-        uint32_t packed[4];
-        mask_bytes(t, uniform64(t - (threadIdx.x & 63)), offset, (uint32_t)seed, (uint32_t)(seed >> 32), threshold,
-                   none, packed);
-        store_mask(mask, 16 * t, n, aligned16, packed);
-    }
+    const uint64_t t = threadIdx.x;
+    if (16 * t >= n) return;
+    uint32_t packed[4];
+    mask_bytes(t, uniform64(t - (threadIdx.x & 63)), offset, (uint32_t)seed, (uint32_t)(seed >> 32), threshold, none, packed);
+    store_mask(mask, 16 * t, n, aligned16, packed);
 }
 
 hipError_t launch_dropout_mask(hipStream_t s, uint64_t* state, uint8_t* mask, uint64_t n,
@@ -1108,7 +1108,7 @@ hipError_t launch_dropout_mask(hipStream_t s, uint64_t* state, uint8_t* mask, ui
     const int aligned16 = (((uintptr_t)mask) & 15) == 0;
     const bool none = threshold > 0xFFFFFFFFull;
     if (n <= kShortMask) {
-        const uint32_t block = lanes >= kMaskGroup ? kMaskGroup : (uint32_t)((lanes + 63) / 64 * 64);
+        const uint32_t block = (uint32_t)((lanes + 63) / 64 * 64);
         hipLaunchKernelGGL(k_dropout_mask_short, dim3(1), dim3(block), 0, s, state, mask, n, (uint32_t)threshold, none,
                            aligned16);
         return hipGetLastError();

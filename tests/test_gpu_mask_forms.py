@@ -14,8 +14,8 @@ if torch.cuda.is_available():
     from paper_2208_14228_amd.job import ESTJob
     DEV = "cuda:0"
 
-SHORT = 2 * 16 * 1024
-NS = [1, 15, 16, 17, 1023, 1024, 1025, 16 * 1024, 16 * 1024 + 1, SHORT - 1, SHORT, SHORT + 1, SHORT + 16,
+SHORT = 16 * 1024
+NS = [1, 15, 16, 17, 1023, 1024, 1025, 2 * SHORT, 2 * SHORT + 1, SHORT - 1, SHORT, SHORT + 1, SHORT + 16,
       4096 * 16 + 5, 300_007]
 # a wave's counters are 256 in a row, the first one a multiple of 256 past the offset
 OFFS = [0, (1 << 32) - 256, (1 << 32) - 255, (1 << 32) - 300, (5 << 32) - 1, (1 << 64) - 100]
