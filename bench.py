@@ -394,7 +394,9 @@ def measure(torch, a, cid, headline, oracle_leg):
     stage_ms = statistics.fmean(stg)
     red_gbps = bytes_reduce / (red_ms * 1e-3) / 1e9
     pv_cacheable = opts["nontemporal_pv"] == 0 and fused
-    kname = ("k_ring_reduce_big" if opts["reduce_big_unroll"] else "k_ring_reduce") + (" (fused SGD)" if fused else "")
+    wave = N <= 64 and P < 8_000_000 and not any(kv.startswith(("reduce_", "nontemporal=")) for kv in a.opt)
+    kname = ("k_ring_reduce_wave" if wave else "k_ring_reduce_big" if opts["reduce_big_unroll"] else "k_ring_reduce")
+    kname += " (fused SGD)" if fused else ""
 
     res = {
         "config": cid,

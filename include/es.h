@@ -427,7 +427,11 @@ int es_checkpoint_import(es_handle* h, const void* host_blob, uint64_t size,
 int es_sync(es_handle* h);
 
 /*
- * Options (never change results).  Names:
+ * Options (never change results).  As long as none of the reduce_* options and no
+ * "nontemporal" = 0 has been set, a reduce of up to 64 ranks over fewer than 8 M
+ * parameters runs in a launch shape of its own (one wave per 64 or 256 elements,
+ * chosen by both numbers); setting one of them puts the shape that the
+ * options describe in its place, there as everywhere.  Names:
  *   "host_slots"          0/1: placement of gradient slots at the NEXT es_set_grouping: 1 =
  *                         pinned host memory mapped into the device (the paper keeps the
  *                         per-EST gradients in host memory, section 3.2; here it is the

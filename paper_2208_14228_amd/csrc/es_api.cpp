@@ -68,6 +68,7 @@ struct es_handle {
     uint64_t hbm_grad_bytes = 0;                // HBM held by gradient arenas allocated in the current regrouping
     uint32_t tile_elems = 2048;
     ReduceShape shape{2, 8, 1, 0, 1, 0, -1};
+    bool auto_shape = true;                     // no option has asked for a particular launch shape
 
     // Swap-in of host-resident gradient slots (option "swap_in"): at the reduce the buckets come
     // back one at a time into two device buffers, bucket b+1 being copied while bucket b is reduced.
@@ -188,6 +189,11 @@ int alloc_worker(es_handle* h, Worker& w, uint32_t n_slots)
 void plan_tiles(const std::vector<es_bucket>& buckets, uint32_t N, uint32_t A, uint64_t T,
                 uint64_t TB, std::vector<Tile>& big, std::vector<Tile>& small)
 {
+    if (!TB && !buckets.empty()) {               // about one tile per T elements and two per chunk
+        const es_bucket& last = buckets.back();
+        const uint64_t elems = last.offset_elems + last.len_elems - buckets.front().offset_elems;
+        small.reserve((size_t)(elems / T + std::min<uint64_t>(elems, 2ull * N * buckets.size())));
+    }
     for (const es_bucket& b : buckets) {
         const uint64_t L = b.len_elems;
         if (L == 0) continue;
@@ -236,13 +242,20 @@ void plan_tiles(const std::vector<es_bucket>& buckets, uint32_t N, uint32_t A, u
 int build_tiles(es_handle* h)
 {
     std::vector<Tile> big, tiles;
-    const uint64_t TB = h->shape.big_unroll ? (uint64_t)kReduceBlock * h->shape.big_unroll * 4 : 0;
-    plan_tiles(h->buckets, h->N, h->A, h->tile_elems, TB, big, tiles);
+    h->shape.wave_width = 0;                     // (wave_shape sets it where that form is the default)
+    if (h->auto_shape && wave_shape(h->N, h->P, h->shape)) {
+        plan_tiles(h->buckets, h->N, h->A, 64u * h->shape.wave_width, 0, big, tiles);
+    } else {
+        const uint64_t TB = h->shape.big_unroll ? (uint64_t)kReduceBlock * h->shape.big_unroll * 4 : 0;
+        plan_tiles(h->buckets, h->N, h->A, h->tile_elems, TB, big, tiles);
+    }
     if (big.size() + tiles.size() > 0x7fffffffull) return ES_EINVAL;
     h->swap_ready = false;                       // the per-bucket tile tables of the swap-in path follow the same shape
     h->n_big = (uint32_t)big.size();
-    big.insert(big.end(), tiles.begin(), tiles.end());
-    tiles.swap(big);
+    if (!big.empty()) {
+        big.insert(big.end(), tiles.begin(), tiles.end());
+        tiles.swap(big);
+    }
     if (h->d_tiles) { dev_release(h, h->d_tiles); h->d_tiles = nullptr; }
     h->n_tiles = (uint32_t)tiles.size();
     if (h->n_tiles) {
@@ -454,6 +467,8 @@ int swap_reduce(es_handle* h, float* avg, float* p, float* v, float lr, float mu
     h->stage_pending = false;
     std::vector<const float*> in_place(h->N, nullptr);
     for (size_t k = 0; k < h->in_place_rank.size(); ++k) in_place[h->in_place_rank[k]] = h->in_place_ptr[k];
+    ReduceShape shape = h->shape;
+    shape.wave_width = 0;                        // the per-bucket tables are for the other kernels
     std::vector<es_swap_op> ops;
     swap_plan((uint32_t)nb, ops);
     for (const es_swap_op& op : ops) {
@@ -475,7 +490,7 @@ int swap_reduce(es_handle* h, float* avg, float* p, float* v, float lr, float mu
             ES_HIP(h, launch_ring_reduce(h->s_main, h->d_swap_tiles + h->swap_tile_off[op.bucket],
                                          h->swap_n_tiles[op.bucket], h->swap_n_big[op.bucket],
                                          h->d_swap_tables + ((size_t)op.half * nb + op.bucket) * h->N, h->N,
-                                         avg, p, v, lr, mu, h->shape));
+                                         avg, p, v, lr, mu, shape));
             ES_HIP(h, hipEventRecord(h->ev_consumed[op.half], h->s_main));
         }
     }
@@ -1291,14 +1306,26 @@ try {
     if (!h || !name) return ES_EINVAL;
     DeviceGuard guard__(h);
     const std::string k(name);
+    // an option that names a launch shape leaves the size-dependent default for good: from here on
+    // the tile table is the one the options describe
+    auto leave_auto = [h] {
+        if (!h->auto_shape) return (int)ES_OK;
+        int rc = sync_all(h);
+        if (rc != ES_OK) return rc;
+        h->auto_shape = false;
+        if (h->shape.wave_width && (rc = build_tiles(h)) != ES_OK) h->auto_shape = true, (void)build_tiles(h);
+        return rc;
+    };
     if (k == "reduce_tile_elems") {
         if (value < 256 || value > 65536 || (value & 3)) return ES_EINVAL;
         int rc = sync_all(h);
         if (rc != ES_OK) return rc;
         const uint32_t old = h->tile_elems;
+        const bool was_auto = h->auto_shape;
         h->tile_elems = (uint32_t)value;
+        h->auto_shape = false;
         rc = build_tiles(h);
-        if (rc != ES_OK) { h->tile_elems = old; (void)build_tiles(h); }
+        if (rc != ES_OK) { h->tile_elems = old; h->auto_shape = was_auto; (void)build_tiles(h); }
         return rc;
     }
     if (k == "reduce_big_unroll" || k == "reduce_big_rank_batch") {
@@ -1311,29 +1338,35 @@ try {
         const int old = field;
         field = (int)value;
         if (h->shape.big_unroll * h->shape.big_rank_batch > 32) { field = old; return ES_EINVAL; }
+        const bool was_auto = h->auto_shape;
+        h->auto_shape = false;
         rc = build_tiles(h);
-        if (rc != ES_OK) { field = old; (void)build_tiles(h); }
+        if (rc != ES_OK) { field = old; h->auto_shape = was_auto; (void)build_tiles(h); }
         return rc;
     }
     if (k == "reduce_lds_pad_kib") {
         if (value < -1 || value > 160) return ES_EINVAL;
-        h->shape.lds_pad_kib = (int)value;
-        return ES_OK;
+        const int rc = value >= 0 ? leave_auto() : ES_OK;
+        if (rc == ES_OK) h->shape.lds_pad_kib = (int)value;
+        return rc;
     }
     if (k == "reduce_unroll") {
         if (value != 1 && value != 2 && value != 4) return ES_EINVAL;
-        h->shape.unroll = (int)value;
-        return ES_OK;
+        const int rc = leave_auto();
+        if (rc == ES_OK) h->shape.unroll = (int)value;
+        return rc;
     }
     if (k == "reduce_rank_batch") {
         if (value != 1 && value != 2 && value != 4 && value != 8 && value != 16) return ES_EINVAL;
-        h->shape.rank_batch = (int)value;
-        return ES_OK;
+        const int rc = leave_auto();
+        if (rc == ES_OK) h->shape.rank_batch = (int)value;
+        return rc;
     }
     if (k == "nontemporal") {
         if (value != 0 && value != 1) return ES_EINVAL;
-        h->shape.nontemporal = (int)value;
-        return ES_OK;
+        const int rc = value ? ES_OK : leave_auto();     // the wave-tile form has streaming loads only
+        if (rc == ES_OK) h->shape.nontemporal = (int)value;
+        return rc;
     }
     if (k == "swap_in") {
         if (value != 0 && value != 1) return ES_EINVAL;

@@ -78,11 +78,52 @@ struct ReduceShape {
                         // averaged gradient
     int lds_pad_kib = -1; // KiB of LDS reserved (and never touched) per workgroup of the small-tile kernel, to cap the
                           // workgroups resident per CU; -1 = default for the rank count (see reduce_lds_pad)
+    // wave-tile form (k_ring_reduce_wave): floats per lane (1 or 4; 0 = the other kernels), ranks
+    // loaded before adds are issued, lanes per workgroup, KiB of LDS reserved per workgroup
+    int wave_width = 0, wave_batch = 0, wave_block = 0, wave_pad_kib = 0;
 };
+
+// The wave-tile form where it is the faster one, by the rank count N and the parameter count P;
+// returns false (and leaves the shape alone) where the other kernels are.  Measured on 13 rank counts
+// x 9 sizes, fused, three jobs in turn (time of the other kernels over this one's):
+//  - N <= 64: the slot table is one pointer per lane.
+//  - P < 8 M: 1.0-1.3 at 4 M, 1.0-2.2 at 1 M, 1.05-3.4 at 20 k; at 8 M 0.97-1.06, at 25 M 0.95-1.02
+//    (there a wave's 1 KiB per stream costs what the saved round trips gain).
+//  - one float per lane below 300 k elements and from 8 ranks on, where four leave SIMDs without a wave
+//    (1.1-1.7 x slower at 100 k, 1.0-1.1 x faster at 500 k); then as many ranks per batch as there are,
+//    up to 64, while a SIMD has at most two waves (P <= 128 k), else 16.
+//  - four floats per lane: batches of 4, of 8 from 8 to 23 ranks (a second round trip less: 1.0-1.1).
+//  - fewer than 8 ranks from 1 M elements on: one wave per workgroup, no cap on residency (1.0 at 1 M,
+//    1.03-1.1 above, 0.9 at 500 k); else four waves and 5 workgroups per CU.
+inline bool wave_shape(uint32_t N, uint64_t P, ReduceShape& sh)
+{
+    if (N == 0 || N > 64 || P >= 8000000) return false;
+    auto pow2_up_to = [N](int most) {
+        int b = most;
+        while (b > 1 && (uint32_t)b > N) b /= 2;
+        return b;
+    };
+    sh.wave_block = 256;
+    sh.wave_pad_kib = 32;
+    if (N >= 8 && P < 300000) {
+        sh.wave_width = 1;
+        sh.wave_batch = pow2_up_to(P <= (128u << 10) ? 64 : 16);
+        sh.wave_pad_kib = 0;
+        return true;
+    }
+    sh.wave_width = 4;
+    sh.wave_batch = pow2_up_to(N >= 8 && N < 24 ? 8 : 4);
+    if (N < 8 && P >= 1000000) {
+        sh.wave_block = 64;
+        sh.wave_pad_kib = 0;
+    }
+    return true;
+}
 
 // ring-ordered N-way reduce (+ optional fused SGD-momentum).
 //  slots: device table of N slot base pointers indexed by virtual rank.
 //  avg may be null only when p and v are given.
+//  With shape.wave_width != 0 every tile holds at most 64 * wave_width elements, and N <= 64.
 //  With shape.big_unroll != 0 the first n_big tiles must be full big tiles
 //  (kBlock * big_unroll * 4 elements, offset a multiple of 4) and all others
 //  at most 2048 elements.

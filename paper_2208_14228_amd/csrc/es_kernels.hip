@@ -11,6 +11,7 @@
 #include "es_internal.h"
 
 #include <mutex>
+#include <type_traits>
 
 namespace es {
 
@@ -20,6 +21,8 @@ typedef uint32_t u4 __attribute__((ext_vector_type(4)));
 // Tables that every lane of a workgroup reads at the same index live in the
 // constant address space so the reads are scalar loads shared by the wave.
 #define ES_CONST_AS __attribute__((address_space(4)))
+// A base put together from registers: without the address space its loads would be flat ones.
+#define ES_GLOBAL_AS __attribute__((address_space(1)))
 #pragma clang diagnostic ignored "-Wold-style-cast"
 
 template <bool NT>
@@ -424,11 +427,160 @@ static hipError_t launch_reduce_big_u(hipStream_t s, const Tile* tiles, uint32_t
     return hipErrorInvalidValue;
 }
 
+// ---------------------------------------------------------------------------
+// Wave-tile form of the same kernel for short vectors and at most 64 ranks: one WAVE
+// per tile of 64 * W elements, W floats per lane.  (Tiles of four waves, for a shorter
+// table, leave waves idle at the end of every chunk, and their workgroups still take
+// turns on a CU: 24 % slower at N = 64, P = 1 M.)
+//
+// What bounds a short reduce is the number of dependent round trips to memory in one
+// wave's life and the number of waves, not bytes.  So: the rank -> slot table is read
+// with one vector load (lane r holds rank r's base) that does not wait for the tile, and
+// a rank's base then comes out of a register (v_readlane) instead of a scalar load in
+// front of every batch; pieces are small enough that every CU has some; a batch is as
+// many ranks as the registers hold when few waves share a SIMD.  Vectors may start at
+// any 4-byte address, and the last one of a tile is shifted back over its neighbour's
+// elements (both lanes of the wave have loaded before either stores, and store the same
+// values), so ragged chunks have no element-wise path; only a tile shorter than a vector
+// is read one float per lane.
+//
+// Fused, default options, three jobs in turn: N = 64, P = 20 k 16.8 -> 4.9 us, P = 200 k
+// 19.0 -> 10.6 us; N = 16, P = 500 k 14.1 -> 7.9 us, P = 4 M 67 -> 53 us; N = 8, P = 1 M
+// 11.4 -> 9.2 us; N = 4, P = 1 M 7.6 -> 6.8 us (4.9 TB/s).
+// ---------------------------------------------------------------------------
+template <int W> struct WaveVec;
+template <> struct WaveVec<1> { typedef float T; };
+template <> struct WaveVec<4> { typedef float T __attribute__((ext_vector_type(4), aligned(4))); };
+
+template <int W, int NB, int NT, bool SGD>
+__device__ __forceinline__ void wave_tile(uint64_t off, uint32_t len, uint32_t rank0, uint32_t base_lo,
+                                          uint32_t base_hi, uint32_t lane, uint32_t N, float* __restrict__ avg,
+                                          float* __restrict__ p, float* __restrict__ v, float lr, float mu)
+{
+    typedef typename WaveVec<W>::T T;
+    const uint32_t i = W * lane;
+    const bool ok = i < len;
+    const uint32_t e = 4u * (i + W <= len ? i : len - W);       // bytes; W <= len
+    auto at = [&](float* base) { return reinterpret_cast<T*>(reinterpret_cast<char*>(base + off) + e); };
+    T pp, vv;
+    if constexpr (SGD) {
+        if constexpr ((NT & 2) != 0) {
+            pp = __builtin_nontemporal_load(at(p));
+            vv = __builtin_nontemporal_load(at(v));
+        } else {
+            pp = *at(p);
+            vv = *at(v);
+        }
+    }
+    T acc;
+    uint32_t k = 0, r = rank0;
+    auto batch = [&](auto count, bool first) {
+        constexpr int C = decltype(count)::value;
+        T x[C];
+#pragma unroll
+        for (int j = 0; j < C; ++j) {
+            const uint32_t lo = __builtin_amdgcn_readlane(base_lo, r), hi = __builtin_amdgcn_readlane(base_hi, r);
+            const ES_GLOBAL_AS T* g = (const ES_GLOBAL_AS T*)(((uint64_t)hi << 32 | lo) + 4 * off + e);
+            x[j] = (NT & 1) ? __builtin_nontemporal_load(g) : *g;
+            r = r + 1 == N ? 0 : r + 1;
+        }
+        __builtin_amdgcn_sched_barrier(0);              // all loads of the batch ahead of its adds
+#pragma unroll
+        for (int j = 0; j < C; ++j) acc = (j == 0 && first) ? x[0] : acc + x[j];
+        k += C;
+    };
+    auto rest = [&](auto self, auto count) {            // batches of NB/2, NB/4, .. 1
+        constexpr int C = decltype(count)::value;
+        if (k + C <= N) batch(count, false);
+        if constexpr (C > 1) self(self, std::integral_constant<int, C / 2>{});
+    };
+    if (N >= (uint32_t)NB) batch(std::integral_constant<int, NB>{}, true);
+    else batch(std::integral_constant<int, 1>{}, true);
+    while (k + NB <= N) batch(std::integral_constant<int, NB>{}, false);
+    if constexpr (NB > 1) rest(rest, std::integral_constant<int, NB / 2>{});
+    if (!ok) return;
+    const T a = acc / (float)N;
+    if (avg) {
+        if constexpr ((NT & 2) != 0) __builtin_nontemporal_store(a, at(avg));
+        else *at(avg) = a;
+    }
+    if constexpr (SGD) {
+        const T mv = mu * vv;
+        const T vn = mv + a;
+        const T st = lr * vn;
+        if constexpr ((NT & 2) != 0) {
+            __builtin_nontemporal_store(vn, at(v));
+            __builtin_nontemporal_store(pp - st, at(p));
+        } else {
+            *at(v) = vn;
+            *at(p) = pp - st;
+        }
+    }
+}
+
+template <int W, int NB, int NT, bool SGD>
+__global__ __launch_bounds__(kReduceBlock) void k_ring_reduce_wave(const Tile* tiles_g, uint32_t n_tiles,
+                                                             const float* const* slots, uint32_t N,
+                                                             float* __restrict__ avg, float* __restrict__ p,
+                                                             float* __restrict__ v, float lr, float mu)
+{
+    const uint32_t lane = threadIdx.x & 63;
+    const uint32_t t = __builtin_amdgcn_readfirstlane(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6));
+    if (t >= n_tiles) return;
+    const uint64_t base = reinterpret_cast<uint64_t>(slots[lane < N ? lane : N - 1]);
+    const uint32_t lo = (uint32_t)base, hi = (uint32_t)(base >> 32);
+    const Tile ES_CONST_AS* tiles = (const Tile ES_CONST_AS*)tiles_g;
+    const uint64_t off = tiles[t].off;
+    const uint32_t len = tiles[t].len;
+    const uint32_t rank0 = tiles[t].rank0;
+    if (len >= W) wave_tile<W, NB, NT, SGD>(off, len, rank0, lo, hi, lane, N, avg, p, v, lr, mu);
+    else wave_tile<1, 8, NT, SGD>(off, len, rank0, lo, hi, lane, N, avg, p, v, lr, mu);
+}
+
+template <int W, int NB>
+static hipError_t launch_reduce_wave(hipStream_t s, const Tile* tiles, uint32_t n_tiles, const float* const* slots,
+                                     uint32_t N, float* avg, float* p, float* v, float lr, float mu, ReduceShape sh)
+{
+    const uint32_t per = (uint32_t)sh.wave_block / 64;
+    const dim3 grid((n_tiles + per - 1) / per), block(sh.wave_block);
+#define ES_LAUNCH(NTV, SGDV)                                                                                      \
+    hipLaunchKernelGGL((k_ring_reduce_wave<W, NB, NTV, SGDV>), grid, block, (uint32_t)sh.wave_pad_kib << 10, s, tiles, \
+                       n_tiles, slots, N, avg, p, v, lr, mu)
+    if (p) {
+        if (sh.nontemporal_pv) ES_LAUNCH(3, true);
+        else ES_LAUNCH(1, true);
+    } else {
+        if (sh.nontemporal_pv) ES_LAUNCH(3, false);
+        else ES_LAUNCH(1, false);
+    }
+#undef ES_LAUNCH
+    return hipGetLastError();
+}
+
+static hipError_t launch_reduce_wave_any(hipStream_t s, const Tile* tiles, uint32_t n_tiles, const float* const* slots,
+                                         uint32_t N, float* avg, float* p, float* v, float lr, float mu, ReduceShape sh)
+{
+    if (N > 64) return hipErrorInvalidValue;            // the table is one pointer per lane
+#define ES_WAVE(W, NB) \
+    if (sh.wave_width == W && sh.wave_batch == NB) return launch_reduce_wave<W, NB>(s, tiles, n_tiles, slots, N, avg, p, v, lr, mu, sh)
+    ES_WAVE(1, 8);
+    ES_WAVE(1, 16);
+    ES_WAVE(1, 32);
+    ES_WAVE(1, 64);
+    ES_WAVE(4, 1);
+    ES_WAVE(4, 2);
+    ES_WAVE(4, 4);
+    ES_WAVE(4, 8);
+#undef ES_WAVE
+    return hipErrorInvalidValue;
+}
+
 hipError_t launch_ring_reduce(hipStream_t s, const Tile* tiles, uint32_t n_tiles, uint32_t n_big,
                               const float* const* slots, uint32_t N, float* avg, float* p,
                               float* v, float lr, float mu, ReduceShape sh)
 {
     if (n_tiles == 0) return hipSuccess;
+    if (sh.wave_width) return launch_reduce_wave_any(s, tiles, n_tiles, slots, N, avg, p, v, lr, mu, sh);
     if (sh.big_unroll) {
         switch (sh.big_unroll) {
         case 8:  return launch_reduce_big_u<8>(s, tiles, n_tiles, n_big, slots, N, avg, p, v, lr, mu, sh);
