@@ -836,6 +836,8 @@ int validate_batch(const es_handle* h, uint32_t est, uint32_t n, const uint32_t*
 // Staging copies as launches of at most kMaxRuns contiguous runs each.
 struct RunBuilder {
     std::vector<CopyRuns> launches;
+    uint32_t block;                          // lanes per workgroup: one size for the whole call
+    explicit RunBuilder(uint64_t floats) : block(copy_block(floats)) {}
     void add(float* dst, const float* src, uint64_t len)
     {
         if (launches.empty()) open();
@@ -857,9 +859,9 @@ struct RunBuilder {
         }
         r->first_block[r->n_runs] = r->first_block[r->n_runs - 1] + (uint32_t)blocks_of(r->n[r->n_runs - 1]);
     }
-    static uint64_t blocks_of(uint64_t len)
+    uint64_t blocks_of(uint64_t len) const
     {
-        const uint64_t blocks = ((len >> 2) + kCopyBlock - 1) / kCopyBlock;
+        const uint64_t blocks = ((len >> 2) + block - 1) / block;
         return blocks ? blocks : 1;
     }
     void open()
@@ -867,10 +869,18 @@ struct RunBuilder {
         launches.emplace_back();
         CopyRuns& r = launches.back();
         r.n_runs = 0;
+        r.block = block;
         for (int k = 0; k <= kMaxRuns; ++k) r.first_block[k] = 0xFFFFFFFFu;   // "no run starts here"
         r.first_block[0] = 0;
     }
 };
+
+uint64_t batch_floats(const es_handle* h, uint32_t n, const uint32_t* buckets)
+{
+    uint64_t sum = 0;
+    for (uint32_t k = 0; k < n; ++k) sum += h->buckets[buckets[k]].len_elems;
+    return sum;
+}
 
 void collect_runs(es_handle* h, uint32_t est, uint32_t n, const uint32_t* buckets, const float* const* srcs,
                   RunBuilder& rb)
@@ -912,7 +922,7 @@ try {
     DeviceGuard guard__(h);
     int rc = validate_batch(h, est, n, buckets, d_grad_buckets);
     if (rc != ES_OK) return rc;
-    RunBuilder rb;
+    RunBuilder rb(batch_floats(h, n, buckets));
     collect_runs(h, est, n, buckets, d_grad_buckets, rb);
     if (!rb.launches.empty()) {
         if ((rc = order_after(h, h->s_stage, h->s_main, h->ev_main)) != ES_OK) return rc;
@@ -931,7 +941,7 @@ try {
     DeviceGuard guard__(h);
     const size_t nb = h->buckets.size();
     const uint64_t vec_bytes = h->P * sizeof(float);
-    if (RunBuilder::blocks_of(h->P) > 0x7fffffffull) return ES_EINVAL;
+    if (((h->P >> 2) + kCopyBlock - 1) / kCopyBlock > 0x7fffffffull) return ES_EINVAL;
     for (uint32_t k = 0; k < n_ests; ++k) {
         const uint32_t e = ests[k];
         if (e >= h->N) return ES_EINVAL;
@@ -943,7 +953,8 @@ try {
             if (h->accumulated[(size_t)e * nb + b]) return ES_ESTATE;
         if (h->P && src != slot_base(h, e) && overlap(src, slot_base(h, e), vec_bytes)) return ES_EINVAL;
     }
-    RunBuilder rb, rb_dma;
+    const uint64_t floats = h->P * n_ests;
+    RunBuilder rb(floats), rb_dma(floats);
     for (uint32_t k = 0; k < n_ests; ++k)
         if (h->P && d_flat_grads[k] != slot_base(h, ests[k]))
             (dma_staging(h, ests[k]) ? rb_dma : rb).add(slot_base(h, ests[k]), d_flat_grads[k], h->P);
@@ -974,7 +985,7 @@ try {
     if (!h->seg_bytes.empty() && !w.bound) return ES_ESTATE;
     int rc = validate_batch(h, est_out, n, buckets, d_grad_buckets);
     if (rc != ES_OK) return rc;
-    RunBuilder rb;
+    RunBuilder rb(batch_floats(h, n, buckets));
     collect_runs(h, est_out, n, buckets, d_grad_buckets, rb);
     const uint32_t n_pieces = h->seg_bytes.empty() ? 0 : w.n_pieces;
     if (h->s_stage != h->s_main) {
@@ -1001,7 +1012,7 @@ try {
         if ((rc = order_after(h, h->s_stage, h->s_main, h->ev_main)) != ES_OK) return rc;
         if (h->s_ctx != h->s_main && (rc = order_after(h, h->s_stage, h->s_ctx, h->ev_ctx)) != ES_OK) return rc;
         const bool dma = dma_staging(h, est_out);
-        RunBuilder none;
+        RunBuilder none(0);
         none.open();
         if (rb.launches.empty()) rb.open();
         ES_HIP(h, launch_est_boundary(h->s_stage, dma ? none.launches[0] : rb.launches[0], w.d_pieces, n_pieces,

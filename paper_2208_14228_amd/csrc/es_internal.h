@@ -27,9 +27,6 @@ static_assert(sizeof(Piece) == 24, "Piece layout");
 
 constexpr uint32_t kPieceBytes = 4096;
 constexpr uint32_t kBlock = 256;
-#ifndef ES_COPY_BLOCK
-#define ES_COPY_BLOCK 64
-#endif
 #ifndef ES_REDUCE_BLOCK
 #define ES_REDUCE_BLOCK 256
 #endif
@@ -55,7 +52,13 @@ inline uint32_t reduce_lds_pad(int option_kib, uint32_t n_ranks, bool streaming_
     if (streaming_pv && (n_ranks == 8 || n_ranks >= 10)) return 160u << 10;
     return 64u << 10;
 }
-constexpr uint32_t kCopyBlock = ES_COPY_BLOCK;   // lanes per workgroup of the batched staging copy
+// Lanes per workgroup of the staging copies: one wave for long ones, two for short ones, which the
+// rate of starting workgroups bounds as much as memory (0.5 M floats 2.49 -> 2.32 us, 1 M 3.40 -> 3.06,
+// 2 M 4.56 -> 3.87 together with plain loads; from 4 M on no better, from 7 M on 3 % worse).
+constexpr uint32_t kCopyBlock = 64;
+constexpr uint32_t kCopyBlockShort = 128;
+constexpr uint64_t kShortCopy = 3ull << 20;      // floats of one call
+inline uint32_t copy_block(uint64_t floats) { return floats < kShortCopy ? kCopyBlockShort : kCopyBlock; }
 
 // Entries of the rank -> gradient-base table that are redirected for one reduce
 // (gradients taken in place from caller memory, no staging copy).
@@ -148,6 +151,7 @@ struct CopyRuns {
     uint32_t     first_block[kMaxRuns + 1]; // prefix sums of workgroups per run; [n_runs] = total,
                                             // entries after it 0xFFFFFFFF
     uint32_t     n_runs;
+    uint32_t     block;                     // lanes per workgroup the prefix sums count (kCopyBlock or kCopyBlockShort)
 };
 hipError_t launch_copy_runs(hipStream_t s, const CopyRuns& runs);
 

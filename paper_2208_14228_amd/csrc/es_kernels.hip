@@ -926,8 +926,11 @@ hipError_t launch_sq_norm_static(hipStream_t s, const float* x, uint64_t n, floa
 // a flat gradient and in the slot - they are aligned alike.
 typedef float f4_dword_aligned __attribute__((ext_vector_type(4), aligned(4)));
 
+// Short copies (two waves per workgroup) load without the hint: the source has just been written
+// and is likely to sit in a cache.
+template <uint32_t lanes>
 __device__ __forceinline__ void copy_span(float* __restrict__ dst, const float* __restrict__ src,
-                                          uint64_t n, uint32_t block, uint32_t lane, uint32_t lanes)
+                                          uint64_t n, uint32_t block, uint32_t lane)
 {
     constexpr uintptr_t kAlign = 128;                    // 1 KiB alignment measured no better
     uint64_t head = ((kAlign - (reinterpret_cast<uintptr_t>(dst) & (kAlign - 1))) & (kAlign - 1)) >> 2;
@@ -938,7 +941,8 @@ __device__ __forceinline__ void copy_span(float* __restrict__ dst, const float* 
     const uint64_t nvec = nb >> 2;
     const uint64_t i = (uint64_t)block * lanes + lane;
     if (i < nvec) {
-        const f4 x = __builtin_nontemporal_load(reinterpret_cast<const f4_dword_aligned*>(sb + 4 * i));
+        const f4_dword_aligned* from = reinterpret_cast<const f4_dword_aligned*>(sb + 4 * i);
+        const f4 x = lanes == kCopyBlockShort ? *from : __builtin_nontemporal_load(from);
         __builtin_nontemporal_store(x, reinterpret_cast<f4*>(db + 4 * i));
     }
     if (block == 0) {
@@ -948,24 +952,28 @@ __device__ __forceinline__ void copy_span(float* __restrict__ dst, const float* 
     }
 }
 
-__global__ __launch_bounds__(kCopyBlock) void k_copy_f4(float* __restrict__ dst,
-                                                    const float* __restrict__ src, uint64_t n)
+template <uint32_t BS>
+__global__ __launch_bounds__(BS) void k_copy_f4(float* __restrict__ dst, const float* __restrict__ src, uint64_t n)
 {
-    copy_span(dst, src, n, blockIdx.x, threadIdx.x, kCopyBlock);
+    copy_span<BS>(dst, src, n, blockIdx.x, threadIdx.x);
 }
 
 hipError_t launch_copy_f32(hipStream_t s, float* dst, const float* src, uint64_t n)
 {
     if (n == 0) return hipSuccess;
-    uint64_t blocks = ((n >> 2) + kCopyBlock - 1) / kCopyBlock;
+    const uint32_t bs = copy_block(n);
+    uint64_t blocks = ((n >> 2) + bs - 1) / bs;
     if (blocks == 0) blocks = 1;
-    hipLaunchKernelGGL(k_copy_f4, dim3((uint32_t)blocks), dim3(kCopyBlock), 0, s, dst, src, n);
+    if (bs == kCopyBlockShort)
+        hipLaunchKernelGGL(k_copy_f4<kCopyBlockShort>, dim3((uint32_t)blocks), dim3(bs), 0, s, dst, src, n);
+    else
+        hipLaunchKernelGGL(k_copy_f4<kCopyBlock>, dim3((uint32_t)blocks), dim3(bs), 0, s, dst, src, n);
     return hipGetLastError();
 }
 
 // Batched staging: the runs arrive as a kernel argument (no table upload); a
 // workgroup finds its run from the prefix sums (wave-uniform, scalar).
-template <int BS>
+template <uint32_t BS>
 __global__ __launch_bounds__(BS) void k_copy_runs(const CopyRuns runs)
 {
     // the run of this workgroup = how many later runs start at or before it.  All prefix sums
@@ -978,7 +986,7 @@ __global__ __launch_bounds__(BS) void k_copy_runs(const CopyRuns runs)
 #pragma unroll
         for (int k = 1; k < kMaxRuns; ++k) r += blockIdx.x >= runs.first_block[k] ? 1u : 0u;
     }
-    copy_span(runs.dst[r], runs.src[r], runs.n[r], blockIdx.x - runs.first_block[r], threadIdx.x, BS);
+    copy_span<BS>(runs.dst[r], runs.src[r], runs.n[r], blockIdx.x - runs.first_block[r], threadIdx.x);
 }
 
 hipError_t launch_copy_runs(hipStream_t s, const CopyRuns& runs)
@@ -986,7 +994,10 @@ hipError_t launch_copy_runs(hipStream_t s, const CopyRuns& runs)
     if (runs.n_runs == 0) return hipSuccess;
     const uint32_t blocks = runs.first_block[runs.n_runs];
     if (blocks == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_copy_runs<kCopyBlock>, dim3(blocks), dim3(kCopyBlock), 0, s, runs);
+    if (runs.block == kCopyBlockShort)
+        hipLaunchKernelGGL(k_copy_runs<kCopyBlockShort>, dim3(blocks), dim3(kCopyBlockShort), 0, s, runs);
+    else
+        hipLaunchKernelGGL(k_copy_runs<kCopyBlock>, dim3(blocks), dim3(kCopyBlock), 0, s, runs);
     return hipGetLastError();
 }
 
@@ -1059,12 +1070,13 @@ __global__ __launch_bounds__(kBlock) void k_ctx(const Piece* pieces_g, uint8_t* 
 // the first n_pieces workgroups move small-state pieces (save, or save + restore per byte in one
 // lane), all others are the staging copy of the outgoing EST's gradient runs.  The two parts touch
 // disjoint memory, so no ordering between them is needed inside the launch.
-__global__ __launch_bounds__(kCopyBlock) void k_est_boundary(const CopyRuns runs, const Piece* pieces_g,
+template <uint32_t BS>
+__global__ __launch_bounds__(BS) void k_est_boundary(const CopyRuns runs, const Piece* pieces_g,
                                                              uint32_t n_pieces, uint8_t* slot_a,
                                                              const uint8_t* slot_b, int dir)
 {
     if (blockIdx.x < n_pieces) {
-        ctx_piece<kCopyBlock>((const Piece ES_CONST_AS*)pieces_g, blockIdx.x, slot_a, slot_b, dir);
+        ctx_piece<BS>((const Piece ES_CONST_AS*)pieces_g, blockIdx.x, slot_a, slot_b, dir);
         return;
     }
     const uint32_t blk = blockIdx.x - n_pieces;
@@ -1073,7 +1085,7 @@ __global__ __launch_bounds__(kCopyBlock) void k_est_boundary(const CopyRuns runs
 #pragma unroll
         for (int k = 1; k < kMaxRuns; ++k) r += blk >= runs.first_block[k] ? 1u : 0u;
     }
-    copy_span(runs.dst[r], runs.src[r], runs.n[r], blk - runs.first_block[r], threadIdx.x, kCopyBlock);
+    copy_span<BS>(runs.dst[r], runs.src[r], runs.n[r], blk - runs.first_block[r], threadIdx.x);
 }
 
 hipError_t launch_est_boundary(hipStream_t s, const CopyRuns& runs, const Piece* pieces, uint32_t n_pieces,
@@ -1081,8 +1093,12 @@ hipError_t launch_est_boundary(hipStream_t s, const CopyRuns& runs, const Piece*
 {
     const uint32_t copy_blocks = runs.n_runs ? runs.first_block[runs.n_runs] : 0;
     if (n_pieces + copy_blocks == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_est_boundary, dim3(n_pieces + copy_blocks), dim3(kCopyBlock), 0, s, runs, pieces,
-                       n_pieces, slot_a, slot_b, (int)dir);
+    if (runs.block == kCopyBlockShort)
+        hipLaunchKernelGGL(k_est_boundary<kCopyBlockShort>, dim3(n_pieces + copy_blocks), dim3(kCopyBlockShort), 0, s,
+                           runs, pieces, n_pieces, slot_a, slot_b, (int)dir);
+    else
+        hipLaunchKernelGGL(k_est_boundary<kCopyBlock>, dim3(n_pieces + copy_blocks), dim3(kCopyBlock), 0, s, runs,
+                           pieces, n_pieces, slot_a, slot_b, (int)dir);
     return hipGetLastError();
 }
 
