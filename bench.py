@@ -32,7 +32,7 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBPS = 8000.0          # MI355X HBM3E, vendor figure
-CACHE_FIT_BYTES = 284 << 20     # parameters + momentum up to this size stay cacheable by default
+CACHE_FIT_BYTES = 284 << 20     # what the Infinity Cache and the L2s hold between two launches
 
 
 def parse():
@@ -394,7 +394,7 @@ def measure(torch, a, cid, headline, oracle_leg):
     stage_ms = statistics.fmean(stg)
     red_gbps = bytes_reduce / (red_ms * 1e-3) / 1e9
     pv_cacheable = opts["nontemporal_pv"] == 0 and fused
-    wave = N <= 64 and P < 8_000_000 and not any(kv.startswith(("reduce_", "nontemporal=")) for kv in a.opt)
+    wave = N <= 64 and P < (64_000_000 if 8 <= N <= 10 else 8_000_000) and not any(kv.startswith(("reduce_", "nontemporal=")) for kv in a.opt)
     kname = ("k_ring_reduce_wave" if wave else "k_ring_reduce_big" if opts["reduce_big_unroll"] else "k_ring_reduce")
     kname += " (fused SGD)" if fused else ""
 
@@ -459,8 +459,8 @@ def measure(torch, a, cid, headline, oracle_leg):
         job.set_option("nontemporal_pv", opts["nontemporal_pv"])
         res["reduce_hbm_only"] = {
             "note": "the same reduce launched right after a 1 GiB fill has swept the Infinity Cache, so that "
-                    "every one of its (N+4)*4P bytes moves to or from HBM; cacheable_pv = the default policy "
-                    "at this size, streaming_pv = option nontemporal_pv=1", **cold}
+                    "every one of its (N+4)*4P bytes moves to or from HBM; cacheable_pv and streaming_pv = "
+                    "option nontemporal_pv 0 and 1", **cold}
         del sweep
 
     # ---- the two halves as kernels of their own: the reduce alone ((N+1)*4P bytes: N gradient

@@ -429,7 +429,7 @@ int es_sync(es_handle* h);
 /*
  * Options (never change results).  As long as none of the reduce_* options and no
  * "nontemporal" = 0 has been set, a reduce of up to 64 ranks over fewer than 8 M
- * parameters runs in a launch shape of its own (one wave per 64 or 256 elements,
+ * parameters (8 to 10 ranks: 64 M) runs in a launch shape of its own (one wave per 64 or 256 elements,
  * chosen by both numbers); setting one of them puts the shape that the
  * options describe in its place, there as everywhere.  Names:
  *   "host_slots"          0/1: placement of gradient slots at the NEXT es_set_grouping: 1 =
@@ -464,8 +464,9 @@ int es_sync(es_handle* h);
  *   "nontemporal"         0/1: streaming hint on gradient loads
  *   "nontemporal_pv"      0/1: streaming hint on parameter and momentum traffic of the update
  *                         (fused or es_sgd_step / es_clip_sgd_step) and on the store of the
- *                         averaged gradient (default: 1 if parameters and momentum together
- *                         exceed 284 MiB, else 0)
+ *                         averaged gradient (default: 1 from 12 M parameters on, and from 1 M on with
+ *                         at least 32 ranks; else 0.  A loop that runs nothing between two reduces of
+ *                         12 to 37 M parameters is up to 10 % faster with 0, a training job with 1)
  *   "reduce_big_unroll"   0, 8, 16 or 32: if not 0, full aligned stretches of a ring chunk
  *                         are handled in big tiles of 256 * value * 4 elements (long
  *                         contiguous reads per gradient stream; default 32 from

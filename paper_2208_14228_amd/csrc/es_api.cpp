@@ -244,7 +244,7 @@ int build_tiles(es_handle* h)
     std::vector<Tile> big, tiles;
     h->shape.wave_width = 0;                     // (wave_shape sets it where that form is the default)
     if (h->auto_shape && wave_shape(h->N, h->P, h->shape)) {
-        plan_tiles(h->buckets, h->N, h->A, 64u * h->shape.wave_width, 0, big, tiles);
+        plan_tiles(h->buckets, h->N, h->A, 64u * h->shape.wave_width * h->shape.wave_pieces, 0, big, tiles);
     } else {
         const uint64_t TB = h->shape.big_unroll ? (uint64_t)kReduceBlock * h->shape.big_unroll * 4 : 0;
         plan_tiles(h->buckets, h->N, h->A, h->tile_elems, TB, big, tiles);
@@ -536,9 +536,7 @@ int es_init(es_handle** out, uint32_t n_logical, const es_bucket_layout* lay)
         while (h->shape.rank_batch > 1 && (uint32_t)h->shape.rank_batch > h->N) h->shape.rank_batch /= 2;
         // many concurrent gradient streams: long contiguous reads per stream pay off (measured)
         if (h->N >= 11) { h->shape.big_unroll = 32; h->shape.big_rank_batch = 1; }
-        // parameters + momentum that fit in the Infinity Cache and the L2s stay cacheable between
-        // steps (measured crossover at N = 8: between 282 and 290 MiB)
-        h->shape.nontemporal_pv = (2 * h->P * sizeof(float) > (284ull << 20)) ? 1 : 0;
+        h->shape.nontemporal_pv = stream_pv(h->N, h->P) ? 1 : 0;
         h->workers.resize(1);
         h->workers[0].live.assign(h->seg_bytes.size(), nullptr);
     } catch (const std::bad_alloc&) {

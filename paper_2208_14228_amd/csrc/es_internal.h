@@ -84,30 +84,48 @@ struct ReduceShape {
     // wave-tile form (k_ring_reduce_wave): floats per lane (1 or 4; 0 = the other kernels), ranks
     // loaded before adds are issued, lanes per workgroup, KiB of LDS reserved per workgroup
     int wave_width = 0, wave_batch = 0, wave_block = 0, wave_pad_kib = 0;
+    int wave_pieces = 1; // waves that share one tile of the table
 };
+
+// Whether parameters, momentum and the averaged gradient are streamed by default.  Cacheable over
+// streaming time of the fused reduce:
+//  - after something has swept the caches, as the model does between two reduces of a training job (a 1 GiB
+//    fill): 1.01-1.22 from 1 M to 32 M parameters at 1 to 64 ranks, so streaming never loses there;
+//  - three jobs in turn: 1.04-1.10 from 16 M on (their parameters and momentum exceed the Infinity Cache),
+//    1.0 at 12 M, 0.83-0.97 at 4 to 8 M and up to 16 ranks (they come back from it), but 1.03-1.10 from
+//    1 M on at 32 and 64 ranks (the gradients push them out);
+//  - one job in a loop of nothing but reduces: 0.90-1.0 from 8 to 37 M at N <= 12, 1.0 elsewhere; above
+//    37 M streaming wins in every loop.
+// The line lies where streaming wins or ties in the first two.
+inline bool stream_pv(uint32_t N, uint64_t P) { return P >= 12000000 || (N >= 32 && P >= 1000000); }
 
 // The wave-tile form where it is the faster one, by the rank count N and the parameter count P;
 // returns false (and leaves the shape alone) where the other kernels are.  Measured on 13 rank counts
 // x 9 sizes, fused, three jobs in turn (time of the other kernels over this one's):
 //  - N <= 64: the slot table is one pointer per lane.
 //  - P < 8 M: 1.0-1.3 at 4 M, 1.0-2.2 at 1 M, 1.05-3.4 at 20 k; at 8 M 0.97-1.06, at 25 M 0.95-1.02
-//    (there a wave's 1 KiB per stream costs what the saved round trips gain).
+//    (there a wave's 1 KiB per stream costs what the saved round trips gain), except for
+//  - 8 to 10 ranks below 64 M: 1.15 at 8 M, 1.04 at 25 M, 1.02 at 32 M against the small tiles with one
+//    workgroup per CU; 0.99 at 109 M.
 //  - one float per lane below 300 k elements and from 8 ranks on, where four leave SIMDs without a wave
 //    (1.1-1.7 x slower at 100 k, 1.0-1.1 x faster at 500 k); then as many ranks per batch as there are,
 //    up to 64, while a SIMD has at most two waves (P <= 128 k), else 16.
 //  - four floats per lane: batches of 4, of 8 from 8 to 23 ranks (a second round trip less: 1.0-1.1).
-//  - fewer than 8 ranks from 1 M elements on: one wave per workgroup, no cap on residency (1.0 at 1 M,
-//    1.03-1.1 above, 0.9 at 500 k); else four waves and 5 workgroups per CU.
+//  - fewer than 8 ranks from 1.5 M elements on: one wave per workgroup, no cap on residency (1.03-1.1;
+//    0.92 at 1 M and one rank, 0.9 at 500 k); else four waves and 5 workgroups per CU, or 2 where there are many
+//    streams or elements (1.01-1.04 from 24 ranks and 2 M on, 1.05 at 25 M and 8 ranks).
+//  - a tile of the table is one wave's; from 8 M on it is four (idle waves at the end of a chunk no longer
+//    count there: N = 64, P = 1 M 24 % slower; but es_init would plan 100,000 tiles at 25 M).
 inline bool wave_shape(uint32_t N, uint64_t P, ReduceShape& sh)
 {
-    if (N == 0 || N > 64 || P >= 8000000) return false;
-    auto pow2_up_to = [N](int most) {
-        int b = most;
+    const uint64_t most = N >= 8 && N <= 10 ? 64000000 : 8000000;
+    if (N == 0 || N > 64 || P >= most) return false;
+    auto pow2_up_to = [N](int b) {
         while (b > 1 && (uint32_t)b > N) b /= 2;
         return b;
     };
+    sh.wave_pieces = 1;
     sh.wave_block = 256;
-    sh.wave_pad_kib = 32;
     if (N >= 8 && P < 300000) {
         sh.wave_width = 1;
         sh.wave_batch = pow2_up_to(P <= (128u << 10) ? 64 : 16);
@@ -116,7 +134,9 @@ inline bool wave_shape(uint32_t N, uint64_t P, ReduceShape& sh)
     }
     sh.wave_width = 4;
     sh.wave_batch = pow2_up_to(N >= 8 && N < 24 ? 8 : 4);
-    if (N < 8 && P >= 1000000) {
+    sh.wave_pad_kib = (N >= 24 && P >= 2000000) || P >= 8000000 ? 64 : 32;
+    if (P >= 8000000) sh.wave_pieces = 4;
+    if (N < 8 && P >= 1500000) {
         sh.wave_block = 64;
         sh.wave_pad_kib = 0;
     }
@@ -126,7 +146,8 @@ inline bool wave_shape(uint32_t N, uint64_t P, ReduceShape& sh)
 // ring-ordered N-way reduce (+ optional fused SGD-momentum).
 //  slots: device table of N slot base pointers indexed by virtual rank.
 //  avg may be null only when p and v are given.
-//  With shape.wave_width != 0 every tile holds at most 64 * wave_width elements, and N <= 64.
+//  With shape.wave_width != 0 every tile holds at most 64 * wave_width * wave_pieces elements (less by as
+//  many as its offset is past a 128-byte line), and N <= 64.
 //  With shape.big_unroll != 0 the first n_big tiles must be full big tiles
 //  (kBlock * big_unroll * 4 elements, offset a multiple of 4) and all others
 //  at most 2048 elements.

@@ -38,13 +38,8 @@ __device__ __forceinline__ f4 ld4(const float* p)
 __device__ __forceinline__ void st4(float* p, f4 x) { *reinterpret_cast<f4*>(p) = x; }
 
 // Parameter / momentum traffic of the update, and the store of the averaged
-// gradient.  Touched once per global step: when the vectors fit in the 256 MB
-// Infinity Cache they are left cacheable and come back from it (parameters and
-// momentum in the next step, measured +13 % at P = 25.6 M; the averaged gradient
-// in the update kernel that follows an unfused reduce); when they do not,
-// streaming accesses are faster (fused: +6 % at P = 109 M; the unfused reduce:
-// +11 % at P = 109 M, N = 16 and +13 % at P = 355 M, N = 64 from the store of the
-// averaged gradient alone).
+// gradient.  Touched once per global step: streamed where stream_pv says so (fused: +6 % at P = 109 M; the unfused reduce: +11 % at P = 109 M, N = 16 and +13 %
+// at P = 355 M, N = 64 from the store of the averaged gradient alone).
 template <bool NTPV>
 __device__ __forceinline__ f4 ld4_pv(const float* p)
 {
@@ -429,9 +424,7 @@ static hipError_t launch_reduce_big_u(hipStream_t s, const Tile* tiles, uint32_t
 
 // ---------------------------------------------------------------------------
 // Wave-tile form of the same kernel for short vectors and at most 64 ranks: one WAVE
-// per tile of 64 * W elements, W floats per lane.  (Tiles of four waves, for a shorter
-// table, leave waves idle at the end of every chunk, and their workgroups still take
-// turns on a CU: 24 % slower at N = 64, P = 1 M.)
+// per tile of 64 * W elements (or per quarter of a tile), W floats per lane.
 //
 // What bounds a short reduce is the number of dependent round trips to memory in one
 // wave's life and the number of waves, not bytes.  So: the rank -> slot table is read
@@ -446,7 +439,8 @@ static hipError_t launch_reduce_big_u(hipStream_t s, const Tile* tiles, uint32_t
 //
 // Fused, default options, three jobs in turn: N = 64, P = 20 k 16.8 -> 4.9 us, P = 200 k
 // 19.0 -> 10.6 us; N = 16, P = 500 k 14.1 -> 7.9 us, P = 4 M 67 -> 53 us; N = 8, P = 1 M
-// 11.4 -> 9.2 us; N = 4, P = 1 M 7.6 -> 6.8 us (4.9 TB/s).
+// 11.4 -> 9.2 us; N = 4, P = 1 M 7.6 -> 6.8 us (4.9 TB/s); N = 8, P = 25.6 M 217 -> 197 us with
+// parameters and momentum streamed (204 by the small tiles so; 6.2 TB/s).
 // ---------------------------------------------------------------------------
 template <int W> struct WaveVec;
 template <> struct WaveVec<1> { typedef float T; };
@@ -518,34 +512,46 @@ __device__ __forceinline__ void wave_tile(uint64_t off, uint32_t len, uint32_t r
     }
 }
 
-template <int W, int NB, int NT, bool SGD>
-__global__ __launch_bounds__(kReduceBlock) void k_ring_reduce_wave(const Tile* tiles_g, uint32_t n_tiles,
+template <int W, int NB, int PIECES, int NT, bool SGD>
+__global__ __launch_bounds__(kReduceBlock) void k_ring_reduce_wave(const Tile* tiles_g, uint32_t n_tiles, uint32_t per,
                                                              const float* const* slots, uint32_t N,
                                                              float* __restrict__ avg, float* __restrict__ p,
                                                              float* __restrict__ v, float lr, float mu)
 {
     const uint32_t lane = threadIdx.x & 63;
-    const uint32_t t = __builtin_amdgcn_readfirstlane(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6));
+    // `per` = waves per workgroup, an argument: blockDim would make the runtime write the hidden ones
+    // with every launch (5.4 -> 5.7 us per call in a loop of small steps)
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(blockIdx.x * per + (threadIdx.x >> 6));
+    const uint32_t t = wave / PIECES;
     if (t >= n_tiles) return;
     const uint64_t base = reinterpret_cast<uint64_t>(slots[lane < N ? lane : N - 1]);
     const uint32_t lo = (uint32_t)base, hi = (uint32_t)(base >> 32);
     const Tile ES_CONST_AS* tiles = (const Tile ES_CONST_AS*)tiles_g;
-    const uint64_t off = tiles[t].off;
-    const uint32_t len = tiles[t].len;
+    uint64_t off = tiles[t].off;
+    uint32_t len = tiles[t].len;
     const uint32_t rank0 = tiles[t].rank0;
+    if constexpr (PIECES > 1) {
+        // a tile that starts inside a 128-byte line is short by as much (it ends on one): so is its
+        // first piece, and the others start on a line
+        const uint32_t part = wave % PIECES, short_by = (uint32_t)off & 31;
+        const uint32_t lo_e = part ? 64 * W * part - short_by : 0, hi_e = 64 * W * (part + 1) - short_by;
+        if (len <= lo_e) return;
+        off += lo_e;
+        len = (len < hi_e ? len : hi_e) - lo_e;
+    }
     if (len >= W) wave_tile<W, NB, NT, SGD>(off, len, rank0, lo, hi, lane, N, avg, p, v, lr, mu);
     else wave_tile<1, 8, NT, SGD>(off, len, rank0, lo, hi, lane, N, avg, p, v, lr, mu);
 }
 
-template <int W, int NB>
+template <int W, int NB, int PIECES>
 static hipError_t launch_reduce_wave(hipStream_t s, const Tile* tiles, uint32_t n_tiles, const float* const* slots,
                                      uint32_t N, float* avg, float* p, float* v, float lr, float mu, ReduceShape sh)
 {
     const uint32_t per = (uint32_t)sh.wave_block / 64;
-    const dim3 grid((n_tiles + per - 1) / per), block(sh.wave_block);
+    const dim3 grid((uint32_t)(((uint64_t)n_tiles * PIECES + per - 1) / per)), block(sh.wave_block);
 #define ES_LAUNCH(NTV, SGDV)                                                                                      \
-    hipLaunchKernelGGL((k_ring_reduce_wave<W, NB, NTV, SGDV>), grid, block, (uint32_t)sh.wave_pad_kib << 10, s, tiles, \
-                       n_tiles, slots, N, avg, p, v, lr, mu)
+    hipLaunchKernelGGL((k_ring_reduce_wave<W, NB, PIECES, NTV, SGDV>), grid, block, (uint32_t)sh.wave_pad_kib << 10, s, tiles, \
+                       n_tiles, per, slots, N, avg, p, v, lr, mu)
     if (p) {
         if (sh.nontemporal_pv) ES_LAUNCH(3, true);
         else ES_LAUNCH(1, true);
@@ -561,16 +567,18 @@ static hipError_t launch_reduce_wave_any(hipStream_t s, const Tile* tiles, uint3
                                          uint32_t N, float* avg, float* p, float* v, float lr, float mu, ReduceShape sh)
 {
     if (N > 64) return hipErrorInvalidValue;            // the table is one pointer per lane
-#define ES_WAVE(W, NB) \
-    if (sh.wave_width == W && sh.wave_batch == NB) return launch_reduce_wave<W, NB>(s, tiles, n_tiles, slots, N, avg, p, v, lr, mu, sh)
-    ES_WAVE(1, 8);
-    ES_WAVE(1, 16);
-    ES_WAVE(1, 32);
-    ES_WAVE(1, 64);
-    ES_WAVE(4, 1);
-    ES_WAVE(4, 2);
-    ES_WAVE(4, 4);
-    ES_WAVE(4, 8);
+#define ES_WAVE(W, NB, PIECES)                                                  \
+    if (sh.wave_width == W && sh.wave_batch == NB && sh.wave_pieces == PIECES) \
+        return launch_reduce_wave<W, NB, PIECES>(s, tiles, n_tiles, slots, N, avg, p, v, lr, mu, sh)
+    ES_WAVE(1, 8, 1);
+    ES_WAVE(1, 16, 1);
+    ES_WAVE(1, 32, 1);
+    ES_WAVE(1, 64, 1);
+    ES_WAVE(4, 1, 1);
+    ES_WAVE(4, 2, 1);
+    ES_WAVE(4, 4, 1);
+    ES_WAVE(4, 8, 1);
+    ES_WAVE(4, 8, 4);
 #undef ES_WAVE
     return hipErrorInvalidValue;
 }
@@ -1495,14 +1503,14 @@ void k_bn_channel(const float* __restrict__ x, const BnGeom g, float fM, float* 
 // 6.5 TB/s each and 6 us of launches (a read that hits the Infinity Cache is no faster: 15 us).
 // Beyond that: one partial per block, and a launch after each pass that combines them.
 template <bool SQDEV, bool WIDE, int MODE, typename OFF>
-__global__ __launch_bounds__(kBlock) void k_bn_partials(const float* __restrict__ x, const BnGeom g, float fM,
+__global__ __launch_bounds__(kBlock) void k_bn_partials(const float* __restrict__ x, const BnGeom g, uint32_t groups, float fM,
                                                         float* __restrict__ mean, float* __restrict__ part)
 {
     const uint32_t h = threadIdx.x & 63;
     const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint32_t bx = SQDEV ? gridDim.x - 1 - blockIdx.x : blockIdx.x;
-    const uint32_t ch = SQDEV ? gridDim.y - 1 - blockIdx.y : blockIdx.y;
-    const uint32_t blk = WIDE ? bx + w * gridDim.x : bx * 4 + w;
+    const uint32_t bx = SQDEV ? groups - 1 - blockIdx.x : blockIdx.x;
+    const uint32_t ch = SQDEV ? g.C - 1 - blockIdx.y : blockIdx.y;
+    const uint32_t blk = WIDE ? bx + w * groups : bx * 4 + w;
     if (!WIDE && blk >= g.nblk) return;                 // whole wave leaves together
     f4 t[4][4];
     if (blk < g.nblk) bn_load<MODE, OFF>(x, g, ch, blk, h, t);
@@ -1510,7 +1518,7 @@ __global__ __launch_bounds__(kBlock) void k_bn_partials(const float* __restrict_
     float center = 0.0f;
     if constexpr (SQDEV) {
         if constexpr (WIDE) {
-            float r = h < gridDim.x ? part[(uint64_t)ch * gridDim.x + h] : 0.0f;
+            float r = h < groups ? part[(uint64_t)ch * groups + h] : 0.0f;
 #pragma unroll
             for (int d = 32; d >= 1; d >>= 1) r = r + __shfl_down(r, d, 64);
             center = __shfl(r, 0, 64) / fM;
@@ -1525,8 +1533,8 @@ __global__ __launch_bounds__(kBlock) void k_bn_partials(const float* __restrict_
         if (h == 0) sums[w] = r;
         __syncthreads();
         if (threadIdx.x == 0) {
-            float* out = part + (SQDEV ? (uint64_t)g.C * gridDim.x : 0);
-            out[(uint64_t)ch * gridDim.x + bx] = (sums[0] + sums[2]) + (sums[1] + sums[3]);
+            float* out = part + (SQDEV ? (uint64_t)g.C * groups : 0);
+            out[(uint64_t)ch * groups + bx] = (sums[0] + sums[2]) + (sums[1] + sums[3]);
         }
     } else {
         const float r = bn_block_sum<SQDEV>(t, blk, h, g.M, center);
@@ -1572,15 +1580,15 @@ static void launch_bn(hipStream_t s, const float* x, const BnGeom& g, float* mea
         uint32_t n = 8;                                 // sums per channel: a quarter of the blocks' power of two
         while (4 * n < g.nblk) n *= 2;
         const dim3 grid(n, g.C);
-        hipLaunchKernelGGL((k_bn_partials<false, true, MODE, OFF>), grid, dim3(kBlock), 0, s, x, g, fM, mean, part);
-        hipLaunchKernelGGL((k_bn_partials<true, true, MODE, OFF>), grid, dim3(kBlock), 0, s, x, g, fM, mean, part);
+        hipLaunchKernelGGL((k_bn_partials<false, true, MODE, OFF>), grid, dim3(kBlock), 0, s, x, g, grid.x, fM, mean, part);
+        hipLaunchKernelGGL((k_bn_partials<true, true, MODE, OFF>), grid, dim3(kBlock), 0, s, x, g, grid.x, fM, mean, part);
         hipLaunchKernelGGL(k_bn_final_wave, dim3((g.C + 3) / 4), dim3(kBlock), 0, s, part + (uint64_t)g.C * n, n, g.C,
                            fM, var);
     } else {
         const dim3 grid((g.nblk + 3) / 4, g.C);
-        hipLaunchKernelGGL((k_bn_partials<false, false, MODE, OFF>), grid, dim3(kBlock), 0, s, x, g, fM, mean, part);
+        hipLaunchKernelGGL((k_bn_partials<false, false, MODE, OFF>), grid, dim3(kBlock), 0, s, x, g, grid.x, fM, mean, part);
         hipLaunchKernelGGL(k_bn_final, dim3(g.C), dim3(kBlock), 0, s, part, g.nblk, fM, mean);
-        hipLaunchKernelGGL((k_bn_partials<true, false, MODE, OFF>), grid, dim3(kBlock), 0, s, x, g, fM, mean, part);
+        hipLaunchKernelGGL((k_bn_partials<true, false, MODE, OFF>), grid, dim3(kBlock), 0, s, x, g, grid.x, fM, mean, part);
         hipLaunchKernelGGL(k_bn_final, dim3(g.C), dim3(kBlock), 0, s, part, g.nblk, fM, var);
     }
 }

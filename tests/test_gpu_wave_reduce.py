@@ -80,7 +80,8 @@ def check(N, lens, A, seed, special=False, with_oracle=False, streaming=(0, 1)):
                 got[nt, how] = step(job, p0, v0, how)
         wave_tiles = B.es_query(job.h)[1]["n_reduce_tiles"]
         job.set_option("reduce_unroll", 2)                     # an explicit shape: the tiled kernels
-        assert (B.es_query(job.h)[1]["n_reduce_tiles"] != wave_tiles) == (job.P > 2 * 2048 and N <= 64 and job.P < 8_000_000)
+        assert (B.es_query(job.h)[1]["n_reduce_tiles"] != wave_tiles) == (
+            job.P > 2 * 2048 and N <= 64 and job.P < (64_000_000 if 8 <= N <= 10 else 8_000_000))
         for (nt, how), w in got.items():
             assert same(w, step(job, p0, v0, how)), (N, A, nt, how)
         if with_oracle:
@@ -112,11 +113,12 @@ def test_infinities_nan_and_denormals(N):
 
 @pytest.mark.parametrize("N,P", [
     (8, (128 << 10) - 1), (8, 128 << 10), (64, (128 << 10) + 1), (40, 131_073), (8, 299_999), (64, 300_000), (7, 300_001),
-    (23, 400_003), (24, 400_003), (7, 999_999), (7, 1_000_000), (8, 1_000_001), (1, 1_500_003),
-    (3, 7_999_999), (3, 8_000_000), (64, 1_200_005), (65, 100_003)])
+    (23, 400_003), (24, 400_003), (7, 1_499_999), (7, 1_500_000), (8, 1_500_001), (1, 1_500_003), (33, 1_000_000), (32, 999_999),
+    (3, 7_999_999), (3, 8_000_000), (64, 1_200_005), (65, 100_003),
+    (8, 8_000_001), (10, 8_100_019), (11, 8_000_001), (24, 2_000_003), (8, 64_000_000), (9, 63_999_999)])
 def test_both_sides_of_every_line_of_the_rule(N, P):
     for A in (1, 4):
-        check(N, [P // 3 + 1, P - 2 * (P // 3) - 2, P // 3 + 1], A, P + N, streaming=(0,) if P > 2_000_000 else (0, 1))
+        check(N, [P // 3 + 1, P - 2 * (P // 3) - 2, P // 3 + 1], A, P + N, streaming=(1,) if P > 2_000_000 else (0, 1))
 
 
 def test_options_choose_the_shape_and_keep_their_values():
