@@ -831,25 +831,26 @@ int validate_batch(const es_handle* h, uint32_t est, uint32_t n, const uint32_t*
     return ES_OK;
 }
 
-// Staging copies as launches of at most kMaxRuns contiguous runs each.
+// Staging copies as launches of at most kMaxRuns contiguous runs each.  The first launch, all there is
+// for up to 16 runs, lives in the object: a boundary call allocates nothing.
 struct RunBuilder {
-    std::vector<CopyRuns> launches;
+    CopyRuns first;
+    std::vector<CopyRuns> more;
+    size_t n_launches = 0;
     uint32_t block;                          // lanes per workgroup: one size for the whole call
     explicit RunBuilder(uint64_t floats) : block(copy_block(floats)) {}
+    bool empty() const { return n_launches == 0; }
+    const CopyRuns& launch(size_t k) const { return k ? more[k - 1] : first; }
     void add(float* dst, const float* src, uint64_t len)
     {
-        if (launches.empty()) open();
-        CopyRuns* r = &launches.back();
+        CopyRuns* r = empty() ? open() : more.empty() ? &first : &more.back();
         // extend the previous run when source and destination both continue it
         if (r->n_runs && r->src[r->n_runs - 1] + r->n[r->n_runs - 1] == src &&
             r->dst[r->n_runs - 1] + r->n[r->n_runs - 1] == dst &&
             r->first_block[r->n_runs - 1] + blocks_of(r->n[r->n_runs - 1] + len) <= 0x7fffffffull) {
             r->n[r->n_runs - 1] += len;
         } else {
-            if (r->n_runs == (uint32_t)kMaxRuns || r->first_block[r->n_runs] + blocks_of(len) > 0x7fffffffull) {
-                open();
-                r = &launches.back();
-            }
+            if (r->n_runs == (uint32_t)kMaxRuns || r->first_block[r->n_runs] + blocks_of(len) > 0x7fffffffull) r = open();
             r->dst[r->n_runs] = dst;
             r->src[r->n_runs] = src;
             r->n[r->n_runs] = len;
@@ -862,14 +863,14 @@ struct RunBuilder {
         const uint64_t blocks = ((len >> 2) + block - 1) / block;
         return blocks ? blocks : 1;
     }
-    void open()
+    CopyRuns* open()
     {
-        launches.emplace_back();
-        CopyRuns& r = launches.back();
-        r.n_runs = 0;
-        r.block = block;
-        for (int k = 0; k <= kMaxRuns; ++k) r.first_block[k] = 0xFFFFFFFFu;   // "no run starts here"
-        r.first_block[0] = 0;
+        if (n_launches) more.emplace_back();
+        CopyRuns* r = n_launches++ ? &more.back() : &first;
+        std::memset(r, 0, sizeof(*r));
+        r->block = block;
+        for (int k = 1; k <= kMaxRuns; ++k) r->first_block[k] = 0xFFFFFFFFu;   // "no run starts here"
+        return r;
     }
 };
 
@@ -892,8 +893,8 @@ void collect_runs(es_handle* h, uint32_t est, uint32_t n, const uint32_t* bucket
 
 int enqueue_staging(es_handle* h, const RunBuilder& rb, bool dma, size_t first_launch = 0)
 {
-    for (size_t k = first_launch; k < rb.launches.size(); ++k) {
-        const CopyRuns& r = rb.launches[k];
+    for (size_t k = first_launch; k < rb.n_launches; ++k) {
+        const CopyRuns& r = rb.launch(k);
         if (!dma) {
             ES_HIP(h, launch_copy_runs(h->s_stage, r));
             continue;
@@ -922,7 +923,7 @@ try {
     if (rc != ES_OK) return rc;
     RunBuilder rb(batch_floats(h, n, buckets));
     collect_runs(h, est, n, buckets, d_grad_buckets, rb);
-    if (!rb.launches.empty()) {
+    if (!rb.empty()) {
         if ((rc = order_after(h, h->s_stage, h->s_main, h->ev_main)) != ES_OK) return rc;
         if ((rc = enqueue_staging(h, rb, dma_staging(h, est))) != ES_OK) return rc;
         h->stage_pending = true;
@@ -956,7 +957,7 @@ try {
     for (uint32_t k = 0; k < n_ests; ++k)
         if (h->P && d_flat_grads[k] != slot_base(h, ests[k]))
             (dma_staging(h, ests[k]) ? rb_dma : rb).add(slot_base(h, ests[k]), d_flat_grads[k], h->P);
-    if (!rb.launches.empty() || !rb_dma.launches.empty()) {
+    if (!rb.empty() || !rb_dma.empty()) {
         int rc = order_after(h, h->s_stage, h->s_main, h->ev_main);
         if (rc == ES_OK) rc = enqueue_staging(h, rb, false);
         if (rc == ES_OK) rc = enqueue_staging(h, rb_dma, true);
@@ -991,7 +992,7 @@ try {
         // fused launch would make main wait for the whole copy.  The copy goes to the stage
         // stream and the small-state switch where es_ctx_switch puts it; main waits for the
         // switch alone.
-        if (!rb.launches.empty()) {
+        if (!rb.empty()) {
             if ((rc = order_after(h, h->s_stage, h->s_main, h->ev_main)) != ES_OK) return rc;
             if ((rc = enqueue_staging(h, rb, dma_staging(h, est_out))) != ES_OK) return rc;
             h->stage_pending = true;
@@ -1005,15 +1006,15 @@ try {
         }
         return ES_OK;
     }
-    if (n_pieces || !rb.launches.empty()) {
+    if (n_pieces || !rb.empty()) {
         // after the outgoing EST's compute on main and after earlier context traffic on the ctx stream
         if ((rc = order_after(h, h->s_stage, h->s_main, h->ev_main)) != ES_OK) return rc;
         if (h->s_ctx != h->s_main && (rc = order_after(h, h->s_stage, h->s_ctx, h->ev_ctx)) != ES_OK) return rc;
         const bool dma = dma_staging(h, est_out);
-        RunBuilder none(0);
-        none.open();
-        if (rb.launches.empty()) rb.open();
-        ES_HIP(h, launch_est_boundary(h->s_stage, dma ? none.launches[0] : rb.launches[0], w.d_pieces, n_pieces,
+        CopyRuns none;                           // no run: the launch moves the pieces only
+        std::memset(&none, 0, sizeof(none));
+        none.block = kCopyBlockShort;
+        ES_HIP(h, launch_est_boundary(h->s_stage, dma || rb.empty() ? none : rb.launch(0), w.d_pieces, n_pieces,
                                       ctx_base(h, est_out), has_in ? ctx_base(h, est_in) : nullptr,
                                       has_in ? kSwitch : kSave));
         if ((rc = enqueue_staging(h, rb, dma, dma ? 0 : 1)) != ES_OK) return rc;

@@ -174,6 +174,11 @@ struct CopyRuns {
     uint32_t     n_runs;
     uint32_t     block;                     // lanes per workgroup the prefix sums count (kCopyBlock or kCopyBlockShort)
 };
+struct CopyRun {                            // the same for a single run
+    float*       dst;
+    const float* src;
+    uint64_t     n;
+};
 hipError_t launch_copy_runs(hipStream_t s, const CopyRuns& runs);
 
 enum CtxDir { kSave = 0, kRestore = 1, kSwitch = 2 };

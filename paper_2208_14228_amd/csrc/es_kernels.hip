@@ -966,10 +966,8 @@ __global__ __launch_bounds__(BS) void k_copy_f4(float* __restrict__ dst, const f
     copy_span<BS>(dst, src, n, blockIdx.x, threadIdx.x);
 }
 
-hipError_t launch_copy_f32(hipStream_t s, float* dst, const float* src, uint64_t n)
+static hipError_t launch_copy(hipStream_t s, float* dst, const float* src, uint64_t n, uint32_t bs)
 {
-    if (n == 0) return hipSuccess;
-    const uint32_t bs = copy_block(n);
     uint64_t blocks = ((n >> 2) + bs - 1) / bs;
     if (blocks == 0) blocks = 1;
     if (bs == kCopyBlockShort)
@@ -977,6 +975,11 @@ hipError_t launch_copy_f32(hipStream_t s, float* dst, const float* src, uint64_t
     else
         hipLaunchKernelGGL(k_copy_f4<kCopyBlock>, dim3((uint32_t)blocks), dim3(bs), 0, s, dst, src, n);
     return hipGetLastError();
+}
+
+hipError_t launch_copy_f32(hipStream_t s, float* dst, const float* src, uint64_t n)
+{
+    return n ? launch_copy(s, dst, src, n, copy_block(n)) : hipSuccess;
 }
 
 // Batched staging: the runs arrive as a kernel argument (no table upload); a
@@ -988,18 +991,18 @@ __global__ __launch_bounds__(BS) void k_copy_runs(const CopyRuns runs)
     // are fetched at once (independent scalar loads of the kernel argument) and compared in
     // registers: a dependent load per run would be most of this short workgroup's life.
     // (Entries past the last run hold 0xFFFFFFFF, so the count needs no bound.)  A single run -
-    // one flat gradient vector, the common case - skips the lookup: it costs 2.7 % there.
+    // one flat gradient vector, the common case - goes to k_copy_f4: the lookup costs 2.7 % there,
+    // and its 24 bytes of arguments are a twentieth of these.
     uint32_t r = 0;
-    if (runs.n_runs > 1) {
 #pragma unroll
-        for (int k = 1; k < kMaxRuns; ++k) r += blockIdx.x >= runs.first_block[k] ? 1u : 0u;
-    }
+    for (int k = 1; k < kMaxRuns; ++k) r += blockIdx.x >= runs.first_block[k] ? 1u : 0u;
     copy_span<BS>(runs.dst[r], runs.src[r], runs.n[r], blockIdx.x - runs.first_block[r], threadIdx.x);
 }
 
 hipError_t launch_copy_runs(hipStream_t s, const CopyRuns& runs)
 {
     if (runs.n_runs == 0) return hipSuccess;
+    if (runs.n_runs == 1) return launch_copy(s, runs.dst[0], runs.src[0], runs.n[0], runs.block);
     const uint32_t blocks = runs.first_block[runs.n_runs];
     if (blocks == 0) return hipSuccess;
     if (runs.block == kCopyBlockShort)
@@ -1078,22 +1081,26 @@ __global__ __launch_bounds__(kBlock) void k_ctx(const Piece* pieces_g, uint8_t* 
 // the first n_pieces workgroups move small-state pieces (save, or save + restore per byte in one
 // lane), all others are the staging copy of the outgoing EST's gradient runs.  The two parts touch
 // disjoint memory, so no ordering between them is needed inside the launch.
-template <uint32_t BS>
-__global__ __launch_bounds__(BS) void k_est_boundary(const CopyRuns runs, const Piece* pieces_g,
-                                                             uint32_t n_pieces, uint8_t* slot_a,
-                                                             const uint8_t* slot_b, int dir)
+// RUNS is CopyRuns, or CopyRun where the gradients are one run (the common case: no lookup, and 24
+// instead of 488 bytes of arguments for the host to write and every workgroup to fetch).
+template <uint32_t BS, typename RUNS>
+__global__ __launch_bounds__(BS) void k_est_boundary(const RUNS runs, const Piece* pieces_g,
+                                                     uint32_t n_pieces, uint8_t* slot_a,
+                                                     const uint8_t* slot_b, int dir)
 {
     if (blockIdx.x < n_pieces) {
         ctx_piece<BS>((const Piece ES_CONST_AS*)pieces_g, blockIdx.x, slot_a, slot_b, dir);
         return;
     }
     const uint32_t blk = blockIdx.x - n_pieces;
-    uint32_t r = 0;
-    if (runs.n_runs > 1) {
+    if constexpr (std::is_same_v<RUNS, CopyRun>) {
+        copy_span<BS>(runs.dst, runs.src, runs.n, blk, threadIdx.x);
+    } else {
+        uint32_t r = 0;
 #pragma unroll
         for (int k = 1; k < kMaxRuns; ++k) r += blk >= runs.first_block[k] ? 1u : 0u;
+        copy_span<BS>(runs.dst[r], runs.src[r], runs.n[r], blk - runs.first_block[r], threadIdx.x);
     }
-    copy_span<BS>(runs.dst[r], runs.src[r], runs.n[r], blk - runs.first_block[r], threadIdx.x);
 }
 
 hipError_t launch_est_boundary(hipStream_t s, const CopyRuns& runs, const Piece* pieces, uint32_t n_pieces,
@@ -1101,12 +1108,18 @@ hipError_t launch_est_boundary(hipStream_t s, const CopyRuns& runs, const Piece*
 {
     const uint32_t copy_blocks = runs.n_runs ? runs.first_block[runs.n_runs] : 0;
     if (n_pieces + copy_blocks == 0) return hipSuccess;
-    if (runs.block == kCopyBlockShort)
-        hipLaunchKernelGGL(k_est_boundary<kCopyBlockShort>, dim3(n_pieces + copy_blocks), dim3(kCopyBlockShort), 0, s,
-                           runs, pieces, n_pieces, slot_a, slot_b, (int)dir);
-    else
-        hipLaunchKernelGGL(k_est_boundary<kCopyBlock>, dim3(n_pieces + copy_blocks), dim3(kCopyBlock), 0, s, runs,
-                           pieces, n_pieces, slot_a, slot_b, (int)dir);
+    const dim3 grid(n_pieces + copy_blocks), block(runs.block);
+#define ES_BOUNDARY(BS, RUNS, R) \
+    hipLaunchKernelGGL((k_est_boundary<BS, RUNS>), grid, block, 0, s, R, pieces, n_pieces, slot_a, slot_b, (int)dir)
+    if (runs.n_runs <= 1) {
+        const CopyRun one{runs.dst[0], runs.src[0], runs.n[0]};   // n_runs = 0: no workgroup gets that far
+        if (runs.block == kCopyBlockShort) ES_BOUNDARY(kCopyBlockShort, CopyRun, one);
+        else ES_BOUNDARY(kCopyBlock, CopyRun, one);
+    } else {
+        if (runs.block == kCopyBlockShort) ES_BOUNDARY(kCopyBlockShort, CopyRuns, runs);
+        else ES_BOUNDARY(kCopyBlock, CopyRuns, runs);
+    }
+#undef ES_BOUNDARY
     return hipGetLastError();
 }
 
