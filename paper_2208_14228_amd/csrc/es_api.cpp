@@ -1319,11 +1319,14 @@ try {
     // an option that names a launch shape leaves the size-dependent default for good: from here on
     // the tile table is the one the options describe
     auto leave_auto = [h] {
-        if (!h->auto_shape) return (int)ES_OK;
-        int rc = sync_all(h);
-        if (rc != ES_OK) return rc;
-        h->auto_shape = false;
-        if (h->shape.wave_width && (rc = build_tiles(h)) != ES_OK) h->auto_shape = true, (void)build_tiles(h);
+        int rc = ES_OK;
+        if (h->auto_shape && h->shape.wave_width) {      // the table in use is the default's: build the other one
+            if ((rc = sync_all(h)) != ES_OK) return rc;
+            h->auto_shape = false;
+            if ((rc = build_tiles(h)) != ES_OK) { h->auto_shape = true; (void)build_tiles(h); }
+        } else {
+            h->auto_shape = false;
+        }
         return rc;
     };
     if (k == "reduce_tile_elems") {
