@@ -619,7 +619,7 @@ def measure(torch, a, cid, headline, oracle_leg):
         job.sync(); torch.cuda.synchronize()
         bn_ms = b0.elapsed_time(b1) / steps
         bn_bytes = 2 * 4 * xbn.numel()
-        res["bn_batch_stats"] = {"note": "k_bn_partials + k_bn_final twice (mean, then variance) on 32x64x112x112 "
+        res["bn_batch_stats"] = {"note": "two passes of k_bn_partials (mean, then variance) and k_bn_final_wave on 32x64x112x112 "
                                          "fp32; bytes = two reads of the activations (the second can come from "
                                          "the Infinity Cache: 103 MB)", "avg_ms": round(bn_ms, 4),
                                  "achieved": round(bn_bytes / (bn_ms * 1e-3) / 1e9, 1), "unit": "GB/s",
