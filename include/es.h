@@ -90,8 +90,10 @@ typedef struct es_bucket_layout {
      *   dev_alloc  returns a DEVICE pointer to `bytes` bytes on the device that is current
      *              at the call, aligned to 256 bytes, or NULL if it cannot (-> ES_ENOMEM);
      *              it must not throw or unwind through the library
-     *   dev_free   releases a pointer dev_alloc returned; called from es_set_grouping and
-     *              es_destroy after the handle's streams have been synchronised
+     *   dev_free   releases a pointer dev_alloc returned; called from es_destroy, es_set_grouping,
+     *              es_bind_live_state, es_set_option (the names that say so there) and, under
+     *              "swap_in", the first reduce after one of these, always with the handle's
+     *              streams synchronised since the last launch that used the memory
      *   user       passed back unchanged
      * The functions must stay callable until es_destroy has returned.  Host-resident
      * slots (option "host_slots") are pinned host memory and never go through them.
@@ -430,8 +432,13 @@ int es_sync(es_handle* h);
  * Options (never change results).  As long as none of the reduce_* options and no
  * "nontemporal" = 0 has been set, a reduce of up to 64 ranks over fewer than 8 M
  * parameters (8 to 10 ranks: 64 M) runs in a launch shape of its own (one wave per 64 or 256 elements,
- * chosen by both numbers); setting one of them puts the shape that the
- * options describe in its place, there as everywhere.  Names:
+ * chosen by both numbers); setting one of them ("reduce_lds_pad_kib" = -1 apart, which asks for
+ * nothing) puts the shape that the options describe in its place, there as everywhere.
+ * "reduce_tile_elems", "reduce_big_unroll", "reduce_big_rank_batch" and "swap_in" wait for the
+ * handle's streams and replace a device table; a launch captured into a graph after an earlier
+ * call of the same kind must be captured again (the tables of es_init stay until es_destroy, so
+ * one captured before the first such call stays valid).  All others only set a field: they take
+ * effect at the next reduce or es_set_grouping and leave captured launches as they are.  Names:
  *   "host_slots"          0/1: placement of gradient slots at the NEXT es_set_grouping: 1 =
  *                         pinned host memory mapped into the device (the paper keeps the
  *                         per-EST gradients in host memory, section 3.2; here it is the

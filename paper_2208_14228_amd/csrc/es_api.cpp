@@ -46,7 +46,14 @@ struct es_handle {
     std::vector<uint32_t> worker_of, slot_of;
     std::vector<Worker> workers;
 
-    Tile* d_tiles = nullptr;
+    // Tile tables of the reduce: the wave-tile form's (where wave_shape chooses that form) and the one the
+    // reduce_* options describe.  The block es_init made, which holds both, stays until es_destroy: a launch
+    // that a caller has captured into a graph keeps its table whatever options are set later.
+    Tile* d_tile_block = nullptr;
+    const Tile* d_wave_tiles = nullptr;         // in the block
+    uint32_t n_wave_tiles = 0;                  // 0: the form is not this job's
+    const Tile* d_tiles = nullptr;              // in the block, or d_tiles_rebuilt
+    Tile* d_tiles_rebuilt = nullptr;            // after an option has changed the decomposition
     uint32_t n_tiles = 0;
     uint32_t n_big = 0;                         // leading big tiles (see k_ring_reduce_big)
     const float** d_slots = nullptr;            // N device pointers, by virtual rank
@@ -239,31 +246,68 @@ void plan_tiles(const std::vector<es_bucket>& buckets, uint32_t N, uint32_t A, u
     }
 }
 
-int build_tiles(es_handle* h)
+// The tile table the reduce_* options describe, behind what `table` holds already.
+int plan_option_tiles(const es_handle* h, std::vector<Tile>& table, uint32_t& n, uint32_t& n_big)
 {
-    std::vector<Tile> big, tiles;
-    h->shape.wave_width = 0;                     // (wave_shape sets it where that form is the default)
-    if (h->auto_shape && wave_shape(h->N, h->P, h->shape)) {
-        plan_tiles(h->buckets, h->N, h->A, 64u * h->shape.wave_width * h->shape.wave_pieces, 0, big, tiles);
-    } else {
-        const uint64_t TB = h->shape.big_unroll ? (uint64_t)kReduceBlock * h->shape.big_unroll * 4 : 0;
-        plan_tiles(h->buckets, h->N, h->A, h->tile_elems, TB, big, tiles);
-    }
-    if (big.size() + tiles.size() > 0x7fffffffull) return ES_EINVAL;
-    h->swap_ready = false;                       // the per-bucket tile tables of the swap-in path follow the same shape
-    h->n_big = (uint32_t)big.size();
-    if (!big.empty()) {
-        big.insert(big.end(), tiles.begin(), tiles.end());
-        tiles.swap(big);
-    }
-    if (h->d_tiles) { dev_release(h, h->d_tiles); h->d_tiles = nullptr; }
-    h->n_tiles = (uint32_t)tiles.size();
-    if (h->n_tiles) {
-        ES_HIP(h, dev_malloc(h, (void**)&h->d_tiles, tiles.size() * sizeof(Tile)));
-        ES_HIP(h, hipMemcpy(h->d_tiles, tiles.data(), tiles.size() * sizeof(Tile), hipMemcpyHostToDevice));
-    }
+    std::vector<Tile> big, small;
+    const uint64_t TB = h->shape.big_unroll ? (uint64_t)kReduceBlock * h->shape.big_unroll * 4 : 0;
+    plan_tiles(h->buckets, h->N, h->A, h->tile_elems, TB, big, small);
+    if (big.size() + small.size() > 0x7fffffffull) return ES_EINVAL;
+    n = (uint32_t)(big.size() + small.size());
+    n_big = (uint32_t)big.size();
+    table.insert(table.end(), big.begin(), big.end());
+    table.insert(table.end(), small.begin(), small.end());
     return ES_OK;
 }
+
+int upload_tiles(es_handle* h, const std::vector<Tile>& table, Tile** out)
+{
+    *out = nullptr;
+    if (table.empty()) return ES_OK;
+    ES_HIP(h, dev_malloc(h, (void**)out, table.size() * sizeof(Tile)));
+    const hipError_t e = hipMemcpy(*out, table.data(), table.size() * sizeof(Tile), hipMemcpyHostToDevice);
+    if (e == hipSuccess) return ES_OK;
+    dev_release(h, *out);
+    *out = nullptr;
+    return hip_fail(h, e);
+}
+
+// es_init: both tables, one block, one copy.
+int build_tile_block(es_handle* h)
+{
+    std::vector<Tile> table, none;
+    if (wave_shape(h->N, h->P, h->shape))
+        plan_tiles(h->buckets, h->N, h->A, 64u * h->shape.wave_width * h->shape.wave_pieces, 0, none, table);
+    if (table.size() > 0x7fffffffull) return ES_EINVAL;
+    const uint32_t n_wave = (uint32_t)table.size();
+    int rc = plan_option_tiles(h, table, h->n_tiles, h->n_big);
+    if (rc == ES_OK) rc = upload_tiles(h, table, &h->d_tile_block);
+    if (rc != ES_OK) return rc;
+    h->d_wave_tiles = h->d_tile_block;
+    h->n_wave_tiles = n_wave;
+    h->d_tiles = h->d_tile_block + n_wave;
+    return ES_OK;
+}
+
+// An option has changed the decomposition.  On failure the table in use stays.
+int rebuild_tiles(es_handle* h)
+{
+    std::vector<Tile> table;
+    uint32_t n = 0, n_big = 0;
+    Tile* d = nullptr;
+    int rc = plan_option_tiles(h, table, n, n_big);
+    if (rc == ES_OK) rc = upload_tiles(h, table, &d);
+    if (rc != ES_OK) return rc;
+    dev_release(h, h->d_tiles_rebuilt);
+    h->d_tiles = h->d_tiles_rebuilt = d;
+    h->n_tiles = n;
+    h->n_big = n_big;
+    h->swap_ready = false;                       // the per-bucket tile tables of the swap-in path follow the same shape
+    return ES_OK;
+}
+
+// Whether the next reduce runs in the wave-tile form.
+bool wave_form(const es_handle* h) { return h->auto_shape && h->n_wave_tiles != 0; }
 
 int validate_layout(uint32_t n_logical, const es_bucket_layout* lay)
 {
@@ -552,7 +596,7 @@ int es_init(es_handle** out, uint32_t n_logical, const es_bucket_layout* lay)
         return ES_EHIP;
     }
     rc = alloc_worker(h, h->workers[0], h->N);
-    if (rc == ES_OK) rc = build_tiles(h);
+    if (rc == ES_OK) rc = build_tile_block(h);
     if (rc == ES_OK) rc = upload_slot_table(h);
     if (rc == ES_OK && h->P) {
         e = dev_malloc(h, (void**)&h->d_partials, ((h->P + 4095) / 4096) * sizeof(float));
@@ -571,7 +615,8 @@ int es_destroy(es_handle* h)
     (void)hipStreamSynchronize(h->s_ctx);
     (void)hipStreamSynchronize(h->s_stage);
     for (Worker& w : h->workers) free_worker(h, w);
-    dev_release(h, h->d_tiles);
+    dev_release(h, h->d_tile_block);
+    dev_release(h, h->d_tiles_rebuilt);
     dev_release(h, (void*)h->d_slots);
     dev_release(h, h->d_partials);
     if (h->s_swap) (void)hipStreamSynchronize(h->s_swap);
@@ -1123,9 +1168,12 @@ static int reduce_common(es_handle* h, float* avg, float* p, float* v, float lr,
     // of the caller's pointers is left as it is until the whole step has been enqueued, so a
     // reduce that failed can be called again and reads the same gradients.
     hipError_t status = patch_table(h, /*to_caller=*/true);
+    const bool wave = wave_form(h);
+    ReduceShape shape = h->shape;
+    if (!wave) shape.wave_width = 0;
     if (status == hipSuccess)
-        status = launch_ring_reduce(h->s_main, h->d_tiles, h->n_tiles, h->n_big, h->d_slots, h->N,
-                                    avg, p, v, lr, mu, h->shape);
+        status = launch_ring_reduce(h->s_main, wave ? h->d_wave_tiles : h->d_tiles, wave ? h->n_wave_tiles : h->n_tiles,
+                                    wave ? 0 : h->n_big, h->d_slots, h->N, avg, p, v, lr, mu, shape);
     const hipError_t restored = patch_table(h, /*to_caller=*/false);
     ES_HIP(h, status);
     ES_HIP(h, restored);
@@ -1316,29 +1364,18 @@ try {
     if (!h || !name) return ES_EINVAL;
     DeviceGuard guard__(h);
     const std::string k(name);
-    // an option that names a launch shape leaves the size-dependent default for good: from here on
-    // the tile table is the one the options describe
-    auto leave_auto = [h] {
-        int rc = ES_OK;
-        if (h->auto_shape && h->shape.wave_width) {      // the table in use is the default's: build the other one
-            if ((rc = sync_all(h)) != ES_OK) return rc;
-            h->auto_shape = false;
-            if ((rc = build_tiles(h)) != ES_OK) { h->auto_shape = true; (void)build_tiles(h); }
-        } else {
-            h->auto_shape = false;
-        }
-        return rc;
-    };
+    // An option that names a launch shape leaves the size-dependent default: the tiled kernels run in that
+    // shape.  Their table is there since es_init, so the options that do not change it set a field and
+    // nothing else: they neither wait, allocate nor free, and may be called while a stream is being captured.
     if (k == "reduce_tile_elems") {
         if (value < 256 || value > 65536 || (value & 3)) return ES_EINVAL;
         int rc = sync_all(h);
         if (rc != ES_OK) return rc;
         const uint32_t old = h->tile_elems;
-        const bool was_auto = h->auto_shape;
         h->tile_elems = (uint32_t)value;
-        h->auto_shape = false;
-        rc = build_tiles(h);
-        if (rc != ES_OK) { h->tile_elems = old; h->auto_shape = was_auto; (void)build_tiles(h); }
+        rc = rebuild_tiles(h);
+        if (rc == ES_OK) h->auto_shape = false;
+        else h->tile_elems = old;
         return rc;
     }
     if (k == "reduce_big_unroll" || k == "reduce_big_rank_batch") {
@@ -1351,35 +1388,34 @@ try {
         const int old = field;
         field = (int)value;
         if (h->shape.big_unroll * h->shape.big_rank_batch > 32) { field = old; return ES_EINVAL; }
-        const bool was_auto = h->auto_shape;
-        h->auto_shape = false;
-        rc = build_tiles(h);
-        if (rc != ES_OK) { field = old; h->auto_shape = was_auto; (void)build_tiles(h); }
+        rc = rebuild_tiles(h);
+        if (rc == ES_OK) h->auto_shape = false;
+        else field = old;
         return rc;
     }
     if (k == "reduce_lds_pad_kib") {
         if (value < -1 || value > 160) return ES_EINVAL;
-        const int rc = value >= 0 ? leave_auto() : ES_OK;
-        if (rc == ES_OK) h->shape.lds_pad_kib = (int)value;
-        return rc;
+        h->shape.lds_pad_kib = (int)value;
+        if (value >= 0) h->auto_shape = false;
+        return ES_OK;
     }
     if (k == "reduce_unroll") {
         if (value != 1 && value != 2 && value != 4) return ES_EINVAL;
-        const int rc = leave_auto();
-        if (rc == ES_OK) h->shape.unroll = (int)value;
-        return rc;
+        h->shape.unroll = (int)value;
+        h->auto_shape = false;
+        return ES_OK;
     }
     if (k == "reduce_rank_batch") {
         if (value != 1 && value != 2 && value != 4 && value != 8 && value != 16) return ES_EINVAL;
-        const int rc = leave_auto();
-        if (rc == ES_OK) h->shape.rank_batch = (int)value;
-        return rc;
+        h->shape.rank_batch = (int)value;
+        h->auto_shape = false;
+        return ES_OK;
     }
     if (k == "nontemporal") {
         if (value != 0 && value != 1) return ES_EINVAL;
-        const int rc = value ? ES_OK : leave_auto();     // the wave-tile form has streaming loads only
-        if (rc == ES_OK) h->shape.nontemporal = (int)value;
-        return rc;
+        h->shape.nontemporal = (int)value;
+        if (!value) h->auto_shape = false;       // the wave-tile form has streaming loads only
+        return ES_OK;
     }
     if (k == "swap_in") {
         if (value != 0 && value != 1) return ES_EINVAL;
@@ -1442,7 +1478,7 @@ int es_query(es_handle* h, uint64_t* n_params, uint32_t* n_buckets, uint64_t* ct
     if (n_buckets) *n_buckets = (uint32_t)h->buckets.size();
     if (ctx_bytes) *ctx_bytes = h->ctx_bytes;
     if (n_workers) *n_workers = (uint32_t)h->workers.size();
-    if (n_reduce_tiles) *n_reduce_tiles = h->n_tiles;
+    if (n_reduce_tiles) *n_reduce_tiles = wave_form(h) ? h->n_wave_tiles : h->n_tiles;
     return ES_OK;
 }
 

@@ -1,0 +1,146 @@
+// Host runtime of libes on a device made of host memory: the HIP calls it uses are defined here and
+// the kernel launchers record what they were given, so a handle's life (tables, options, waits,
+// allocations) can be followed without a GPU.  Test program: argv[1] names the check, exit status 0 = passed.
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <map>
+#include <vector>
+
+#include "es.h"
+#include "es_internal.h"
+
+static std::map<char*, size_t> g_live;          // what the handle holds of the caller's allocator
+static int g_allocs = 0, g_frees = 0, g_waits = 0;
+
+static void* dev_alloc(size_t bytes, void*)
+{
+    void* p = std::aligned_alloc(256, (bytes + 255) / 256 * 256);
+    g_live[(char*)p] = bytes;
+    ++g_allocs;
+    return p;
+}
+static void dev_free(void* p, void*)
+{
+    g_live.erase((char*)p);
+    ++g_frees;
+    std::free(p);
+}
+
+extern "C" {
+hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
+hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t hipMalloc(void** p, size_t n) { *p = std::malloc(n); return hipSuccess; }
+hipError_t hipFree(void* p) { std::free(p); return hipSuccess; }
+hipError_t hipHostMalloc(void** p, size_t n, unsigned) { *p = std::aligned_alloc(256, (n + 255) / 256 * 256); return hipSuccess; }
+hipError_t hipHostFree(void* p) { std::free(p); return hipSuccess; }
+hipError_t hipMemset(void* p, int v, size_t n) { std::memset(p, v, n); return hipSuccess; }
+hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) { std::memcpy(d, s, n); return hipSuccess; }
+hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) { std::memcpy(d, s, n); return hipSuccess; }
+hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { *e = nullptr; return hipSuccess; }
+hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
+hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) { *s = nullptr; return hipSuccess; }
+hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { ++g_waits; return hipSuccess; }
+}
+
+namespace es {
+// What the last reduce was launched with, and a copy of its tiles.
+static const Tile* l_tiles;
+static uint32_t l_n, l_big;
+static ReduceShape l_shape;
+static std::vector<Tile> l_copy;
+
+hipError_t launch_ring_reduce(hipStream_t, const Tile* t, uint32_t n, uint32_t n_big, const float* const*, uint32_t,
+                              float*, float*, float*, float, float, ReduceShape sh)
+{
+    l_tiles = t; l_n = n; l_big = n_big; l_shape = sh;
+    l_copy.assign(t, t + n);
+    return hipSuccess;
+}
+hipError_t launch_sgd(hipStream_t, float*, float*, const float*, uint64_t, float, float, bool) { return hipSuccess; }
+hipError_t launch_copy_f32(hipStream_t, float*, const float*, uint64_t) { return hipSuccess; }
+hipError_t launch_copy_runs(hipStream_t, const CopyRuns&) { return hipSuccess; }
+hipError_t launch_patch_slots(hipStream_t, const float**, const InPlace&) { return hipSuccess; }
+hipError_t launch_ctx(hipStream_t, const Piece*, uint32_t, uint8_t*, const uint8_t*, CtxDir) { return hipSuccess; }
+hipError_t launch_est_boundary(hipStream_t, const CopyRuns&, const Piece*, uint32_t, uint8_t*, const uint8_t*, CtxDir) { return hipSuccess; }
+hipError_t launch_sgd_clip(hipStream_t, float*, float*, const float*, uint64_t, const float*, float, float, float, float, bool) { return hipSuccess; }
+hipError_t launch_bn_batch_stats(hipStream_t, const float*, uint32_t, uint32_t, uint32_t, float*, float*, float*) { return hipSuccess; }
+hipError_t launch_copy_bytes(hipStream_t, uint8_t*, const uint8_t*, uint64_t) { return hipSuccess; }
+hipError_t launch_sq_norm(hipStream_t, const float*, uint64_t, float*, float*) { return hipSuccess; }
+hipError_t launch_sq_norm_static(hipStream_t, const float*, uint64_t, float*) { return hipSuccess; }
+hipError_t launch_dropout_mask(hipStream_t, uint64_t*, uint8_t*, uint64_t, uint64_t) { return hipSuccess; }
+}  // namespace es
+using namespace es;
+
+#define CHECK(c) do { if (!(c)) { std::fprintf(stderr, "check failed at line %d: %s\n", __LINE__, #c); return 1; } } while (0)
+
+struct Job {
+    es_handle* h = nullptr;
+    uint32_t N;
+    uint64_t P;
+    std::vector<float> avg;
+    Job(uint32_t n, uint64_t p) : N(n), P(p), avg(p + 64)
+    {
+        es_bucket b[2] = {{0, p / 3}, {p / 3, p - p / 3}};
+        es_bucket_layout lay = {p, 2, b, 1, 0, nullptr, dev_alloc, dev_free, nullptr};
+        if (es_init(&h, n, &lay) != ES_OK) h = nullptr;
+    }
+    ~Job() { if (h) es_destroy(h); }
+    int reduce()
+    {
+        for (uint32_t e = 0; e < N; ++e) {
+            const float* g = es_grad_slot(h, e, 0);
+            const int rc = es_accumulate_many(h, 1, &e, &g);
+            if (rc != ES_OK) return rc;
+        }
+        return es_ring_order_reduce(h, (float*)(((uintptr_t)avg.data() + 15) & ~(uintptr_t)15));
+    }
+};
+
+// Whether `n` tiles from `t` on lie in memory the handle still holds.
+static bool held(const Tile* t, size_t n)
+{
+    for (const auto& m : g_live)
+        if ((const char*)t >= m.first && (const char*)(t + n) <= m.first + m.second) return true;
+    return false;
+}
+
+// A launch captured into a graph keeps its tables: the options that name a launch shape without
+// changing the decomposition neither wait, allocate nor free, and no option gives the first table back.
+static int check_options()
+{
+    for (uint32_t N : {4u, 9u, 48u}) {
+        Job j(N, 70001);
+        CHECK(j.h && j.reduce() == ES_OK && l_n > 0 && l_shape.wave_width != 0);
+        const Tile* tiles = l_tiles;
+        const std::vector<Tile> wave = l_copy;
+        const struct { const char* name; int64_t value; } fields[] = {
+            {"reduce_unroll", 4}, {"reduce_rank_batch", 2}, {"reduce_lds_pad_kib", 16}, {"nontemporal", 0}, {"nontemporal_pv", 1}};
+        for (const auto& f : fields) {
+            const int a = g_allocs, fr = g_frees, w = g_waits;
+            CHECK(es_set_option(j.h, f.name, f.value) == ES_OK);
+            CHECK(g_allocs == a && g_frees == fr && g_waits == w);
+        }
+        CHECK(j.reduce() == ES_OK && l_shape.wave_width == 0 && l_shape.unroll == 4 && l_shape.rank_batch == 2 && l_shape.lds_pad_kib == 16 && !l_shape.nontemporal);
+        const std::vector<Tile> tiled = l_copy;
+        const Tile* tiled_at = l_tiles;
+        for (int64_t v : {512, 1024, 2048}) CHECK(es_set_option(j.h, "reduce_tile_elems", v) == ES_OK && j.reduce() == ES_OK);
+        CHECK(l_n == tiled.size() && std::memcmp(l_copy.data(), tiled.data(), l_n * sizeof(Tile)) == 0);
+        CHECK(held(tiles, wave.size()) && std::memcmp(tiles, wave.data(), wave.size() * sizeof(Tile)) == 0);
+        CHECK(held(tiled_at, tiled.size()) && std::memcmp(tiled_at, tiled.data(), tiled.size() * sizeof(Tile)) == 0);
+    }
+    CHECK(g_live.empty());                      // es_destroy has given everything back
+    return 0;
+}
+
+int main(int argc, char** argv)
+{
+    const char* what = argc > 1 ? argv[1] : "";
+    int rc = 2;
+    if (!std::strcmp(what, "options")) rc = check_options();
+    if (rc == 0) std::printf("%s: passed\n", what);
+    return rc;
+}

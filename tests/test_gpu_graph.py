@@ -97,3 +97,42 @@ def test_captured_step_replays_bit_exactly(flow):
         S.assert_same(got, ref_by_step[-1], "after graph replays")
     finally:
         job.close()
+
+
+@pytest.mark.parametrize("N,P", [(4, 70_001), (9, 70_001), (48, 300_003)])
+def test_captured_reduce_survives_launch_shape_options(N, P):
+    """Options set after the capture change later launches, not the captured one: each replay gives
+    the bits of the reduce that was captured (another launch shape gives the same bits)."""
+    from paper_2208_14228_amd.job import ESTJob
+    job = ESTJob(N, P, [(0, P // 3), (P // 3, P - P // 3)], 1, use_streams="one")
+    try:
+        base = B.es_grad_slot(job.h, 0, 0)
+        slots = job.memory.blocks[base].view(torch.float32)
+        g = torch.Generator(device=G.DEV)
+        g.manual_seed(N + P)
+        slots.normal_(0.0, 1.0, generator=g)
+        ids, ptrs = list(range(N)), [B.es_grad_slot(job.h, e, 0) for e in range(N)]
+
+        def one():
+            B.check(B.es_accumulate_many(job.h, ids, ptrs), "es_accumulate_many", job.h)
+            job.ring_order_reduce()
+
+        torch.cuda.synchronize()
+        one()
+        job.sync()
+        want = job.avg.clone()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=job.main):
+            one()
+        for name, value in (("reduce_unroll", 4), ("reduce_rank_batch", 2), ("reduce_lds_pad_kib", 0), ("nontemporal", 0),
+                            ("reduce_tile_elems", 512), ("reduce_big_unroll", 8), ("reduce_tile_elems", 1024)):
+            job.set_option(name, value)
+            for launch in (graph.replay, one):
+                job.avg.fill_(3.0)
+                torch.cuda.synchronize()
+                launch()
+                job.sync()
+                torch.cuda.synchronize()
+                assert torch.equal(job.avg.view(torch.int32), want.view(torch.int32)), (name, value, launch)
+    finally:
+        job.close()
