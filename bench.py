@@ -244,7 +244,7 @@ def measure(torch, a, cid, headline, oracle_leg):
         job.set_option(k, int(v))
     opts = {k: B.es_get_option(job.h, k)[1] for k in
             ("reduce_tile_elems", "reduce_unroll", "reduce_rank_batch", "nontemporal", "nontemporal_pv",
-             "reduce_big_unroll", "reduce_big_rank_batch")}
+             "reduce_big_unroll", "reduce_big_rank_batch", "reduce_auto", "reduce_wave_width")}
 
     # synthetic inputs, resident in HBM before anything is timed
     src = []
@@ -394,8 +394,7 @@ def measure(torch, a, cid, headline, oracle_leg):
     stage_ms = statistics.fmean(stg)
     red_gbps = bytes_reduce / (red_ms * 1e-3) / 1e9
     pv_cacheable = opts["nontemporal_pv"] == 0 and fused
-    wave = N <= 64 and P < (64_000_000 if 8 <= N <= 10 else 8_000_000) and not any(kv.startswith(("reduce_", "nontemporal=")) for kv in a.opt)
-    kname = ("k_ring_reduce_wave" if wave else "k_ring_reduce_big" if opts["reduce_big_unroll"] else "k_ring_reduce")
+    kname = ("k_ring_reduce_wave" if opts["reduce_wave_width"] else "k_ring_reduce_big" if opts["reduce_big_unroll"] else "k_ring_reduce")
     kname += " (fused SGD)" if fused else ""
 
     res = {

@@ -429,11 +429,12 @@ int es_checkpoint_import(es_handle* h, const void* host_blob, uint64_t size,
 int es_sync(es_handle* h);
 
 /*
- * Options (never change results).  As long as none of the reduce_* options and no
- * "nontemporal" = 0 has been set, a reduce of up to 64 ranks over fewer than 8 M
- * parameters (8 to 10 ranks: 64 M) runs in a launch shape of its own (one wave per 64 or 256 elements,
- * chosen by both numbers); setting one of them ("reduce_lds_pad_kib" = -1 apart, which asks for
- * nothing) puts the shape that the options describe in its place, there as everywhere.
+ * Options (never change results).  As long as "reduce_auto" is 1, a reduce of up to 64 ranks over
+ * fewer than 8 M parameters (8 to 10 ranks: 64 M) runs in the wave-tile form, a launch shape of its
+ * own (one wave per 64 or 256 elements, chosen by both numbers) that the other reduce_* options do
+ * not describe.  Setting one of those ("reduce_lds_pad_kib" = -1 apart, which asks for nothing), or
+ * "nontemporal" = 0, also to the value it has, sets "reduce_auto" to 0: the shape they describe
+ * takes the form's place, there as everywhere, until "reduce_auto" is set to 1 again.
  * "reduce_tile_elems", "reduce_big_unroll", "reduce_big_rank_batch" and "swap_in" wait for the
  * handle's streams and replace a device table; a launch captured into a graph after an earlier
  * call of the same kind must be captured again (the tables of es_init stay until es_destroy, so
@@ -458,6 +459,9 @@ int es_sync(es_handle* h);
  *                         library's own copy queue while bucket b is reduced (es_plan_swap_in);
  *                         slots that are in HBM are read where they are.  Same bits either way
  *   "slots_on_host"       read-only (es_get_option): ESTs whose gradient slot is on the host
+ *   "reduce_auto"         0/1 (default 1): the wave-tile form where it is the default, see above
+ *   "reduce_wave_width"   read-only: floats per lane of the wave-tile form if the next reduce runs in
+ *                         it, else 0
  *   "reduce_tile_elems"   elements of one bucket chunk handled by one workgroup
  *                         (multiple of 4, 256 .. 65536)
  *   "reduce_unroll"       16-byte vectors per lane in flight per rank (1, 2, 4)

@@ -75,7 +75,7 @@ struct es_handle {
     uint64_t hbm_grad_bytes = 0;                // HBM held by gradient arenas allocated in the current regrouping
     uint32_t tile_elems = 2048;
     ReduceShape shape{2, 8, 1, 0, 1, 0, -1};
-    bool auto_shape = true;                     // no option has asked for a particular launch shape
+    bool auto_shape = true;                     // option reduce_auto: no option has asked for a particular launch shape
 
     // Swap-in of host-resident gradient slots (option "swap_in"): at the reduce the buckets come
     // back one at a time into two device buffers, bucket b+1 being copied while bucket b is reduced.
@@ -1417,6 +1417,11 @@ try {
         if (!value) h->auto_shape = false;       // the wave-tile form has streaming loads only
         return ES_OK;
     }
+    if (k == "reduce_auto") {
+        if (value != 0 && value != 1) return ES_EINVAL;
+        h->auto_shape = value != 0;
+        return ES_OK;
+    }
     if (k == "swap_in") {
         if (value != 0 && value != 1) return ES_EINVAL;
         if (h->n_accumulated != 0) return ES_ESTATE;     // staged gradients would be read the other way
@@ -1464,6 +1469,8 @@ int es_get_option(es_handle* h, const char* name, int64_t* value)
         for (uint32_t e = 0; e < h->N; ++e) n += h->workers[h->worker_of[e]].grad_on_host ? 1 : 0;
         *value = n;
     }
+    else if (k == "reduce_auto") *value = h->auto_shape ? 1 : 0;
+    else if (k == "reduce_wave_width") *value = wave_form(h) ? h->shape.wave_width : 0;     // read-only
     else if (k == "reduce_big_unroll") *value = h->shape.big_unroll;
     else if (k == "reduce_big_rank_batch") *value = h->shape.big_rank_batch;
     else return ES_EINVAL;

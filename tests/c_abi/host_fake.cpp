@@ -136,11 +136,44 @@ static int check_options()
     return 0;
 }
 
+static int64_t option(es_handle* h, const char* name)
+{
+    int64_t v = -99;
+    return es_get_option(h, name, &v) == ES_OK ? v : -98;
+}
+
+// The automatic launch shape can be seen, left and taken up again, and gives the same launch as before.
+static int check_auto()
+{
+    for (uint32_t N : {1u, 9u, 64u, 65u}) {
+        Job j(N, 70001);
+        CHECK(j.h && option(j.h, "reduce_auto") == 1 && j.reduce() == ES_OK);
+        const int width = l_shape.wave_width;
+        const std::vector<Tile> tiles = l_copy;
+        CHECK((width != 0) == (N <= 64) && option(j.h, "reduce_wave_width") == width);
+        CHECK(es_set_option(j.h, "reduce_lds_pad_kib", -1) == ES_OK && es_set_option(j.h, "nontemporal", 1) == ES_OK);
+        CHECK(option(j.h, "reduce_auto") == 1);
+        const char* leave[] = {"reduce_unroll", "reduce_rank_batch", "reduce_tile_elems", "reduce_big_unroll", "reduce_big_rank_batch", "nontemporal"};
+        for (const char* name : leave) {
+            const int64_t was = option(j.h, name);
+            CHECK(es_set_option(j.h, name, std::strcmp(name, "nontemporal") ? was : 0) == ES_OK);
+            CHECK(option(j.h, "reduce_auto") == 0 && option(j.h, "reduce_wave_width") == 0);
+            CHECK(j.reduce() == ES_OK && l_shape.wave_width == 0);
+            CHECK(es_set_option(j.h, name, was) == ES_OK && es_set_option(j.h, "reduce_auto", 1) == ES_OK);
+            CHECK(option(j.h, "reduce_wave_width") == width && j.reduce() == ES_OK && l_shape.wave_width == width);
+            CHECK(l_copy.size() == tiles.size() && std::memcmp(l_copy.data(), tiles.data(), tiles.size() * sizeof(Tile)) == 0);
+        }
+        CHECK(es_set_option(j.h, "reduce_auto", 2) == ES_EINVAL && es_set_option(j.h, "reduce_wave_width", 4) == ES_EINVAL);
+    }
+    return 0;
+}
+
 int main(int argc, char** argv)
 {
     const char* what = argc > 1 ? argv[1] : "";
     int rc = 2;
     if (!std::strcmp(what, "options")) rc = check_options();
+    if (!std::strcmp(what, "auto")) rc = check_auto();
     if (rc == 0) std::printf("%s: passed\n", what);
     return rc;
 }

@@ -78,10 +78,10 @@ def check(N, lens, A, seed, special=False, with_oracle=False, streaming=(0, 1)):
             job.set_option("nontemporal_pv", nt)
             for how in ("reduce", "fused", "fused+avg"):
                 got[nt, how] = step(job, p0, v0, how)
-        wave_tiles = B.es_query(job.h)[1]["n_reduce_tiles"]
+        assert (B.es_get_option(job.h, "reduce_wave_width")[1] != 0) == (
+            N <= 64 and job.P < (64_000_000 if 8 <= N <= 10 else 8_000_000))
         job.set_option("reduce_unroll", 2)                     # an explicit shape: the tiled kernels
-        assert (B.es_query(job.h)[1]["n_reduce_tiles"] != wave_tiles) == (
-            job.P > 2 * 2048 and N <= 64 and job.P < (64_000_000 if 8 <= N <= 10 else 8_000_000))
+        assert B.es_get_option(job.h, "reduce_wave_width")[1] == 0
         for (nt, how), w in got.items():
             assert same(w, step(job, p0, v0, how)), (N, A, nt, how)
         if with_oracle:
