@@ -168,12 +168,30 @@ static int check_auto()
     return 0;
 }
 
+// Gradients in host memory, all of them or some, are not for the wave-tile form.
+static int check_host_slots()
+{
+    Job j(4, 70001);
+    const uint32_t one[4] = {0, 0, 0, 0}, slots[4] = {0, 1, 2, 3}, two[4] = {0, 0, 1, 1}, slots2[4] = {0, 1, 0, 1};
+    CHECK(j.h && j.reduce() == ES_OK && l_shape.wave_width);
+    CHECK(es_set_option(j.h, "host_slots", 1) == ES_OK && j.reduce() == ES_OK && l_shape.wave_width);   // from the next grouping on
+    CHECK(es_set_grouping(j.h, 1, one, slots) == ES_OK && option(j.h, "slots_on_host") == 4);
+    CHECK(option(j.h, "reduce_wave_width") == 0 && j.reduce() == ES_OK && !l_shape.wave_width && option(j.h, "reduce_auto") == 1);
+    CHECK(es_set_option(j.h, "host_slots", 0) == ES_OK && es_set_option(j.h, "hbm_slot_budget_mib", 1) == ES_OK);
+    CHECK(es_set_grouping(j.h, 2, two, slots2) == ES_OK && option(j.h, "slots_on_host") == 2);
+    CHECK(option(j.h, "reduce_wave_width") == 0 && j.reduce() == ES_OK && !l_shape.wave_width);
+    CHECK(es_set_option(j.h, "hbm_slot_budget_mib", -1) == ES_OK && es_set_grouping(j.h, 2, two, slots2) == ES_OK);
+    CHECK(option(j.h, "slots_on_host") == 0 && option(j.h, "reduce_wave_width") && j.reduce() == ES_OK && l_shape.wave_width);
+    return 0;
+}
+
 int main(int argc, char** argv)
 {
     const char* what = argc > 1 ? argv[1] : "";
     int rc = 2;
     if (!std::strcmp(what, "options")) rc = check_options();
     if (!std::strcmp(what, "auto")) rc = check_auto();
+    if (!std::strcmp(what, "host slots")) rc = check_host_slots();
     if (rc == 0) std::printf("%s: passed\n", what);
     return rc;
 }
