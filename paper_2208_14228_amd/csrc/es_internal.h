@@ -82,8 +82,8 @@ struct ReduceShape {
     int lds_pad_kib = -1; // KiB of LDS reserved (and never touched) per workgroup of the small-tile kernel, to cap the
                           // workgroups resident per CU; -1 = default for the rank count (see reduce_lds_pad)
     // wave-tile form (k_ring_reduce_wave): floats per lane (1 or 4; 0 = the other kernels), ranks
-    // loaded before adds are issued, lanes per workgroup, KiB of LDS reserved per workgroup
-    int wave_width = 0, wave_batch = 0, wave_block = 0, wave_pad_kib = 0;
+    // loaded before adds are issued, KiB of LDS reserved per workgroup
+    int wave_width = 0, wave_batch = 0, wave_pad_kib = 0;
     int wave_pieces = 1; // waves that share one tile of the table
 };
 
@@ -111,9 +111,12 @@ inline bool stream_pv(uint32_t N, uint64_t P) { return P >= 12000000 || (N >= 32
 //    (1.1-1.7 x slower at 100 k, 1.0-1.1 x faster at 500 k); then as many ranks per batch as there are,
 //    up to 64, while a SIMD has at most two waves (P <= 128 k), else 16.
 //  - four floats per lane: batches of 4, of 8 from 8 to 23 ranks (a second round trip less: 1.0-1.1).
-//  - fewer than 8 ranks from 1.5 M elements on: one wave per workgroup, no cap on residency (1.03-1.1;
-//    0.92 at 1 M and one rank, 0.9 at 500 k); else four waves and 5 workgroups per CU, or 2 where there are many
-//    streams or elements (1.01-1.04 from 24 ranks and 2 M on, 1.05 at 25 M and 8 ranks).
+//  - 5 workgroups per CU, or 2 where there are many streams or elements (1.01-1.04 from 24 ranks and 2 M on, 1.05
+//    at 25 M and 8 ranks); no cap with fewer than 8 ranks from 1.5 M elements on, where 5 per CU cost 0.86-0.98 of
+//    the other kernels' rate in zero-copy steps of one to three ranks and none costs nothing: staged steps 1.0-1.2
+//    on one stream and, as three jobs on a stream each, 21.0 us for 21.2 at 2 ranks and 3.3 M, 38.1 for 39.1 at 4
+//    and 4 M, 69.8 for 70.7 at 4 and 7.6 M.  (One wave per workgroup is 2-4 % faster alone, and slower than
+//    the other kernels beside other jobs' copies: 22.2, 41.3 and 73.6 us.)
 //  - a tile of the table is one wave's; from 8 M on it is four (idle waves at the end of a chunk no longer
 //    count there: N = 64, P = 1 M 24 % slower; but es_init would plan 100,000 tiles at 25 M).
 inline bool wave_shape(uint32_t N, uint64_t P, ReduceShape& sh)
@@ -125,7 +128,6 @@ inline bool wave_shape(uint32_t N, uint64_t P, ReduceShape& sh)
         return b;
     };
     sh.wave_pieces = 1;
-    sh.wave_block = 256;
     if (N >= 8 && P < 300000) {
         sh.wave_width = 1;
         sh.wave_batch = pow2_up_to(P <= (128u << 10) ? 64 : 16);
@@ -136,10 +138,7 @@ inline bool wave_shape(uint32_t N, uint64_t P, ReduceShape& sh)
     sh.wave_batch = pow2_up_to(N >= 8 && N < 24 ? 8 : 4);
     sh.wave_pad_kib = (N >= 24 && P >= 2000000) || P >= 8000000 ? 64 : 32;
     if (P >= 8000000) sh.wave_pieces = 4;
-    if (N < 8 && P >= 1500000) {
-        sh.wave_block = 64;
-        sh.wave_pad_kib = 0;
-    }
+    if (N < 8 && P >= 1500000) sh.wave_pad_kib = 0;
     return true;
 }
 

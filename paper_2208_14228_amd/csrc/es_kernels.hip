@@ -513,15 +513,15 @@ __device__ __forceinline__ void wave_tile(uint64_t off, uint32_t len, uint32_t r
 }
 
 template <int W, int NB, int PIECES, int NT, bool SGD>
-__global__ __launch_bounds__(kReduceBlock) void k_ring_reduce_wave(const Tile* tiles_g, uint32_t n_tiles, uint32_t per,
+__global__ __launch_bounds__(kReduceBlock) void k_ring_reduce_wave(const Tile* tiles_g, uint32_t n_tiles,
                                                              const float* const* slots, uint32_t N,
                                                              float* __restrict__ avg, float* __restrict__ p,
                                                              float* __restrict__ v, float lr, float mu)
 {
     const uint32_t lane = threadIdx.x & 63;
-    // `per` = waves per workgroup, an argument: blockDim would make the runtime write the hidden ones
-    // with every launch (5.4 -> 5.7 us per call in a loop of small steps)
-    const uint32_t wave = __builtin_amdgcn_readfirstlane(blockIdx.x * per + (threadIdx.x >> 6));
+    // (blockDim for the constant would make the runtime write the hidden arguments with every launch:
+    // 5.4 -> 5.7 us per call in a loop of small steps)
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(blockIdx.x * (kReduceBlock / 64) + (threadIdx.x >> 6));
     const uint32_t t = wave / PIECES;
     if (t >= n_tiles) return;
     const uint64_t base = reinterpret_cast<uint64_t>(slots[lane < N ? lane : N - 1]);
@@ -547,11 +547,11 @@ template <int W, int NB, int PIECES>
 static hipError_t launch_reduce_wave(hipStream_t s, const Tile* tiles, uint32_t n_tiles, const float* const* slots,
                                      uint32_t N, float* avg, float* p, float* v, float lr, float mu, ReduceShape sh)
 {
-    const uint32_t per = (uint32_t)sh.wave_block / 64;
-    const dim3 grid((uint32_t)(((uint64_t)n_tiles * PIECES + per - 1) / per)), block(sh.wave_block);
+    constexpr uint32_t per = kReduceBlock / 64;
+    const dim3 grid((uint32_t)(((uint64_t)n_tiles * PIECES + per - 1) / per)), block(kReduceBlock);
 #define ES_LAUNCH(NTV, SGDV)                                                                                      \
     hipLaunchKernelGGL((k_ring_reduce_wave<W, NB, PIECES, NTV, SGDV>), grid, block, (uint32_t)sh.wave_pad_kib << 10, s, tiles, \
-                       n_tiles, per, slots, N, avg, p, v, lr, mu)
+                       n_tiles, slots, N, avg, p, v, lr, mu)
     if (p) {
         if (sh.nontemporal_pv) ES_LAUNCH(3, true);
         else ES_LAUNCH(1, true);

@@ -185,6 +185,28 @@ static int check_host_slots()
     return 0;
 }
 
+// Which form a job's size chooses, on both sides of every line.
+static int check_rule()
+{
+    const struct { uint32_t n; uint64_t p; int width, batch, pad; } lines[] = {
+        {1, 1499999, 4, 1, 32}, {1, 1500000, 4, 1, 0}, {2, 1500000, 4, 2, 0}, {7, 1499999, 4, 4, 32}, {7, 1500000, 4, 4, 0},
+        {7, 7999999, 4, 4, 0}, {7, 8000000, 0, 0, 0}, {8, 299999, 1, 8, 0}, {8, 300000, 4, 8, 32}, {64, 131072, 1, 64, 0},
+        {64, 131073, 1, 16, 0}, {23, 2000000, 4, 8, 32}, {24, 1999999, 4, 4, 32}, {24, 2000000, 4, 4, 64}, {65, 100000, 0, 0, 0}};
+    for (const auto& l : lines) {
+        Job j(l.n, l.p);
+        CHECK(j.h && j.reduce() == ES_OK && l_shape.wave_width == l.width);
+        if (l.width) CHECK(l_shape.wave_batch == l.batch && l_shape.wave_pad_kib == l.pad);
+        uint64_t sum = 0;
+        for (const Tile& t : l_copy) {
+            CHECK(t.off == sum || !l.width);    // big tiles are listed first
+            if (l.width) CHECK(t.len <= 64u * l.width);
+            sum += t.len;
+        }
+        CHECK(sum == l.p);
+    }
+    return 0;
+}
+
 int main(int argc, char** argv)
 {
     const char* what = argc > 1 ? argv[1] : "";
@@ -192,6 +214,7 @@ int main(int argc, char** argv)
     if (!std::strcmp(what, "options")) rc = check_options();
     if (!std::strcmp(what, "auto")) rc = check_auto();
     if (!std::strcmp(what, "host slots")) rc = check_host_slots();
+    if (!std::strcmp(what, "rule")) rc = check_rule();
     if (rc == 0) std::printf("%s: passed\n", what);
     return rc;
 }
