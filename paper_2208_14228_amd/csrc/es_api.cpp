@@ -277,7 +277,7 @@ int build_tile_block(es_handle* h)
 {
     std::vector<Tile> table, none;
     if (wave_shape(h->N, h->P, h->shape))
-        plan_tiles(h->buckets, h->N, h->A, 64u * h->shape.wave_width * h->shape.wave_pieces, 0, none, table);
+        plan_tiles(h->buckets, h->N, h->A, 64u * h->shape.wave_width, 0, none, table);
     if (table.size() > 0x7fffffffull) return ES_EINVAL;
     const uint32_t n_wave = (uint32_t)table.size();
     int rc = plan_option_tiles(h, table, h->n_tiles, h->n_big);

@@ -84,7 +84,6 @@ struct ReduceShape {
     // wave-tile form (k_ring_reduce_wave): floats per lane (1 or 4; 0 = the other kernels), ranks
     // loaded before adds are issued, KiB of LDS reserved per workgroup
     int wave_width = 0, wave_batch = 0, wave_pad_kib = 0;
-    int wave_pieces = 1; // waves that share one tile of the table
 };
 
 // Whether parameters, momentum and the averaged gradient are streamed by default.  Cacheable over
@@ -104,30 +103,25 @@ inline bool stream_pv(uint32_t N, uint64_t P) { return P >= 12000000 || (N >= 32
 // x 9 sizes, fused, three jobs in turn (time of the other kernels over this one's):
 //  - N <= 64: the slot table is one pointer per lane.
 //  - P < 8 M: 1.0-1.3 at 4 M, 1.0-2.2 at 1 M, 1.05-3.4 at 20 k; at 8 M 0.97-1.06, at 25 M 0.95-1.02
-//    (there a wave's 1 KiB per stream costs what the saved round trips gain), except for
-//  - 8 to 10 ranks below 64 M: 1.15 at 8 M, 1.04 at 25 M, 1.02 at 32 M against the small tiles with one
-//    workgroup per CU; 0.99 at 109 M.
+//    (there a wave's 1 KiB per stream costs what the saved round trips gain).  With 8 to 10 ranks and
+//    25.6 M too, both with parameters and momentum streamed: fused 0.98-1.02 alone and 0.96-0.98 beside
+//    other jobs, staged and hooked steps 1.0, unfused 0.92-0.97.
 //  - one float per lane below 300 k elements and from 8 ranks on, where four leave SIMDs without a wave
 //    (1.1-1.7 x slower at 100 k, 1.0-1.1 x faster at 500 k); then as many ranks per batch as there are,
 //    up to 64, while a SIMD has at most two waves (P <= 128 k), else 16.
 //  - four floats per lane: batches of 4, of 8 from 8 to 23 ranks (a second round trip less: 1.0-1.1).
-//  - 5 workgroups per CU, or 2 where there are many streams or elements (1.01-1.04 from 24 ranks and 2 M on, 1.05
-//    at 25 M and 8 ranks); no cap with fewer than 8 ranks from 1.5 M elements on, where 5 per CU cost 0.86-0.98 of
+//  - 5 workgroups per CU, or 2 where there are many streams (1.01-1.04 from 24 ranks and 2 M on); no cap with fewer than 8 ranks from 1.5 M elements on, where 5 per CU cost 0.86-0.98 of
 //    the other kernels' rate in zero-copy steps of one to three ranks and none costs nothing: staged steps 1.0-1.2
 //    on one stream and, as three jobs on a stream each, 21.0 us for 21.2 at 2 ranks and 3.3 M, 38.1 for 39.1 at 4
 //    and 4 M, 69.8 for 70.7 at 4 and 7.6 M.  (One wave per workgroup is 2-4 % faster alone, and slower than
 //    the other kernels beside other jobs' copies: 22.2, 41.3 and 73.6 us.)
-//  - a tile of the table is one wave's; from 8 M on it is four (idle waves at the end of a chunk no longer
-//    count there: N = 64, P = 1 M 24 % slower; but es_init would plan 100,000 tiles at 25 M).
 inline bool wave_shape(uint32_t N, uint64_t P, ReduceShape& sh)
 {
-    const uint64_t most = N >= 8 && N <= 10 ? 64000000 : 8000000;
-    if (N == 0 || N > 64 || P >= most) return false;
+    if (N == 0 || N > 64 || P >= 8000000) return false;
     auto pow2_up_to = [N](int b) {
         while (b > 1 && (uint32_t)b > N) b /= 2;
         return b;
     };
-    sh.wave_pieces = 1;
     if (N >= 8 && P < 300000) {
         sh.wave_width = 1;
         sh.wave_batch = pow2_up_to(P <= (128u << 10) ? 64 : 16);
@@ -136,8 +130,7 @@ inline bool wave_shape(uint32_t N, uint64_t P, ReduceShape& sh)
     }
     sh.wave_width = 4;
     sh.wave_batch = pow2_up_to(N >= 8 && N < 24 ? 8 : 4);
-    sh.wave_pad_kib = (N >= 24 && P >= 2000000) || P >= 8000000 ? 64 : 32;
-    if (P >= 8000000) sh.wave_pieces = 4;
+    sh.wave_pad_kib = N >= 24 && P >= 2000000 ? 64 : 32;
     if (N < 8 && P >= 1500000) sh.wave_pad_kib = 0;
     return true;
 }
@@ -145,8 +138,7 @@ inline bool wave_shape(uint32_t N, uint64_t P, ReduceShape& sh)
 // ring-ordered N-way reduce (+ optional fused SGD-momentum).
 //  slots: device table of N slot base pointers indexed by virtual rank.
 //  avg may be null only when p and v are given.
-//  With shape.wave_width != 0 every tile holds at most 64 * wave_width * wave_pieces elements (less by as
-//  many as its offset is past a 128-byte line), and N <= 64.
+//  With shape.wave_width != 0 every tile holds at most 64 * wave_width elements, and N <= 64.
 //  With shape.big_unroll != 0 the first n_big tiles must be full big tiles
 //  (kBlock * big_unroll * 4 elements, offset a multiple of 4) and all others
 //  at most 2048 elements.

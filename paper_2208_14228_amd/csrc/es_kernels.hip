@@ -424,13 +424,13 @@ static hipError_t launch_reduce_big_u(hipStream_t s, const Tile* tiles, uint32_t
 
 // ---------------------------------------------------------------------------
 // Wave-tile form of the same kernel for short vectors and at most 64 ranks: one WAVE
-// per tile of 64 * W elements (or per quarter of a tile), W floats per lane.
+// per tile of 64 * W elements, W floats per lane.
 //
 // What bounds a short reduce is the number of dependent round trips to memory in one
 // wave's life and the number of waves, not bytes.  So: the rank -> slot table is read
 // with one vector load (lane r holds rank r's base) that does not wait for the tile, and
 // a rank's base then comes out of a register (v_readlane) instead of a scalar load in
-// front of every batch; pieces are small enough that every CU has some; a batch is as
+// front of every batch; tiles are small enough that every CU has some; a batch is as
 // many ranks as the registers hold when few waves share a SIMD.  Vectors may start at
 // any 4-byte address, and the last one of a tile is shifted back over its neighbour's
 // elements (both lanes of the wave have loaded before either stores, and store the same
@@ -439,8 +439,7 @@ static hipError_t launch_reduce_big_u(hipStream_t s, const Tile* tiles, uint32_t
 //
 // Fused, default options, three jobs in turn: N = 64, P = 20 k 16.8 -> 4.9 us, P = 200 k
 // 19.0 -> 10.6 us; N = 16, P = 500 k 14.1 -> 7.9 us, P = 4 M 67 -> 53 us; N = 8, P = 1 M
-// 11.4 -> 9.2 us; N = 4, P = 1 M 7.6 -> 6.8 us (4.9 TB/s); N = 8, P = 25.6 M 217 -> 197 us with
-// parameters and momentum streamed (204 by the small tiles so; 6.2 TB/s).
+// 11.4 -> 9.2 us; N = 4, P = 1 M 7.6 -> 6.8 us (4.9 TB/s).
 // ---------------------------------------------------------------------------
 template <int W> struct WaveVec;
 template <> struct WaveVec<1> { typedef float T; };
@@ -512,7 +511,7 @@ __device__ __forceinline__ void wave_tile(uint64_t off, uint32_t len, uint32_t r
     }
 }
 
-template <int W, int NB, int PIECES, int NT, bool SGD>
+template <int W, int NB, int NT, bool SGD>
 __global__ __launch_bounds__(kReduceBlock) void k_ring_reduce_wave(const Tile* tiles_g, uint32_t n_tiles,
                                                              const float* const* slots, uint32_t N,
                                                              float* __restrict__ avg, float* __restrict__ p,
@@ -521,36 +520,26 @@ __global__ __launch_bounds__(kReduceBlock) void k_ring_reduce_wave(const Tile* t
     const uint32_t lane = threadIdx.x & 63;
     // (blockDim for the constant would make the runtime write the hidden arguments with every launch:
     // 5.4 -> 5.7 us per call in a loop of small steps)
-    const uint32_t wave = __builtin_amdgcn_readfirstlane(blockIdx.x * (kReduceBlock / 64) + (threadIdx.x >> 6));
-    const uint32_t t = wave / PIECES;
+    const uint32_t t = __builtin_amdgcn_readfirstlane(blockIdx.x * (kReduceBlock / 64) + (threadIdx.x >> 6));
     if (t >= n_tiles) return;
     const uint64_t base = reinterpret_cast<uint64_t>(slots[lane < N ? lane : N - 1]);
     const uint32_t lo = (uint32_t)base, hi = (uint32_t)(base >> 32);
     const Tile ES_CONST_AS* tiles = (const Tile ES_CONST_AS*)tiles_g;
-    uint64_t off = tiles[t].off;
-    uint32_t len = tiles[t].len;
+    const uint64_t off = tiles[t].off;
+    const uint32_t len = tiles[t].len;
     const uint32_t rank0 = tiles[t].rank0;
-    if constexpr (PIECES > 1) {
-        // a tile that starts inside a 128-byte line is short by as much (it ends on one): so is its
-        // first piece, and the others start on a line
-        const uint32_t part = wave % PIECES, short_by = (uint32_t)off & 31;
-        const uint32_t lo_e = part ? 64 * W * part - short_by : 0, hi_e = 64 * W * (part + 1) - short_by;
-        if (len <= lo_e) return;
-        off += lo_e;
-        len = (len < hi_e ? len : hi_e) - lo_e;
-    }
     if (len >= W) wave_tile<W, NB, NT, SGD>(off, len, rank0, lo, hi, lane, N, avg, p, v, lr, mu);
     else wave_tile<1, 8, NT, SGD>(off, len, rank0, lo, hi, lane, N, avg, p, v, lr, mu);
 }
 
-template <int W, int NB, int PIECES>
+template <int W, int NB>
 static hipError_t launch_reduce_wave(hipStream_t s, const Tile* tiles, uint32_t n_tiles, const float* const* slots,
                                      uint32_t N, float* avg, float* p, float* v, float lr, float mu, ReduceShape sh)
 {
     constexpr uint32_t per = kReduceBlock / 64;
-    const dim3 grid((uint32_t)(((uint64_t)n_tiles * PIECES + per - 1) / per)), block(kReduceBlock);
+    const dim3 grid((uint32_t)(((uint64_t)n_tiles + per - 1) / per)), block(kReduceBlock);
 #define ES_LAUNCH(NTV, SGDV)                                                                                      \
-    hipLaunchKernelGGL((k_ring_reduce_wave<W, NB, PIECES, NTV, SGDV>), grid, block, (uint32_t)sh.wave_pad_kib << 10, s, tiles, \
+    hipLaunchKernelGGL((k_ring_reduce_wave<W, NB, NTV, SGDV>), grid, block, (uint32_t)sh.wave_pad_kib << 10, s, tiles, \
                        n_tiles, slots, N, avg, p, v, lr, mu)
     if (p) {
         if (sh.nontemporal_pv) ES_LAUNCH(3, true);
@@ -567,18 +556,17 @@ static hipError_t launch_reduce_wave_any(hipStream_t s, const Tile* tiles, uint3
                                          uint32_t N, float* avg, float* p, float* v, float lr, float mu, ReduceShape sh)
 {
     if (N > 64) return hipErrorInvalidValue;            // the table is one pointer per lane
-#define ES_WAVE(W, NB, PIECES)                                                  \
-    if (sh.wave_width == W && sh.wave_batch == NB && sh.wave_pieces == PIECES) \
-        return launch_reduce_wave<W, NB, PIECES>(s, tiles, n_tiles, slots, N, avg, p, v, lr, mu, sh)
-    ES_WAVE(1, 8, 1);
-    ES_WAVE(1, 16, 1);
-    ES_WAVE(1, 32, 1);
-    ES_WAVE(1, 64, 1);
-    ES_WAVE(4, 1, 1);
-    ES_WAVE(4, 2, 1);
-    ES_WAVE(4, 4, 1);
-    ES_WAVE(4, 8, 1);
-    ES_WAVE(4, 8, 4);
+#define ES_WAVE(W, NB)                                   \
+    if (sh.wave_width == W && sh.wave_batch == NB)      \
+        return launch_reduce_wave<W, NB>(s, tiles, n_tiles, slots, N, avg, p, v, lr, mu, sh)
+    ES_WAVE(1, 8);
+    ES_WAVE(1, 16);
+    ES_WAVE(1, 32);
+    ES_WAVE(1, 64);
+    ES_WAVE(4, 1);
+    ES_WAVE(4, 2);
+    ES_WAVE(4, 4);
+    ES_WAVE(4, 8);
 #undef ES_WAVE
     return hipErrorInvalidValue;
 }

@@ -79,7 +79,7 @@ def check(N, lens, A, seed, special=False, with_oracle=False, streaming=(0, 1)):
             for how in ("reduce", "fused", "fused+avg"):
                 got[nt, how] = step(job, p0, v0, how)
         assert (B.es_get_option(job.h, "reduce_wave_width")[1] != 0) == (
-            N <= 64 and job.P < (64_000_000 if 8 <= N <= 10 else 8_000_000))
+            N <= 64 and job.P < 8_000_000)
         job.set_option("reduce_unroll", 2)                     # an explicit shape: the tiled kernels
         assert B.es_get_option(job.h, "reduce_wave_width")[1] == 0
         for (nt, how), w in got.items():
