@@ -430,7 +430,7 @@ int es_sync(es_handle* h);
 
 /*
  * Options (never change results).  As long as "reduce_auto" is 1, a reduce of up to 64 ranks over
- * fewer than 8 M parameters, all gradient slots in HBM, runs in the wave-tile
+ * fewer than 8 M parameters (from 8 ranks on 5 M), all gradient slots in HBM, runs in the wave-tile
  * form, a launch shape of its own (one wave per 64 or 256 elements, chosen by both numbers) that the
  * other reduce_* options do not describe.  Setting one of those ("reduce_lds_pad_kib" = -1 apart, which asks for nothing), or
  * "nontemporal" = 0, also to the value it has, sets "reduce_auto" to 0: the shape they describe

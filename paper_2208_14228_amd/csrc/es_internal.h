@@ -102,10 +102,14 @@ inline bool stream_pv(uint32_t N, uint64_t P) { return P >= 12000000 || (N >= 32
 // returns false (and leaves the shape alone) where the other kernels are.  Measured on 13 rank counts
 // x 9 sizes, fused, three jobs in turn (time of the other kernels over this one's):
 //  - N <= 64: the slot table is one pointer per lane.
-//  - P < 8 M: 1.0-1.3 at 4 M, 1.0-2.2 at 1 M, 1.05-3.4 at 20 k; at 8 M 0.97-1.06, at 25 M 0.95-1.02
-//    (there a wave's 1 KiB per stream costs what the saved round trips gain).  With 8 to 10 ranks and
-//    25.6 M too, both with parameters and momentum streamed: fused 0.98-1.02 alone and 0.96-0.98 beside
-//    other jobs, staged and hooked steps 1.0, unfused 0.92-0.97.
+//  - P < 8 M, from 8 ranks on 5 M: 1.0-1.3 at 4 M, 1.0-2.2 at 1 M, 1.05-3.4 at 20 k.  Above, a wave's 1 KiB per
+//    stream costs what the saved round trips gain.  From 12 ranks on, one stream / three jobs on a stream each:
+//    zero-copy 1.05-1.12 / 0.92-0.97 at 4.5 M, 0.94-1.03 / 0.87-0.93 at 5.5 M, 0.90-0.98 / 0.93-0.99 at 6.5 M; clipped
+//    1.11-1.13 / 0.94-1.0, 0.98-1.03 / 0.90-1.0, 0.94-1.0 / 0.93-0.99; staged steps gain to 8 M, by 1-5 %.  8 to 10 ranks,
+//    zero-copy: 1.02-1.05 / 0.95-1.06 at 3.3 M, 0.96-0.99 / 0.94-0.99 at 5.5 M.  With 8 to 10 ranks at 25.6 M, both with
+//    parameters and momentum streamed: fused 0.98-1.02 / 0.96-0.98, staged and hooked steps 1.0, unfused 0.92-0.97.
+//    (Where three zero-copy jobs fill the chip together the other kernels' long reads win from 2 M and 12 ranks on, by
+//    3-14 %; a job that has the GPU to itself is 1.05-1.75 times as fast by this form there, so the line follows that.)
 //  - one float per lane below 300 k elements and from 8 ranks on, where four leave SIMDs without a wave
 //    (1.1-1.7 x slower at 100 k, 1.0-1.1 x faster at 500 k); then as many ranks per batch as there are,
 //    up to 64, while a SIMD has at most two waves (P <= 128 k), else 16.
@@ -117,7 +121,7 @@ inline bool stream_pv(uint32_t N, uint64_t P) { return P >= 12000000 || (N >= 32
 //    the other kernels beside other jobs' copies: 22.2, 41.3 and 73.6 us.)
 inline bool wave_shape(uint32_t N, uint64_t P, ReduceShape& sh)
 {
-    if (N == 0 || N > 64 || P >= 8000000) return false;
+    if (N == 0 || N > 64 || P >= (N < 8 ? 8000000u : 5000000u)) return false;
     auto pow2_up_to = [N](int b) {
         while (b > 1 && (uint32_t)b > N) b /= 2;
         return b;

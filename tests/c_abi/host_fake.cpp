@@ -190,7 +190,7 @@ static int check_rule()
 {
     const struct { uint32_t n; uint64_t p; int width, batch, pad; } lines[] = {
         {1, 1499999, 4, 1, 32}, {1, 1500000, 4, 1, 0}, {2, 1500000, 4, 2, 0}, {7, 1499999, 4, 4, 32}, {7, 1500000, 4, 4, 0},
-        {7, 7999999, 4, 4, 0}, {7, 8000000, 0, 0, 0}, {8, 8000000, 0, 0, 0}, {10, 8000001, 0, 0, 0}, {8, 299999, 1, 8, 0}, {8, 300000, 4, 8, 32}, {64, 131072, 1, 64, 0},
+        {7, 7999999, 4, 4, 0}, {7, 8000000, 0, 0, 0}, {8, 4999999, 4, 8, 32}, {8, 5000000, 0, 0, 0}, {24, 4999999, 4, 4, 64}, {64, 5000000, 0, 0, 0}, {10, 8000001, 0, 0, 0}, {8, 299999, 1, 8, 0}, {8, 300000, 4, 8, 32}, {64, 131072, 1, 64, 0},
         {64, 131073, 1, 16, 0}, {23, 2000000, 4, 8, 32}, {24, 1999999, 4, 4, 32}, {24, 2000000, 4, 4, 64}, {65, 100000, 0, 0, 0}};
     for (const auto& l : lines) {
         Job j(l.n, l.p);

@@ -1,4 +1,4 @@
-"""The wave-tile form of the reduce (the default below 8 M parameters and up to 64 ranks) at the edges
+"""The wave-tile form of the reduce (the default below 5 M parameters and up to 64 ranks, 8 M below 8) at the edges
 of its rule and of its tiles: against the oracle's ring where that is small enough, and everywhere
 against the tiled kernels an explicit launch-shape option selects, bit for bit."""
 import numpy as np
@@ -79,7 +79,7 @@ def check(N, lens, A, seed, special=False, with_oracle=False, streaming=(0, 1)):
             for how in ("reduce", "fused", "fused+avg"):
                 got[nt, how] = step(job, p0, v0, how)
         assert (B.es_get_option(job.h, "reduce_wave_width")[1] != 0) == (
-            N <= 64 and job.P < 8_000_000)
+            N <= 64 and job.P < (8_000_000 if N < 8 else 5_000_000))
         job.set_option("reduce_unroll", 2)                     # an explicit shape: the tiled kernels
         assert B.es_get_option(job.h, "reduce_wave_width")[1] == 0
         for (nt, how), w in got.items():
@@ -115,7 +115,7 @@ def test_infinities_nan_and_denormals(N):
     (8, (128 << 10) - 1), (8, 128 << 10), (64, (128 << 10) + 1), (40, 131_073), (8, 299_999), (64, 300_000), (7, 300_001),
     (23, 400_003), (24, 400_003), (7, 1_499_999), (7, 1_500_000), (8, 1_500_001), (1, 1_500_003), (33, 1_000_000), (32, 999_999),
     (3, 7_999_999), (3, 8_000_000), (64, 1_200_005), (65, 100_003),
-    (8, 8_000_001), (10, 8_100_019), (11, 8_000_001), (24, 2_000_003), (8, 64_000_000), (9, 63_999_999)])
+    (8, 4_999_999), (12, 5_000_000), (8, 8_000_001), (10, 8_100_019), (11, 8_000_001), (24, 2_000_003), (8, 64_000_000), (9, 63_999_999)])
 def test_both_sides_of_every_line_of_the_rule(N, P):
     for A in (1, 4):
         check(N, [P // 3 + 1, P - 2 * (P // 3) - 2, P // 3 + 1], A, P + N, streaming=(1,) if P > 2_000_000 else (0, 1))
