@@ -475,9 +475,11 @@ int es_sync(es_handle* h);
  *   "nontemporal"         0/1: streaming hint on gradient loads
  *   "nontemporal_pv"      0/1: streaming hint on parameter and momentum traffic of the update
  *                         (fused or es_sgd_step / es_clip_sgd_step) and on the store of the
- *                         averaged gradient (default: 1 from 12 M parameters on, and from 1 M on with
- *                         at least 32 ranks; else 0.  A loop that runs nothing between two reduces of
- *                         12 to 37 M parameters is up to 10 % faster with 0, a training job with 1)
+ *                         averaged gradient (default: 1 from 14 M parameters on, and from 1 M to
+ *                         5 M with at least 32 ranks; else 0.  A loop that runs nothing between two
+ *                         fused reduces of 14 to 37 M parameters is up to 12 % faster with 0, one of
+ *                         reduce, norm and clipped update up to 5 %; a training job, whose model uses
+ *                         the caches in between, is up to 10 % faster with 1)
  *   "reduce_big_unroll"   0, 8, 16 or 32: if not 0, full aligned stretches of a ring chunk
  *                         are handled in big tiles of 256 * value * 4 elements (long
  *                         contiguous reads per gradient stream; default 32 from

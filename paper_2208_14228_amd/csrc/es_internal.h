@@ -87,16 +87,22 @@ struct ReduceShape {
 };
 
 // Whether parameters, momentum and the averaged gradient are streamed by default.  Cacheable over
-// streaming time of the fused reduce:
+// streaming time of a zero-copy step, fused / with clipping (reduce, norm and update kernel):
 //  - after something has swept the caches, as the model does between two reduces of a training job (a 1 GiB
-//    fill): 1.01-1.22 from 1 M to 32 M parameters at 1 to 64 ranks, so streaming never loses there;
-//  - three jobs in turn: 1.04-1.10 from 16 M on (their parameters and momentum exceed the Infinity Cache),
-//    1.0 at 12 M, 0.83-0.97 at 4 to 8 M and up to 16 ranks (they come back from it), but 1.03-1.10 from
-//    1 M on at 32 and 64 ranks (the gradients push them out);
-//  - one job in a loop of nothing but reduces: 0.90-1.0 from 8 to 37 M at N <= 12, 1.0 elsewhere; above
-//    37 M streaming wins in every loop.
-// The line lies where streaming wins or ties in the first two.
-inline bool stream_pv(uint32_t N, uint64_t P) { return P >= 12000000 || (N >= 32 && P >= 1000000); }
+//    fill): 0.98-1.22 / 0.99-1.14 from 1 M to 32 M parameters at 1 to 64 ranks;
+//  - three jobs in turn on one stream: 1.03-1.10 / 1.0-1.10 from 14 M on (their parameters and momentum exceed the
+//    Infinity Cache), 0.94-1.02 / 1.0-1.07 at 12 M, 0.83-1.0 / 0.98-1.03 at 4 to 10 M (they come back from it), but
+//    1.0-1.08 / 0.99-1.03 from 1 M to 5 M with 32 ranks or more (wave tiles; the gradients push them out);
+//  - three jobs on a stream each: 0.95-1.10 / 0.93-1.10 from 14 M on, 0.90-1.02 / 0.93-1.05 at 12 M, 0.87-0.99 / 0.92-1.02 at
+//    8 to 10 M, 0.94-1.05 / 0.92-1.02 from 1 M to 5 M with 32 ranks or more;
+//  - one job in a loop of nothing but these calls: 0.88-0.98 / 0.95-1.02 from 8 to 37 M up to 12 ranks, 0.96-1.0 /
+//    0.98-1.02 beyond.  The update kernel alone takes 0.0893 ms for 0.0817 in such a loop at 25.6 M, the
+//    reduce alone gains from the average's store; above 37 M streaming wins in every loop.
+// The line lies where streaming wins or ties in the first two, and in the third for the most part.
+inline bool stream_pv(uint32_t N, uint64_t P)
+{
+    return P >= 14000000 || (N >= 32 && P >= 1000000 && P < 5000000);
+}
 
 // The wave-tile form where it is the faster one, by the rank count N and the parameter count P;
 // returns false (and leaves the shape alone) where the other kernels are.  Measured on 13 rank counts

@@ -204,6 +204,12 @@ static int check_rule()
         }
         CHECK(sum == l.p);
     }
+    const struct { uint32_t n; uint64_t p; int streamed; } policy[] = {
+        {1, 13999999, 0}, {1, 14000000, 1}, {31, 4999999, 0}, {32, 999999, 0}, {32, 1000000, 1}, {64, 4999999, 1}, {64, 5000000, 0}};
+    for (const auto& l : policy) {
+        Job j(l.n, l.p);
+        CHECK(j.h && j.reduce() == ES_OK && l_shape.nontemporal_pv == l.streamed && option(j.h, "nontemporal_pv") == l.streamed);
+    }
     return 0;
 }
 
