@@ -1319,11 +1319,13 @@ struct BnGeom {
 };
 
 // How four consecutive terms lie in memory.
-constexpr uint32_t kBnLongHW = 1024;
+constexpr uint32_t kBnLongHW = 128;
 enum { kBnVector = 0, kBnLong = 1, kBnWrap = 2, kBnAny = 3 };
 // kBnVector: HW is a multiple of 4, so they are one 16-byte vector of one image.
 // kBnLong:   any HW >= kBnLongHW: one vector too, except where an image (or the channel) ends
-//            inside the wave's 256 terms; there four single loads.
+//            inside the wave's 256 terms; there four single loads.  Against kBnWrap 1.0 at 129 positions,
+//            1.07 at 169, 1.2-1.4 at 289 and 1.3-2.2 from 441 on, most where a channel is 16 blocks or
+//            more (four loads for one saturate the L1: 158x134x841 44.5 us by kBnWrap, 29.4 so).
 // kBnWrap:   4 <= HW, any remainder: the image can end once inside them; four single loads
 //            (neighbouring lanes share the lines, so the L1 serves three of the four).
 // kBnAny:    HW < 4.

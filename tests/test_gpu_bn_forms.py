@@ -23,6 +23,8 @@ SHAPES = [
     (1, 32 * BLK), (1, 32 * BLK + 1), (7, 9 * BLK + 3), (100, 3 * BLK + 2), (1, 256 * BLK), (1, 256 * BLK + 1),
     (255, 1), (4097, 1), (1400, 3), (70_001, 2), (40_000, 5), (30_000, 7), (1, 1), (2, 4), (1, 6),
     (3, 255), (3, 256), (3, 257), (17, 258),
+    # both sides of the line between short and long images, in every form
+    (32, 127), (31, 129), (400, 127), (400, 129), (700, 127), (700, 129), (1100, 127), (1100, 131), (8500, 127), (8500, 129),
 ]
 
 
