@@ -1497,7 +1497,7 @@ void k_bn_channel(const float* __restrict__ x, const BnGeom g, float fM, float* 
 // Longer channels read x twice (second pass over blocks in reverse: what the first read last may
 // still be in the L2s).
 //
-// Up to 256 blocks (WIDE): the four waves of a workgroup take the blocks b, b + W/4,
+// Up to 256 blocks, and few channels of tiny images from 8 on (WIDE): the four waves of a workgroup take the blocks b, b + W/4,
 // b + W/2 and b + 3W/4, W being the number of blocks rounded up to a power of two, so the first
 // two levels of the partials' tree (strides W/2 and W/4) happen in the workgroup: W/4 sums per
 // channel are left, few enough for both passes' to fit in the workspace side by side and for one
@@ -1571,16 +1571,24 @@ template <int MODE, typename OFF>
 static void launch_bn(hipStream_t s, const float* x, const BnGeom& g, float* mean, float* var, float* part)
 {
     const float fM = (float)g.M;
+    // Few channels of many tiny images (a line of memory holds an image's few values of a channel, the rest
+    // belongs to others): a channel's loads queue in the L1 of the one CU that has it, and most CUs have
+    // none.  Three launches spread a channel over several workgroups instead.  16 blocks in one launch and in
+    // three: 16 channels of 1, 3, 4 and 5 positions 57 / 31, 64 / 30, 25 / 15.4 and 38 / 16.8 us, 64 channels 74 / 43,
+    // 78 / 37, 35 / 20 and 60 / 20.7; 64 channels of 8 and 12 positions 20 / 18 and 21 / 17.  With 160 channels
+    // one launch is ahead again (1 and 3 positions 90 / 127 and 83 / 101 us) except for vectors of one image each
+    // (4 positions 51 / 42), and from 16 positions on it is everywhere as fast as two launches per pass.
+    const bool spread = g.HW < 8 ? g.nblk >= 8 && g.C <= (g.HW == 4 ? 255 : 128) : g.HW < 16 && g.nblk > 12 && g.C <= 64;
     if (g.nblk == 1) {
         hipLaunchKernelGGL((k_bn_channel<MODE, OFF, kBnSingle>), dim3((g.C + kBnSingles - 1) / kBnSingles),
                            dim3(64 * kBnSingles), 0, s, x, g, fM, mean, var);
-    } else if (g.nblk <= kBnWaves) {
+    } else if (g.nblk <= kBnWaves && !spread) {
         hipLaunchKernelGGL((k_bn_channel<MODE, OFF, kBnRegs>), dim3(g.C), dim3(64 * g.nblk), 0, s, x, g, fM, mean, var);
-    } else if (g.nblk <= kBnWaves + kBnExtra) {
+    } else if (g.nblk <= kBnWaves + kBnExtra && !spread) {
         hipLaunchKernelGGL((k_bn_channel<MODE, OFF, kBnParked>), dim3(g.C), dim3(64 * kBnWaves),
                            (g.nblk - kBnWaves) * 4096 * sizeof(float), s, x, g, fM, mean, var);
     } else if (g.nblk <= 256) {
-        uint32_t n = 8;                                 // sums per channel: a quarter of the blocks' power of two
+        uint32_t n = 4;                                 // sums per channel: a quarter of the blocks' power of two
         while (4 * n < g.nblk) n *= 2;
         const dim3 grid(n, g.C);
         hipLaunchKernelGGL((k_bn_partials<false, true, MODE, OFF>), grid, dim3(kBlock), 0, s, x, g, grid.x, fM, mean, part);

@@ -25,6 +25,9 @@ SHAPES = [
     (3, 255), (3, 256), (3, 257), (17, 258),
     # both sides of the line between short and long images, in every form
     (32, 127), (31, 129), (400, 127), (400, 129), (700, 127), (700, 129), (1100, 127), (1100, 131), (8500, 127), (8500, 129),
+    # few channels of tiny images, around where they are spread over several workgroups
+    (7 * BLK, 1), (7 * BLK + 1, 1), (8 * BLK, 1), (16 * BLK + 5, 1), (25 * BLK, 1), (12_289, 3), (21_850, 3), (9 * BLK // 4, 4),
+    (7_400, 5), (13_106, 5), (20_479, 5), (6_144, 8), (6_145, 8), (3_641, 15), (6_826, 15), (5_000, 16), (26 * BLK - 9, 1),
 ]
 
 
@@ -38,6 +41,15 @@ def test_every_form_at_its_edges(Bn, HW):
             got_m, got_v = gpu_bn(x, shift)
             assert np.array_equal(bits(got_m), bits(want_m)), ("mean", C, shift)
             assert np.array_equal(bits(got_v), bits(want_v)), ("var", C, shift)
+
+
+@pytest.mark.parametrize("Bn,C,HW", [(7_373, 128, 5), (7_373, 129, 5), (9_300, 255, 4), (9_300, 256, 4), (4_800, 64, 12), (4_800, 65, 12)])
+def test_both_sides_of_the_channel_lines_for_tiny_images(Bn, C, HW):
+    rng = np.random.default_rng(C)
+    x = (rng.standard_normal((Bn, C, HW), dtype=np.float32) * 3 + 1).astype(np.float32)
+    want_m, want_v = oracle.bn_batch_stats(x)
+    got_m, got_v = gpu_bn(x)
+    assert np.array_equal(bits(got_m), bits(want_m)) and np.array_equal(bits(got_v), bits(want_v))
 
 
 @pytest.mark.parametrize("HW", [49, 196, 4 * BLK + 3, 20 * BLK, 40 * BLK + 1])
