@@ -1,6 +1,7 @@
 // Host runtime of libes on a device made of host memory: the HIP calls it uses are defined here and
 // the kernel launchers record what they were given, so a handle's life (tables, options, waits,
 // allocations) can be followed without a GPU.  Test program: argv[1] names the check, exit status 0 = passed.
+#include <algorithm>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -79,13 +80,13 @@ using namespace es;
 
 struct Job {
     es_handle* h = nullptr;
-    uint32_t N;
+    uint32_t N, A;
     uint64_t P;
     std::vector<float> avg;
-    Job(uint32_t n, uint64_t p) : N(n), P(p), avg(p + 64)
+    Job(uint32_t n, uint64_t p, uint32_t a = 1) : N(n), A(a), P(p), avg(p + 64)
     {
         es_bucket b[2] = {{0, p / 3}, {p / 3, p - p / 3}};
-        es_bucket_layout lay = {p, 2, b, 1, 0, nullptr, dev_alloc, dev_free, nullptr};
+        es_bucket_layout lay = {p, 2, b, a, 0, nullptr, dev_alloc, dev_free, nullptr};
         if (es_init(&h, n, &lay) != ES_OK) h = nullptr;
     }
     ~Job() { if (h) es_destroy(h); }
@@ -185,6 +186,24 @@ static int check_host_slots()
     return 0;
 }
 
+// The tiles of the last launch against the ring's chunks: each in one chunk of one bucket, opened by the
+// rank of the chunk, and all of them [0, P) without a gap.
+static bool tiles_follow_the_ring(const Job& j)
+{
+    const uint64_t start[3] = {0, j.P / 3, j.P};
+    uint64_t next = 0;
+    std::vector<Tile> t = l_copy;               // big tiles are listed first
+    std::sort(t.begin(), t.end(), [](const Tile& x, const Tile& y) { return x.off < y.off; });
+    for (const Tile& x : t) {
+        const int b = x.off >= start[1] ? 1 : 0;
+        const uint64_t len = start[b + 1] - start[b], chunk = ((len + j.N - 1) / j.N + j.A - 1) / j.A * j.A;
+        const uint64_t lo = x.off - start[b], hi = lo + x.len;
+        if (x.off != next || x.len == 0 || hi > len || lo / chunk != x.rank0 || (hi - 1) / chunk != x.rank0) return false;
+        next += x.len;
+    }
+    return next == j.P;
+}
+
 // Which form a job's size chooses, on both sides of every line.
 static int check_rule()
 {
@@ -196,14 +215,17 @@ static int check_rule()
         Job j(l.n, l.p);
         CHECK(j.h && j.reduce() == ES_OK && l_shape.wave_width == l.width);
         if (l.width) CHECK(l_shape.wave_batch == l.batch && l_shape.wave_pad_kib == l.pad);
-        uint64_t sum = 0;
-        for (const Tile& t : l_copy) {
-            CHECK(t.off == sum || !l.width);    // big tiles are listed first
-            if (l.width) CHECK(t.len <= 64u * l.width);
-            sum += t.len;
-        }
-        CHECK(sum == l.p);
+        for (const Tile& t : l_copy) CHECK(!l.width || t.len <= 64u * l.width);
+        CHECK(tiles_follow_the_ring(j));
+        CHECK(es_set_option(j.h, "reduce_auto", 0) == ES_OK && j.reduce() == ES_OK && tiles_follow_the_ring(j));
     }
+    for (uint32_t a : {1u, 3u, 4u, 64u})
+        for (uint64_t p : {1ull, 5ull, 63ull, 64ull, 200ull, 1001ull, 70001ull, 300007ull, 2000003ull})
+            for (uint32_t n : {1u, 2u, 7u, 8u, 33u, 64u}) {
+                Job j(n, p, a);
+                CHECK(j.h && j.reduce() == ES_OK && l_shape.wave_width && tiles_follow_the_ring(j));
+                for (const Tile& t : l_copy) CHECK(t.len <= 64u * l_shape.wave_width);
+            }
     const struct { uint32_t n; uint64_t p; int streamed; } policy[] = {
         {1, 13999999, 0}, {1, 14000000, 1}, {31, 4999999, 0}, {32, 999999, 0}, {32, 1000000, 1}, {64, 4999999, 1}, {64, 5000000, 0}};
     for (const auto& l : policy) {

@@ -69,9 +69,16 @@ def test_infinities_and_nan_stay_in_their_channel(HW):
     assert np.isfinite(got_m[[0, 2, 4, 5]]).all() and np.isinf(got_m[1]) and np.isnan(got_m[3])
 
 
-@pytest.mark.parametrize("Bn,C,HW", [(2, 140_000 // 4, 15_361), (2, 9_000, 60_000), (1, 1_100, 1_000_001)])
+@pytest.mark.parametrize("Bn,C,HW", [
+    (2, 140_000 // 4, 15_361), (2, 9_000, 60_000), (1, 1_100, 1_000_001),
+    # short ragged images and images below four positions: up to 16 blocks, up to 25, up to 256, more
+    (600, 40_000, 49), (1_700, 13_000, 49), (3_000, 7_400, 49), (25_000, 900, 49),
+    (20_000, 20_000, 3), (30_000, 12_000, 3), (50_000, 7_200, 3), (400_000, 900, 3),
+    # long images and whole vectors in the forms not reached above
+    (100, 12_000, 901), (1_200, 1_000, 901), (100, 12_000, 900), (1_200, 1_000, 900)])
 def test_offsets_beyond_32_bits(Bn, C, HW):
-    """x of more than 4 GiB: the same bits as its channels a slice at a time (32-bit offsets)."""
+    """x of more than 4 GiB: the same bits as its channels a slice at a time (32-bit offsets).  A channel of
+    one block cannot get there: 65,535 of them are 1.07 GB."""
     assert 4 * Bn * C * HW > 1 << 32
     g = torch.Generator(device=DEV)
     g.manual_seed(HW)

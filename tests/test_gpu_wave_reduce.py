@@ -70,11 +70,11 @@ def same(a, b):
     return True
 
 
-def check(N, lens, A, seed, special=False, with_oracle=False, streaming=(0, 1)):
+def check(N, lens, A, seed, special=False, with_oracle=False):
     job, rows, p0, v0, buckets = make(N, lens, A, seed, special)
     try:
         got = {}
-        for nt in streaming:
+        for nt in (0, 1):
             job.set_option("nontemporal_pv", nt)
             for how in ("reduce", "fused", "fused+avg"):
                 got[nt, how] = step(job, p0, v0, how)
@@ -90,7 +90,7 @@ def check(N, lens, A, seed, special=False, with_oracle=False, streaming=(0, 1)):
                                    for o, n in buckets if n])
             pw, vw = p0.cpu().numpy().copy(), v0.cpu().numpy().copy()
             oracle.sgd_momentum(pw, vw, want, LR, MU)
-            for nt in streaming:
+            for nt in (0, 1):
                 avg, p, v = (t.cpu().numpy().view(np.uint32) for t in got[nt, "fused+avg"])
                 assert np.array_equal(avg, want.view(np.uint32)), (N, A, nt)
                 assert np.array_equal(p, pw.view(np.uint32)) and np.array_equal(v, vw.view(np.uint32)), (N, A, nt)
@@ -118,7 +118,7 @@ def test_infinities_nan_and_denormals(N):
     (8, 4_999_999), (12, 5_000_000), (8, 8_000_001), (10, 8_100_019), (11, 8_000_001), (24, 2_000_003), (8, 64_000_000), (9, 63_999_999)])
 def test_both_sides_of_every_line_of_the_rule(N, P):
     for A in (1, 4):
-        check(N, [P // 3 + 1, P - 2 * (P // 3) - 2, P // 3 + 1], A, P + N, streaming=(1,) if P > 2_000_000 else (0, 1))
+        check(N, [P // 3 + 1, P - 2 * (P // 3) - 2, P // 3 + 1], A, P + N)
 
 
 def test_options_choose_the_shape_and_keep_their_values():
