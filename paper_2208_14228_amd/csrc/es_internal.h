@@ -54,7 +54,9 @@ inline uint32_t reduce_lds_pad(int option_kib, uint32_t n_ranks, bool streaming_
 }
 // Lanes per workgroup of the staging copies: one wave for long ones, two for short ones, which the
 // rate of starting workgroups bounds as much as memory (0.5 M floats 2.49 -> 2.32 us, 1 M 3.40 -> 3.06,
-// 2 M 4.56 -> 3.87 together with plain loads; from 4 M on no better, from 7 M on 3 % worse).
+// 2 M 4.56 -> 3.87 together with plain loads; 4.2 M 7.03 -> 6.35, but from 7 M on 3-10 % worse).  In a staged
+// step the plain loads also fill the caches that the reduce reads from: at 2.9 M floats per copy the short
+// form gains 3-5 % up to 4 ranks, nothing at 5, and loses 5 % at 7, so the line is not drawn higher.
 constexpr uint32_t kCopyBlock = 64;
 constexpr uint32_t kCopyBlockShort = 128;
 constexpr uint64_t kShortCopy = 3ull << 20;      // floats of one call

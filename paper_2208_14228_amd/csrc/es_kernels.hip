@@ -38,8 +38,9 @@ __device__ __forceinline__ f4 ld4(const float* p)
 __device__ __forceinline__ void st4(float* p, f4 x) { *reinterpret_cast<f4*>(p) = x; }
 
 // Parameter / momentum traffic of the update, and the store of the averaged
-// gradient.  Touched once per global step: streamed where stream_pv says so (fused: +6 % at P = 109 M; the unfused reduce: +11 % at P = 109 M, N = 16 and +13 %
-// at P = 355 M, N = 64 from the store of the averaged gradient alone).
+// gradient.  Touched once per global step: streamed where stream_pv says so
+// (fused: +6 % at P = 109 M; the unfused reduce: +11 % at P = 109 M, N = 16 and
+// +13 % at P = 355 M, N = 64 from the store of the averaged gradient alone).
 template <bool NTPV>
 __device__ __forceinline__ f4 ld4_pv(const float* p)
 {
@@ -817,7 +818,7 @@ __global__ __launch_bounds__(kBlock) void k_sq_partials(const float* __restrict_
 // workgroup does this while the GPU waits, so what counts is the number of round trips to memory:
 // 32 loads are issued ahead of their adds while that many are left (without the clamp of the
 // last round: it kept the loads from going out together), then 8.  The norm of 355 M values
-// (86,627 partials) went from 232 to 222 us, of 109 M from 73.6 to 71.0 us.
+// (86,627 partials) went from 224.7 to 216.2 us, of 109 M from 72.9 to 70.3 us.
 __device__ __forceinline__ float lane_partials(const float* __restrict__ part, uint64_t nblk)
 {
     float s = 0.0f;
@@ -1070,7 +1071,8 @@ __global__ __launch_bounds__(kBlock) void k_ctx(const Piece* pieces_g, uint8_t* 
 // lane), all others are the staging copy of the outgoing EST's gradient runs.  The two parts touch
 // disjoint memory, so no ordering between them is needed inside the launch.
 // RUNS is CopyRuns, or CopyRun where the gradients are one run (the common case: no lookup, and 24
-// instead of 488 bytes of arguments for the host to write and every workgroup to fetch).
+// instead of 464 bytes of a table, 60 instead of 500 of arguments in all, for the host to write and every
+// workgroup to fetch).
 template <uint32_t BS, typename RUNS>
 __global__ __launch_bounds__(BS) void k_est_boundary(const RUNS runs, const Piece* pieces_g,
                                                      uint32_t n_pieces, uint8_t* slot_a,
@@ -1579,8 +1581,8 @@ static void launch_bn(hipStream_t s, const float* x, const BnGeom& g, float* mea
     // one launch is ahead again (1 and 3 positions 90 / 127 and 83 / 101 us) except for vectors of one image each
     // (4 positions 51 / 42), and from 16 positions on it is everywhere as fast as two launches per pass.
     const bool spread = g.HW < 8 ? g.nblk >= 8 && g.C <= (g.HW == 4 ? 255 : 128) : g.HW < 16 && g.nblk > 12 && g.C <= 64;
-    if (g.nblk == 1) {
-        hipLaunchKernelGGL((k_bn_channel<MODE, OFF, kBnSingle>), dim3((g.C + kBnSingles - 1) / kBnSingles),
+    if (g.nblk == 1) {                                  // at most 65,535 x 4096 values: 32-bit offsets always
+        hipLaunchKernelGGL((k_bn_channel<MODE, uint32_t, kBnSingle>), dim3((g.C + kBnSingles - 1) / kBnSingles),
                            dim3(64 * kBnSingles), 0, s, x, g, fM, mean, var);
     } else if (g.nblk <= kBnWaves && !spread) {
         hipLaunchKernelGGL((k_bn_channel<MODE, OFF, kBnRegs>), dim3(g.C), dim3(64 * g.nblk), 0, s, x, g, fM, mean, var);
