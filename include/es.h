@@ -110,7 +110,9 @@ typedef struct es_bucket_layout {
  * Starts with one simulated worker that holds all ESTs (slot = rank), all
  * streams = the null stream, and no live state bound.
  * Allocates n_logical gradient slots of n_params floats and n_logical small
- * context slots on the device.  *out is set only on success.
+ * context slots on the device, and uploads the tile tables of the reduce (16 bytes per
+ * 2048 to 32768 elements; for a job the wave-tile form is for, see es_set_option, also
+ * 16 bytes per 64 or 256: 0.03 to 0.1 ms more than without).  *out is set only on success.
  */
 int es_init(es_handle** out, uint32_t n_logical, const es_bucket_layout* layout);
 
@@ -432,9 +434,10 @@ int es_sync(es_handle* h);
  * Options (never change results).  As long as "reduce_auto" is 1, a reduce of up to 64 ranks over
  * fewer than 8 M parameters (from 8 ranks on 5 M), all gradient slots in HBM, runs in the wave-tile
  * form, a launch shape of its own (one wave per 64 or 256 elements, chosen by both numbers) that the
- * other reduce_* options do not describe.  Setting one of those ("reduce_lds_pad_kib" = -1 apart, which asks for nothing), or
- * "nontemporal" = 0, also to the value it has, sets "reduce_auto" to 0: the shape they describe
- * takes the form's place, there as everywhere, until "reduce_auto" is set to 1 again.
+ * other reduce_* options do not describe.  Setting one of those ("reduce_lds_pad_kib" = -1 apart,
+ * which asks for nothing), or "nontemporal" = 0, also to the value it has, sets "reduce_auto" to 0:
+ * the shape they describe takes the form's place, there as everywhere, until "reduce_auto" is set
+ * to 1 again.
  * "reduce_tile_elems", "reduce_big_unroll", "reduce_big_rank_batch" and "swap_in" wait for the
  * handle's streams and replace a device table; a launch captured into a graph after an earlier
  * call of the same kind must be captured again (the tables of es_init stay until es_destroy, so
@@ -515,7 +518,8 @@ int es_plan_swap_in(uint32_t n_buckets, es_swap_op* out, uint64_t capacity, uint
 
 /*
  * Host-only planning helper (touches no device): the work decomposition of the
- * ring-ordered reduce for a layout.  Each tile is a range of the flat parameter
+ * ring-ordered reduce for a layout, as the options describe it (the wave-tile form cuts
+ * the same chunks into tiles of 64 or 256 elements by the same rule).  Each tile is a range of the flat parameter
  * space that lies inside ONE ring chunk of one bucket; start_rank is the virtual
  * rank whose gradient opens the fold for every element of the tile (= the chunk
  * index, see es_ring_order_reduce).  The first *n_big tiles are big tiles of

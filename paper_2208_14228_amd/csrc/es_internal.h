@@ -115,7 +115,7 @@ inline bool stream_pv(uint32_t N, uint64_t P)
 //    zero-copy 1.05-1.12 / 0.92-0.97 at 4.5 M, 0.94-1.03 / 0.87-0.93 at 5.5 M, 0.90-0.98 / 0.93-0.99 at 6.5 M; clipped
 //    1.11-1.13 / 0.94-1.0, 0.98-1.03 / 0.90-1.0, 0.94-1.0 / 0.93-0.99; staged steps gain to 8 M, by 1-5 %.  8 to 10 ranks,
 //    zero-copy: 1.02-1.05 / 0.95-1.06 at 3.3 M, 0.96-0.99 / 0.94-0.99 at 5.5 M.  With 8 to 10 ranks at 25.6 M, both with
-//    parameters and momentum streamed: fused 0.98-1.02 / 0.96-0.98, staged and hooked steps 1.0, unfused 0.92-0.97.
+//    parameters and momentum streamed: fused 0.98-1.03 / 0.96-0.98, staged and hooked steps 1.0, unfused 0.92-0.97.
 //    (Where three zero-copy jobs fill the chip together the other kernels' long reads win from 2 M and 12 ranks on, by
 //    3-14 %; a job that has the GPU to itself is 1.05-1.75 times as fast by this form there, so the line follows that.)
 //  - one float per lane below 300 k elements and from 8 ranks on, where four leave SIMDs without a wave
