@@ -90,17 +90,18 @@ struct ReduceShape {
 
 // Whether parameters, momentum and the averaged gradient are streamed by default.  Cacheable over
 // streaming time of a zero-copy step, fused / with clipping (reduce, norm and update kernel):
-//  - after something has swept the caches, as the model does between two reduces of a training job (a 1 GiB
-//    fill): 0.98-1.22 / 0.99-1.14 from 1 M to 32 M parameters at 1 to 64 ranks;
-//  - three jobs in turn on one stream: 1.03-1.10 / 1.0-1.10 from 14 M on (their parameters and momentum exceed the
-//    Infinity Cache), 0.94-1.02 / 1.0-1.07 at 12 M, 0.83-1.0 / 0.98-1.03 at 4 to 10 M (they come back from it), but
-//    1.0-1.08 / 0.99-1.03 from 1 M to 5 M with 32 ranks or more (wave tiles; the gradients push them out);
-//  - three jobs on a stream each: 0.95-1.10 / 0.93-1.10 from 14 M on, 0.90-1.02 / 0.93-1.05 at 12 M, 0.87-0.99 / 0.92-1.02 at
-//    8 to 10 M, 0.94-1.05 / 0.92-1.02 from 1 M to 5 M with 32 ranks or more;
-//  - one job in a loop of nothing but these calls: 0.88-0.98 / 0.95-1.02 from 8 to 37 M up to 12 ranks, 0.96-1.0 /
-//    0.98-1.02 beyond.  The update kernel alone takes 0.0893 ms for 0.0817 in such a loop at 25.6 M, the
-//    reduce alone gains from the average's store; above 37 M streaming wins in every loop.
-// The line lies where streaming wins or ties in the first two, and in the third for the most part.
+//
+//                             1 to 5 M, 32 ranks +   8 to 10 M                12 M                    14 to 25 M
+//  caches swept before        1.04-1.10 / 1.00-1.11  0.96-1.11 / 0.99-1.07  0.97-1.12 / 0.99-1.06  0.98-1.14 / 0.98-1.09
+//  three jobs on one stream   0.99-1.08 / 0.98-1.03  0.86-1.00 / 0.98-1.04  0.93-1.03 / 1.00-1.07  1.00-1.11 / 0.99-1.08
+//  three, on a stream each    0.94-1.05 / 0.92-1.11  0.87-0.99 / 0.92-1.02  0.91-1.06 / 0.93-1.05  0.93-1.10 / 0.95-1.10
+//  one job, nothing else      0.95-1.09 / 0.97-1.05  0.88-1.04 / 0.96-1.03  0.91-0.99 / 0.97-1.02  0.88-1.05 / 0.95-1.04
+//
+// The first is a training job, whose model uses the caches between two reduces; in the others parameters
+// and momentum can come back from the Infinity Cache, up to 37 M for one job and 12 M for three, unless the
+// gradients push them out (32 ranks or more, wave tiles).  The line lies where streaming wins or ties in the
+// first two and for the most part in the third.  One bit rules the update kernel as well, which alone in a
+// loop takes 0.0893 ms for 0.0817 at 25.6 M; above 37 M streaming wins in every loop.
 inline bool stream_pv(uint32_t N, uint64_t P)
 {
     return P >= 14000000 || (N >= 32 && P >= 1000000 && P < 5000000);
@@ -111,22 +112,27 @@ inline bool stream_pv(uint32_t N, uint64_t P)
 // x 9 sizes, fused, three jobs in turn (time of the other kernels over this one's):
 //  - N <= 64: the slot table is one pointer per lane.
 //  - P < 8 M, from 8 ranks on 5 M: 1.0-1.3 at 4 M, 1.0-2.2 at 1 M, 1.05-3.4 at 20 k.  Above, a wave's 1 KiB per
-//    stream costs what the saved round trips gain.  From 12 ranks on, one stream / three jobs on a stream each:
-//    zero-copy 1.05-1.12 / 0.92-0.97 at 4.5 M, 0.94-1.03 / 0.87-0.93 at 5.5 M, 0.90-0.98 / 0.93-0.99 at 6.5 M; clipped
-//    1.11-1.13 / 0.94-1.0, 0.98-1.03 / 0.90-1.0, 0.94-1.0 / 0.93-0.99; staged steps gain to 8 M, by 1-5 %.  8 to 10 ranks,
-//    zero-copy: 1.02-1.05 / 0.95-1.06 at 3.3 M, 0.96-0.99 / 0.94-0.99 at 5.5 M.  With 8 to 10 ranks at 25.6 M, both with
-//    parameters and momentum streamed: fused 0.98-1.03 / 0.96-0.98, staged and hooked steps 1.0, unfused 0.92-0.97.
-//    (Where three zero-copy jobs fill the chip together the other kernels' long reads win from 2 M and 12 ranks on, by
-//    3-14 %; a job that has the GPU to itself is 1.05-1.75 times as fast by this form there, so the line follows that.)
+//    stream costs what the saved round trips gain.  On one stream / three jobs on a stream each:
+//      12 ranks and more, zero-copy  1.05-1.12 / 0.92-0.97 at 4.5 M, 0.94-1.03 / 0.87-0.93 at 5.5 M, 0.90-0.98 /
+//                                    0.93-0.99 at 6.5 M
+//      the same, clipped             1.11-1.13 / 0.94-1.0, 0.98-1.03 / 0.90-1.0, 0.94-1.0 / 0.93-0.99
+//      the same, staged              1.05-1.09 / 1.06-1.11, 1.02-1.05 / 1.0-1.16, 1.0-1.04 / 1.01-1.11
+//      8 to 10 ranks, zero-copy      1.02-1.05 / 0.95-1.06 at 3.3 M, 0.96-0.99 / 0.94-0.99 at 5.5 M
+//      8 to 10 ranks at 25.6 M, both with parameters and momentum streamed: fused 0.98-1.03 / 0.96-0.98,
+//                                    staged and hooked 1.0, unfused 0.92-0.97
+//    Where three zero-copy jobs fill the chip together the other kernels' long reads win from 2 M and 12 ranks
+//    on, by 3-14 %; a job that has the GPU to itself is 1.05-1.75 times as fast by this form there, and the
+//    line follows that.
 //  - one float per lane below 300 k elements and from 8 ranks on, where four leave SIMDs without a wave
 //    (1.1-1.7 x slower at 100 k, 1.0-1.1 x faster at 500 k); then as many ranks per batch as there are,
 //    up to 64, while a SIMD has at most two waves (P <= 128 k), else 16.
 //  - four floats per lane: batches of 4, of 8 from 8 to 23 ranks (a second round trip less: 1.0-1.1).
-//  - 5 workgroups per CU, or 2 where there are many streams (1.01-1.04 from 24 ranks and 2 M on); no cap with fewer than 8 ranks from 1.5 M elements on, where 5 per CU cost 0.86-0.98 of
-//    the other kernels' rate in zero-copy steps of one to three ranks and none costs nothing: staged steps 1.0-1.2
-//    on one stream and, as three jobs on a stream each, 21.0 us for 21.2 at 2 ranks and 3.3 M, 38.1 for 39.1 at 4
-//    and 4 M, 69.8 for 70.7 at 4 and 7.6 M.  (One wave per workgroup is 2-4 % faster alone, and slower than
-//    the other kernels beside other jobs' copies: 22.2, 41.3 and 73.6 us.)
+//  - 5 workgroups per CU, or 2 where there are many streams (1.01-1.04 from 24 ranks and 2 M on); no cap with
+//    fewer than 8 ranks from 1.5 M elements on, where 5 per CU reach 0.86-0.98 of the other kernels' rate in
+//    zero-copy steps of one to three ranks and no cap costs nothing: staged steps 1.0-1.2 on one stream and, as
+//    three jobs on a stream each, 21.0 us for 21.2 at 2 ranks and 3.3 M, 38.1 for 39.1 at 4 and 4 M, 69.8 for
+//    70.7 at 4 and 7.6 M.  (One wave per workgroup is 2-4 % faster alone, and slower than the other kernels
+//    beside other jobs' copies: 22.2, 41.3 and 73.6 us.)
 inline bool wave_shape(uint32_t N, uint64_t P, ReduceShape& sh)
 {
     if (N == 0 || N > 64 || P >= (N < 8 ? 8000000u : 5000000u)) return false;
