@@ -23,7 +23,7 @@ struct Worker {
     uint32_t n_slots = 0;
     float* grad_arena = nullptr;        // n_slots * grad_stride floats
     bool grad_on_host = false;          // arena is pinned host memory mapped into the device
-    uint8_t* ctx_arena = nullptr;       // n_slots * ctx_stride bytes
+    uint8_t* ctx_arena = nullptr;       // n_slots * ctx_stride bytes, then the mask launches' counters
     std::vector<void*> live;            // bound live tensors (device addresses)
     Piece* d_pieces = nullptr;
     uint32_t n_pieces = 0;
@@ -39,6 +39,8 @@ struct es_handle {
     uint32_t A = 1;
     std::vector<es_bucket> buckets;
     std::vector<uint64_t> seg_bytes, seg_off;   // seg_off: byte offset inside a context slot
+    std::vector<uint32_t> seg_counter;          // 16-byte segments (RNG states): which of the n_counters counter sets
+    uint32_t n_counters = 0;                    // behind a worker's context slots is this segment's
     uint64_t ctx_bytes = 0;                     // payload of one context slot (16-byte padded segments)
     uint64_t ctx_stride = 0;                    // bytes between context slots
     uint64_t grad_stride = 0;                   // floats between gradient slots
@@ -170,7 +172,7 @@ int alloc_worker(es_handle* h, Worker& w, uint32_t n_slots)
 {
     w.n_slots = n_slots;
     const uint64_t gbytes = (uint64_t)n_slots * h->grad_stride * sizeof(float);
-    const uint64_t cbytes = (uint64_t)n_slots * h->ctx_stride;
+    const uint64_t cbytes = (uint64_t)n_slots * h->ctx_stride + (uint64_t)h->n_counters * kArrivalWords * sizeof(uint32_t);
     if (gbytes) {
         // host placement: pinned, device-mapped memory; the staging copy and the reduce then
         // reach the gradients over the host link with the same kernels (memory-pressure mode)
@@ -575,6 +577,8 @@ int es_init(es_handle** out, uint32_t n_logical, const es_bucket_layout* lay)
         for (uint32_t j = 0; j < lay->n_state_segs; ++j) {
             h->seg_bytes.push_back(lay->state_seg_bytes[j]);
             h->seg_off.push_back(off);
+            h->seg_counter.push_back(h->n_counters);
+            if (lay->state_seg_bytes[j] == 16) ++h->n_counters;
             off += round_up(lay->state_seg_bytes[j], 16);
         }
         h->ctx_bytes = off;
@@ -1121,7 +1125,14 @@ int es_dropout_mask(es_handle* h, uint32_t est, uint32_t state_seg, uint8_t* d_m
     if (!w.bound) return ES_ESTATE;
     if (((uintptr_t)w.live[state_seg]) & 7) return ES_EINVAL;
     uint64_t thr = p >= 1.0 ? (1ull << 32) : (uint64_t)(p * 4294967296.0);
-    ES_HIP(h, launch_dropout_mask(h->s_main, (uint64_t*)w.live[state_seg], d_mask, n, thr));
+    uint64_t* state = (uint64_t*)w.live[state_seg];
+    if (n <= kShortMask || !launch_dropout_mask_long) {
+        ES_HIP(h, launch_dropout_mask(h->s_main, state, d_mask, n, thr));
+    } else {
+        uint32_t* counters = (uint32_t*)(w.ctx_arena + (uint64_t)w.n_slots * h->ctx_stride);
+        ES_HIP(h, launch_dropout_mask_long(h->s_main, state, d_mask, n, thr,
+                                           counters + (uint64_t)h->seg_counter[state_seg] * kArrivalWords));
+    }
     return ES_OK;
 }
 

@@ -224,7 +224,21 @@ hipError_t launch_sgd_clip(hipStream_t s, float* p, float* v, const float* g, ui
 hipError_t launch_bn_batch_stats(hipStream_t s, const float* x, uint32_t B, uint32_t C, uint32_t HW,
                                  float* mean, float* var, float* part);
 
+// mask[0..n) from state = {seed, offset}, offset += ceil(n / 4); n <= kShortMask, threshold <= 2^32
+constexpr uint32_t kMaskGroup = 1024;            // lanes of the one workgroup
+constexpr uint64_t kShortMask = 16 * kMaskGroup;
 hipError_t launch_dropout_mask(hipStream_t s, uint64_t* state, uint8_t* mask, uint64_t n,
                                uint64_t threshold);
+
+// The same for any n, given counters of the workgroups that have read the state: 32-bit words a line apart,
+// zero before the first launch and left at zero by every one.  Launches that can be in flight at the same
+// time need different ones, as they need different states.
+constexpr uint32_t kOneCounter = 64;             // workgroups that share one counter
+constexpr uint32_t kCounters = 16;               // counters beyond that, and one more
+constexpr uint32_t kCounterStep = 32;            // words between two counters
+constexpr uint32_t kArrivalWords = (kCounters + 1) * kCounterStep;
+// (weak, so that a host program whose launchers do nothing can do without it)
+__attribute__((weak)) hipError_t launch_dropout_mask_long(hipStream_t s, uint64_t* state, uint8_t* mask, uint64_t n,
+                                                          uint64_t threshold, uint32_t* arrivals);
 
 }  // namespace es

@@ -1184,36 +1184,54 @@ __device__ __forceinline__ void philox4x32_10_uniform_hi(uint32_t c0, uint32_t h
     out[0] = c0; out[1] = c1; out[2] = c2; out[3] = c3;
 }
 
-// The 16 mask bytes of lane index t (4 counter values): byte j is 1 iff its word is >= threshold.
-// `offset`, k0 and k1 are uniform; `first` is the t of the wave's lane 0.
-__device__ __forceinline__ void mask_bytes(uint64_t t, uint64_t first, uint64_t offset, uint32_t k0, uint32_t k1,
-                                           uint32_t threshold, bool none, uint32_t (&packed)[4])
+// 1 if w >= threshold, else 0, for keep = 2^32 - threshold: the carry of a 64-bit sum.  (A comparison and a
+// selection through a mask register take 12.7 cycles of a SIMD, this product by one 4.6; 2^32 and 0 are
+// thresholds like any other.)
+__device__ __forceinline__ uint32_t kept(uint32_t w, uint64_t keep)
 {
-    if (none) {                                         // threshold 2^32: nothing is kept
-#pragma unroll
-        for (int q = 0; q < 4; ++q) packed[q] = 0;
-        return;
-    }
+    uint64_t sum, carry;
+    asm("v_mad_u64_u32 %0, %1, %2, 1, %3" : "=v"(sum), "=s"(carry) : "v"(w), "s"(keep));
+    return (uint32_t)(sum >> 32);
+}
+
+// bytes << 8 | kept(w, keep) in one instruction more (the compiler, which cannot know that the second is 0 or 1,
+// makes two or three of it)
+__device__ __forceinline__ uint32_t push_kept(uint32_t bytes, uint32_t w, uint64_t keep)
+{
+    uint32_t r;
+    asm("v_lshl_or_b32 %0, %1, 8, %2" : "=v"(r) : "v"(bytes), "v"(kept(w, keep)));
+    return r;
+}
+
+// The 16 mask bytes (4 counter values) of a lane of the wave that starts at the 16 bytes number `first`:
+// byte j is 1 iff its word reaches the threshold.  All arguments but the lane are uniform.
+__device__ __forceinline__ void mask_bytes(uint32_t lane, uint64_t first, uint64_t offset, uint32_t k0, uint32_t k1,
+                                           uint64_t keep, uint32_t (&packed)[4])
+{
     const uint64_t base = offset + 4 * first;           // the wave's counters are base .. base + 255
-    const bool carries = (uint32_t)base > 0xFFFFFFFFu - 255u;
-    const uint64_t pos0 = offset + 4 * t;
+    auto pack = [&](const uint32_t (&w)[4]) {
+        return push_kept(push_kept(push_kept(kept(w[3], keep), w[2], keep), w[1], keep), w[0], keep);
+    };
+    if ((uint32_t)base <= 0xFFFFFFFFu - 255u) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        uint32_t w[4];
-        if (carries) {
-            const uint64_t pos = pos0 + q;
-            philox4x32_10((uint32_t)pos, (uint32_t)(pos >> 32), 0u, 0u, k0, k1, w);
-        } else {
-            philox4x32_10_uniform_hi((uint32_t)pos0 + q, (uint32_t)(base >> 32), k0, k1, w);
+        for (int q = 0; q < 4; ++q) {
+            uint32_t w[4];
+            philox4x32_10_uniform_hi((uint32_t)base + (4 * lane + q), (uint32_t)(base >> 32), k0, k1, w);
+            packed[q] = pack(w);
         }
-        uint32_t word = 0;
+    } else {                                            // a carry into the second word inside the wave
 #pragma unroll
-        for (int k = 0; k < 4; ++k) word |= w[k] >= threshold ? 1u << (8 * k) : 0u;
-        packed[q] = word;
+        for (int q = 0; q < 4; ++q) {
+            uint32_t w[4];
+            const uint64_t pos = base + (4 * lane + q);
+            philox4x32_10((uint32_t)pos, (uint32_t)(pos >> 32), 0u, 0u, k0, k1, w);
+            packed[q] = pack(w);
+        }
     }
 }
 
-__device__ __forceinline__ void store_mask(uint8_t* __restrict__ mask, uint64_t j0, uint64_t n, int aligned16,
+// Bytes j0 .. j0 + 15 of a mask of which n bytes are left; none beyond.
+__device__ __forceinline__ void store_mask(uint8_t* __restrict__ mask, uint32_t j0, uint64_t n, int aligned16,
                                            const uint32_t (&packed)[4])
 {
     if (aligned16 && j0 + 16 <= n) {
@@ -1234,70 +1252,81 @@ __device__ __forceinline__ uint64_t uniform64(uint64_t v)
     return (uint64_t)hi << 32 | lo;
 }
 
-// Each lane draws 4 counter values = 16 mask bytes.  Integer-ALU bound: 16x12x512x512 bytes with
-// their advance launch 21.4 -> 16.9 us (3.0 TB/s of stores) by the shorter rounds above, one-instruction
-// exclusive ors of three words and 32-bit instead of 64-bit comparisons with the threshold.
-__global__ __launch_bounds__(kBlock) void k_dropout_mask(const uint64_t* __restrict__ state,
-                                                         uint8_t* __restrict__ mask, uint64_t n,
-                                                         uint32_t threshold, bool none, int aligned16)
+constexpr uint64_t kMaskGroups = 2048;                  // 8 workgroups of 4 waves per CU: all that are resident
+
+// Each lane draws 4 counter values = 16 mask bytes at a time.  Whichever workgroup is the last to have
+// read the state advances the offset, so no second launch is needed; no workgroup waits for another.
+// `arrivals` (one line per counter, zero between launches) counts them: on one counter up to kOneCounter
+// workgroups, beyond in kCounters groups whose last members meet on one more (an addition to a word
+// that others add to as well takes 12 ns: 1,024 of them 13 us on one word, nothing to be seen on 16).
+//
+// Integer-ALU bound: per four bytes 18 products, 19 exclusive ors and 7 instructions to compare and pack.
+// One launch instead of two, enqueued from the host: 16 KiB to 10 MB 7.0 -> 4.0 us a mask (that is what a launch
+// costs the host); GPU time of 70 kB 5.1 -> 3.7, 3.7 MB 5.9 -> 5.1.  16x12x512x512 bytes 16.9 -> 15.3 us
+// (3.3 TB/s of stores) where passes overlap, 23.9 -> 22.5 one after the other; 143 MB 47.0 -> 44.2.
+__global__ __launch_bounds__(kBlock) void k_dropout_mask(uint64_t* __restrict__ state, uint8_t* __restrict__ mask,
+                                                         uint64_t n, uint64_t keep, int aligned16,
+                                                         uint32_t* __restrict__ arrivals, uint32_t groups)
 {
-    const uint64_t seed = state[0];
-    const uint64_t offset = state[1];
-    const uint64_t t = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
-    const uint64_t j0 = 16 * t;
-    if (j0 >= n) return;
-    uint32_t packed[4];
-    mask_bytes(t, uniform64(t - (threadIdx.x & 63)), offset, (uint32_t)seed, (uint32_t)(seed >> 32), threshold, none, packed);
-    store_mask(mask, j0, n, aligned16, packed);
+    const uint64_t seed = uniform64(state[0]);
+    const uint64_t offset = uniform64(state[1]);
+    __syncthreads();                                    // every wave has its copy of the state
+    const uint32_t counters = groups > kOneCounter ? kCounters : 1;
+    const uint32_t mine = blockIdx.x % counters;
+    uint32_t before = 0;
+    if (threadIdx.x == 0)
+        before = __hip_atomic_fetch_add(arrivals + mine * kCounterStep, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const uint32_t lane = threadIdx.x & 63;
+    uint64_t first = (uint64_t)blockIdx.x * kBlock + __builtin_amdgcn_readfirstlane(threadIdx.x & ~63u);
+    for (; 16 * first < n; first += groups * kBlock) {  // `first` and the bounds stay in scalar registers
+        uint32_t packed[4];
+        mask_bytes(lane, first, offset, (uint32_t)seed, (uint32_t)(seed >> 32), keep, packed);
+        store_mask(mask + 16 * first, 16 * lane, n - 16 * first, aligned16, packed);
+    }
+    if (threadIdx.x != 0 || before + 1 != (groups - mine + counters - 1) / counters) return;
+    __hip_atomic_store(arrivals + mine * kCounterStep, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (counters > 1) {
+        uint32_t* last = arrivals + kCounters * kCounterStep;
+        if (__hip_atomic_fetch_add(last, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 != counters) return;
+        __hip_atomic_store(last, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    state[1] = offset + (n + 3) / 4;
 }
 
-__global__ void k_philox_advance(uint64_t* state, uint64_t blocks)
-{
-    if (blockIdx.x == 0 && threadIdx.x == 0) state[1] = state[1] + blocks;
-}
-
-// A short mask: one workgroup draws all of it and then advances the offset it has read, so the
-// second launch (which every other workgroup of a longer mask has to have read the state before)
-// goes away: a 1003-byte mask and an EST switch 10.8 -> 8.0 us.  Up to 16 KiB, 16 bytes for each of
-// its lanes: 3.35 us on the GPU against 4.2 for the pair; with a second round 24 KiB take 4.04 us and
-// 32 KiB 4.9, and the pair is as fast or faster.
-constexpr uint32_t kMaskGroup = 1024;
-constexpr uint64_t kShortMask = 16 * kMaskGroup;
-
+// A short mask: one workgroup of up to 16 waves draws all of it and advances the offset it has read.
 __global__ __launch_bounds__(kMaskGroup) void k_dropout_mask_short(uint64_t* __restrict__ state,
                                                                    uint8_t* __restrict__ mask, uint64_t n,
-                                                                   uint32_t threshold, bool none, int aligned16)
+                                                                   uint64_t keep, int aligned16)
 {
     const uint64_t seed = uniform64(state[0]);
     const uint64_t offset = uniform64(state[1]);
     __syncthreads();                                    // every wave has its copy of the state
     if (threadIdx.x == 0) state[1] = offset + (n + 3) / 4;
-    const uint64_t t = threadIdx.x;
-    if (16 * t >= n) return;
+    const uint32_t lane = threadIdx.x & 63;
+    const uint32_t first = __builtin_amdgcn_readfirstlane(threadIdx.x & ~63u);
     uint32_t packed[4];
-    mask_bytes(t, uniform64(t - (threadIdx.x & 63)), offset, (uint32_t)seed, (uint32_t)(seed >> 32), threshold, none, packed);
-    store_mask(mask, 16 * t, n, aligned16, packed);
+    mask_bytes(lane, first, offset, (uint32_t)seed, (uint32_t)(seed >> 32), keep, packed);
+    store_mask(mask + 16 * first, 16 * lane, n - 16 * first, aligned16, packed);
 }
 
-hipError_t launch_dropout_mask(hipStream_t s, uint64_t* state, uint8_t* mask, uint64_t n,
-                               uint64_t threshold)
+hipError_t launch_dropout_mask(hipStream_t s, uint64_t* state, uint8_t* mask, uint64_t n, uint64_t threshold)
 {
     if (n == 0) return hipSuccess;
-    const uint64_t lanes = (n + 15) / 16;
-    const int aligned16 = (((uintptr_t)mask) & 15) == 0;
-    const bool none = threshold > 0xFFFFFFFFull;
-    if (n <= kShortMask) {
-        const uint32_t block = (uint32_t)((lanes + 63) / 64 * 64);
-        hipLaunchKernelGGL(k_dropout_mask_short, dim3(1), dim3(block), 0, s, state, mask, n, (uint32_t)threshold, none,
-                           aligned16);
-        return hipGetLastError();
-    }
-    const uint64_t blocks = (lanes + kBlock - 1) / kBlock;
-    hipLaunchKernelGGL(k_dropout_mask, dim3((uint32_t)blocks), dim3(kBlock), 0, s, state, mask, n,
-                       (uint32_t)threshold, none, aligned16);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_philox_advance, dim3(1), dim3(64), 0, s, state, (n + 3) / 4);
+    if (n > kShortMask) return hipErrorInvalidValue;
+    const uint32_t block = (uint32_t)(((n + 15) / 16 + 63) / 64 * 64);
+    hipLaunchKernelGGL(k_dropout_mask_short, dim3(1), dim3(block), 0, s, state, mask, n, (1ull << 32) - threshold,
+                       ((uintptr_t)mask & 15) == 0);
+    return hipGetLastError();
+}
+
+hipError_t launch_dropout_mask_long(hipStream_t s, uint64_t* state, uint8_t* mask, uint64_t n, uint64_t threshold,
+                                    uint32_t* arrivals)
+{
+    if (n == 0) return hipSuccess;
+    const uint64_t all = ((n + 15) / 16 + kBlock - 1) / kBlock;
+    const uint32_t groups = (uint32_t)(all < kMaskGroups ? all : kMaskGroups);
+    hipLaunchKernelGGL(k_dropout_mask, dim3(groups), dim3(kBlock), 0, s, state, mask, n, (1ull << 32) - threshold,
+                       ((uintptr_t)mask & 15) == 0, arrivals, groups);
     return hipGetLastError();
 }
 
