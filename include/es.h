@@ -364,7 +364,7 @@ int es_clip_sgd_step(es_handle* h, float* d_param, float* d_momentum, const floa
  * the terms of the tree described at es_grad_sq_norm (terms instead of squares, terms beyond M
  * count as +0):  mean = T(y) / (float)M ;  var = T((y - mean)^2) / (float)M  (biased variance),
  * every subtraction, square, add and division rounded to fp32.  No atomics; the first stage
- * uses wave shuffles, the second an LDS stage.
+ * uses lane exchanges, the second an LDS stage.
  *   d_workspace      DEVICE scratch of at least es_bn_workspace_floats(..) floats, 4-byte aligned
  *   stream           HOST value of a hipStream_t on the current device (NULL = null stream)
  * Limits: M < 2^31, n_channels <= 65535, n_images and n_positions > 0 (ES_EINVAL otherwise;
