@@ -224,6 +224,11 @@ hipError_t launch_sgd_clip(hipStream_t s, float* p, float* v, const float* g, ui
 hipError_t launch_bn_batch_stats(hipStream_t s, const float* x, uint32_t B, uint32_t C, uint32_t HW,
                                  float* mean, float* var, float* part);
 
+// The same; where workgroups wait for each other's sums, each looks for them `polls` times and then reads
+// what it needs for itself.
+hipError_t launch_bn_batch_stats_polls(hipStream_t s, const float* x, uint32_t B, uint32_t C, uint32_t HW,
+                                       float* mean, float* var, float* part, uint32_t polls);
+
 // mask[0..n) from state = {seed, offset}, offset += ceil(n / 4); n <= kShortMask, threshold <= 2^32
 constexpr uint32_t kMaskGroup = 1024;            // lanes of the one workgroup
 constexpr uint64_t kShortMask = 16 * kMaskGroup;

@@ -10,6 +10,10 @@
 //  - loads may be issued early and in any order, only the add chain is ordered.
 #include "es_internal.h"
 
+#include <unistd.h>
+
+#include <atomic>
+#include <chrono>
 #include <mutex>
 #include <type_traits>
 
@@ -1544,16 +1548,263 @@ void k_bn_channel(const float* __restrict__ x, const BnGeom g, float fM, float* 
     }
 }
 
-// Longer channels read x twice (second pass over blocks in reverse: what the first read last may
-// still be in the L2s).
+// A channel of 26 to 1,024 blocks, x read once all the same: several workgroups hold its blocks, three per
+// wave in registers and one in LDS (32 per CU: 134 MB on the chip), and wait for each other's sums of the first
+// pass.  Workgroup g of G (a power of two) has the blocks g, g + G, g + 2G, ..: tree lanes t and t + 256 and the
+// strides down to G stay inside it, and its one sum is lane g of the tree's last levels.
+//
+// The sums travel through the workspace, whose contents are not known beforehand, so every one carries the launch's
+// tag: 64 bits that no other launch of the process has and that other contents hold with a probability of
+// 2^-64.  (A launch before this one could clear the workspace instead, at 3 us; a captured launch, whose tag comes
+// back with every replay, has that.)  Nothing depends on all workgroups of a channel being resident at once: one that has
+// looked for the others' sums `polls` times computes them from memory and goes on.
+//
+// Bound by reading x, then by one exchange of sums (2 us) and the second pass over what is held (3 us of three
+// operations per value).  Against reading x twice in three launches: 32x64x112x112 37.6 -> 21.7 us (captured, with the
+// clearing launch, 38.7 -> 24.9), 144x51x53x53 30.3 -> 19.9, 64x512x56x56 (411 MB, several rounds of workgroups) 138
+// -> 74, 26x4x64x64 8.4 -> 6.6, 256x3x120x120 19.1 -> 13.4.
+constexpr uint32_t kBnPerWave = 3;
+constexpr uint32_t kBnHeld = 4 * (kBnPerWave + 1);      // blocks per workgroup
+constexpr uint32_t kBnMostGroups = 64;                  // one per lane
+constexpr uint32_t kBnPolls = 100;                      // 100 to 200 us
+
+// A sum s under a tag: s, s ^ low half, s ^ high half.  Three words that were not all written together pass
+// for a sum only where they hold the right one.
+struct BnSum {
+    uint32_t word[3];
+};
+
+__device__ __forceinline__ void bn_publish(BnSum* to, float sum, uint64_t tag, uint32_t h)
+{
+    const uint32_t key = h == 0 ? 0 : (uint32_t)(h == 1 ? tag : tag >> 32);
+    if (h < 3) __hip_atomic_store(&to->word[h], __float_as_uint(sum) ^ key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Lane g of `sum`: what workgroup g has published at from[g]; lanes in `have` hold theirs already.  Returns the lanes
+// whose sum has not come.
+__device__ __forceinline__ unsigned long long bn_collect(BnSum* from, uint32_t groups, uint64_t tag, uint32_t polls,
+                                                         uint32_t h, bool have, float& sum)
+{
+    bool wanted = h < groups && !have;
+    for (uint32_t k = 0;; ++k) {
+        if (wanted) {
+            uint32_t v[3];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) v[k] = __hip_atomic_load(&from[h].word[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if ((v[0] ^ v[1]) == (uint32_t)tag && (v[0] ^ v[2]) == (uint32_t)(tag >> 32)) {
+                sum = __uint_as_float(v[0]);
+                wanted = false;
+            }
+        }
+        const unsigned long long missing = __ballot(wanted);
+        if (missing == 0 || k >= polls) return missing;
+        __builtin_amdgcn_s_sleep(1);
+    }
+}
+
+__global__ __launch_bounds__(kBlock) void k_bn_clear(uint32_t* __restrict__ words, uint32_t n)
+{
+    const uint32_t i = blockIdx.x * kBlock + threadIdx.x;
+    if (i < n) words[i] = 0;
+}
+
+// The sums part[0 .. n-1] of one workgroup's blocks, as the tree over its 256 / groups lanes combines them
+// (what further lanes and strides add is +0, and no sum is -0).
+__device__ __forceinline__ float bn_group_sum(const float* part, uint32_t n, uint32_t groups, uint32_t h)
+{
+    const uint32_t lanes = 256 / groups;
+    float r = 0.0f;
+    if (h < lanes)
+        for (uint32_t j = h; j < n; j += lanes) r = r + part[j];
+    return lane0(tree16(r));
+}
+
+// The sums of the workgroups in `missing` from memory into other[]; every wave of the workgroup calls it.
+template <bool SQDEV, int MODE, typename OFF>
+__device__ __forceinline__ void bn_recompute(const float* __restrict__ x, const BnGeom& g, uint32_t ch, uint32_t groups,
+                                             unsigned long long missing, float center, float* part, float* other,
+                                             uint32_t w, uint32_t h)
+{
+    for (; missing != 0; missing &= missing - 1) {
+        const uint32_t from = __builtin_ctzll(missing);
+        const uint32_t n = (g.nblk - from + groups - 1) / groups;
+        for (uint32_t j = w; j < n; j += 4) {
+            f4 t[4][4];
+            bn_load<MODE, OFF>(x, g, ch, from + j * groups, h, t);
+            const float s = bn_block_sum<SQDEV>(t, from + j * groups, h, g.M, center);
+            if (h == 0) part[j] = s;
+        }
+        __syncthreads();
+        if (w == 0) {
+            const float s = bn_group_sum(part, n, groups, h);
+            if (h == 0) other[from] = s;
+        }
+        __syncthreads();
+    }
+}
+
+template <int MODE, typename OFF>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void k_bn_shared(const float* __restrict__ x, const BnGeom g, uint32_t groups, float fM, float* __restrict__ mean,
+                 float* __restrict__ var, BnSum* __restrict__ sums, uint64_t tag, uint32_t polls)
+{
+    extern __shared__ __align__(16) float park[];       // [wave][vector][lane], if any wave has a fourth block
+    __shared__ float part[2][kBnHeld];
+    __shared__ float other[kBnMostGroups];
+    __shared__ unsigned long long s_missing;
+    const uint32_t h = threadIdx.x & 63;
+    const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t ch = blockIdx.x / groups;
+    const uint32_t grp = blockIdx.x % groups;
+    const uint32_t n = (g.nblk - grp + groups - 1) / groups;
+    auto block = [&](uint32_t j) { return grp + j * groups; };
+    auto load = [&](uint32_t j, f4 (&r)[4][4]) {
+        if (j < n) {
+            bn_load<MODE, OFF>(x, g, ch, block(j), h, r);
+        } else {                                        // not used, but no old value has to be kept for it either
+#pragma unroll
+            for (int i = 0; i < 16; ++i) r[i & 3][i >> 2] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+        }
+    };
+    f4* mine = reinterpret_cast<f4*>(park) + w * 16 * 64 + h;
+    BnSum* first = sums + (uint64_t)ch * 2 * groups;
+    BnSum* second = first + groups;
+    f4 t[kBnPerWave][4][4];
+    const uint32_t parked = 4 * kBnPerWave + w;
+    constexpr uint32_t kLast = kBnPerWave - 1;
+    // the parked block passes through the registers of the last one, behind the loads of the others
+    if (parked < n) bn_load<MODE, OFF>(x, g, ch, block(parked), h, t[kLast]);
+#pragma unroll
+    for (uint32_t k = 0; k < kLast; ++k) {
+        __builtin_amdgcn_sched_barrier(0);              // one block's addresses at a time
+        load(4 * k + w, t[k]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if (parked < n) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) mine[64 * i] = t[kLast][i & 3][i >> 2];
+        const float s = bn_block_sum<false>(t[kLast], block(parked), h, g.M, 0.0f);
+        if (h == 0) part[0][parked] = s;
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    load(4 * kLast + w, t[kLast]);
+#pragma unroll
+    for (uint32_t k = 0; k < kBnPerWave; ++k) {
+        __builtin_amdgcn_sched_barrier(0);
+        if (4 * k + w < n) {
+            const float s = bn_block_sum<false>(t[k], block(4 * k + w), h, g.M, 0.0f);
+            if (h == 0) part[0][4 * k + w] = s;
+        }
+    }
+    __syncthreads();
+    if (w == 0) {
+        float sum = bn_group_sum(part[0], n, groups, h);
+        bn_publish(first + grp, sum, tag, h);
+        const unsigned long long missing = bn_collect(first, groups, tag, polls, h, h == grp, sum);
+        if (h < groups) other[h] = sum;
+        if (h == 0) s_missing = missing;
+    }
+    __syncthreads();
+    unsigned long long missing = uniform64(s_missing);
+    if (missing != 0) {                                 // at the cost of this workgroup's own blocks, which are read again
+        bn_recompute<false, MODE, OFF>(x, g, ch, groups, missing, 0.0f, part[0], other, w, h);
+        uint32_t zero = 0;
+        asm volatile("" : "+s"(zero));                  // no address is kept from above for this
+#pragma unroll
+        for (uint32_t k = 0; k < kBnPerWave; ++k) {
+            __builtin_amdgcn_sched_barrier(0);
+            load(4 * k + w + zero, t[k]);
+        }
+    }
+    const float mu = lane0(tree64(h < groups ? other[h] : 0.0f)) / fM;
+#pragma unroll
+    for (uint32_t k = 0; k < kBnPerWave; ++k) {
+        __builtin_amdgcn_sched_barrier(0);
+        if (4 * k + w < n) {
+            const float s = bn_block_sum<true>(t[k], block(4 * k + w), h, g.M, mu);
+            if (h == 0) part[1][4 * k + w] = s;
+        }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if (parked < n) {                                   // what a lane parks only that lane reads back
+#pragma unroll
+        for (int i = 0; i < 16; ++i) t[0][i & 3][i >> 2] = mine[64 * i];
+        const float s = bn_block_sum<true>(t[0], block(parked), h, g.M, mu);
+        if (h == 0) part[1][parked] = s;
+    }
+    __syncthreads();
+    if (grp != 0) {
+        if (w == 0) bn_publish(second + grp, bn_group_sum(part[1], n, groups, h), tag, h);
+        return;
+    }
+    if (w == 0) {
+        float sum = bn_group_sum(part[1], n, groups, h);
+        missing = bn_collect(second, groups, tag, polls, h, h == 0, sum);
+        if (h < groups) other[h] = sum;
+        if (h == 0) s_missing = missing;
+    }
+    __syncthreads();
+    bn_recompute<true, MODE, OFF>(x, g, ch, groups, uniform64(s_missing), mu, part[1], other, w, h);
+    const float va = lane0(tree64(h < groups ? other[h] : 0.0f)) / fM;
+    if (threadIdx.x == 0) {
+        mean[ch] = mu;
+        var[ch] = va;
+    }
+}
+
+// The number of workgroups per channel: as few as hold it, more while they are all resident at once (two
+// per CU) and their sums fit the workspace of nblk floats per channel.
+static uint32_t bn_groups(uint32_t C, uint32_t nblk)
+{
+    constexpr uint32_t floats = 2 * sizeof(BnSum) / sizeof(float);
+    uint32_t n = 2;
+    while (n * kBnHeld < nblk) n *= 2;
+    while (n < kBnMostGroups && 2ull * n * C <= 512 && 2 * n * floats <= nblk) n *= 2;
+    return n;
+}
+
+// 64 bits that differ from launch to launch (the mixing steps are invertible), and from process to process.
+static uint64_t bn_tag()
+{
+    static const uint64_t seed = [] {
+        uint64_t s = 0;
+        if (getentropy(&s, sizeof(s)) != 0) s = (uint64_t)std::chrono::steady_clock::now().time_since_epoch().count();
+        return s;
+    }();
+    static std::atomic<uint64_t> launches{0};
+    uint64_t z = seed + 0x9E3779B97F4A7C15ull * ++launches;
+    z = (z ^ z >> 30) * 0xBF58476D1CE4E5B9ull;          // splitmix64
+    z = (z ^ z >> 27) * 0x94D049BB133111EBull;
+    z ^= z >> 31;
+    return z ? z : 1;                                   // a cleared workspace has no tag
+}
+
+// part: C * nblk floats, nblk >= 26; polls: see k_bn_shared
+template <int MODE, typename OFF>
+static void launch_bn_shared(hipStream_t s, const float* x, const BnGeom& g, float* mean, float* var, float* part, uint32_t polls,
+                             bool captured)
+{
+    const uint32_t n = bn_groups(g.C, g.nblk);
+    BnSum* sums = reinterpret_cast<BnSum*>(part);
+    if (captured) {
+        const uint32_t clear = (uint32_t)(2ull * g.C * n * (sizeof(BnSum) / sizeof(uint32_t)));
+        hipLaunchKernelGGL(k_bn_clear, dim3((clear + kBlock - 1) / kBlock), dim3(kBlock), 0, s, (uint32_t*)sums, clear);
+    }
+    const uint32_t most = (g.nblk + n - 1) / n;
+    const uint32_t parked = most > 4 * kBnPerWave ? most - 4 * kBnPerWave : 0;
+    hipLaunchKernelGGL((k_bn_shared<MODE, OFF>), dim3(g.C * n), dim3(kBlock), parked * 4096 * sizeof(float), s, x, g, n,
+                       (float)g.M, mean, var, sums, bn_tag(), polls);
+}
+
+// Longer channels, short images and little captured work read x twice (second pass over blocks in reverse:
+// what the first read last may still be in the L2s).
 //
 // Up to 256 blocks, and few channels of tiny images from 8 on (WIDE): the four waves of a workgroup take the blocks b, b + W/4,
 // b + W/2 and b + 3W/4, W being the number of blocks rounded up to a power of two, so the first
 // two levels of the partials' tree (strides W/2 and W/4) happen in the workgroup: W/4 sums per
 // channel are left, few enough for both passes' to fit in the workspace side by side and for one
 // wave to add up.  Every wave of the second pass forms the mean for itself while its terms are on
-// their way; three launches.  32x64x112x112 (98 blocks): 47.8 -> 37.4 us, two reads of 103 MB at
-// 6.5 TB/s each and 6 us of launches (a read that hits the Infinity Cache is no faster: 15 us).
+// their way; three launches.  (A read that hits the Infinity Cache is no faster than one that does not.)
 // Beyond that: one partial per block, and a launch after each pass that combines them.
 template <bool SQDEV, bool WIDE, int MODE, typename OFF>
 __global__ __launch_bounds__(kBlock) void k_bn_partials(const float* __restrict__ x, const BnGeom g, uint32_t groups, float fM,
@@ -1612,8 +1863,31 @@ __global__ __launch_bounds__(kBlock) void k_bn_final(const float* __restrict__ p
     if (threadIdx.x == 0) out[blockIdx.x] = s / fM;
 }
 
+// Whether a launch on the stream would be recorded instead of run.
+static bool bn_captured(hipStream_t s)
+{
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();                            // the legacy stream while another one is captured, say
+    return true;
+}
+
+// Whether several workgroups share a channel (k_bn_shared).  Up to 25 blocks one workgroup is 1.2-1.5 times as
+// fast, and images so short that they are read in single loads keep the forms below.  Captured, with the
+// clearing launch before it, little work takes longer so: 26 blocks 7.2 -> 10.4 us for 4 channels (0.4 MB each), 9.1
+// -> 9.6 for 20, 11.9 -> 10.7 for 40; 120 blocks 11.1 -> 11.3 for 8, 12.3 -> 12.2 for 10; 240 blocks 12.1 -> 12.7 for 5.
+// Enqueued, with no other launch than itself, it is ahead everywhere (1 to 8 channels of 26 to 1,000 blocks 1.2-1.5).
+template <int MODE>
+static bool bn_shares(const BnGeom& g, hipStream_t s, bool& captured)
+{
+    if ((MODE != kBnVector && MODE != kBnLong) || g.HW < 16) return false;
+    if (g.nblk <= kBnWaves + kBnExtra || g.nblk > kBnMostGroups * kBnHeld) return false;
+    captured = bn_captured(s);
+    return !captured || (uint64_t)g.C * g.nblk >= (g.nblk <= 64 ? 1000 : 1300);
+}
+
 template <int MODE, typename OFF>
-static void launch_bn(hipStream_t s, const float* x, const BnGeom& g, float* mean, float* var, float* part)
+static void launch_bn(hipStream_t s, const float* x, const BnGeom& g, float* mean, float* var, float* part, uint32_t polls)
 {
     const float fM = (float)g.M;
     // Few channels of many tiny images (a line of memory holds an image's few values of a channel, the rest
@@ -1624,6 +1898,7 @@ static void launch_bn(hipStream_t s, const float* x, const BnGeom& g, float* mea
     // one launch is ahead again (1 and 3 positions 90 / 127 and 83 / 101 us) except for vectors of one image each
     // (4 positions 51 / 42), and from 16 positions on it is everywhere as fast as two launches per pass.
     const bool spread = g.HW < 8 ? g.nblk >= 8 && g.C <= (g.HW == 4 ? 255 : 128) : g.HW < 16 && g.nblk > 12 && g.C <= 64;
+    bool captured = false;
     if (g.nblk == 1) {                                  // at most 65,535 x 4096 values: 32-bit offsets always
         hipLaunchKernelGGL((k_bn_channel<MODE, uint32_t, kBnSingle>), dim3((g.C + kBnSingles - 1) / kBnSingles),
                            dim3(64 * kBnSingles), 0, s, x, g, fM, mean, var);
@@ -1632,6 +1907,9 @@ static void launch_bn(hipStream_t s, const float* x, const BnGeom& g, float* mea
     } else if (g.nblk <= kBnWaves + kBnExtra && !spread) {
         hipLaunchKernelGGL((k_bn_channel<MODE, OFF, kBnParked>), dim3(g.C), dim3(64 * kBnWaves),
                            (g.nblk - kBnWaves) * 4096 * sizeof(float), s, x, g, fM, mean, var);
+    } else if (bn_shares<MODE>(g, s, captured)) {
+        if constexpr (MODE == kBnVector || MODE == kBnLong)
+            launch_bn_shared<MODE, OFF>(s, x, g, mean, var, part, polls, captured);
     } else if (g.nblk <= 256) {
         uint32_t n = 4;                                 // sums per channel: a quarter of the blocks' power of two
         while (4 * n < g.nblk) n *= 2;
@@ -1652,6 +1930,12 @@ static void launch_bn(hipStream_t s, const float* x, const BnGeom& g, float* mea
 hipError_t launch_bn_batch_stats(hipStream_t s, const float* x, uint32_t B, uint32_t C, uint32_t HW,
                                  float* mean, float* var, float* part)
 {
+    return launch_bn_batch_stats_polls(s, x, B, C, HW, mean, var, part, kBnPolls);
+}
+
+hipError_t launch_bn_batch_stats_polls(hipStream_t s, const float* x, uint32_t B, uint32_t C, uint32_t HW,
+                                       float* mean, float* var, float* part, uint32_t polls)
+{
     if (C == 0) return hipSuccess;
     BnGeom g;
     g.C = C;
@@ -1668,8 +1952,8 @@ hipError_t launch_bn_batch_stats(hipStream_t s, const float* x, uint32_t B, uint
     const bool small = (uint64_t)B * C * HW * sizeof(float) <= 0xFFFFFFFFull;
 #define ES_BN(MODE)                                                              \
     do {                                                                         \
-        if (small) launch_bn<MODE, uint32_t>(s, x, g, mean, var, part);          \
-        else launch_bn<MODE, uint64_t>(s, x, g, mean, var, part);                \
+        if (small) launch_bn<MODE, uint32_t>(s, x, g, mean, var, part, polls);          \
+        else launch_bn<MODE, uint64_t>(s, x, g, mean, var, part, polls);                \
     } while (0)
     if (HW % 4 == 0) ES_BN(kBnVector);
     else if (HW >= kBnLongHW) ES_BN(kBnLong);
