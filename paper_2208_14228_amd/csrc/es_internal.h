@@ -107,6 +107,13 @@ inline bool stream_pv(uint32_t N, uint64_t P)
     return P >= 14000000 || (N >= 32 && P >= 1000000 && P < 5000000);
 }
 
+// Whether the unfused reduce streams its average where stream_pv holds: what follows reads it once or twice,
+// and a short one is still in the Infinity Cache then.  Reduce, norm and clipped update, streamed over cacheable:
+// 15 M 1.00-1.02, 20 M 1.01-1.02, 25.6 M 1.00-1.02 up to 8 ranks and 0.98 with 24, 32 M 0.97-1.01, 40 M
+// 0.96-0.99, 50 M 0.96-0.99; 32 and 48 ranks with 1.5 to 4.5 M 1.01-1.05; reduce and update without a norm 1.01-1.05
+// from 15 to 18 M.  (A reduce alone, whose average nobody reads: 0.95-0.97.)
+inline bool stream_avg(uint64_t P) { return P >= 22000000; }
+
 // The wave-tile form where it is the faster one, by the rank count N and the parameter count P;
 // returns false (and leaves the shape alone) where the other kernels are.  Measured on 13 rank counts
 // x 9 sizes, fused, three jobs in turn (time of the other kernels over this one's):

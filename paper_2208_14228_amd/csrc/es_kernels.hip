@@ -794,19 +794,42 @@ __device__ __forceinline__ float tree256(float s, float* lds)
 // h+128 and h+192, so the strides 128 and 64 are adds between its own registers,
 // 32 .. 1 are wave shuffles, and no LDS or barrier is needed; all 16 loads of a
 // lane are in flight before the first add.
+//
+// Bound by reading x.  What usually follows is the clipped update, which reads the same vector from its start:
+// the first kNormKept blocks are read last and without the streaming hint, so that the Infinity Cache
+// (256 MB) still has them.  Reduce, norm and update together, all of x streamed / so: 15 M and 4 ranks 110 / 102 us,
+// 25.6 M and 8 ranks 267 / 252, 50 M and 12 ranks 650 / 621, 100 M and 8 ranks 1013 / 990, 109 M and 16 ranks
+// 1729 / 1707.  Kept blocks of 64, 128, 192 and 256 MB: 50 M and 2 ranks 284, 281, 288, 290 us (299 without), 150 M
+// and 2 ranks 920, 910, 906, 914; whether the others are read forwards or backwards makes no difference.  The norm alone,
+// 150 M: 85.1 / 85.8 us, and 94.6 with all of it kept: a cacheable read costs more unless something reads it again.
+constexpr uint64_t kNormKept = 10240;                   // 168 MB
+
+template <bool STREAM>
+__device__ __forceinline__ void load_block(const float* __restrict__ x, uint32_t h, f4 (&v)[4][4])
+{
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[j][q] = ld4<STREAM>(x + 4ull * (256 * q + 64 * j + h));
+}
+
 __global__ __launch_bounds__(kBlock) void k_sq_partials(const float* __restrict__ x, uint64_t n,
                                                         uint64_t nblk, float* __restrict__ part)
 {
     const uint32_t h = threadIdx.x & 63;
-    const uint64_t blk = (uint64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (blk >= nblk) return;                            // whole wave leaves together
+    const uint64_t k = (uint64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (k >= nblk) return;                              // whole wave leaves together
+    const uint64_t blk = nblk - 1 - k;
     const uint64_t base = blk * 4096;
     f4 v[4][4];                                         // [tree lane h + 64 j][q]
     if (base + 4096 <= n) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) v[j][q] = ld4<true>(x + base + 4ull * (256 * q + 64 * j + h));
+        if (blk >= kNormKept) {
+            asm volatile("" ::: "memory");              // (and behind the loads: or the compiler makes one
+            load_block<true>(x + base, h, v);           // branch of the two, without the hint)
+            asm volatile("" ::: "memory");
+        } else {
+            load_block<false>(x + base, h, v);
+        }
     } else {
 #pragma unroll
         for (int q = 0; q < 4; ++q)
