@@ -1190,7 +1190,7 @@ static int reduce_common(es_handle* h, float* avg, float* p, float* v, float lr,
     const bool wave = wave_form(h);
     ReduceShape shape = h->shape;
     if (!wave) shape.wave_width = 0;
-    if (!p && !h->pv_option && !stream_avg(h->P)) shape.nontemporal_pv = 0;
+    shape.cached_avg = !p && !h->pv_option && !stream_avg(h->P);
     if (status == hipSuccess)
         status = launch_ring_reduce(h->s_main, wave ? h->d_wave_tiles : h->d_tiles, wave ? h->n_wave_tiles : h->n_tiles,
                                     wave ? 0 : h->n_big, h->d_slots, h->N, avg, p, v, lr, mu, shape);

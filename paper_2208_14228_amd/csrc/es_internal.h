@@ -83,9 +83,11 @@ struct ReduceShape {
                         // averaged gradient
     int lds_pad_kib = -1; // KiB of LDS reserved (and never touched) per workgroup of the small-tile kernel, to cap the
                           // workgroups resident per CU; -1 = default for the rank count (see reduce_lds_pad)
+    int cached_avg = 0;   // the unfused reduce stores the average without the hint, whatever nontemporal_pv says
     // wave-tile form (k_ring_reduce_wave): floats per lane (1 or 4; 0 = the other kernels), ranks
     // loaded before adds are issued, KiB of LDS reserved per workgroup
     int wave_width = 0, wave_batch = 0, wave_pad_kib = 0;
+    bool streams_stores() const { return nontemporal_pv && !cached_avg; }
 };
 
 // Whether parameters, momentum and the averaged gradient are streamed by default.  Cacheable over
