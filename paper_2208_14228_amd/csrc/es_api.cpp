@@ -60,6 +60,7 @@ struct es_handle {
     uint32_t n_big = 0;                         // leading big tiles (see k_ring_reduce_big)
     const float** d_slots = nullptr;            // N device pointers, by virtual rank
     float* d_partials = nullptr;                // ceil(P / 4096) block partials of es_grad_sq_norm
+    uint64_t partials_counters = 0;             // where in d_partials its counters of workgroups start; 0: none
 
     // ESTs whose gradients the next reduce reads in place (rank, caller's flat gradient)
     std::vector<uint32_t> in_place_rank;
@@ -613,7 +614,15 @@ int es_init(es_handle** out, uint32_t n_logical, const es_bucket_layout* lay)
     if (rc == ES_OK) rc = build_tile_block(h);
     if (rc == ES_OK) rc = upload_slot_table(h);
     if (rc == ES_OK && h->P) {
-        e = dev_malloc(h, (void**)&h->d_partials, ((h->P + 4095) / 4096) * sizeof(float));
+        const uint64_t nblk = (h->P + 4095) / 4096;
+        const bool counted = nblk <= kCountedBlocks;
+        h->partials_counters = counted ? round_up(nblk, kCounterStep) : 0;
+        e = dev_malloc(h, (void**)&h->d_partials,
+                       (counted ? h->partials_counters + kArrivalWords : nblk) * sizeof(float));
+        if (e == hipSuccess && counted) {
+            const uint32_t zeros[kArrivalWords] = {};
+            e = hipMemcpy(h->d_partials + h->partials_counters, zeros, sizeof(zeros), hipMemcpyHostToDevice);
+        }
         if (e != hipSuccess) rc = hip_fail(h, e);
     }
     if (rc != ES_OK) { es_destroy(h); return rc; }
@@ -1231,7 +1240,11 @@ int es_grad_sq_norm(es_handle* h, const float* d_vec, float* d_out2)
     if (!h || !d_out2 || (((uintptr_t)d_out2) & 3)) return ES_EINVAL;
     DeviceGuard guard__(h);
     if (h->P && (!d_vec || !aligned16(d_vec))) return ES_EINVAL;
-    ES_HIP(h, launch_sq_norm(h->s_main, d_vec, h->P, h->d_partials, d_out2));
+    if (h->partials_counters && launch_sq_norm_counted)
+        ES_HIP(h, launch_sq_norm_counted(h->s_main, d_vec, h->P, h->d_partials, d_out2,
+                                         (uint32_t*)(h->d_partials + h->partials_counters)));
+    else
+        ES_HIP(h, launch_sq_norm(h->s_main, d_vec, h->P, h->d_partials, d_out2));
     return ES_OK;
 }
 

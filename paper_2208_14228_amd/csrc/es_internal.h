@@ -218,6 +218,13 @@ hipError_t launch_copy_bytes(hipStream_t s, uint8_t* dst, const uint8_t* src, ui
 // part: scratch of ceil(n / 4096) floats
 hipError_t launch_sq_norm(hipStream_t s, const float* x, uint64_t n, float* part, float* out);
 
+// The same in one launch up to kCountedBlocks blocks, given kArrivalWords counters that are zero before
+// the first launch and left at zero by every one; launches that share them run one after the other.
+// (weak, so that a host program whose launchers do nothing can do without it)
+constexpr uint64_t kCountedBlocks = 2048;
+__attribute__((weak)) hipError_t launch_sq_norm_counted(hipStream_t s, const float* x, uint64_t n, float* part, float* out,
+                                                        uint32_t* arrivals);
+
 // The same with the block partials in a file-scope device array of kStaticPartials floats
 // (1 MiB per GPU): no allocation; n <= kStaticPartials * 4096, else hipErrorInvalidValue.
 // Runs on the current device.

@@ -813,13 +813,9 @@ __device__ __forceinline__ void load_block(const float* __restrict__ x, uint32_t
         for (int j = 0; j < 4; ++j) v[j][q] = ld4<STREAM>(x + 4ull * (256 * q + 64 * j + h));
 }
 
-__global__ __launch_bounds__(kBlock) void k_sq_partials(const float* __restrict__ x, uint64_t n,
-                                                        uint64_t nblk, float* __restrict__ part)
+// The sum of squares of block `blk` (the same in the whole wave), valid in lane 0.
+__device__ __forceinline__ float sq_block_sum(const float* __restrict__ x, uint64_t n, uint64_t blk, uint32_t h)
 {
-    const uint32_t h = threadIdx.x & 63;
-    const uint64_t k = (uint64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (k >= nblk) return;                              // whole wave leaves together
-    const uint64_t blk = nblk - 1 - k;
     const uint64_t base = blk * 4096;
     f4 v[4][4];                                         // [tree lane h + 64 j][q]
     if (base + 4096 <= n) {
@@ -861,8 +857,17 @@ __global__ __launch_bounds__(kBlock) void k_sq_partials(const float* __restrict_
     }
     float r0 = s[0] + s[2];                             // stride 128: lanes h and h+64
     float r1 = s[1] + s[3];
-    float r = r0 + r1;                                  // stride 64
-    r = tree64(r);
+    return tree64(r0 + r1);                             // stride 64 and the rest
+}
+
+__global__ __launch_bounds__(kBlock) void k_sq_partials(const float* __restrict__ x, uint64_t n,
+                                                        uint64_t nblk, float* __restrict__ part)
+{
+    const uint32_t h = threadIdx.x & 63;
+    const uint64_t k = (uint64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (k >= nblk) return;                              // whole wave leaves together
+    const uint64_t blk = nblk - 1 - k;
+    const float r = sq_block_sum(x, n, blk, h);
     if (h == 0) part[blk] = r;
 }
 
@@ -913,6 +918,84 @@ hipError_t launch_sq_norm(hipStream_t s, const float* x, uint64_t n, float* part
     const uint64_t nblk = (n + 4095) / 4096;
     if (nblk) hipLaunchKernelGGL(k_sq_partials, dim3((uint32_t)((nblk + 3) / 4)), dim3(kBlock), kAuxLdsPad, s, x, n, nblk, part);
     hipLaunchKernelGGL(k_sq_final, dim3(1), dim3(kBlock), 0, s, part, nblk, out);
+    return hipGetLastError();
+}
+
+// Counts a workgroup in (one lane of it calls) and says whether it was the last of all: on one word up to
+// kOneCounter workgroups, beyond in kCounters groups whose last members meet on one more, because an addition to
+// a word that others add to as well takes 12 ns.  The words are left at zero.
+__device__ __forceinline__ bool arrived_last(uint32_t* arrivals, uint32_t groups)
+{
+    const uint32_t counters = groups > kOneCounter ? kCounters : 1;
+    const uint32_t mine = blockIdx.x % counters;
+    uint32_t* word = arrivals + mine * kCounterStep;
+    if (__hip_atomic_fetch_add(word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 !=
+        (groups - mine + counters - 1) / counters)
+        return false;
+    __hip_atomic_store(word, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (counters == 1) return true;
+    word = arrivals + kCounters * kCounterStep;
+    if (__hip_atomic_fetch_add(word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 != counters) return false;
+    __hip_atomic_store(word, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return true;
+}
+
+// The norm of a short vector in one launch: the workgroup whose partials come last adds them all up, with the lanes
+// and in the order of k_sq_final; no workgroup waits.
+//
+// Partials are stored and loaded at agent scope, past the L2 that each compute die has to itself; the one lane
+// that stores a workgroup's waits until its stores have been acknowledged before it counts the workgroup in.  (A
+// release fence for it writes back the whole L2, of the reduce's average too: 4 M 5.7 -> 7.9 us, 8 M 5.9 -> 16.)
+//
+// Bound by the launch and two round trips.  Against two launches, enqueued from the host: 4 k to 1 M 6.7 -> 3.4 us (host
+// bound), 4 M 6.6 -> 3.4, 8 M 5.9 -> 5.2; reduce, norm and update of 200 k and 16 ranks 17.3 -> 13.7.  Beyond 2,048 blocks a
+// launch is less than a hundredth of such a step.
+__global__ __launch_bounds__(kBlock) void k_sq_norm(const float* __restrict__ x, uint64_t n, uint32_t nblk,
+                                                    float* part, float* __restrict__ out,
+                                                    uint32_t* __restrict__ arrivals, uint32_t groups)
+{
+    __shared__ float lds[kBlock];
+    __shared__ bool last;
+    const uint32_t h = threadIdx.x & 63;
+    const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t k = blockIdx.x * 4 + w;
+    const float r = k < nblk ? sq_block_sum(x, n, nblk - 1 - k, h) : 0.0f;
+    if (h == 0) lds[w] = r;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (uint32_t j = 0; j < 4; ++j)
+            if (blockIdx.x * 4 + j < nblk)
+                __hip_atomic_store(part + (nblk - 1 - (blockIdx.x * 4 + j)), lds[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        last = arrived_last(arrivals, groups);
+    }
+    __syncthreads();
+    if (!last) return;
+    float s = 0.0f;
+    constexpr uint32_t kMost = kCountedBlocks / kBlock;
+    float v[kMost];
+#pragma unroll
+    for (uint32_t j = 0; j < kMost; ++j) {
+        const uint32_t i = threadIdx.x + j * kBlock;
+        v[j] = __hip_atomic_load(part + (i < nblk ? i : nblk - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+#pragma unroll
+    for (uint32_t j = 0; j < kMost; ++j)
+        if (threadIdx.x + j * kBlock < nblk) s = s + v[j];
+    s = tree256(s, lds);
+    if (threadIdx.x == 0) {
+        out[0] = s;
+        out[1] = sqrtf(s);
+    }
+}
+
+hipError_t launch_sq_norm_counted(hipStream_t s, const float* x, uint64_t n, float* part, float* out, uint32_t* arrivals)
+{
+    const uint64_t nblk = (n + 4095) / 4096;
+    if (nblk == 0 || nblk > kCountedBlocks) return launch_sq_norm(s, x, n, part, out);
+    const uint32_t groups = (uint32_t)((nblk + 3) / 4);
+    hipLaunchKernelGGL(k_sq_norm, dim3(groups), dim3(kBlock), 0, s, x, n, (uint32_t)nblk, part, out, arrivals, groups);
     return hipGetLastError();
 }
 
