@@ -5,6 +5,7 @@ import hashlib
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -15,6 +16,12 @@ SOURCES = [os.path.join(CSRC, "es_kernels.hip"), os.path.join(CSRC, "es_api.cpp"
            os.path.join(CSRC, "es_sched.cpp")]
 HEADERS = [os.path.join(CSRC, "es_internal.h"), os.path.join(ROOT, "include", "es.h"),
            os.path.join(ROOT, "include", "es_sched.h")]
+
+# The binding's native calls: an extension module of the running interpreter, where its headers are installed
+# (without it the binding makes every call through ctypes).
+PYCALL_SOURCE = os.path.join(CSRC, "es_pycall.cpp")
+PYCALL = os.path.join(HERE, "_pycall" + (sysconfig.get_config_var("EXT_SUFFIX") or ".so"))
+PYCALL_STAMP = os.path.join(HERE, "_pycall.srchash")
 
 # -ffp-contract=off: no fused multiply-add may be formed (bit-exact SGD update)
 # -fhip-fp32-correctly-rounded-divide-sqrt: IEEE division for the /N
@@ -56,6 +63,32 @@ def stale() -> bool:
         return True
 
 
+def _pycall_hash() -> str:
+    with open(PYCALL_SOURCE, "rb") as fh:
+        return hashlib.sha256(fh.read() + os.path.basename(PYCALL).encode()).hexdigest()[:16]
+
+
+def build_pycall(force: bool, verbose: bool) -> None:
+    include = sysconfig.get_paths()["include"]
+    if not os.path.exists(os.path.join(include, "Python.h")):
+        return
+    tag = _pycall_hash()
+    if not force and os.path.exists(PYCALL):
+        try:
+            with open(PYCALL_STAMP) as fh:
+                if fh.read().strip() == tag:
+                    return
+        except OSError:
+            pass
+    # (-x c++: hipcc takes it for an ordinary C++ file, no device code)
+    cmd = [hipcc(), "-x", "c++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I", include, PYCALL_SOURCE, "-o", PYCALL]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.check_call(cmd)
+    with open(PYCALL_STAMP, "w") as fh:
+        fh.write(tag + "\n")
+
+
 def build(force: bool = True, verbose: bool = False) -> str:
     if force or stale():
         tag = source_hash()
@@ -65,6 +98,7 @@ def build(force: bool = True, verbose: bool = False) -> str:
         subprocess.check_call(cmd)
         with open(STAMP, "w") as fh:
             fh.write(tag + "\n")
+    build_pycall(force, verbose)
     return LIB
 
 
