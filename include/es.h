@@ -286,7 +286,9 @@ int es_stage_fence(es_handle* h);
  *   p          drop probability in [0, 1]; threshold = floor(p * 2^32)
  * Byte j becomes 1 (keep) iff word (j mod 4) of Philox4x32-10 (Salmon et al.,
  * SC'11) with key = seed and counter = (offset + j/4, 0, 0) is >= threshold;
- * then offset += ceil(n/4).  Runs on main.
+ * then offset += ceil(n/4).  Runs on main.  A call captured into a graph records kernels that use the
+ * live state and the mask alone: the graph stays valid as long as these two do, whatever
+ * happens to the grouping, the bindings or the handle.
  */
 int es_dropout_mask(es_handle* h, uint32_t est, uint32_t state_seg,
                     uint8_t* d_mask, uint64_t n, double p);

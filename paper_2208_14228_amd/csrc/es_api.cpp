@@ -23,7 +23,7 @@ struct Worker {
     uint32_t n_slots = 0;
     float* grad_arena = nullptr;        // n_slots * grad_stride floats
     bool grad_on_host = false;          // arena is pinned host memory mapped into the device
-    uint8_t* ctx_arena = nullptr;       // n_slots * ctx_stride bytes, then the mask launches' counters
+    uint8_t* ctx_arena = nullptr;       // n_slots * ctx_stride bytes
     std::vector<void*> live;            // bound live tensors (device addresses)
     Piece* d_pieces = nullptr;
     uint32_t n_pieces = 0;
@@ -39,8 +39,6 @@ struct es_handle {
     uint32_t A = 1;
     std::vector<es_bucket> buckets;
     std::vector<uint64_t> seg_bytes, seg_off;   // seg_off: byte offset inside a context slot
-    std::vector<uint32_t> seg_counter;          // 16-byte segments (RNG states): which of the n_counters counter sets
-    uint32_t n_counters = 0;                    // behind a worker's context slots is this segment's
     uint64_t ctx_bytes = 0;                     // payload of one context slot (16-byte padded segments)
     uint64_t ctx_stride = 0;                    // bytes between context slots
     uint64_t grad_stride = 0;                   // floats between gradient slots
@@ -61,6 +59,7 @@ struct es_handle {
     const float** d_slots = nullptr;            // N device pointers, by virtual rank
     float* d_partials = nullptr;                // ceil(P / 4096) block partials of es_grad_sq_norm
     uint64_t partials_counters = 0;             // where in d_partials its counters of workgroups start; 0: none
+    uint32_t* d_mask_counters = nullptr;        // kArrivalWords, for the long masks enqueued on main: one draw after the other
 
     // ESTs whose gradients the next reduce reads in place (rank, caller's flat gradient)
     std::vector<uint32_t> in_place_rank;
@@ -174,7 +173,7 @@ int alloc_worker(es_handle* h, Worker& w, uint32_t n_slots)
 {
     w.n_slots = n_slots;
     const uint64_t gbytes = (uint64_t)n_slots * h->grad_stride * sizeof(float);
-    const uint64_t cbytes = (uint64_t)n_slots * h->ctx_stride + (uint64_t)h->n_counters * kArrivalWords * sizeof(uint32_t);
+    const uint64_t cbytes = (uint64_t)n_slots * h->ctx_stride;
     if (gbytes) {
         // host placement: pinned, device-mapped memory; the staging copy and the reduce then
         // reach the gradients over the host link with the same kernels (memory-pressure mode)
@@ -579,8 +578,6 @@ int es_init(es_handle** out, uint32_t n_logical, const es_bucket_layout* lay)
         for (uint32_t j = 0; j < lay->n_state_segs; ++j) {
             h->seg_bytes.push_back(lay->state_seg_bytes[j]);
             h->seg_off.push_back(off);
-            h->seg_counter.push_back(h->n_counters);
-            if (lay->state_seg_bytes[j] == 16) ++h->n_counters;
             off += round_up(lay->state_seg_bytes[j], 16);
         }
         h->ctx_bytes = off;
@@ -625,6 +622,12 @@ int es_init(es_handle** out, uint32_t n_logical, const es_bucket_layout* lay)
         }
         if (e != hipSuccess) rc = hip_fail(h, e);
     }
+    if (rc == ES_OK && std::count(h->seg_bytes.begin(), h->seg_bytes.end(), 16)) {
+        const uint32_t zeros[kArrivalWords] = {};
+        e = dev_malloc(h, (void**)&h->d_mask_counters, sizeof(zeros));
+        if (e == hipSuccess) e = hipMemcpy(h->d_mask_counters, zeros, sizeof(zeros), hipMemcpyHostToDevice);
+        if (e != hipSuccess) rc = e == hipErrorOutOfMemory ? ES_ENOMEM : hip_fail(h, e);
+    }
     if (rc != ES_OK) { es_destroy(h); return rc; }
     *out = h;
     return ES_OK;
@@ -642,6 +645,7 @@ int es_destroy(es_handle* h)
     dev_release(h, h->d_tiles_rebuilt);
     dev_release(h, (void*)h->d_slots);
     dev_release(h, h->d_partials);
+    dev_release(h, h->d_mask_counters);
     if (h->s_swap) (void)hipStreamSynchronize(h->s_swap);
     swap_release(h);
     if (h->s_swap) (void)hipStreamDestroy(h->s_swap);
@@ -1136,13 +1140,12 @@ int es_dropout_mask(es_handle* h, uint32_t est, uint32_t state_seg, uint8_t* d_m
     if (((uintptr_t)w.live[state_seg]) & 7) return ES_EINVAL;
     uint64_t thr = p >= 1.0 ? (1ull << 32) : (uint64_t)(p * 4294967296.0);
     uint64_t* state = (uint64_t*)w.live[state_seg];
-    if (n <= kShortMask || !launch_dropout_mask_long) {
+    if (n <= kShortMask || !launch_dropout_mask_long)
         ES_HIP(h, launch_dropout_mask(h->s_main, state, d_mask, n, thr));
-    } else {
-        uint32_t* counters = (uint32_t*)(w.ctx_arena + (uint64_t)w.n_slots * h->ctx_stride);
-        ES_HIP(h, launch_dropout_mask_long(h->s_main, state, d_mask, n, thr,
-                                           counters + (uint64_t)h->seg_counter[state_seg] * kArrivalWords));
-    }
+    else if (stream_captured(h->s_main))        // must depend on the live state and the mask alone
+        ES_HIP(h, launch_dropout_mask_captured(h->s_main, state, d_mask, n, thr));
+    else
+        ES_HIP(h, launch_dropout_mask_long(h->s_main, state, d_mask, n, thr, h->d_mask_counters));
     return ES_OK;
 }
 

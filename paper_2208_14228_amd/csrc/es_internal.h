@@ -252,8 +252,7 @@ hipError_t launch_dropout_mask(hipStream_t s, uint64_t* state, uint8_t* mask, ui
                                uint64_t threshold);
 
 // The same for any n, given counters of the workgroups that have read the state: 32-bit words a line apart,
-// zero before the first launch and left at zero by every one.  Launches that can be in flight at the same
-// time need different ones, as they need different states.
+// zero before the first launch and left at zero by every one; launches that share them run one after the other.
 constexpr uint32_t kOneCounter = 64;             // workgroups that share one counter
 constexpr uint32_t kCounters = 16;               // counters beyond that, and one more
 constexpr uint32_t kCounterStep = 32;            // words between two counters
@@ -261,5 +260,18 @@ constexpr uint32_t kArrivalWords = (kCounters + 1) * kCounterStep;
 // (weak, so that a host program whose launchers do nothing can do without it)
 __attribute__((weak)) hipError_t launch_dropout_mask_long(hipStream_t s, uint64_t* state, uint8_t* mask, uint64_t n,
                                                           uint64_t threshold, uint32_t* arrivals);
+
+// The same for any n without counters, in two launches: for launches that a caller captures, which can be replayed
+// after the handle is gone and beside its other draws.
+hipError_t launch_dropout_mask_captured(hipStream_t s, uint64_t* state, uint8_t* mask, uint64_t n, uint64_t threshold);
+
+// Whether a launch on the stream would be recorded instead of run.
+inline bool stream_captured(hipStream_t s)
+{
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();                            // the legacy stream while another one is captured, say
+    return true;
+}
 
 }  // namespace es

@@ -1399,6 +1399,10 @@ constexpr uint64_t kMaskGroups = 2048;                  // 8 workgroups of 4 wav
 // One launch instead of two, enqueued from the host: 16 KiB to 10 MB 7.0 -> 4.0 us a mask (that is what a launch
 // costs the host); GPU time of 70 kB 5.1 -> 3.7, 3.7 MB 5.9 -> 5.1.  16x12x512x512 bytes 16.9 -> 15.3 us
 // (3.3 TB/s of stores) where passes overlap, 23.9 -> 22.5 one after the other; 143 MB 47.0 -> 44.2.
+//
+// A draw that is captured into a graph can be replayed when the counters are gone, or beside another draw that uses
+// them: it only reads the state (COUNTED = false), and k_philox_advance follows it.
+template <bool COUNTED>
 __global__ __launch_bounds__(kBlock) void k_dropout_mask(uint64_t* __restrict__ state, uint8_t* __restrict__ mask,
                                                          uint64_t n, uint64_t keep, int aligned16,
                                                          uint32_t* __restrict__ arrivals, uint32_t groups)
@@ -1409,7 +1413,7 @@ __global__ __launch_bounds__(kBlock) void k_dropout_mask(uint64_t* __restrict__ 
     const uint32_t counters = groups > kOneCounter ? kCounters : 1;
     const uint32_t mine = blockIdx.x % counters;
     uint32_t before = 0;
-    if (threadIdx.x == 0)
+    if (COUNTED && threadIdx.x == 0)
         before = __hip_atomic_fetch_add(arrivals + mine * kCounterStep, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const uint32_t lane = threadIdx.x & 63;
     uint64_t first = (uint64_t)blockIdx.x * kBlock + __builtin_amdgcn_readfirstlane(threadIdx.x & ~63u);
@@ -1418,7 +1422,7 @@ __global__ __launch_bounds__(kBlock) void k_dropout_mask(uint64_t* __restrict__ 
         mask_bytes(lane, first, offset, (uint32_t)seed, (uint32_t)(seed >> 32), keep, packed);
         store_mask(mask + 16 * first, 16 * lane, n - 16 * first, aligned16, packed);
     }
-    if (threadIdx.x != 0 || before + 1 != (groups - mine + counters - 1) / counters) return;
+    if (!COUNTED || threadIdx.x != 0 || before + 1 != (groups - mine + counters - 1) / counters) return;
     __hip_atomic_store(arrivals + mine * kCounterStep, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (counters > 1) {
         uint32_t* last = arrivals + kCounters * kCounterStep;
@@ -1426,6 +1430,11 @@ __global__ __launch_bounds__(kBlock) void k_dropout_mask(uint64_t* __restrict__ 
         __hip_atomic_store(last, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     state[1] = offset + (n + 3) / 4;
+}
+
+__global__ void k_philox_advance(uint64_t* state, uint64_t blocks)
+{
+    if (threadIdx.x == 0) state[1] = state[1] + blocks;
 }
 
 // A short mask: one workgroup of up to 16 waves draws all of it and advances the offset it has read.
@@ -1454,13 +1463,30 @@ hipError_t launch_dropout_mask(hipStream_t s, uint64_t* state, uint8_t* mask, ui
     return hipGetLastError();
 }
 
+static uint32_t mask_groups(uint64_t n)
+{
+    const uint64_t all = ((n + 15) / 16 + kBlock - 1) / kBlock;
+    return (uint32_t)(all < kMaskGroups ? all : kMaskGroups);
+}
+
+hipError_t launch_dropout_mask_captured(hipStream_t s, uint64_t* state, uint8_t* mask, uint64_t n, uint64_t threshold)
+{
+    if (n == 0) return hipSuccess;
+    const uint32_t groups = mask_groups(n);
+    hipLaunchKernelGGL(k_dropout_mask<false>, dim3(groups), dim3(kBlock), 0, s, state, mask, n, (1ull << 32) - threshold,
+                       ((uintptr_t)mask & 15) == 0, nullptr, groups);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_philox_advance, dim3(1), dim3(64), 0, s, state, (n + 3) / 4);
+    return hipGetLastError();
+}
+
 hipError_t launch_dropout_mask_long(hipStream_t s, uint64_t* state, uint8_t* mask, uint64_t n, uint64_t threshold,
                                     uint32_t* arrivals)
 {
     if (n == 0) return hipSuccess;
-    const uint64_t all = ((n + 15) / 16 + kBlock - 1) / kBlock;
-    const uint32_t groups = (uint32_t)(all < kMaskGroups ? all : kMaskGroups);
-    hipLaunchKernelGGL(k_dropout_mask, dim3(groups), dim3(kBlock), 0, s, state, mask, n, (1ull << 32) - threshold,
+    const uint32_t groups = mask_groups(n);
+    hipLaunchKernelGGL(k_dropout_mask<true>, dim3(groups), dim3(kBlock), 0, s, state, mask, n, (1ull << 32) - threshold,
                        ((uintptr_t)mask & 15) == 0, arrivals, groups);
     return hipGetLastError();
 }
@@ -1969,15 +1995,6 @@ __global__ __launch_bounds__(kBlock) void k_bn_final(const float* __restrict__ p
     if (threadIdx.x == 0) out[blockIdx.x] = s / fM;
 }
 
-// Whether a launch on the stream would be recorded instead of run.
-static bool bn_captured(hipStream_t s)
-{
-    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
-    (void)hipGetLastError();                            // the legacy stream while another one is captured, say
-    return true;
-}
-
 // Whether several workgroups share a channel (k_bn_shared).  Up to 25 blocks one workgroup is 1.2-1.5 times as
 // fast, and images so short that they are read in single loads keep the forms below.  Captured, with the
 // clearing launch before it, little work takes longer so: 26 blocks 7.2 -> 10.4 us for 4 channels (0.4 MB each), 9.1
@@ -1988,7 +2005,7 @@ static bool bn_shares(const BnGeom& g, hipStream_t s, bool& captured)
 {
     if ((MODE != kBnVector && MODE != kBnLong) || g.HW < 16) return false;
     if (g.nblk <= kBnWaves + kBnExtra || g.nblk > kBnMostGroups * kBnHeld) return false;
-    captured = bn_captured(s);
+    captured = stream_captured(s);
     return !captured || (uint64_t)g.C * g.nblk >= (g.nblk <= 64 ? 1000 : 1300);
 }
 

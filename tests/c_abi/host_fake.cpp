@@ -45,6 +45,14 @@ hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuc
 hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) { *s = nullptr; return hipSuccess; }
 hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { ++g_waits; return hipSuccess; }
+// what is asked about any stream: 0 = runs, 1 = is captured, -1 = cannot be said
+static int g_capturing = 0;
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* st)
+{
+    *st = g_capturing == 1 ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+    return g_capturing < 0 ? hipErrorStreamCaptureImplicit : hipSuccess;
+}
+hipError_t hipGetLastError() { return hipSuccess; }
 }
 
 namespace es {
@@ -72,7 +80,20 @@ hipError_t launch_bn_batch_stats(hipStream_t, const float*, uint32_t, uint32_t, 
 hipError_t launch_copy_bytes(hipStream_t, uint8_t*, const uint8_t*, uint64_t) { return hipSuccess; }
 hipError_t launch_sq_norm(hipStream_t, const float*, uint64_t, float*, float*) { return hipSuccess; }
 hipError_t launch_sq_norm_static(hipStream_t, const float*, uint64_t, float*) { return hipSuccess; }
-hipError_t launch_dropout_mask(hipStream_t, uint64_t*, uint8_t*, uint64_t, uint64_t) { return hipSuccess; }
+
+// The last mask: which launcher drew it, from which state, with which counters.
+enum { kNone, kShort, kLong, kCaptured };
+static int m_form;
+static uint64_t* m_state;
+static uint32_t* m_counters;
+static hipError_t drew(int form, uint64_t* state, uint32_t* counters)
+{
+    m_form = form; m_state = state; m_counters = counters;
+    return hipSuccess;
+}
+hipError_t launch_dropout_mask(hipStream_t, uint64_t* st, uint8_t*, uint64_t, uint64_t) { return drew(kShort, st, nullptr); }
+hipError_t launch_dropout_mask_captured(hipStream_t, uint64_t* st, uint8_t*, uint64_t, uint64_t) { return drew(kCaptured, st, nullptr); }
+hipError_t launch_dropout_mask_long(hipStream_t, uint64_t* st, uint8_t*, uint64_t, uint64_t, uint32_t* c) { return drew(kLong, st, c); }
 }  // namespace es
 using namespace es;
 
@@ -235,6 +256,56 @@ static int check_rule()
     return 0;
 }
 
+// Words the handle holds, all zero.
+static bool zeros_held(const uint32_t* w, size_t n)
+{
+    for (const auto& m : g_live)
+        if ((const char*)w >= m.first && (const char*)(w + n) <= m.first + m.second)
+            return std::all_of(w, w + n, [](uint32_t v) { return v == 0; });
+    return false;
+}
+
+// A long mask counts its workgroups on words of the handle; one that is recorded into a graph, which can be replayed
+// when the handle has regrouped its ESTs or is gone, and beside other draws, gets none.
+static int check_masks()
+{
+    const uint64_t segs[5] = {24, 16, 7, 16, 40};
+    es_bucket b = {0, 4};
+    es_bucket_layout lay = {4, 1, &b, 4, 5, segs, dev_alloc, dev_free, nullptr};
+    es_handle* h = nullptr;
+    CHECK(es_init(&h, 3, &lay) == ES_OK);
+    alignas(16) static uint64_t live[2][5][8];
+    static uint8_t mask[kShortMask + 1];
+    const uint32_t workers[3] = {0, 1, 1}, slots[3] = {0, 0, 1};
+    void* ptrs[2][5];
+    for (int w = 0; w < 2; ++w)
+        for (int j = 0; j < 5; ++j) ptrs[w][j] = live[w][j];
+    const uint32_t* counters = nullptr;
+    for (int round = 0; round < 3; ++round) {
+        if (round == 1) CHECK(es_set_grouping(h, 2, workers, slots) == ES_OK);
+        for (uint32_t w = 0; w < (round ? 2u : 1u); ++w)        // in the last round the same states, the other way round
+            CHECK(es_bind_live_state(h, w, ptrs[round == 2 ? 1 - w : w]) == ES_OK);
+        for (uint32_t e = 0; e < 3; ++e)
+            for (uint32_t seg : {1u, 3u}) {
+                uint64_t* state = live[round == 0 ? 0 : round == 1 ? workers[e] : 1 - workers[e]][seg];
+                for (int capturing : {1, -1, 0}) {
+                    g_capturing = capturing;
+                    CHECK(es_dropout_mask(h, e, seg, mask, kShortMask + 1, 0.5) == ES_OK && m_state == state);
+                    CHECK(m_form == (capturing ? kCaptured : kLong));
+                    if (!capturing) {
+                        CHECK(zeros_held(m_counters, kArrivalWords) && (!counters || m_counters == counters));
+                        counters = m_counters;                  // not the regrouping's to free
+                    }
+                    CHECK(es_dropout_mask(h, e, seg, mask, kShortMask, 0.5) == ES_OK && m_form == kShort && m_state == state);
+                }
+            }
+        m_form = kNone;
+        CHECK(es_dropout_mask(h, 0, 0, mask, kShortMask + 1, 0.5) == ES_EINVAL && m_form == kNone);
+    }
+    CHECK(es_destroy(h) == ES_OK && g_live.empty());
+    return 0;
+}
+
 int main(int argc, char** argv)
 {
     const char* what = argc > 1 ? argv[1] : "";
@@ -243,6 +314,7 @@ int main(int argc, char** argv)
     if (!std::strcmp(what, "auto")) rc = check_auto();
     if (!std::strcmp(what, "host slots")) rc = check_host_slots();
     if (!std::strcmp(what, "rule")) rc = check_rule();
+    if (!std::strcmp(what, "masks")) rc = check_masks();
     if (rc == 0) std::printf("%s: passed\n", what);
     return rc;
 }

@@ -1,6 +1,7 @@
 """Masks of more than one workgroup, drawn and advanced in one launch: one counter of arrivals and
-several, one workgroup per share of the mask and several shares each, two states of one job in turn
-(each has counters of its own), and a captured draw replayed; bit for bit with the state left behind."""
+several, one workgroup per share of the mask and several shares each, two states of one job in turn on
+the same counters, and a captured draw replayed: between eager ones, after a regrouping, after its job's
+end, and beside the draws of another state; bit for bit with the state left behind."""
 import numpy as np
 import pytest
 import torch
@@ -10,6 +11,7 @@ import oracle
 pytestmark = pytest.mark.gpu
 
 if torch.cuda.is_available():
+    from paper_2208_14228_amd import binding as B
     from paper_2208_14228_amd.job import ESTJob
     DEV = "cuda:0"
 
@@ -67,5 +69,69 @@ def test_replays_of_a_captured_draw():
                 torch.cuda.synchronize()
             assert np.array_equal(mask.cpu().numpy(), oracle.dropout_mask(st, n, 0.5)), k
             assert np.array_equal(_state(job, 0), st), k
+    finally:
+        job.close()
+
+
+def _captured(job, mask, p):
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=job.main):
+        job.dropout_mask(0, 0, mask, p)
+    return g
+
+
+@pytest.mark.parametrize("n", [16 * 1024 + 1, 70 * GROUP + 9, RESIDENT + GROUP + 5])
+def test_a_captured_draw_outlives_the_grouping_and_the_job(n):
+    """What is recorded uses the live state and the mask alone, so memory that the library gives back is left alone."""
+    live = torch.zeros(32, dtype=torch.uint8, device=DEV)[:16]
+    job = ESTJob(2, 4, [(0, 4)], 1, [16], use_streams="one", live_alloc=lambda nb: live)
+    mask = torch.zeros(n, dtype=torch.uint8, device=DEV)
+    st = _set(job, 0, 987654321, (1 << 32) - 3)
+    g = _captured(job, mask, 0.25)
+    others = []
+    for k in range(4):
+        if k == 1:
+            job.set_grouping([0, 0], [1, 0])
+        if k == 3:
+            job.close()
+        # whatever has been given back is now someone else's: 512 bytes are torch's smallest block
+        others += [torch.full((nb,), 0x5A, dtype=torch.uint8, device=DEV) for nb in [512] * 8 + [4096] * 8]
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(mask.cpu().numpy(), oracle.dropout_mask(st, n, 0.25)), k
+        assert np.array_equal(live.cpu().numpy().view(np.uint64), st), k
+        assert all(bool((t == 0x5A).all()) for t in others), k
+        if k < 3:                               # and an eager draw of the job as it is now
+            job.dropout_mask(0, 0, mask, 0.25)
+            job.sync()
+            assert np.array_equal(mask.cpu().numpy(), oracle.dropout_mask(st, n, 0.25)), k
+
+
+def test_captured_and_eager_draws_side_by_side():
+    """Two states bound one after the other: the first's draws replayed on a stream of their own while the second's
+    are enqueued."""
+    n = 3000 * GROUP + 1
+    lives = [torch.zeros(16, dtype=torch.uint8, device=DEV) for _ in range(2)]
+    job = ESTJob(1, 4, [(0, 4)], 1, [16], use_streams="one", live_alloc=lambda nb: lives[0])
+    try:
+        masks = [torch.zeros(n, dtype=torch.uint8, device=DEV) for _ in range(2)]
+        st = [np.array([seed, 5], dtype=np.uint64) for seed in (11, 22)]
+        for live, s in zip(lives, st):
+            live.copy_(torch.from_numpy(s.view(np.uint8)))
+        torch.cuda.synchronize()
+        g = _captured(job, masks[0], 0.5)
+        B.check(B.es_bind_live_state(job.h, 0, [lives[1].data_ptr()]), "es_bind_live_state", job.h)
+        own = torch.cuda.Stream(DEV)
+        for _ in range(6):
+            with torch.cuda.stream(own):
+                g.replay()
+            job.dropout_mask(0, 0, masks[1], 0.5)
+        torch.cuda.synchronize()
+        for live, mask, s in zip(lives, masks, st):
+            for _ in range(5):
+                oracle.dropout_mask(s, n, 0.5)
+            assert np.array_equal(mask.cpu().numpy(), oracle.dropout_mask(s, n, 0.5))
+            assert np.array_equal(live.cpu().numpy().view(np.uint64), s)
     finally:
         job.close()
