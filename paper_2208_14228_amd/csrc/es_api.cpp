@@ -1140,7 +1140,7 @@ int es_dropout_mask(es_handle* h, uint32_t est, uint32_t state_seg, uint8_t* d_m
     if (((uintptr_t)w.live[state_seg]) & 7) return ES_EINVAL;
     uint64_t thr = p >= 1.0 ? (1ull << 32) : (uint64_t)(p * 4294967296.0);
     uint64_t* state = (uint64_t*)w.live[state_seg];
-    if (n <= kShortMask || !launch_dropout_mask_long)
+    if (n <= kShortMask)
         ES_HIP(h, launch_dropout_mask(h->s_main, state, d_mask, n, thr));
     else if (stream_captured(h->s_main))        // must depend on the live state and the mask alone
         ES_HIP(h, launch_dropout_mask_captured(h->s_main, state, d_mask, n, thr));
@@ -1243,7 +1243,7 @@ int es_grad_sq_norm(es_handle* h, const float* d_vec, float* d_out2)
     if (!h || !d_out2 || (((uintptr_t)d_out2) & 3)) return ES_EINVAL;
     DeviceGuard guard__(h);
     if (h->P && (!d_vec || !aligned16(d_vec))) return ES_EINVAL;
-    if (h->partials_counters && launch_sq_norm_counted)
+    if (h->partials_counters)
         ES_HIP(h, launch_sq_norm_counted(h->s_main, d_vec, h->P, h->d_partials, d_out2,
                                          (uint32_t*)(h->d_partials + h->partials_counters)));
     else

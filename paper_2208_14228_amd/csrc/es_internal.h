@@ -220,10 +220,8 @@ hipError_t launch_sq_norm(hipStream_t s, const float* x, uint64_t n, float* part
 
 // The same in one launch up to kCountedBlocks blocks, given kArrivalWords counters that are zero before
 // the first launch and left at zero by every one; launches that share them run one after the other.
-// (weak, so that a host program whose launchers do nothing can do without it)
 constexpr uint64_t kCountedBlocks = 2048;
-__attribute__((weak)) hipError_t launch_sq_norm_counted(hipStream_t s, const float* x, uint64_t n, float* part, float* out,
-                                                        uint32_t* arrivals);
+hipError_t launch_sq_norm_counted(hipStream_t s, const float* x, uint64_t n, float* part, float* out, uint32_t* arrivals);
 
 // The same with the block partials in a file-scope device array of kStaticPartials floats
 // (1 MiB per GPU): no allocation; n <= kStaticPartials * 4096, else hipErrorInvalidValue.
@@ -257,9 +255,8 @@ constexpr uint32_t kOneCounter = 64;             // workgroups that share one co
 constexpr uint32_t kCounters = 16;               // counters beyond that, and one more
 constexpr uint32_t kCounterStep = 32;            // words between two counters
 constexpr uint32_t kArrivalWords = (kCounters + 1) * kCounterStep;
-// (weak, so that a host program whose launchers do nothing can do without it)
-__attribute__((weak)) hipError_t launch_dropout_mask_long(hipStream_t s, uint64_t* state, uint8_t* mask, uint64_t n,
-                                                          uint64_t threshold, uint32_t* arrivals);
+hipError_t launch_dropout_mask_long(hipStream_t s, uint64_t* state, uint8_t* mask, uint64_t n, uint64_t threshold,
+                                    uint32_t* arrivals);
 
 // The same for any n without counters, in two launches: for launches that a caller captures, which can be replayed
 // after the handle is gone and beside its other draws.

@@ -78,7 +78,19 @@ hipError_t launch_est_boundary(hipStream_t, const CopyRuns&, const Piece*, uint3
 hipError_t launch_sgd_clip(hipStream_t, float*, float*, const float*, uint64_t, const float*, float, float, float, float, bool) { return hipSuccess; }
 hipError_t launch_bn_batch_stats(hipStream_t, const float*, uint32_t, uint32_t, uint32_t, float*, float*, float*) { return hipSuccess; }
 hipError_t launch_copy_bytes(hipStream_t, uint8_t*, const uint8_t*, uint64_t) { return hipSuccess; }
-hipError_t launch_sq_norm(hipStream_t, const float*, uint64_t, float*, float*) { return hipSuccess; }
+// The last norm: its partials and, in the form that has them, its counters.
+static float* n_part;
+static uint32_t* n_counters;
+hipError_t launch_sq_norm(hipStream_t, const float*, uint64_t, float* part, float*)
+{
+    n_part = part; n_counters = nullptr;
+    return hipSuccess;
+}
+hipError_t launch_sq_norm_counted(hipStream_t, const float*, uint64_t, float* part, float*, uint32_t* counters)
+{
+    n_part = part; n_counters = counters;
+    return hipSuccess;
+}
 hipError_t launch_sq_norm_static(hipStream_t, const float*, uint64_t, float*) { return hipSuccess; }
 
 // The last mask: which launcher drew it, from which state, with which counters.
@@ -306,6 +318,25 @@ static int check_masks()
     return 0;
 }
 
+// The norm's partials, and behind them, on a line of their own, the counters of its one-launch form.
+static int check_norms()
+{
+    const uint64_t block = 4096;
+    for (uint64_t blocks : {1ull, 2ull, 31ull, 32ull, 33ull, 2047ull, 2048ull, 2049ull})
+        for (uint64_t n : {blocks * block, (blocks - 1) * block + 1}) {
+            Job j(1, n);
+            float* x = (float*)(((uintptr_t)j.avg.data() + 15) & ~(uintptr_t)15);
+            float out[2];
+            CHECK(j.h && es_grad_sq_norm(j.h, x, out) == ES_OK && (n_counters != nullptr) == (blocks <= kCountedBlocks));
+            std::fill(n_part, n_part + blocks, 1.0f);           // all of them, and no counter
+            if (!n_counters) continue;
+            CHECK(zeros_held(n_counters, kArrivalWords) && (float*)n_counters >= n_part + blocks);
+            CHECK(((char*)n_counters - (char*)n_part) % 128 == 0);
+        }
+    CHECK(g_live.empty());
+    return 0;
+}
+
 int main(int argc, char** argv)
 {
     const char* what = argc > 1 ? argv[1] : "";
@@ -315,6 +346,7 @@ int main(int argc, char** argv)
     if (!std::strcmp(what, "host slots")) rc = check_host_slots();
     if (!std::strcmp(what, "rule")) rc = check_rule();
     if (!std::strcmp(what, "masks")) rc = check_masks();
+    if (!std::strcmp(what, "norms")) rc = check_norms();
     if (rc == 0) std::printf("%s: passed\n", what);
     return rc;
 }

@@ -22,9 +22,11 @@ hipError_t launch_sgd_clip(hipStream_t, float*, float*, const float*, uint64_t, 
 hipError_t launch_bn_batch_stats(hipStream_t, const float*, uint32_t, uint32_t, uint32_t, float*, float*, float*) { return hipSuccess; }
 hipError_t launch_copy_bytes(hipStream_t, uint8_t*, const uint8_t*, uint64_t) { return hipSuccess; }
 hipError_t launch_sq_norm(hipStream_t, const float*, uint64_t, float*, float*) { return hipSuccess; }
+hipError_t launch_sq_norm_counted(hipStream_t, const float*, uint64_t, float*, float*, uint32_t*) { return hipSuccess; }
 hipError_t launch_sq_norm_static(hipStream_t, const float*, uint64_t, float*) { return hipSuccess; }
 hipError_t launch_dropout_mask(hipStream_t, uint64_t*, uint8_t*, uint64_t, uint64_t) { return hipSuccess; }
 hipError_t launch_dropout_mask_captured(hipStream_t, uint64_t*, uint8_t*, uint64_t, uint64_t) { return hipSuccess; }
+hipError_t launch_dropout_mask_long(hipStream_t, uint64_t*, uint8_t*, uint64_t, uint64_t, uint32_t*) { return hipSuccess; }
 }  // namespace es
 
 #define CHECK(c) do { if (!(c)) { std::fprintf(stderr, "check failed at line %d: %s\n", __LINE__, #c); return 1; } } while (0)

@@ -44,3 +44,24 @@ def test_host_runtime_is_clean_under_asan_ubsan(tmp_path):
         pytest.skip("a preloaded library prevents running ASan binaries in this environment")
     assert out.returncode == 0, out.stdout + out.stderr
     assert "plans clean" in out.stdout
+
+
+@pytest.fixture(scope="module")
+def host_fake_san(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("host_fake_san") / "host_fake_san")
+    pkg = os.path.join(ROOT, "paper_2208_14228_amd", "csrc")
+    subprocess.check_call(["g++", "-O1", "-g", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-fsanitize=address,undefined",
+                           "-fno-sanitize-recover=all", "-I", os.path.join(ROOT, "include"), "-I", pkg, "-I",
+                           "/opt/rocm/include", os.path.join(HERE, "c_abi", "host_fake.cpp"),
+                           os.path.join(pkg, "es_api.cpp"), "-o", exe])
+    return exe
+
+
+@pytest.mark.parametrize("what", ["options", "host slots", "masks", "norms"])
+def test_handle_is_clean_under_asan_ubsan(what, host_fake_san):
+    """The same with a handle on a device made of host memory, parts of which the launchers are given."""
+    out = subprocess.run([host_fake_san, what], capture_output=True, text=True, timeout=300)
+    if "ASan runtime does not come first" in out.stderr:
+        pytest.skip("a preloaded library prevents running ASan binaries in this environment")
+    assert out.returncode == 0, out.stdout + out.stderr
+    assert f"{what}: passed" in out.stdout
