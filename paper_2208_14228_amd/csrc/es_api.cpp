@@ -73,7 +73,6 @@ struct es_handle {
 
     // one pass per workgroup: 256 lanes x 2 vectors x 4 floats (measured best on MI355X)
     bool host_slots = false;                    // where the next arena allocation places gradient slots
-    bool pv_option = false;                     // nontemporal_pv was set by the caller and rules every store
     int64_t hbm_budget_mib = -1;                // >= 0: gradient arenas beyond this many MiB of HBM go to the host
     uint64_t hbm_grad_bytes = 0;                // HBM held by gradient arenas allocated in the current regrouping
     uint32_t tile_elems = 2048;
@@ -1202,7 +1201,6 @@ static int reduce_common(es_handle* h, float* avg, float* p, float* v, float lr,
     const bool wave = wave_form(h);
     ReduceShape shape = h->shape;
     if (!wave) shape.wave_width = 0;
-    shape.cached_avg = !p && !h->pv_option && !stream_avg(h->P);
     if (status == hipSuccess)
         status = launch_ring_reduce(h->s_main, wave ? h->d_wave_tiles : h->d_tiles, wave ? h->n_wave_tiles : h->n_tiles,
                                     wave ? 0 : h->n_big, h->d_slots, h->N, avg, p, v, lr, mu, shape);
@@ -1480,7 +1478,6 @@ try {
     if (k == "nontemporal_pv") {
         if (value != 0 && value != 1) return ES_EINVAL;
         h->shape.nontemporal_pv = (int)value;
-        h->pv_option = true;
         return ES_OK;
     }
     return ES_EINVAL;

@@ -83,11 +83,9 @@ struct ReduceShape {
                         // averaged gradient
     int lds_pad_kib = -1; // KiB of LDS reserved (and never touched) per workgroup of the small-tile kernel, to cap the
                           // workgroups resident per CU; -1 = default for the rank count (see reduce_lds_pad)
-    int cached_avg = 0;   // the unfused reduce stores the average without the hint, whatever nontemporal_pv says
     // wave-tile form (k_ring_reduce_wave): floats per lane (1 or 4; 0 = the other kernels), ranks
     // loaded before adds are issued, KiB of LDS reserved per workgroup
     int wave_width = 0, wave_batch = 0, wave_pad_kib = 0;
-    bool streams_stores() const { return nontemporal_pv && !cached_avg; }
 };
 
 // Whether parameters, momentum and the averaged gradient are streamed by default.  Cacheable over
@@ -108,13 +106,6 @@ inline bool stream_pv(uint32_t N, uint64_t P)
 {
     return P >= 14000000 || (N >= 32 && P >= 1000000 && P < 5000000);
 }
-
-// Whether the unfused reduce streams its average where stream_pv holds: what follows reads it once or twice,
-// and a short one is still in the Infinity Cache then.  Reduce, norm and clipped update, streamed over cacheable:
-// 15 M 1.00-1.02, 20 M 1.01-1.02, 25.6 M 1.00-1.02 up to 8 ranks and 0.98 with 24, 32 M 0.97-1.01, 40 M
-// 0.96-0.99, 50 M 0.96-0.99; 32 and 48 ranks with 1.5 to 4.5 M 1.01-1.05; reduce and update without a norm 1.01-1.05
-// from 15 to 18 M.  (A reduce alone, whose average nobody reads: 0.95-0.97.)
-inline bool stream_avg(uint64_t P) { return P >= 22000000; }
 
 // The wave-tile form where it is the faster one, by the rank count N and the parameter count P;
 // returns false (and leaves the shape alone) where the other kernels are.  Measured on 13 rank counts

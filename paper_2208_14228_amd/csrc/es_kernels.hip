@@ -368,7 +368,7 @@ static hipError_t launch_reduce_u(hipStream_t s, const Tile* tiles, uint32_t n_t
                                   const float* const* slots, uint32_t N, float* avg, float* p,
                                   float* v, float lr, float mu, ReduceShape sh)
 {
-    const int nt = (sh.nontemporal ? 1 : 0) | (sh.streams_stores() ? 2 : 0);
+    const int nt = (sh.nontemporal ? 1 : 0) | (sh.nontemporal_pv ? 2 : 0);
     switch (sh.rank_batch) {
     case 1:  return launch_reduce_unb<U, 1>(s, tiles, n_tiles, slots, N, avg, p, v, lr, mu, nt, reduce_lds_pad(sh.lds_pad_kib, N, sh.nontemporal_pv != 0 && p != nullptr, p != nullptr));
     case 2:  return launch_reduce_unb<U, 2>(s, tiles, n_tiles, slots, N, avg, p, v, lr, mu, nt, reduce_lds_pad(sh.lds_pad_kib, N, sh.nontemporal_pv != 0 && p != nullptr, p != nullptr));
@@ -412,7 +412,7 @@ static hipError_t launch_reduce_big_u(hipStream_t s, const Tile* tiles, uint32_t
                                       const float* const* slots, uint32_t N, float* avg, float* p,
                                       float* v, float lr, float mu, ReduceShape sh)
 {
-    const int nt = (sh.nontemporal ? 1 : 0) | (sh.streams_stores() ? 2 : 0);
+    const int nt = (sh.nontemporal ? 1 : 0) | (sh.nontemporal_pv ? 2 : 0);
     // only shapes whose loads in flight fit the register file exist: UB * batch <= 32
     if (sh.big_rank_batch == 1)
         return launch_reduce_big<UB, 1>(s, tiles, n_tiles, n_big, slots, N, avg, p, v, lr, mu, nt);
@@ -550,7 +550,7 @@ static hipError_t launch_reduce_wave(hipStream_t s, const Tile* tiles, uint32_t 
         if (sh.nontemporal_pv) ES_LAUNCH(3, true);
         else ES_LAUNCH(1, true);
     } else {
-        if (sh.streams_stores()) ES_LAUNCH(3, false);
+        if (sh.nontemporal_pv) ES_LAUNCH(3, false);
         else ES_LAUNCH(1, false);
     }
 #undef ES_LAUNCH

@@ -264,6 +264,9 @@ static int check_rule()
     for (const auto& l : policy) {
         Job j(l.n, l.p);
         CHECK(j.h && j.reduce() == ES_OK && l_shape.nontemporal_pv == l.streamed && option(j.h, "nontemporal_pv") == l.streamed);
+        const ReduceShape chosen = l_shape;     // the option set to what it is: the same launch
+        CHECK(es_set_option(j.h, "nontemporal_pv", l.streamed) == ES_OK && j.reduce() == ES_OK);
+        CHECK(std::memcmp(&chosen, &l_shape, sizeof(chosen)) == 0);
     }
     return 0;
 }
