@@ -337,7 +337,8 @@ int es_reduce_sgd_step(es_handle* h, float* d_param, float* d_momentum,
  *   Every square and add is rounded to fp32; no atomics.
  *   d_vec   DEVICE, n_params floats, 16-byte aligned
  *   d_out2  DEVICE, 2 floats: [0] sum of squares, [1] its correctly rounded square root
- * Runs on main.
+ * Runs on main.  The sums pass through memory of the handle: a call captured into a graph must not be
+ * replayed beside another norm of the handle, nor after es_destroy.
  */
 int es_grad_sq_norm(es_handle* h, const float* d_vec, float* d_out2);
 

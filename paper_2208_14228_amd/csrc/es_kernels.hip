@@ -795,14 +795,26 @@ __device__ __forceinline__ float tree256(float s, float* lds)
 // 32 .. 1 are wave shuffles, and no LDS or barrier is needed; all 16 loads of a
 // lane are in flight before the first add.
 //
-// Bound by reading x.  What usually follows is the clipped update, which reads the same vector from its start:
-// the first kNormKept blocks are read last and without the streaming hint, so that the Infinity Cache
-// (256 MB) still has them.  Reduce, norm and update together, all of x streamed / so: 15 M and 4 ranks 110 / 102 us,
-// 25.6 M and 8 ranks 267 / 252, 50 M and 12 ranks 650 / 621, 100 M and 8 ranks 1013 / 990, 109 M and 16 ranks
-// 1729 / 1707.  Kept blocks of 64, 128, 192 and 256 MB: 50 M and 2 ranks 284, 281, 288, 290 us (299 without), 150 M
-// and 2 ranks 920, 910, 906, 914; whether the others are read forwards or backwards makes no difference.  The norm alone,
-// 150 M: 85.1 / 85.8 us, and 94.6 with all of it kept: a cacheable read costs more unless something reads it again.
+// Bound by reading x.  What follows the norm of a job's average is the clipped update, which reads the same vector from
+// its start: the first kNormKept blocks are read last and without the streaming hint (kSqFrontKept), so that the Infinity
+// Cache (256 MB) still has them.  Kept blocks of 64, 128, 192 and 256 MB: 50 M and 2 ranks 284, 281, 288, 290 us (299
+// without); whether the others are read forwards or backwards makes no difference.  Reduce, norm and update in us, all of x
+// streamed / so, by what ran before them:
+//
+//                    writes of all gradients  staging copies   nothing else     reads of 1 GiB   a 1 GiB fill
+//   11 M x  8 ranks      116 /  113             120 /  117       117 /  111       121 /  118       131 /  128
+//   25.6 M x 8           253 /  242             252 /  243       252 /  243       251 /  244       250 /  262
+//   50 M x   2           293 /  279             295 /  283       292 /  281       298 /  281       297 /  312
+//   100 M x  8           984 /  946             981 /  949       996 /  971       977 /  955       979 /  987
+//   109 M x 16          1612 / 1599            1616 / 1595      1613 / 1599      1620 / 1596      1616 / 1634
+//
+// What loses is a cacheable read behind a fill, which has to write the fill's lines back first, and any cacheable read that
+// nothing follows.  The norm alone, cacheable over streamed, 8.5 / 15 / 25.6 / 41.9 / 150 M: behind a fill 1.50 / 1.75 /
+// 1.84 / 2.09 / 1.35, behind reads 1.01 / 1.03 / 1.06 / 1.08 / 1.02, of a vector just written 1.00-1.02.  So the norm that
+// belongs to no job (kSqStreamed) does without, and reads forwards: 110 M and 150 M just written 71.5 and 100 us, backwards
+// 75.4 and 105.
 constexpr uint64_t kNormKept = 10240;                   // 168 MB
+enum { kSqStreamed = 0, kSqFrontKept = 1, kSqKept = 2 };
 
 template <bool STREAM>
 __device__ __forceinline__ void load_block(const float* __restrict__ x, uint32_t h, f4 (&v)[4][4])
@@ -814,12 +826,15 @@ __device__ __forceinline__ void load_block(const float* __restrict__ x, uint32_t
 }
 
 // The sum of squares of block `blk` (the same in the whole wave), valid in lane 0.
+template <int READ>
 __device__ __forceinline__ float sq_block_sum(const float* __restrict__ x, uint64_t n, uint64_t blk, uint32_t h)
 {
     const uint64_t base = blk * 4096;
     f4 v[4][4];                                         // [tree lane h + 64 j][q]
     if (base + 4096 <= n) {
-        if (blk >= kNormKept) {
+        if constexpr (READ != kSqFrontKept) {
+            load_block<READ == kSqStreamed>(x + base, h, v);
+        } else if (blk >= kNormKept) {
             asm volatile("" ::: "memory");              // (and behind the loads: or the compiler makes one
             load_block<true>(x + base, h, v);           // branch of the two, without the hint)
             asm volatile("" ::: "memory");
@@ -860,14 +875,15 @@ __device__ __forceinline__ float sq_block_sum(const float* __restrict__ x, uint6
     return tree64(r0 + r1);                             // stride 64 and the rest
 }
 
+template <int READ>
 __global__ __launch_bounds__(kBlock) void k_sq_partials(const float* __restrict__ x, uint64_t n,
                                                         uint64_t nblk, float* __restrict__ part)
 {
     const uint32_t h = threadIdx.x & 63;
     const uint64_t k = (uint64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (k >= nblk) return;                              // whole wave leaves together
-    const uint64_t blk = nblk - 1 - k;
-    const float r = sq_block_sum(x, n, blk, h);
+    const uint64_t blk = READ == kSqStreamed ? k : nblk - 1 - k;
+    const float r = sq_block_sum<READ>(x, n, blk, h);
     if (h == 0) part[blk] = r;
 }
 
@@ -913,12 +929,19 @@ __global__ __launch_bounds__(kBlock) void k_sq_final(const float* __restrict__ p
     }
 }
 
-hipError_t launch_sq_norm(hipStream_t s, const float* x, uint64_t n, float* part, float* out)
+template <int READ>
+static hipError_t launch_sq_pair(hipStream_t s, const float* x, uint64_t n, float* part, float* out)
 {
     const uint64_t nblk = (n + 4095) / 4096;
-    if (nblk) hipLaunchKernelGGL(k_sq_partials, dim3((uint32_t)((nblk + 3) / 4)), dim3(kBlock), kAuxLdsPad, s, x, n, nblk, part);
+    if (nblk)
+        hipLaunchKernelGGL(k_sq_partials<READ>, dim3((uint32_t)((nblk + 3) / 4)), dim3(kBlock), kAuxLdsPad, s, x, n, nblk, part);
     hipLaunchKernelGGL(k_sq_final, dim3(1), dim3(kBlock), 0, s, part, nblk, out);
     return hipGetLastError();
+}
+
+hipError_t launch_sq_norm(hipStream_t s, const float* x, uint64_t n, float* part, float* out)
+{
+    return launch_sq_pair<kSqFrontKept>(s, x, n, part, out);
 }
 
 // Counts a workgroup in (one lane of it calls) and says whether it was the last of all: on one word up to
@@ -959,7 +982,7 @@ __global__ __launch_bounds__(kBlock) void k_sq_norm(const float* __restrict__ x,
     const uint32_t h = threadIdx.x & 63;
     const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t k = blockIdx.x * 4 + w;
-    const float r = k < nblk ? sq_block_sum(x, n, nblk - 1 - k, h) : 0.0f;
+    const float r = k < nblk ? sq_block_sum<kSqKept>(x, n, nblk - 1 - k, h) : 0.0f;
     if (h == 0) lds[w] = r;
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -993,7 +1016,8 @@ __global__ __launch_bounds__(kBlock) void k_sq_norm(const float* __restrict__ x,
 hipError_t launch_sq_norm_counted(hipStream_t s, const float* x, uint64_t n, float* part, float* out, uint32_t* arrivals)
 {
     const uint64_t nblk = (n + 4095) / 4096;
-    if (nblk == 0 || nblk > kCountedBlocks) return launch_sq_norm(s, x, n, part, out);
+    static_assert(kCountedBlocks <= kNormKept, "k_sq_norm reads every block without the hint");
+    if (nblk == 0 || nblk > kCountedBlocks) return hipErrorInvalidValue;
     const uint32_t groups = (uint32_t)((nblk + 3) / 4);
     hipLaunchKernelGGL(k_sq_norm, dim3(groups), dim3(kBlock), 0, s, x, n, (uint32_t)nblk, part, out, arrivals, groups);
     return hipGetLastError();
@@ -1038,7 +1062,7 @@ hipError_t launch_sq_norm_static(hipStream_t s, const float* x, uint64_t n, floa
     if (e != hipSuccess) return e;
     // k_sq_partials writes partials [0, nblk) before k_sq_final reads exactly those, so what
     // an earlier call left in the array is never read and nothing has to be cleared
-    return launch_sq_norm(s, x, n, part, out);
+    return launch_sq_pair<kSqStreamed>(s, x, n, part, out);
 }
 
 // ---------------------------------------------------------------------------
