@@ -10,6 +10,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 from typing import Optional, Sequence, Tuple
 
 from . import build as _build
@@ -167,6 +168,10 @@ def _bind_native(L: ctypes.CDLL) -> None:
     try:
         from . import _pycall
     except ImportError:                    # built where the interpreter's headers are not installed
+        return
+    if getattr(_pycall, "SOURCE_HASH", None) != _build.pycall_hash():
+        warnings.warn(f"{_build.PYCALL} was built from other sources than the tree holds and is not used: every call goes "
+                      f"through ctypes (python -m paper_2208_14228_amd.build builds it)", RuntimeWarning, stacklevel=3)
         return
     for name in _pycall.NAMES:
         general = _boundary_general if name == "es_est_boundary" else globals()[name]

@@ -63,16 +63,20 @@ def stale() -> bool:
         return True
 
 
-def _pycall_hash() -> str:
-    with open(PYCALL_SOURCE, "rb") as fh:
-        return hashlib.sha256(fh.read() + os.path.basename(PYCALL).encode()).hexdigest()[:16]
+def pycall_hash() -> str:
+    """Identifies what the extension module was built from and for; compiled into it as SOURCE_HASH."""
+    h = hashlib.sha256(os.path.basename(PYCALL).encode())
+    for f in (PYCALL_SOURCE, os.path.join(ROOT, "include", "es.h")):
+        with open(f, "rb") as fh:
+            h.update(b"\0" + fh.read())
+    return h.hexdigest()[:16]
 
 
 def build_pycall(force: bool, verbose: bool) -> None:
     include = sysconfig.get_paths()["include"]
     if not os.path.exists(os.path.join(include, "Python.h")):
         return
-    tag = _pycall_hash()
+    tag = pycall_hash()
     if not force and os.path.exists(PYCALL):
         try:
             with open(PYCALL_STAMP) as fh:
@@ -81,7 +85,8 @@ def build_pycall(force: bool, verbose: bool) -> None:
         except OSError:
             pass
     # (-x c++: hipcc takes it for an ordinary C++ file, no device code)
-    cmd = [hipcc(), "-x", "c++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I", include, PYCALL_SOURCE, "-o", PYCALL]
+    cmd = [hipcc(), "-x", "c++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I", include, "-I", os.path.join(ROOT, "include"),
+           f'-DES_PYCALL_HASH="{tag}"', PYCALL_SOURCE, "-o", PYCALL]
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.check_call(cmd)

@@ -15,6 +15,8 @@
 #include <tuple>
 #include <utility>
 
+#include "es.h"
+
 namespace {
 
 struct Bound {
@@ -43,11 +45,12 @@ bool get(PyObject* o, uint32_t& out)
     out = (uint32_t)v;
     return true;
 }
-bool get(PyObject* o, void*& out)
+template <class T>
+bool get(PyObject* o, T*& out)
 {
     uint64_t v = 0;
     if (o != Py_None && !unsigned_of(o, ~0ull, v)) return false;
-    out = (void*)(uintptr_t)v;
+    out = (T*)(uintptr_t)v;
     return true;
 }
 bool get(PyObject* o, double& out)
@@ -64,8 +67,10 @@ bool get(PyObject* o, float& out)
     return true;
 }
 
+template <class F>
+struct Call;
 template <class... A>
-struct Call {
+struct Call<int (*)(A...)> {
     template <size_t... I>
     static bool convert(PyObject* const* args, std::tuple<A...>& to, std::index_sequence<I...>)
     {
@@ -87,28 +92,26 @@ struct Call {
     }
 };
 
-// The argument types as include/es.h has them.
-typedef void* P;
-typedef uint32_t u32;
-typedef uint64_t u64;
 const struct {
     const char* name;
     vectorcallfunc call;
 } kCalls[] = {
-    {"es_ctx_restore", Call<P, u32>::call},
-    {"es_ctx_save", Call<P, u32>::call},
-    {"es_ctx_switch", Call<P, u32, u32>::call},
-    {"es_accumulate", Call<P, u32, u32, P>::call},
-    {"es_est_boundary", Call<P, u32, u32, u32, P, P>::call},
-    {"es_stage_fence", Call<P>::call},
-    {"es_dropout_mask", Call<P, u32, u32, P, u64, double>::call},
-    {"es_ring_order_reduce", Call<P, P>::call},
-    {"es_sgd_step", Call<P, P, P, P, float, float>::call},
-    {"es_reduce_sgd_step", Call<P, P, P, P, float, float>::call},
-    {"es_grad_sq_norm", Call<P, P, P>::call},
-    {"es_grad_sq_norm_static", Call<P, u64, P, P>::call},
-    {"es_clip_sgd_step", Call<P, P, P, P, P, float, float, float, float>::call},
-    {"es_bn_batch_stats", Call<P, u64, u64, u64, P, P, P, u64, P>::call},
+#define ES_CALL(f) {#f, Call<decltype(&f)>::call}
+    ES_CALL(es_ctx_restore),
+    ES_CALL(es_ctx_save),
+    ES_CALL(es_ctx_switch),
+    ES_CALL(es_accumulate),
+    ES_CALL(es_est_boundary),
+    ES_CALL(es_stage_fence),
+    ES_CALL(es_dropout_mask),
+    ES_CALL(es_ring_order_reduce),
+    ES_CALL(es_sgd_step),
+    ES_CALL(es_reduce_sgd_step),
+    ES_CALL(es_grad_sq_norm),
+    ES_CALL(es_grad_sq_norm_static),
+    ES_CALL(es_clip_sgd_step),
+    ES_CALL(es_bn_batch_stats),
+#undef ES_CALL
 };
 
 void bound_dealloc(PyObject* self)
@@ -180,5 +183,6 @@ PyMODINIT_FUNC PyInit__pycall()
         PyTuple_SET_ITEM(names, i, s);
     }
     if (PyModule_AddObject(m, "NAMES", names) < 0) { Py_DECREF(names); Py_DECREF(m); return nullptr; }
+    if (PyModule_AddStringConstant(m, "SOURCE_HASH", ES_PYCALL_HASH) < 0) { Py_DECREF(m); return nullptr; }
     return m;
 }

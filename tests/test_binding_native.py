@@ -89,3 +89,14 @@ def test_bound_calls_keep_names_defaults_and_status():
     assert B.es_est_boundary_m(None, 0, None, m) == B.ES_EINVAL
     with pytest.raises(ValueError):
         native.bind("es_init", 1, len)
+
+
+def test_a_module_built_from_other_sources_is_not_used(monkeypatch):
+    import types
+
+    import paper_2208_14228_amd as package
+    for attrs in ({"SOURCE_HASH": "0" * 16}, {}):
+        stale = types.SimpleNamespace(NAMES=native.NAMES, bind=lambda *a: pytest.fail("a stale module is bound"), **attrs)
+        monkeypatch.setattr(package, "_pycall", stale)
+        with pytest.warns(RuntimeWarning, match="built from other sources"):
+            B._bind_native(B.lib())
