@@ -174,12 +174,11 @@ def _bind_native(L: ctypes.CDLL) -> None:
                       f"through ctypes (python -m paper_2208_14228_amd.build builds it)", RuntimeWarning, stacklevel=3)
         return
     for name in _pycall.NAMES:
-        general = _boundary_general if name == "es_est_boundary" else globals()[name]
-        call = _pycall.bind(name, ctypes.cast(getattr(L, name), _VP).value, getattr(general, "__wrapped__", general))
+        address = ctypes.cast(getattr(L, name), _VP).value
         if name == "es_est_boundary":
-            _boundary = call
-        else:
-            globals()[name] = call
+            _boundary = _pycall.bind(name, address, _boundary_general)
+        elif globals()[name] is _OWN[name]:     # a function that a caller has put there stays
+            globals()[name] = _pycall.bind(name, address, _OWN[name])
 
 
 def check(status: int, where: str, h: Optional[int] = None) -> int:
@@ -437,3 +436,6 @@ def es_sched_grouping(n_used, est_per_gpu, max_p: int):
     if st != ES_OK:
         return st, 0, [], []
     return st, nw.value, list(wo[:max_p]), list(so[:max_p])
+
+
+_OWN = {name: globals()[name] for name in EXPORTS if name in globals()}     # this module's functions, see _bind_native

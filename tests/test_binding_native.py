@@ -2,11 +2,16 @@
 notes its arguments, with plain values at the ends of their ranges and with what only ctypes converts."""
 import ctypes
 import math
+import os
+import subprocess
+import sys
 
 import numpy as np
 import pytest
 
 from paper_2208_14228_amd import binding as B
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 B.lib()
 native = pytest.importorskip("paper_2208_14228_amd._pycall")
@@ -100,3 +105,20 @@ def test_a_module_built_from_other_sources_is_not_used(monkeypatch):
         monkeypatch.setattr(package, "_pycall", stale)
         with pytest.warns(RuntimeWarning, match="built from other sources"):
             B._bind_native(B.lib())
+
+
+def test_a_function_put_in_before_the_library_is_loaded_stays():
+    code = """
+import functools
+from paper_2208_14228_amd import binding as B
+seen = []
+plain = lambda h: seen.append(h) or -9
+@functools.wraps(B.es_ctx_save)
+def traced(h, est): seen.append(est); return B.es_ctx_save.__wrapped__(h, est)
+B.es_stage_fence, B.es_ctx_save = plain, traced
+B.lib()
+assert B.es_stage_fence is plain and B.es_stage_fence(None) == -9
+assert B.es_ctx_save is traced and B.es_ctx_save(None, 7) == B.ES_EINVAL and seen == [None, 7]
+assert type(B.es_ctx_restore).__name__ == "Bound" and B.es_ctx_restore(None, 0) == B.ES_EINVAL
+"""
+    subprocess.run([sys.executable, "-c", code], check=True, timeout=120, cwd=ROOT)
