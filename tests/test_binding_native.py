@@ -88,12 +88,26 @@ def test_bound_calls_keep_names_defaults_and_status():
         assert f.__wrapped__.__module__ == B.__name__
     assert B.es_bn_batch_stats(None, 0, 1, 1, None, None, None, 0) == B.ES_EINVAL
     assert B.es_stage_fence(h=None) == B.ES_EINVAL
-    m = B.Marshalled([0], [64])
-    assert B.es_est_boundary_m(None, 0, None, m) == B.ES_EINVAL
-    m.g = (ctypes.c_void_p * 1)(64)                     # an array put in its place is the one that is used
-    assert B.es_est_boundary_m(None, 0, None, m) == B.ES_EINVAL
     with pytest.raises(ValueError):
         native.bind("es_init", 1, len)
+
+
+@pytest.mark.parametrize("which", ["b", "g"])
+def test_an_array_put_in_the_place_of_a_marshalled_one_is_used(monkeypatch, which):
+    notes = []
+    monkeypatch.setattr(B, "_boundary", lambda *a: notes.append(a) or -7)
+    proto = ctypes.CFUNCTYPE(ctypes.c_int, *B._SIGS["es_est_boundary"][1])
+    general = proto(lambda h, out, into, n, b, g: notes.append((h, out, into, n, b[0], g[0])) or -8)
+    class Library:
+        es_est_boundary = general
+    monkeypatch.setattr(B, "lib", lambda: Library)
+    m = B.Marshalled([3], [64])
+    at = ctypes.addressof(m.b), ctypes.addressof(m.g)
+    assert B.es_est_boundary_m(5, 0, None, m) == -7 and notes == [(5, 0, B.ES_NO_EST, 1, *at)]
+    setattr(m, which, (ctypes.c_uint32 * 1)(9) if which == "b" else (ctypes.c_void_p * 1)(128))
+    notes.clear()
+    assert B.es_est_boundary_m(5, 0, 2, m) == -8
+    assert notes == [(5, 0, 2, 1, *((9, 64) if which == "b" else (3, 128)))]
 
 
 def test_a_module_built_from_other_sources_is_not_used(monkeypatch):
