@@ -58,8 +58,11 @@ struct es_handle {
     uint32_t n_big = 0;                         // leading big tiles (see k_ring_reduce_big)
     const float** d_slots = nullptr;            // N device pointers, by virtual rank
     float* d_partials = nullptr;                // ceil(P / 4096) block partials of es_grad_sq_norm
-    uint64_t partials_counters = 0;             // where in d_partials its counters of workgroups start; 0: none
-    uint32_t* d_mask_counters = nullptr;        // kArrivalWords, for the long masks enqueued on main: one draw after the other
+
+    // Counters of workgroups, kArrivalWords each, in the tile block as well: what uses them runs on main, one launch
+    // after the other.
+    uint32_t* d_norm_counters = nullptr;        // the norm in one launch; null: two launches
+    uint32_t* d_mask_counters = nullptr;        // long masks, if any state segment can be an RNG state
 
     // ESTs whose gradients the next reduce reads in place (rank, caller's flat gradient)
     std::vector<uint32_t> in_place_rank;
@@ -274,7 +277,7 @@ int upload_tiles(es_handle* h, const std::vector<Tile>& table, Tile** out)
     return hip_fail(h, e);
 }
 
-// es_init: both tables, one block, one copy.
+// es_init: both tables and behind them, on lines of their own, the counters (zeros): one block, one copy.
 int build_tile_block(es_handle* h)
 {
     std::vector<Tile> table, none;
@@ -283,8 +286,17 @@ int build_tile_block(es_handle* h)
     if (table.size() > 0x7fffffffull) return ES_EINVAL;
     const uint32_t n_wave = (uint32_t)table.size();
     int rc = plan_option_tiles(h, table, h->n_tiles, h->n_big);
-    if (rc == ES_OK) rc = upload_tiles(h, table, &h->d_tile_block);
     if (rc != ES_OK) return rc;
+    const uint64_t nblk = (h->P + 4095) / 4096;
+    const bool norm = nblk != 0 && nblk <= kCountedBlocks;
+    const bool mask = std::count(h->seg_bytes.begin(), h->seg_bytes.end(), 16) != 0;
+    constexpr size_t line = kCounterStep * sizeof(uint32_t) / sizeof(Tile), set = kArrivalWords * sizeof(uint32_t) / sizeof(Tile);
+    const size_t at = round_up(table.size(), line);
+    if (norm || mask) table.resize(at + (norm ? set : 0) + (mask ? set : 0));
+    rc = upload_tiles(h, table, &h->d_tile_block);
+    if (rc != ES_OK) return rc;
+    if (norm) h->d_norm_counters = (uint32_t*)(h->d_tile_block + at);
+    if (mask) h->d_mask_counters = (uint32_t*)(h->d_tile_block + at + (norm ? set : 0));
     h->d_wave_tiles = h->d_tile_block;
     h->n_wave_tiles = n_wave;
     h->d_tiles = h->d_tile_block + n_wave;
@@ -610,22 +622,8 @@ int es_init(es_handle** out, uint32_t n_logical, const es_bucket_layout* lay)
     if (rc == ES_OK) rc = build_tile_block(h);
     if (rc == ES_OK) rc = upload_slot_table(h);
     if (rc == ES_OK && h->P) {
-        const uint64_t nblk = (h->P + 4095) / 4096;
-        const bool counted = nblk <= kCountedBlocks;
-        h->partials_counters = counted ? round_up(nblk, kCounterStep) : 0;
-        e = dev_malloc(h, (void**)&h->d_partials,
-                       (counted ? h->partials_counters + kArrivalWords : nblk) * sizeof(float));
-        if (e == hipSuccess && counted) {
-            const uint32_t zeros[kArrivalWords] = {};
-            e = hipMemcpy(h->d_partials + h->partials_counters, zeros, sizeof(zeros), hipMemcpyHostToDevice);
-        }
+        e = dev_malloc(h, (void**)&h->d_partials, ((h->P + 4095) / 4096) * sizeof(float));
         if (e != hipSuccess) rc = hip_fail(h, e);
-    }
-    if (rc == ES_OK && std::count(h->seg_bytes.begin(), h->seg_bytes.end(), 16)) {
-        const uint32_t zeros[kArrivalWords] = {};
-        e = dev_malloc(h, (void**)&h->d_mask_counters, sizeof(zeros));
-        if (e == hipSuccess) e = hipMemcpy(h->d_mask_counters, zeros, sizeof(zeros), hipMemcpyHostToDevice);
-        if (e != hipSuccess) rc = e == hipErrorOutOfMemory ? ES_ENOMEM : hip_fail(h, e);
     }
     if (rc != ES_OK) { es_destroy(h); return rc; }
     *out = h;
@@ -644,7 +642,6 @@ int es_destroy(es_handle* h)
     dev_release(h, h->d_tiles_rebuilt);
     dev_release(h, (void*)h->d_slots);
     dev_release(h, h->d_partials);
-    dev_release(h, h->d_mask_counters);
     if (h->s_swap) (void)hipStreamSynchronize(h->s_swap);
     swap_release(h);
     if (h->s_swap) (void)hipStreamDestroy(h->s_swap);
@@ -1241,9 +1238,8 @@ int es_grad_sq_norm(es_handle* h, const float* d_vec, float* d_out2)
     if (!h || !d_out2 || (((uintptr_t)d_out2) & 3)) return ES_EINVAL;
     DeviceGuard guard__(h);
     if (h->P && (!d_vec || !aligned16(d_vec))) return ES_EINVAL;
-    if (h->partials_counters)
-        ES_HIP(h, launch_sq_norm_counted(h->s_main, d_vec, h->P, h->d_partials, d_out2,
-                                         (uint32_t*)(h->d_partials + h->partials_counters)));
+    if (h->d_norm_counters)
+        ES_HIP(h, launch_sq_norm_counted(h->s_main, d_vec, h->P, h->d_partials, d_out2, h->d_norm_counters));
     else
         ES_HIP(h, launch_sq_norm(h->s_main, d_vec, h->P, h->d_partials, d_out2));
     return ES_OK;

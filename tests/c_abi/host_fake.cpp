@@ -314,6 +314,9 @@ static int check_masks()
                     CHECK(es_dropout_mask(h, e, seg, mask, kShortMask, 0.5) == ES_OK && m_form == kShort && m_state == state);
                 }
             }
+        alignas(16) float x[4] = {}, out[2];    // the norm has words of its own
+        CHECK(es_grad_sq_norm(h, x, out) == ES_OK && zeros_held(n_counters, kArrivalWords));
+        CHECK(n_counters + kArrivalWords <= counters || counters + kArrivalWords <= n_counters);
         m_form = kNone;
         CHECK(es_dropout_mask(h, 0, 0, mask, kShortMask + 1, 0.5) == ES_EINVAL && m_form == kNone);
     }
@@ -321,7 +324,7 @@ static int check_masks()
     return 0;
 }
 
-// The norm's partials, and behind them, on a line of their own, the counters of its one-launch form.
+// The norm's partials, and the counters of its one-launch form on lines of their own.
 static int check_norms()
 {
     const uint64_t block = 4096;
@@ -333,8 +336,8 @@ static int check_norms()
             CHECK(j.h && es_grad_sq_norm(j.h, x, out) == ES_OK && (n_counters != nullptr) == (blocks <= kCountedBlocks));
             std::fill(n_part, n_part + blocks, 1.0f);           // all of them, and no counter
             if (!n_counters) continue;
-            CHECK(zeros_held(n_counters, kArrivalWords) && (float*)n_counters >= n_part + blocks);
-            CHECK(((char*)n_counters - (char*)n_part) % 128 == 0);
+            CHECK(zeros_held(n_counters, kArrivalWords) && (uintptr_t)n_counters % 128 == 0);
+            CHECK(j.reduce() == ES_OK && (const char*)(l_tiles + l_n) <= (const char*)n_counters);
         }
     CHECK(g_live.empty());
     return 0;
