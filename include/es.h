@@ -28,8 +28,9 @@
  *    gradient, gradient sources, live state tensors and masks belong to the
  *    caller and must stay valid until the work enqueued on them has finished.
  *  - A handle is not thread-safe; calls on one handle must not overlap.
- *  - No kernel of this library uses atomics, and every floating-point result
- *    is independent of grid size and launch configuration.
+ *  - Every floating-point result is independent of grid size and launch
+ *    configuration: no atomic does arithmetic on one (atomics count workgroups, or
+ *    carry a finished sum from one workgroup to another).
  */
 #ifndef ES_H
 #define ES_H
@@ -334,7 +335,7 @@ int es_reduce_sgd_step(es_handle* h, float* d_param, float* d_momentum,
  *   (0..255) adds, from +0, the squares of elements 4*(256*q + t) + c, q = 0..3 outer,
  *   c = 0..3 inner; lane sums combine as v[t] += v[t+s] for t < s, s = 128, 64, .., 1;
  *   block partials combine the same way (lane t first adds partials t, t+256, ...).
- *   Every square and add is rounded to fp32; no atomics.
+ *   Every square and add is rounded to fp32.
  *   d_vec   DEVICE, n_params floats, 16-byte aligned
  *   d_out2  DEVICE, 2 floats: [0] sum of squares, [1] its correctly rounded square root
  * Runs on main.  The sums pass through memory of the handle: a call captured into a graph must not be
@@ -366,8 +367,7 @@ int es_clip_sgd_step(es_handle* h, float* d_param, float* d_momentum, const floa
  * For every channel the M = n_images * n_positions values in the order (image, position) are
  * the terms of the tree described at es_grad_sq_norm (terms instead of squares, terms beyond M
  * count as +0):  mean = T(y) / (float)M ;  var = T((y - mean)^2) / (float)M  (biased variance),
- * every subtraction, square, add and division rounded to fp32.  No atomics; the first stage
- * uses lane exchanges, the second an LDS stage.
+ * every subtraction, square, add and division rounded to fp32.
  *   d_workspace      DEVICE scratch of at least es_bn_workspace_floats(..) floats, 4-byte aligned
  *   stream           HOST value of a hipStream_t on the current device (NULL = null stream)
  * Limits: M < 2^31, n_channels <= 65535, n_images and n_positions > 0 (ES_EINVAL otherwise;

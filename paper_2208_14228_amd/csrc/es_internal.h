@@ -206,7 +206,7 @@ hipError_t launch_est_boundary(hipStream_t s, const CopyRuns& runs, const Piece*
 hipError_t launch_copy_bytes(hipStream_t s, uint8_t* dst, const uint8_t* src, uint64_t n);
 
 // out[0] = fixed-tree sum of squares of x[0..n), out[1] = its square root;
-// part: scratch of ceil(n / 4096) floats
+// part: scratch of ceil(n / 4096) floats.  Leaves the front of x in the caches for the update that follows.
 hipError_t launch_sq_norm(hipStream_t s, const float* x, uint64_t n, float* part, float* out);
 
 // The same in one launch up to kCountedBlocks blocks, given kArrivalWords counters that are zero before
@@ -214,7 +214,7 @@ hipError_t launch_sq_norm(hipStream_t s, const float* x, uint64_t n, float* part
 constexpr uint64_t kCountedBlocks = 2048;
 hipError_t launch_sq_norm_counted(hipStream_t s, const float* x, uint64_t n, float* part, float* out, uint32_t* arrivals);
 
-// The same with the block partials in a file-scope device array of kStaticPartials floats
+// The same (but all of x streamed) with the block partials in a file-scope device array of kStaticPartials floats
 // (1 MiB per GPU): no allocation; n <= kStaticPartials * 4096, else hipErrorInvalidValue.
 // Runs on the current device.
 constexpr uint64_t kStaticPartials = 1ull << 18;

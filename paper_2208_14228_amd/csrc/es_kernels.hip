@@ -4,9 +4,10 @@
 // Bit-exactness rules that hold for every kernel in this file:
 //  - fp32 IEEE arithmetic, denormals kept, no fused multiply-add (the file is
 //    compiled with -ffp-contract=off), division correctly rounded;
-//  - no atomics; no arithmetic across lanes: a sum over N ranks is a chain of
-//    N-1 adds in one lane in program order, so neither the grid shape nor the
-//    order in which loads return can change a bit;
+//  - a sum over N ranks is a chain of N-1 adds in one lane in program order, and sums
+//    across lanes follow a fixed tree, so neither the grid shape nor the order in which
+//    loads return can change a bit; no atomic does arithmetic on a floating-point value
+//    (they count workgroups, or carry a finished sum from one to another);
 //  - loads may be issued early and in any order, only the add chain is ordered.
 #include "es_internal.h"
 
@@ -744,12 +745,12 @@ hipError_t launch_sgd_clip(hipStream_t s, float* p, float* v, const float* g, ui
 // 4*(256*q + t) + c, q = 0..3 outer, c = 0..3 inner, starting from +0; the 256
 // lane sums combine as v[t] += v[t+s], s = 128 .. 1; block partials combine the
 // same way in one more workgroup (lane t adds partials t, t+256, ... first).
-// No atomics; wave shuffles (and LDS in the last stage) carry the tree.
+// Lane exchanges (and LDS in the last stage) carry the tree; no atomic adds to a sum.
 // ---------------------------------------------------------------------------
 // The strides 32 .. 1 of a stride-halving tree (v[t] += v[t + s]) over the wave; the sum is valid in lane 0.
 // Lane exchanges of the vector ALU only: a permutation through LDS in each of six steps in a row was
 // most of what a wave did between its loads and its result (BatchNorm statistics 32x2048x7x7 6.5 -> 6.1 us,
-// 4x375x13788 17.8 -> 16.6, one channel of 12 blocks 5.3 -> 4.7).
+// 4x375x13788 17.8 -> 16.6).
 template <uint32_t ROW_SHIFT>
 __device__ __forceinline__ float add_shifted(float r)       // lane t: r + lane t + ROW_SHIFT of its row of 16
 {
@@ -792,7 +793,7 @@ __device__ __forceinline__ float tree256(float s, float* lds)
 
 // One WAVE per 4096-element block: hardware lane h plays the tree's lanes h, h+64,
 // h+128 and h+192, so the strides 128 and 64 are adds between its own registers,
-// 32 .. 1 are wave shuffles, and no LDS or barrier is needed; all 16 loads of a
+// 32 .. 1 are lane exchanges, and no LDS or barrier is needed; all 16 loads of a
 // lane are in flight before the first add.
 //
 // Bound by reading x.  What follows the norm of a job's average is the clipped update, which reads the same vector from
@@ -967,12 +968,15 @@ __device__ __forceinline__ bool arrived_last(uint32_t* arrivals, uint32_t groups
 // and in the order of k_sq_final; no workgroup waits.
 //
 // Partials are stored and loaded at agent scope, past the L2 that each compute die has to itself; the one lane
-// that stores a workgroup's waits until its stores have been acknowledged before it counts the workgroup in.  (A
-// release fence for it writes back the whole L2, of the reduce's average too: 4 M 5.7 -> 7.9 us, 8 M 5.9 -> 16.)
+// that stores a workgroup's waits until its stores have been acknowledged before it counts the workgroup in.  The
+// language's memory model would ask for a release and an acquire around the count; that these accesses in this order are
+// enough is a property of this target, where an agent-scope store is acknowledged at the memory all dies share.  (A
+// release fence writes back the whole L2, of the reduce's average too: 4 M 5.7 -> 7.9 us, 8 M 5.9 -> 16.)
 //
-// Bound by the launch and two round trips.  Against two launches, enqueued from the host: 4 k to 1 M 6.7 -> 3.4 us (host
-// bound), 4 M 6.6 -> 3.4, 8 M 5.9 -> 5.2; reduce, norm and update of 200 k and 16 ranks 17.3 -> 13.7.  Beyond 2,048 blocks a
-// launch is less than a hundredth of such a step.
+// Bound by the launch and two round trips.  Against two launches, called from Python one after the other (0.4 us of it the
+// binding): 4 k 6.3 -> 3.6 us, 200 k 6.3 -> 4.7, 1 M 6.4 -> 4.9, 4 M 6.4 -> 5.1, 8 M 7.4 -> 5.6; reduce, norm and update of 20 k and
+// 4 ranks 15.4 -> 12.2, 200 k and 16 ranks 16.2 -> 13.4, 1 M and 8 ranks 18.5 -> 17.9.  Beyond 2,048 blocks a launch is less than
+// a hundredth of such a step.
 __global__ __launch_bounds__(kBlock) void k_sq_norm(const float* __restrict__ x, uint64_t n, uint32_t nblk,
                                                     float* part, float* __restrict__ out,
                                                     uint32_t* __restrict__ arrivals, uint32_t groups)
@@ -1417,15 +1421,18 @@ constexpr uint64_t kMaskGroups = 2048;                  // 8 workgroups of 4 wav
 // read the state advances the offset, so no second launch is needed; no workgroup waits for another.
 // `arrivals` (one line per counter, zero between launches) counts them: on one counter up to kOneCounter
 // workgroups, beyond in kCounters groups whose last members meet on one more (an addition to a word
-// that others add to as well takes 12 ns: 1,024 of them 13 us on one word, nothing to be seen on 16).
+// that others add to as well takes 12 ns: 1,024 of them 13 us on one word, nothing to be seen on 16).  That is
+// what arrived_last does, written out: the draw lies between the count and its evaluation here, and
+// with the helper called after it 16x12x512x512 bytes took 16.6 us for 15.2.
 //
 // Integer-ALU bound: per four bytes 18 products, 19 exclusive ors and 7 instructions to compare and pack.
-// One launch instead of two, enqueued from the host: 16 KiB to 10 MB 7.0 -> 4.0 us a mask (that is what a launch
-// costs the host); GPU time of 70 kB 5.1 -> 3.7, 3.7 MB 5.9 -> 5.1.  16x12x512x512 bytes 16.9 -> 15.3 us
-// (3.3 TB/s of stores) where passes overlap, 23.9 -> 22.5 one after the other; 143 MB 47.0 -> 44.2.
+// One launch instead of two, called from Python one after the other (0.7 us of it the binding): 16 KiB to 1 MB 6.5 ->
+// 3.5 us a mask (that is what a launch costs the host), 3.7 MB 6.8 -> 4.5, 10 MB 8.0 -> 7.1, 16x12x512x512 bytes 22.6 -> 20.9,
+// 143 MB 52.1 -> 49.6; 16x12x512x512 where passes overlap 16.9 -> 15.5 (3.2 TB/s of stores).
 //
 // A draw that is captured into a graph can be replayed when the counters are gone, or beside another draw that uses
-// them: it only reads the state (COUNTED = false), and k_philox_advance follows it.
+// them: it only reads the state (COUNTED = false), and k_philox_advance follows it (in a graph 4.2 us up to 1 MB, 5.5 for
+// 3.7 MB).
 template <bool COUNTED>
 __global__ __launch_bounds__(kBlock) void k_dropout_mask(uint64_t* __restrict__ state, uint8_t* __restrict__ mask,
                                                          uint64_t n, uint64_t keep, int aligned16,
@@ -1525,7 +1532,7 @@ hipError_t launch_dropout_mask_long(hipStream_t s, uint64_t* state, uint8_t* mas
 // partials t, t+256, ...).  mean = T(y) / M, var = T((y - mean)^2) / M.
 //
 // One WAVE per block of one channel; hardware lane h plays tree lanes h, h+64, h+128, h+192
-// (strides 128 and 64 are adds between its own registers, 32..1 wave shuffles).  No atomics.
+// (strides 128 and 64 are adds between its own registers, 32..1 lane exchanges).
 // ---------------------------------------------------------------------------
 struct BnGeom {
     uint32_t C, HW, M, nblk;
@@ -1722,7 +1729,15 @@ void k_bn_channel(const float* __restrict__ x, const BnGeom g, float fM, float* 
 constexpr uint32_t kBnPerWave = 3;
 constexpr uint32_t kBnHeld = 4 * (kBnPerWave + 1);      // blocks per workgroup
 constexpr uint32_t kBnMostGroups = 64;                  // one per lane
-constexpr uint32_t kBnPolls = 100;                      // 100 to 200 us
+
+// How often a workgroup looks for the others' sums before it computes the missing ones.  A look takes 0.165 us, so it gives
+// up after 17 us (a workgroup alone in its grid: 400 looks in each of two passes 131 us more than none).  No layer measured
+// needs more than 30, neither on an idle card nor beside a 1 GiB copy on another stream; with 10, a large layer takes 1.5 times
+// as long.  Giving up too early is the dearer mistake: a sum of 16 blocks takes 4.7 us from memory, and a workgroup of 64 that
+// misses them all 300 us.  Beside a kernel that holds all but 128 / 64 / 32 CUs, reading x twice over this: 32x64x112x112 42.6 /
+// 54 / 91 over 30 / 43 / 73 us, 144x51x53x53 40 / 57 / 94 over 33 / 54 / 88, but 256x3x120x120, which reads little and waits
+// most, 24 / 24 / 24 over 21 / 27 / 40.
+constexpr uint32_t kBnPolls = 100;
 
 // A sum s under a tag: s, s ^ low half, s ^ high half.  Three words that were not all written together pass
 // for a sum only where they hold the right one.
@@ -1746,7 +1761,7 @@ __device__ __forceinline__ unsigned long long bn_collect(BnSum* from, uint32_t g
         if (wanted) {
             uint32_t v[3];
 #pragma unroll
-            for (int k = 0; k < 3; ++k) v[k] = __hip_atomic_load(&from[h].word[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            for (int i = 0; i < 3; ++i) v[i] = __hip_atomic_load(&from[h].word[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if ((v[0] ^ v[1]) == (uint32_t)tag && (v[0] ^ v[2]) == (uint32_t)(tag >> 32)) {
                 sum = __uint_as_float(v[0]);
                 wanted = false;
@@ -1908,8 +1923,9 @@ void k_bn_shared(const float* __restrict__ x, const BnGeom g, uint32_t groups, f
     }
 }
 
-// The number of workgroups per channel: as few as hold it, more while they are all resident at once (two
-// per CU) and their sums fit the workspace of nblk floats per channel.
+// The number of workgroups per channel: as few as hold it, more while they are all resident at once (two on each of
+// the 256 CUs; with fewer CUs to be had, some wait for the others in vain, see kBnPolls) and their sums fit the workspace of
+// nblk floats per channel.
 static uint32_t bn_groups(uint32_t C, uint32_t nblk)
 {
     constexpr uint32_t floats = 2 * sizeof(BnSum) / sizeof(float);
