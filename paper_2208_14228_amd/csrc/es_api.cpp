@@ -69,6 +69,8 @@ struct es_handle {
     std::vector<const float*> in_place_ptr;
     std::vector<uint8_t> accumulated;           // [est * n_buckets + bucket]
     uint64_t n_accumulated = 0;
+    std::vector<uint64_t> named_in;             // [est]: the last es_accumulate_many call that named it, by number
+    uint64_t call = 0;
 
     hipStream_t s_main = nullptr, s_ctx = nullptr, s_stage = nullptr;
     hipEvent_t ev_main = nullptr, ev_ctx = nullptr, ev_stage = nullptr;
@@ -598,6 +600,7 @@ int es_init(es_handle** out, uint32_t n_logical, const es_bucket_layout* lay)
         h->slot_of.resize(h->N);
         for (uint32_t e = 0; e < h->N; ++e) h->slot_of[e] = e;
         h->accumulated.assign((size_t)h->N * h->buckets.size(), 0);
+        h->named_in.assign(h->N, 0);
         // fewer ranks than the default batch: the largest power of two that fits, so that the
         // opening loads of a fold are still issued together (measured +4 % at N = 5..7)
         while (h->shape.rank_batch > 1 && (uint32_t)h->shape.rank_batch > h->N) h->shape.rank_batch /= 2;
@@ -1009,13 +1012,14 @@ try {
     const size_t nb = h->buckets.size();
     const uint64_t vec_bytes = h->P * sizeof(float);
     if (((h->P >> 2) + kCopyBlock - 1) / kCopyBlock > 0x7fffffffull) return ES_EINVAL;
+    ++h->call;
     for (uint32_t k = 0; k < n_ests; ++k) {
         const uint32_t e = ests[k];
         if (e >= h->N) return ES_EINVAL;
         const float* src = d_flat_grads[k];
         if (h->P && (!src || (((uintptr_t)src) & 3))) return ES_EINVAL;
-        for (uint32_t j = 0; j < k; ++j)
-            if (ests[j] == e) return ES_ESTATE;
+        if (h->named_in[e] == h->call) return ES_ESTATE;
+        h->named_in[e] = h->call;
         for (size_t b = 0; b < nb; ++b)
             if (h->accumulated[(size_t)e * nb + b]) return ES_ESTATE;
         if (h->P && src != slot_base(h, e) && overlap(src, slot_base(h, e), vec_bytes)) return ES_EINVAL;

@@ -343,6 +343,24 @@ static int check_norms()
     return 0;
 }
 
+// An EST is named once per es_accumulate_many call, and once per step; a call that is refused leaves nothing behind.
+static int check_many()
+{
+    Job j(5, 4001);
+    const float* g[6];
+    for (uint32_t e = 0; e < 5; ++e) g[e] = es_grad_slot(j.h, e, 0);
+    g[5] = g[0];
+    const uint32_t all[6] = {0, 1, 2, 3, 4, 0}, far[2] = {3, 5};
+    for (int step = 0; step < 3; ++step) {
+        CHECK(es_accumulate_many(j.h, 6, all, g) == ES_ESTATE && es_accumulate_many(j.h, 2, far, g + 3) == ES_EINVAL);
+        CHECK(es_accumulate_many(j.h, 3, all, g) == ES_OK && es_accumulate_many(j.h, 3, all + 2, g + 2) == ES_ESTATE);
+        CHECK(es_accumulate_many(j.h, 2, all + 3, g + 3) == ES_OK && es_accumulate_many(j.h, 1, all + 4, g + 4) == ES_ESTATE);
+        CHECK(es_accumulate_many(j.h, 0, nullptr, nullptr) == ES_OK);
+        CHECK(es_ring_order_reduce(j.h, (float*)(((uintptr_t)j.avg.data() + 15) & ~(uintptr_t)15)) == ES_OK);
+    }
+    return 0;
+}
+
 int main(int argc, char** argv)
 {
     const char* what = argc > 1 ? argv[1] : "";
@@ -353,6 +371,7 @@ int main(int argc, char** argv)
     if (!std::strcmp(what, "rule")) rc = check_rule();
     if (!std::strcmp(what, "masks")) rc = check_masks();
     if (!std::strcmp(what, "norms")) rc = check_norms();
+    if (!std::strcmp(what, "many")) rc = check_many();
     if (rc == 0) std::printf("%s: passed\n", what);
     return rc;
 }
