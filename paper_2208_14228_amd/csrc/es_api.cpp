@@ -621,9 +621,13 @@ int es_init(es_handle** out, uint32_t n_logical, const es_bucket_layout* lay)
         es_destroy(h);
         return ES_EHIP;
     }
-    rc = alloc_worker(h, h->workers[0], h->N);
-    if (rc == ES_OK) rc = build_tile_block(h);
-    if (rc == ES_OK) rc = upload_slot_table(h);
+    try {
+        rc = alloc_worker(h, h->workers[0], h->N);
+        if (rc == ES_OK) rc = build_tile_block(h);
+        if (rc == ES_OK) rc = upload_slot_table(h);
+    } catch (const std::bad_alloc&) {
+        rc = ES_ENOMEM;
+    }
     if (rc == ES_OK && h->P) {
         e = dev_malloc(h, (void**)&h->d_partials, ((h->P + 4095) / 4096) * sizeof(float));
         if (e != hipSuccess) rc = hip_fail(h, e);

@@ -6,6 +6,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <map>
+#include <new>
 #include <vector>
 
 #include "es.h"
@@ -27,6 +28,19 @@ static void dev_free(void* p, void*)
     ++g_frees;
     std::free(p);
 }
+
+// Host memory: no single allocation above the limit.
+static size_t g_host_limit = ~(size_t)0;
+#ifndef __SANITIZE_ADDRESS__                     // which has an operator new of its own
+void* operator new(size_t n)
+{
+    void* p = n > g_host_limit ? nullptr : std::malloc(n ? n : 1);
+    if (!p) throw std::bad_alloc();
+    return p;
+}
+void operator delete(void* p) noexcept { std::free(p); }
+void operator delete(void* p, size_t) noexcept { std::free(p); }
+#endif
 
 extern "C" {
 hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
@@ -361,6 +375,21 @@ static int check_many()
     return 0;
 }
 
+// Where the host's memory does not suffice for the tile tables, es_init says so and holds nothing.
+static int check_no_memory()
+{
+    es_bucket b = {0, 1u << 22};
+    es_bucket_layout lay = {1u << 22, 1, &b, 4, 0, nullptr, dev_alloc, dev_free, nullptr};
+    for (size_t limit : {(size_t)1 << 15, (size_t)1 << 16}) {
+        es_handle* h = nullptr;
+        g_host_limit = limit;
+        const int rc = es_init(&h, 4, &lay);
+        g_host_limit = ~(size_t)0;
+        CHECK(rc == ES_ENOMEM && !h && g_live.empty());
+    }
+    return 0;
+}
+
 int main(int argc, char** argv)
 {
     const char* what = argc > 1 ? argv[1] : "";
@@ -372,6 +401,7 @@ int main(int argc, char** argv)
     if (!std::strcmp(what, "masks")) rc = check_masks();
     if (!std::strcmp(what, "norms")) rc = check_norms();
     if (!std::strcmp(what, "many")) rc = check_many();
+    if (!std::strcmp(what, "no memory")) rc = check_no_memory();
     if (rc == 0) std::printf("%s: passed\n", what);
     return rc;
 }

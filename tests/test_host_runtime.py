@@ -19,7 +19,7 @@ def program(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("what", ["options", "auto", "host slots", "rule", "masks", "norms", "many"])
+@pytest.mark.parametrize("what", ["options", "auto", "host slots", "rule", "masks", "norms", "many", "no memory"])
 def test_handle(program, what):
     out = subprocess.run([program, what], capture_output=True, text=True, timeout=120)
     assert out.returncode == 0 and f"{what}: passed" in out.stdout, out.stdout + out.stderr
