@@ -27,11 +27,14 @@ PYCALL_STAMP = os.path.join(HERE, "_pycall.srchash")
 # -fhip-fp32-correctly-rounded-divide-sqrt: IEEE division for the /N
 # -fno-gpu-flush-denormals-to-zero: fp32 denormals are kept
 # packed-fp32 instructions are switched off for the device code
+# kernel arguments that are single words arrive in registers (as many as 16 hold) instead of by a load, whose round
+# trip precedes every address of a short kernel
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
     "-ffp-contract=off", "-fhip-fp32-correctly-rounded-divide-sqrt",
     "-fno-gpu-flush-denormals-to-zero", "-fno-fast-math",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    "-mllvm", "-amdgpu-kernarg-preload-count=16",
     "-Wall", "-Wno-unused-command-line-argument",
     "-I", os.path.join(ROOT, "include"), "-I", CSRC,
 ]
