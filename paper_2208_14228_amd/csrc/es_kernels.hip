@@ -1551,16 +1551,20 @@ struct BnGeom {
     BnGeom { C, HW, M, (M + 4095) >> 12, magic, shift_step & 0xFF, shift_step >> 8, 256 - (shift_step >> 8) * HW }
 
 // How four consecutive terms lie in memory.
-constexpr uint32_t kBnLongHW = 128;
 enum { kBnVector = 0, kBnLong = 1, kBnWrap = 2, kBnAny = 3 };
 // kBnVector: HW is a multiple of 4, so they are one 16-byte vector of one image.
-// kBnLong:   any HW >= kBnLongHW: one vector too, except where an image (or the channel) ends
-//            inside the wave's 256 terms; there four single loads.  Against kBnWrap 1.0 at 129 positions,
-//            1.07 at 169, 1.2-1.4 at 289 and 1.3-2.2 from 441 on, most where a channel is 16 blocks or
-//            more (four loads for one saturate the L1: 158x134x841 44.5 us by kBnWrap, 29.4 so).
-// kBnWrap:   4 <= HW, any remainder: the image can end once inside them; four single loads
-//            (neighbouring lanes share the lines, so the L1 serves three of the four).
+// kBnWrap:   4 <= HW, any remainder: the image can end once inside them.  One vector all the same; where the image ends, the
+//            values behind its end are loaded over it one by one (a vector and at most three loads of a few lanes each, for
+//            four loads of all lanes 16 bytes apart, which fetch every line four times: 32x2048x7x7 5.42 -> 3.86 us,
+//            200x64x11x11 7.74 -> 4.89, 158x134x13x13 7.74 -> 4.69, 256x512x3x3 4.89 -> 3.69; from two
+//            blocks of up to 9 positions on 0.9-1.27 of the time, 2000x256x7 7.8 and 9.9, so those keep single loads).
+// kBnLong:   long images, HW >= kBnLongHW: a plain vector if no image (nor the channel) ends inside the wave's 256 terms,
+//            else four single loads.  Fewer instructions where images seldom end.  kBnWrap over it, up to 25 blocks a
+//            channel: 0.65 at 289 positions, 0.74 at 625, 0.81-0.98 at 841, 0.77-0.97 at 961 to 1,369, 0.98-1.0 at 2,025, 0.97-1.02
+//            at 3,025; where workgroups share a channel, which then is read at the rate of the HBM, 1.06 at 841
+//            and 1.03 at 2,809.
 // kBnAny:    HW < 4.
+constexpr uint32_t kBnLongHW = 2560, kBnLongSharedHW = 128;
 
 // The 16 vectors of lane h of block `blk`, [tree lane h + 64 j][q].  Where a term lies beyond M
 // some value of the channel is loaded instead; bn_block_sum drops it.
@@ -1580,6 +1584,37 @@ __device__ __forceinline__ void bn_load(const float* __restrict__ x, const BnGeo
     uint32_t img = (uint32_t)(((uint64_t)m * g.magic) >> g.shift);
     uint32_t pos = m - img * g.HW;
     OFF off = first + image * img + (OFF)4 * pos;
+    // Single loads for all terms even so: the end of the last channel where it fills no vector (there may be nothing to read
+    // behind it), and longer channels of tiny images, where a wave's 256 terms end an image in every second or third lane.
+    const bool end = ch + 1 == g.C && (g.M & 3) != 0 && g.M >> 12 == blk;
+    const bool tiny = g.HW < 10 && g.M > 4096;
+    if (MODE == kBnWrap && !end && !tiny) {
+        uint32_t left = g.HW - 1 - pos;                 // values of the image behind the vector's first
+        const int at = 4 * (int)h;
+        const int ends = (int)(g.M - blk * 4096u);      // terms from the block's first to the channel's end
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            f4& e = t[i & 3][i >> 2];
+            if (256 * i >= ends) {                      // the whole wave is beyond M: no loads
+                e = f4{0.0f, 0.0f, 0.0f, 0.0f};
+            } else {
+                e = *reinterpret_cast<const f4_dword_aligned*>(xb + (at < ends - 256 * i ? off : first));
+                if (left < 3 && at < ends - 256 * i - 3) {
+                    OFF next = off + wrap;
+                    asm volatile("" : "+v"(next));      // the branches below need no address of their own
+                    e.w = *reinterpret_cast<const float*>(xb + next + 12);
+                    if (left < 2) {
+                        e.z = *reinterpret_cast<const float*>(xb + next + 8);
+                        if (left < 1) e.y = *reinterpret_cast<const float*>(xb + next + 4);
+                    }
+                }
+            }
+            off += step + (left < g.step_pos ? wrap : (OFF)0);
+            const uint32_t down = left - g.step_pos, over = down + g.HW;
+            left = down < over ? down : over;           // whichever has not passed 2^32
+        }
+        return;
+    }
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
         f4& e = t[i & 3][i >> 2];
@@ -2155,7 +2190,7 @@ hipError_t launch_bn_batch_stats_polls(hipStream_t s, const float* x, uint32_t B
         else launch_bn<MODE, uint64_t>(s, x, g, mean, var, part, polls);                \
     } while (0)
     if (HW % 4 == 0) ES_BN(kBnVector);
-    else if (HW >= kBnLongHW) ES_BN(kBnLong);
+    else if (HW >= (g.nblk > kBnWaves + kBnExtra ? kBnLongSharedHW : kBnLongHW)) ES_BN(kBnLong);
     else if (HW >= 4) ES_BN(kBnWrap);
     else ES_BN(kBnAny);
 #undef ES_BN
