@@ -762,12 +762,16 @@ __device__ __forceinline__ float tree16(float r)
     return add_shifted<1>(add_shifted<2>(add_shifted<4>(add_shifted<8>(r))));
 }
 
+__device__ __forceinline__ float tree32(float r)
+{
+    const auto rows = __builtin_amdgcn_permlane16_swap(__float_as_uint(r), __float_as_uint(r), false, false);
+    return tree16(__uint_as_float(rows[0]) + __uint_as_float(rows[1]));
+}
+
 __device__ __forceinline__ float tree64(float r)
 {
     const auto halves = __builtin_amdgcn_permlane32_swap(__float_as_uint(r), __float_as_uint(r), false, false);
-    r = __uint_as_float(halves[0]) + __uint_as_float(halves[1]);
-    const auto rows = __builtin_amdgcn_permlane16_swap(__float_as_uint(r), __float_as_uint(r), false, false);
-    return tree16(__uint_as_float(rows[0]) + __uint_as_float(rows[1]));
+    return tree32(__uint_as_float(halves[0]) + __uint_as_float(halves[1]));
 }
 
 __device__ __forceinline__ float lane0(float r)
@@ -1794,7 +1798,7 @@ void k_bn_channel(const float* __restrict__ x, float* __restrict__ mean, float* 
 // clearing launch, 38.7 -> 24.9), 144x51x53x53 30.3 -> 19.9, 64x512x56x56 (411 MB, several rounds of workgroups) 138
 // -> 74, 26x4x64x64 8.4 -> 6.6, 256x3x120x120 19.1 -> 13.4.
 constexpr uint32_t kBnPerWave = 3;
-constexpr uint32_t kBnHeld = 4 * (kBnPerWave + 1);      // blocks per workgroup
+constexpr uint32_t kBnHeld = kBnPerWave + 1;            // blocks per wave
 constexpr uint32_t kBnMostGroups = 64;                  // one per lane
 
 // How often a workgroup looks for the others' sums before it computes the missing ones.  A look takes 0.165 us, so it gives
@@ -1848,17 +1852,19 @@ __global__ __launch_bounds__(kBlock) void k_bn_clear(uint32_t* __restrict__ word
 
 // The sums part[0 .. n-1] of one workgroup's blocks, as the tree over its 256 / groups lanes combines them
 // (what further lanes and strides add is +0, and no sum is -0).
+template <uint32_t WAVES>
 __device__ __forceinline__ float bn_group_sum(const float* part, uint32_t n, uint32_t groups, uint32_t h)
 {
+    static_assert(WAVES * kBnHeld == 16 || WAVES * kBnHeld == 32, "the sums lie in one or two rows of lanes");
     const uint32_t lanes = 256 / groups;
     float r = 0.0f;
     if (h < lanes)
         for (uint32_t j = h; j < n; j += lanes) r = r + part[j];
-    return lane0(tree16(r));
+    return lane0(WAVES * kBnHeld == 16 ? tree16(r) : tree32(r));
 }
 
 // The sums of the workgroups in `missing` from memory into other[]; every wave of the workgroup calls it.
-template <bool SQDEV, int MODE, typename OFF>
+template <bool SQDEV, int MODE, typename OFF, uint32_t WAVES>
 __device__ __forceinline__ void bn_recompute(const float* __restrict__ x, const BnGeom& g, uint32_t ch, uint32_t groups,
                                              unsigned long long missing, float center, float* part, float* other,
                                              uint32_t w, uint32_t h)
@@ -1866,7 +1872,7 @@ __device__ __forceinline__ void bn_recompute(const float* __restrict__ x, const 
     for (; missing != 0; missing &= missing - 1) {
         const uint32_t from = __builtin_ctzll(missing);
         const uint32_t n = (g.nblk - from + groups - 1) / groups;
-        for (uint32_t j = w; j < n; j += 4) {
+        for (uint32_t j = w; j < n; j += WAVES) {
             f4 t[4][4];
             bn_load<MODE, OFF>(x, g, ch, from + j * groups, h, t);
             const float s = bn_block_sum<SQDEV>(t, from + j * groups, h, g.M, center);
@@ -1874,22 +1880,22 @@ __device__ __forceinline__ void bn_recompute(const float* __restrict__ x, const 
         }
         __syncthreads();
         if (w == 0) {
-            const float s = bn_group_sum(part, n, groups, h);
+            const float s = bn_group_sum<WAVES>(part, n, groups, h);
             if (h == 0) other[from] = s;
         }
         __syncthreads();
     }
 }
 
-template <int MODE, typename OFF>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2)))
+template <int MODE, typename OFF, uint32_t WAVES>
+__global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void k_bn_shared(const float* __restrict__ x, ES_BN_GEOM_PARAMS, uint32_t groups, uint32_t polls, BnSum* __restrict__ sums,
                  uint64_t tag, float* __restrict__ mean, float* __restrict__ var)
 {
     const BnGeom g = ES_BN_GEOM;
     const float fM = (float)M;
     extern __shared__ __align__(16) float park[];       // [wave][vector][lane], if any wave has a fourth block
-    __shared__ float part[2][kBnHeld];
+    __shared__ float part[2][WAVES * kBnHeld];
     __shared__ float other[kBnMostGroups];
     __shared__ unsigned long long s_missing;
     const uint32_t h = threadIdx.x & 63;
@@ -1910,14 +1916,14 @@ void k_bn_shared(const float* __restrict__ x, ES_BN_GEOM_PARAMS, uint32_t groups
     BnSum* first = sums + (uint64_t)ch * 2 * groups;
     BnSum* second = first + groups;
     f4 t[kBnPerWave][4][4];
-    const uint32_t parked = 4 * kBnPerWave + w;
+    const uint32_t parked = WAVES * kBnPerWave + w;
     constexpr uint32_t kLast = kBnPerWave - 1;
     // the parked block passes through the registers of the last one, behind the loads of the others
     if (parked < n) bn_load<MODE, OFF>(x, g, ch, block(parked), h, t[kLast]);
 #pragma unroll
     for (uint32_t k = 0; k < kLast; ++k) {
         __builtin_amdgcn_sched_barrier(0);              // one block's addresses at a time
-        load(4 * k + w, t[k]);
+        load(WAVES * k + w, t[k]);
     }
     __builtin_amdgcn_sched_barrier(0);
     if (parked < n) {
@@ -1927,18 +1933,18 @@ void k_bn_shared(const float* __restrict__ x, ES_BN_GEOM_PARAMS, uint32_t groups
         if (h == 0) part[0][parked] = s;
     }
     __builtin_amdgcn_sched_barrier(0);
-    load(4 * kLast + w, t[kLast]);
+    load(WAVES * kLast + w, t[kLast]);
 #pragma unroll
     for (uint32_t k = 0; k < kBnPerWave; ++k) {
         __builtin_amdgcn_sched_barrier(0);
-        if (4 * k + w < n) {
-            const float s = bn_block_sum<false>(t[k], block(4 * k + w), h, g.M, 0.0f);
-            if (h == 0) part[0][4 * k + w] = s;
+        if (WAVES * k + w < n) {
+            const float s = bn_block_sum<false>(t[k], block(WAVES * k + w), h, g.M, 0.0f);
+            if (h == 0) part[0][WAVES * k + w] = s;
         }
     }
     __syncthreads();
     if (w == 0) {
-        float sum = bn_group_sum(part[0], n, groups, h);
+        float sum = bn_group_sum<WAVES>(part[0], n, groups, h);
         bn_publish(first + grp, sum, tag, h);
         const unsigned long long missing = bn_collect(first, groups, tag, polls, h, h == grp, sum);
         if (h < groups) other[h] = sum;
@@ -1947,22 +1953,22 @@ void k_bn_shared(const float* __restrict__ x, ES_BN_GEOM_PARAMS, uint32_t groups
     __syncthreads();
     unsigned long long missing = uniform64(s_missing);
     if (missing != 0) {                                 // at the cost of this workgroup's own blocks, which are read again
-        bn_recompute<false, MODE, OFF>(x, g, ch, groups, missing, 0.0f, part[0], other, w, h);
+        bn_recompute<false, MODE, OFF, WAVES>(x, g, ch, groups, missing, 0.0f, part[0], other, w, h);
         uint32_t zero = 0;
         asm volatile("" : "+s"(zero));                  // no address is kept from above for this
 #pragma unroll
         for (uint32_t k = 0; k < kBnPerWave; ++k) {
             __builtin_amdgcn_sched_barrier(0);
-            load(4 * k + w + zero, t[k]);
+            load(WAVES * k + w + zero, t[k]);
         }
     }
     const float mu = lane0(tree64(h < groups ? other[h] : 0.0f)) / fM;
 #pragma unroll
     for (uint32_t k = 0; k < kBnPerWave; ++k) {
         __builtin_amdgcn_sched_barrier(0);
-        if (4 * k + w < n) {
-            const float s = bn_block_sum<true>(t[k], block(4 * k + w), h, g.M, mu);
-            if (h == 0) part[1][4 * k + w] = s;
+        if (WAVES * k + w < n) {
+            const float s = bn_block_sum<true>(t[k], block(WAVES * k + w), h, g.M, mu);
+            if (h == 0) part[1][WAVES * k + w] = s;
         }
     }
     __builtin_amdgcn_sched_barrier(0);
@@ -1974,17 +1980,17 @@ void k_bn_shared(const float* __restrict__ x, ES_BN_GEOM_PARAMS, uint32_t groups
     }
     __syncthreads();
     if (grp != 0) {
-        if (w == 0) bn_publish(second + grp, bn_group_sum(part[1], n, groups, h), tag, h);
+        if (w == 0) bn_publish(second + grp, bn_group_sum<WAVES>(part[1], n, groups, h), tag, h);
         return;
     }
     if (w == 0) {
-        float sum = bn_group_sum(part[1], n, groups, h);
+        float sum = bn_group_sum<WAVES>(part[1], n, groups, h);
         missing = bn_collect(second, groups, tag, polls, h, h == 0, sum);
         if (h < groups) other[h] = sum;
         if (h == 0) s_missing = missing;
     }
     __syncthreads();
-    bn_recompute<true, MODE, OFF>(x, g, ch, groups, uniform64(s_missing), mu, part[1], other, w, h);
+    bn_recompute<true, MODE, OFF, WAVES>(x, g, ch, groups, uniform64(s_missing), mu, part[1], other, w, h);
     const float va = lane0(tree64(h < groups ? other[h] : 0.0f)) / fM;
     if (threadIdx.x == 0) {
         mean[ch] = mu;
@@ -1992,15 +1998,15 @@ void k_bn_shared(const float* __restrict__ x, ES_BN_GEOM_PARAMS, uint32_t groups
     }
 }
 
-// The number of workgroups per channel: as few as hold it, more while they are all resident at once (two on each of
-// the 256 CUs; with fewer CUs to be had, some wait for the others in vain, see kBnPolls) and their sums fit the workspace of
+// The number of workgroups per channel: as few as hold it, more while they are all resident at once (eight waves on each
+// of the 256 CUs; with fewer CUs to be had, some wait for the others in vain, see kBnPolls) and their sums fit the workspace of
 // nblk floats per channel.
-static uint32_t bn_groups(uint32_t C, uint32_t nblk)
+static uint32_t bn_groups(uint32_t C, uint32_t nblk, uint32_t waves)
 {
     constexpr uint32_t floats = 2 * sizeof(BnSum) / sizeof(float);
     uint32_t n = 2;
-    while (n * kBnHeld < nblk) n *= 2;
-    while (n < kBnMostGroups && 2ull * n * C <= 512 && 2 * n * floats <= nblk) n *= 2;
+    while (n * waves * kBnHeld < nblk) n *= 2;
+    while (n < kBnMostGroups && 2ull * n * C <= 2048 / waves && 2 * n * floats <= nblk) n *= 2;
     return n;
 }
 
@@ -2021,19 +2027,19 @@ static uint64_t bn_tag()
 }
 
 // part: C * nblk floats, nblk >= 26; polls: see k_bn_shared
-template <int MODE, typename OFF>
+template <int MODE, typename OFF, uint32_t WAVES>
 static void launch_bn_shared(hipStream_t s, const float* x, const BnGeom& g, float* mean, float* var, float* part, uint32_t polls,
                              bool captured)
 {
-    const uint32_t n = bn_groups(g.C, g.nblk);
+    const uint32_t n = bn_groups(g.C, g.nblk, WAVES);
     BnSum* sums = reinterpret_cast<BnSum*>(part);
     if (captured) {
         const uint32_t clear = (uint32_t)(2ull * g.C * n * (sizeof(BnSum) / sizeof(uint32_t)));
         hipLaunchKernelGGL(k_bn_clear, dim3((clear + kBlock - 1) / kBlock), dim3(kBlock), 0, s, (uint32_t*)sums, clear);
     }
     const uint32_t most = (g.nblk + n - 1) / n;
-    const uint32_t parked = most > 4 * kBnPerWave ? most - 4 * kBnPerWave : 0;
-    hipLaunchKernelGGL((k_bn_shared<MODE, OFF>), dim3(g.C * n), dim3(kBlock), parked * 4096 * sizeof(float), s, x,
+    const uint32_t parked = most > WAVES * kBnPerWave ? most - WAVES * kBnPerWave : 0;
+    hipLaunchKernelGGL((k_bn_shared<MODE, OFF, WAVES>), dim3(g.C * n), dim3(64 * WAVES), parked * 4096 * sizeof(float), s, x,
                        ES_BN_GEOM_ARGS(g), n, polls, sums, bn_tag(), mean, var);
 }
 
@@ -2115,7 +2121,7 @@ template <int MODE>
 static bool bn_shares(const BnGeom& g, hipStream_t s, bool& captured)
 {
     if ((MODE != kBnVector && MODE != kBnLong) || g.HW < 16) return false;
-    if (g.nblk <= kBnWaves + kBnExtra || g.nblk > kBnMostGroups * kBnHeld) return false;
+    if (g.nblk <= kBnWaves + kBnExtra || g.nblk > kBnMostGroups * 4 * kBnHeld) return false;
     captured = stream_captured(s);
     return !captured || (uint64_t)g.C * g.nblk >= (g.nblk <= 64 ? 1000 : 1300);
 }
@@ -2142,8 +2148,20 @@ static void launch_bn(hipStream_t s, const float* x, const BnGeom& g, float* mea
         hipLaunchKernelGGL((k_bn_channel<MODE, OFF, kBnParked>), dim3(g.C), dim3(64 * kBnWaves),
                            (g.nblk - kBnWaves) * 4096 * sizeof(float), s, x, mean, var, ES_BN_GEOM_ARGS(g));
     } else if (bn_shares<MODE>(g, s, captured)) {
-        if constexpr (MODE == kBnVector || MODE == kBnLong)
-            launch_bn_shared<MODE, OFF>(s, x, g, mean, var, part, polls, captured);
+        if constexpr (MODE == kBnVector || MODE == kBnLong) {
+            // Little work (25 MB; 32-bit offsets therefore): workgroups of eight waves, half as many sums to wait for.  26x4x64x64
+            // 6.2 -> 5.6 us, 250x20x31x31 9.0 -> 7.9, 256x8x50x50 8.9 -> 8.2, 1x1x4190208 10.6 -> 9.6; beside a staging copy on another
+            // stream 22.9 -> 21.2, 28.7 -> 27.4, 28.3 -> 25.6.  The line lies where that copy's waves begin to keep a CU from being
+            // free for so large a workgroup: 1,664 blocks (26x64x64x64) 9.5 -> 9.1 us alone, but 25.3 -> 33.8 beside it, 5,100
+            // (144x51x53x53) 19.1 -> 17.6 and 39 -> 47.  (In several rounds eight waves lose alone, too: 64x512x56x56 72 -> 79.)
+            if constexpr (sizeof(OFF) == 4) {
+                if ((uint64_t)g.C * g.nblk <= 1500) {
+                    launch_bn_shared<MODE, OFF, 8>(s, x, g, mean, var, part, polls, captured);
+                    return;
+                }
+            }
+            launch_bn_shared<MODE, OFF, 4>(s, x, g, mean, var, part, polls, captured);
+        }
     } else if (g.nblk <= 256) {
         uint32_t n = 4;                                 // sums per channel: a quarter of the blocks' power of two
         while (4 * n < g.nblk) n *= 2;
