@@ -16,6 +16,7 @@
 #include <atomic>
 #include <chrono>
 #include <mutex>
+#include <tuple>
 #include <type_traits>
 
 namespace es {
@@ -29,6 +30,27 @@ typedef uint32_t u4 __attribute__((ext_vector_type(4)));
 // A base put together from registers: without the address space its loads would be flat ones.
 #define ES_GLOBAL_AS __attribute__((address_space(1)))
 #pragma clang diagnostic ignored "-Wold-style-cast"
+
+// A launch in one call of the runtime.  (kernel<<<>>> makes three and the query of the last error is a fourth: 2.48 us a launch
+// on three streams in turn, 2.28 so; a hipFunction_t in the place of the kernel's address saves nothing more.)
+template <typename... P, typename... A>
+static hipError_t run_kernel(void (*kernel)(P...), dim3 grid, dim3 block, uint32_t lds, hipStream_t s, const A&... a)
+{
+    std::tuple<P...> args(static_cast<P>(a)...);
+    const hipError_t e = std::apply(
+        [&](P&... v) {
+            void* at[] = {&v...};
+            return hipLaunchKernel(reinterpret_cast<const void*>(kernel), grid, block, at, lds, s);
+        },
+        args);
+    if (e != hipSuccess) (void)hipGetLastError();       // the caller has it: no later call is to find it
+    return e;
+}
+#define ES_RUN(kernel, grid, block, lds, s, ...)                                                                      \
+    do {                                                                                                              \
+        const hipError_t e__ = run_kernel(kernel, grid, block, lds, s, __VA_ARGS__);                                  \
+        if (e__ != hipSuccess) return e__;                                                                            \
+    } while (0)
 
 template <bool NT>
 __device__ __forceinline__ f4 ld4(const float* p)
@@ -344,7 +366,7 @@ static hipError_t launch_reduce_unb(hipStream_t s, const Tile* tiles, uint32_t n
     const bool sgd = p != nullptr;
     dim3 grid(n_tiles), block(kReduceBlock);
 #define ES_LAUNCH(NTV, SGDV) \
-    hipLaunchKernelGGL((k_ring_reduce<U, NB, NTV, SGDV>), grid, block, lds_pad, s, tiles, slots, N, avg, p, v, lr, mu)
+    ES_RUN((k_ring_reduce<U, NB, NTV, SGDV>), grid, block, lds_pad, s, tiles, slots, N, avg, p, v, lr, mu)
     if (!sgd) {
         switch (nt & 3) {
         case 0: ES_LAUNCH(0, false); break;
@@ -361,7 +383,7 @@ static hipError_t launch_reduce_unb(hipStream_t s, const Tile* tiles, uint32_t n
         }
     }
 #undef ES_LAUNCH
-    return hipGetLastError();
+    return hipSuccess;
 }
 
 template <int U>
@@ -388,7 +410,7 @@ static hipError_t launch_reduce_big(hipStream_t s, const Tile* tiles, uint32_t n
     const bool sgd = p != nullptr;
     dim3 grid(n_tiles), block(kReduceBlock);
 #define ES_LAUNCH(NTV, SGDV) \
-    hipLaunchKernelGGL((k_ring_reduce_big<UB, NBB, NTV, SGDV>), grid, block, 0, s, tiles, n_big, slots, N, avg, p, v, lr, mu)
+    ES_RUN((k_ring_reduce_big<UB, NBB, NTV, SGDV>), grid, block, 0, s, tiles, n_big, slots, N, avg, p, v, lr, mu)
     if (!sgd) {
         switch (nt & 3) {
         case 0: ES_LAUNCH(0, false); break;
@@ -405,7 +427,7 @@ static hipError_t launch_reduce_big(hipStream_t s, const Tile* tiles, uint32_t n
         }
     }
 #undef ES_LAUNCH
-    return hipGetLastError();
+    return hipSuccess;
 }
 
 template <int UB>
@@ -545,7 +567,7 @@ static hipError_t launch_reduce_wave(hipStream_t s, const Tile* tiles, uint32_t 
     constexpr uint32_t per = kReduceBlock / 64;
     const dim3 grid((uint32_t)(((uint64_t)n_tiles + per - 1) / per)), block(kReduceBlock);
 #define ES_LAUNCH(NTV, SGDV)                                                                                      \
-    hipLaunchKernelGGL((k_ring_reduce_wave<W, NB, NTV, SGDV>), grid, block, (uint32_t)sh.wave_pad_kib << 10, s, tiles, \
+    ES_RUN((k_ring_reduce_wave<W, NB, NTV, SGDV>), grid, block, (uint32_t)sh.wave_pad_kib << 10, s, tiles, \
                        n_tiles, slots, N, avg, p, v, lr, mu)
     if (p) {
         if (sh.nontemporal_pv) ES_LAUNCH(3, true);
@@ -555,7 +577,7 @@ static hipError_t launch_reduce_wave(hipStream_t s, const Tile* tiles, uint32_t 
         else ES_LAUNCH(1, false);
     }
 #undef ES_LAUNCH
-    return hipGetLastError();
+    return hipSuccess;
 }
 
 static hipError_t launch_reduce_wave_any(hipStream_t s, const Tile* tiles, uint32_t n_tiles, const float* const* slots,
@@ -608,8 +630,8 @@ __global__ void k_patch_slots(const float** table, const InPlace patch)
 hipError_t launch_patch_slots(hipStream_t s, const float** table, const InPlace& patch)
 {
     if (patch.n == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_patch_slots, dim3(1), dim3(64), 0, s, table, patch);
-    return hipGetLastError();
+    ES_RUN(k_patch_slots, dim3(1), dim3(64), 0, s, table, patch);
+    return hipSuccess;
 }
 
 // ---------------------------------------------------------------------------
@@ -665,10 +687,10 @@ hipError_t launch_sgd(hipStream_t s, float* p, float* v, const float* g, uint64_
     uint64_t blocks = (nvec + kBlock * kSgdU - 1) / (kBlock * kSgdU);
     if (blocks == 0) blocks = 1;
     if (stream_pv)
-        hipLaunchKernelGGL(k_sgd<true>, dim3((uint32_t)blocks), dim3(kBlock), kAuxLdsPad, s, p, v, g, n, lr, mu);
+        ES_RUN(k_sgd<true>, dim3((uint32_t)blocks), dim3(kBlock), kAuxLdsPad, s, p, v, g, n, lr, mu);
     else
-        hipLaunchKernelGGL(k_sgd<false>, dim3((uint32_t)blocks), dim3(kBlock), kAuxLdsPad, s, p, v, g, n, lr, mu);
-    return hipGetLastError();
+        ES_RUN(k_sgd<false>, dim3((uint32_t)blocks), dim3(kBlock), kAuxLdsPad, s, p, v, g, n, lr, mu);
+    return hipSuccess;
 }
 
 // The same update with the gradient clipped by its global norm first: every lane forms
@@ -729,12 +751,12 @@ hipError_t launch_sgd_clip(hipStream_t s, float* p, float* v, const float* g, ui
     uint64_t blocks = (nvec + kBlock * kSgdU - 1) / (kBlock * kSgdU);
     if (blocks == 0) blocks = 1;
     if (stream_pv)
-        hipLaunchKernelGGL(k_sgd_clip<true>, dim3((uint32_t)blocks), dim3(kBlock), kAuxLdsPad, s, p, v, g, n, norm2,
+        ES_RUN(k_sgd_clip<true>, dim3((uint32_t)blocks), dim3(kBlock), kAuxLdsPad, s, p, v, g, n, norm2,
                            max_norm, eps, lr, mu);
     else
-        hipLaunchKernelGGL(k_sgd_clip<false>, dim3((uint32_t)blocks), dim3(kBlock), kAuxLdsPad, s, p, v, g, n, norm2,
+        ES_RUN(k_sgd_clip<false>, dim3((uint32_t)blocks), dim3(kBlock), kAuxLdsPad, s, p, v, g, n, norm2,
                            max_norm, eps, lr, mu);
-    return hipGetLastError();
+    return hipSuccess;
 }
 
 // ---------------------------------------------------------------------------
@@ -939,9 +961,9 @@ static hipError_t launch_sq_pair(hipStream_t s, const float* x, uint64_t n, floa
 {
     const uint64_t nblk = (n + 4095) / 4096;
     if (nblk)
-        hipLaunchKernelGGL(k_sq_partials<READ>, dim3((uint32_t)((nblk + 3) / 4)), dim3(kBlock), kAuxLdsPad, s, x, n, nblk, part);
-    hipLaunchKernelGGL(k_sq_final, dim3(1), dim3(kBlock), 0, s, part, nblk, out);
-    return hipGetLastError();
+        ES_RUN(k_sq_partials<READ>, dim3((uint32_t)((nblk + 3) / 4)), dim3(kBlock), kAuxLdsPad, s, x, n, nblk, part);
+    ES_RUN(k_sq_final, dim3(1), dim3(kBlock), 0, s, part, nblk, out);
+    return hipSuccess;
 }
 
 hipError_t launch_sq_norm(hipStream_t s, const float* x, uint64_t n, float* part, float* out)
@@ -1027,8 +1049,8 @@ hipError_t launch_sq_norm_counted(hipStream_t s, const float* x, uint64_t n, flo
     static_assert(kCountedBlocks <= kNormKept, "k_sq_norm reads every block without the hint");
     if (nblk == 0 || nblk > kCountedBlocks) return hipErrorInvalidValue;
     const uint32_t groups = (uint32_t)((nblk + 3) / 4);
-    hipLaunchKernelGGL(k_sq_norm, dim3(groups), dim3(kBlock), 0, s, x, n, (uint32_t)nblk, part, out, arrivals, groups);
-    return hipGetLastError();
+    ES_RUN(k_sq_norm, dim3(groups), dim3(kBlock), 0, s, x, n, (uint32_t)nblk, part, out, arrivals, groups);
+    return hipSuccess;
 }
 
 // Block partials of the allocation-free norm: one array per GPU, part of the code
@@ -1127,10 +1149,10 @@ static hipError_t launch_copy(hipStream_t s, float* dst, const float* src, uint6
     uint64_t blocks = ((n >> 2) + bs - 1) / bs;
     if (blocks == 0) blocks = 1;
     if (bs == kCopyBlockShort)
-        hipLaunchKernelGGL(k_copy_f4<kCopyBlockShort>, dim3((uint32_t)blocks), dim3(bs), 0, s, dst, src, n);
+        ES_RUN(k_copy_f4<kCopyBlockShort>, dim3((uint32_t)blocks), dim3(bs), 0, s, dst, src, n);
     else
-        hipLaunchKernelGGL(k_copy_f4<kCopyBlock>, dim3((uint32_t)blocks), dim3(bs), 0, s, dst, src, n);
-    return hipGetLastError();
+        ES_RUN(k_copy_f4<kCopyBlock>, dim3((uint32_t)blocks), dim3(bs), 0, s, dst, src, n);
+    return hipSuccess;
 }
 
 hipError_t launch_copy_f32(hipStream_t s, float* dst, const float* src, uint64_t n)
@@ -1162,10 +1184,10 @@ hipError_t launch_copy_runs(hipStream_t s, const CopyRuns& runs)
     const uint32_t blocks = runs.first_block[runs.n_runs];
     if (blocks == 0) return hipSuccess;
     if (runs.block == kCopyBlockShort)
-        hipLaunchKernelGGL(k_copy_runs<kCopyBlockShort>, dim3(blocks), dim3(kCopyBlockShort), 0, s, runs);
+        ES_RUN(k_copy_runs<kCopyBlockShort>, dim3(blocks), dim3(kCopyBlockShort), 0, s, runs);
     else
-        hipLaunchKernelGGL(k_copy_runs<kCopyBlock>, dim3(blocks), dim3(kCopyBlock), 0, s, runs);
-    return hipGetLastError();
+        ES_RUN(k_copy_runs<kCopyBlock>, dim3(blocks), dim3(kCopyBlock), 0, s, runs);
+    return hipSuccess;
 }
 
 __global__ __launch_bounds__(kBlock) void k_copy_bytes(uint8_t* __restrict__ dst,
@@ -1181,8 +1203,8 @@ hipError_t launch_copy_bytes(hipStream_t s, uint8_t* dst, const uint8_t* src, ui
     if (n == 0) return hipSuccess;
     const uint64_t n16 = n >> 4;
     const uint64_t blocks = (n16 + kBlock - 1) / kBlock;
-    hipLaunchKernelGGL(k_copy_bytes, dim3((uint32_t)blocks), dim3(kBlock), 0, s, dst, src, n16);
-    return hipGetLastError();
+    ES_RUN(k_copy_bytes, dim3((uint32_t)blocks), dim3(kBlock), 0, s, dst, src, n16);
+    return hipSuccess;
 }
 
 // ---------------------------------------------------------------------------
@@ -1267,7 +1289,7 @@ hipError_t launch_est_boundary(hipStream_t s, const CopyRuns& runs, const Piece*
     if (n_pieces + copy_blocks == 0) return hipSuccess;
     const dim3 grid(n_pieces + copy_blocks), block(runs.block);
 #define ES_BOUNDARY(BS, RUNS, R) \
-    hipLaunchKernelGGL((k_est_boundary<BS, RUNS>), grid, block, 0, s, R, pieces, n_pieces, slot_a, slot_b, (int)dir)
+    ES_RUN((k_est_boundary<BS, RUNS>), grid, block, 0, s, R, pieces, n_pieces, slot_a, slot_b, (int)dir)
     if (runs.n_runs <= 1) {
         const CopyRun one{runs.dst[0], runs.src[0], runs.n[0]};   // n_runs = 0: no workgroup gets that far
         if (runs.block == kCopyBlockShort) ES_BOUNDARY(kCopyBlockShort, CopyRun, one);
@@ -1277,15 +1299,15 @@ hipError_t launch_est_boundary(hipStream_t s, const CopyRuns& runs, const Piece*
         else ES_BOUNDARY(kCopyBlock, CopyRuns, runs);
     }
 #undef ES_BOUNDARY
-    return hipGetLastError();
+    return hipSuccess;
 }
 
 hipError_t launch_ctx(hipStream_t s, const Piece* pieces, uint32_t n_pieces, uint8_t* slot_a,
                       const uint8_t* slot_b, CtxDir dir)
 {
     if (n_pieces == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_ctx, dim3(n_pieces), dim3(kBlock), 0, s, pieces, slot_a, slot_b, (int)dir);
-    return hipGetLastError();
+    ES_RUN(k_ctx, dim3(n_pieces), dim3(kBlock), 0, s, pieces, slot_a, slot_b, (int)dir);
+    return hipSuccess;
 }
 
 // ---------------------------------------------------------------------------
@@ -1493,9 +1515,9 @@ hipError_t launch_dropout_mask(hipStream_t s, uint64_t* state, uint8_t* mask, ui
     if (n == 0) return hipSuccess;
     if (n > kShortMask) return hipErrorInvalidValue;
     const uint32_t block = (uint32_t)(((n + 15) / 16 + 63) / 64 * 64);
-    hipLaunchKernelGGL(k_dropout_mask_short, dim3(1), dim3(block), 0, s, state, mask, n, (1ull << 32) - threshold,
+    ES_RUN(k_dropout_mask_short, dim3(1), dim3(block), 0, s, state, mask, n, (1ull << 32) - threshold,
                        ((uintptr_t)mask & 15) == 0);
-    return hipGetLastError();
+    return hipSuccess;
 }
 
 static uint32_t mask_groups(uint64_t n)
@@ -1508,12 +1530,10 @@ hipError_t launch_dropout_mask_captured(hipStream_t s, uint64_t* state, uint8_t*
 {
     if (n == 0) return hipSuccess;
     const uint32_t groups = mask_groups(n);
-    hipLaunchKernelGGL(k_dropout_mask<false>, dim3(groups), dim3(kBlock), 0, s, state, mask, n, (1ull << 32) - threshold,
+    ES_RUN(k_dropout_mask<false>, dim3(groups), dim3(kBlock), 0, s, state, mask, n, (1ull << 32) - threshold,
                        ((uintptr_t)mask & 15) == 0, nullptr, groups);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_philox_advance, dim3(1), dim3(64), 0, s, state, (n + 3) / 4);
-    return hipGetLastError();
+    ES_RUN(k_philox_advance, dim3(1), dim3(64), 0, s, state, (n + 3) / 4);
+    return hipSuccess;
 }
 
 hipError_t launch_dropout_mask_long(hipStream_t s, uint64_t* state, uint8_t* mask, uint64_t n, uint64_t threshold,
@@ -1521,9 +1541,9 @@ hipError_t launch_dropout_mask_long(hipStream_t s, uint64_t* state, uint8_t* mas
 {
     if (n == 0) return hipSuccess;
     const uint32_t groups = mask_groups(n);
-    hipLaunchKernelGGL(k_dropout_mask<true>, dim3(groups), dim3(kBlock), 0, s, state, mask, n, (1ull << 32) - threshold,
+    ES_RUN(k_dropout_mask<true>, dim3(groups), dim3(kBlock), 0, s, state, mask, n, (1ull << 32) - threshold,
                        ((uintptr_t)mask & 15) == 0, arrivals, groups);
-    return hipGetLastError();
+    return hipSuccess;
 }
 
 // ---------------------------------------------------------------------------
@@ -2028,19 +2048,20 @@ static uint64_t bn_tag()
 
 // part: C * nblk floats, nblk >= 26; polls: see k_bn_shared
 template <int MODE, typename OFF, uint32_t WAVES>
-static void launch_bn_shared(hipStream_t s, const float* x, const BnGeom& g, float* mean, float* var, float* part, uint32_t polls,
+static hipError_t launch_bn_shared(hipStream_t s, const float* x, const BnGeom& g, float* mean, float* var, float* part, uint32_t polls,
                              bool captured)
 {
     const uint32_t n = bn_groups(g.C, g.nblk, WAVES);
     BnSum* sums = reinterpret_cast<BnSum*>(part);
     if (captured) {
         const uint32_t clear = (uint32_t)(2ull * g.C * n * (sizeof(BnSum) / sizeof(uint32_t)));
-        hipLaunchKernelGGL(k_bn_clear, dim3((clear + kBlock - 1) / kBlock), dim3(kBlock), 0, s, (uint32_t*)sums, clear);
+        ES_RUN(k_bn_clear, dim3((clear + kBlock - 1) / kBlock), dim3(kBlock), 0, s, (uint32_t*)sums, clear);
     }
     const uint32_t most = (g.nblk + n - 1) / n;
     const uint32_t parked = most > WAVES * kBnPerWave ? most - WAVES * kBnPerWave : 0;
-    hipLaunchKernelGGL((k_bn_shared<MODE, OFF, WAVES>), dim3(g.C * n), dim3(64 * WAVES), parked * 4096 * sizeof(float), s, x,
+    ES_RUN((k_bn_shared<MODE, OFF, WAVES>), dim3(g.C * n), dim3(64 * WAVES), parked * 4096 * sizeof(float), s, x,
                        ES_BN_GEOM_ARGS(g), n, polls, sums, bn_tag(), mean, var);
+    return hipSuccess;
 }
 
 // Longer channels, short images and little captured work read x twice (second pass over blocks in reverse:
@@ -2127,7 +2148,7 @@ static bool bn_shares(const BnGeom& g, hipStream_t s, bool& captured)
 }
 
 template <int MODE, typename OFF>
-static void launch_bn(hipStream_t s, const float* x, const BnGeom& g, float* mean, float* var, float* part, uint32_t polls)
+static hipError_t launch_bn(hipStream_t s, const float* x, const BnGeom& g, float* mean, float* var, float* part, uint32_t polls)
 {
     const float fM = (float)g.M;
     // Few channels of many tiny images (a line of memory holds an image's few values of a channel, the rest
@@ -2140,12 +2161,12 @@ static void launch_bn(hipStream_t s, const float* x, const BnGeom& g, float* mea
     const bool spread = g.HW < 8 ? g.nblk >= 8 && g.C <= (g.HW == 4 ? 255 : 128) : g.HW < 16 && g.nblk > 12 && g.C <= 64;
     bool captured = false;
     if (g.nblk == 1) {                                  // at most 65,535 x 4096 values: 32-bit offsets always
-        hipLaunchKernelGGL((k_bn_channel<MODE, uint32_t, kBnSingle>), dim3((g.C + kBnSingles - 1) / kBnSingles),
+        ES_RUN((k_bn_channel<MODE, uint32_t, kBnSingle>), dim3((g.C + kBnSingles - 1) / kBnSingles),
                            dim3(64 * kBnSingles), 0, s, x, mean, var, ES_BN_GEOM_ARGS(g));
     } else if (g.nblk <= kBnWaves && !spread) {
-        hipLaunchKernelGGL((k_bn_channel<MODE, OFF, kBnRegs>), dim3(g.C), dim3(64 * g.nblk), 0, s, x, mean, var, ES_BN_GEOM_ARGS(g));
+        ES_RUN((k_bn_channel<MODE, OFF, kBnRegs>), dim3(g.C), dim3(64 * g.nblk), 0, s, x, mean, var, ES_BN_GEOM_ARGS(g));
     } else if (g.nblk <= kBnWaves + kBnExtra && !spread) {
-        hipLaunchKernelGGL((k_bn_channel<MODE, OFF, kBnParked>), dim3(g.C), dim3(64 * kBnWaves),
+        ES_RUN((k_bn_channel<MODE, OFF, kBnParked>), dim3(g.C), dim3(64 * kBnWaves),
                            (g.nblk - kBnWaves) * 4096 * sizeof(float), s, x, mean, var, ES_BN_GEOM_ARGS(g));
     } else if (bn_shares<MODE>(g, s, captured)) {
         if constexpr (MODE == kBnVector || MODE == kBnLong) {
@@ -2155,28 +2176,27 @@ static void launch_bn(hipStream_t s, const float* x, const BnGeom& g, float* mea
             // free for so large a workgroup: 1,664 blocks (26x64x64x64) 9.5 -> 9.1 us alone, but 25.3 -> 33.8 beside it, 5,100
             // (144x51x53x53) 19.1 -> 17.6 and 39 -> 47.  (In several rounds eight waves lose alone, too: 64x512x56x56 72 -> 79.)
             if constexpr (sizeof(OFF) == 4) {
-                if ((uint64_t)g.C * g.nblk <= 1500) {
-                    launch_bn_shared<MODE, OFF, 8>(s, x, g, mean, var, part, polls, captured);
-                    return;
-                }
+                if ((uint64_t)g.C * g.nblk <= 1500)
+                    return launch_bn_shared<MODE, OFF, 8>(s, x, g, mean, var, part, polls, captured);
             }
-            launch_bn_shared<MODE, OFF, 4>(s, x, g, mean, var, part, polls, captured);
+            return launch_bn_shared<MODE, OFF, 4>(s, x, g, mean, var, part, polls, captured);
         }
     } else if (g.nblk <= 256) {
         uint32_t n = 4;                                 // sums per channel: a quarter of the blocks' power of two
         while (4 * n < g.nblk) n *= 2;
         const dim3 grid(n, g.C);
-        hipLaunchKernelGGL((k_bn_partials<false, true, MODE, OFF>), grid, dim3(kBlock), 0, s, x, ES_BN_GEOM_ARGS(g), grid.x, mean, part);
-        hipLaunchKernelGGL((k_bn_partials<true, true, MODE, OFF>), grid, dim3(kBlock), 0, s, x, ES_BN_GEOM_ARGS(g), grid.x, mean, part);
-        hipLaunchKernelGGL(k_bn_final_wave, dim3((g.C + 3) / 4), dim3(kBlock), 0, s, part + (uint64_t)g.C * n, n, g.C,
+        ES_RUN((k_bn_partials<false, true, MODE, OFF>), grid, dim3(kBlock), 0, s, x, ES_BN_GEOM_ARGS(g), grid.x, mean, part);
+        ES_RUN((k_bn_partials<true, true, MODE, OFF>), grid, dim3(kBlock), 0, s, x, ES_BN_GEOM_ARGS(g), grid.x, mean, part);
+        ES_RUN(k_bn_final_wave, dim3((g.C + 3) / 4), dim3(kBlock), 0, s, part + (uint64_t)g.C * n, n, g.C,
                            fM, var);
     } else {
         const dim3 grid((g.nblk + 3) / 4, g.C);
-        hipLaunchKernelGGL((k_bn_partials<false, false, MODE, OFF>), grid, dim3(kBlock), 0, s, x, ES_BN_GEOM_ARGS(g), grid.x, mean, part);
-        hipLaunchKernelGGL(k_bn_final, dim3(g.C), dim3(kBlock), 0, s, part, g.nblk, fM, mean);
-        hipLaunchKernelGGL((k_bn_partials<true, false, MODE, OFF>), grid, dim3(kBlock), 0, s, x, ES_BN_GEOM_ARGS(g), grid.x, mean, part);
-        hipLaunchKernelGGL(k_bn_final, dim3(g.C), dim3(kBlock), 0, s, part, g.nblk, fM, var);
+        ES_RUN((k_bn_partials<false, false, MODE, OFF>), grid, dim3(kBlock), 0, s, x, ES_BN_GEOM_ARGS(g), grid.x, mean, part);
+        ES_RUN(k_bn_final, dim3(g.C), dim3(kBlock), 0, s, part, g.nblk, fM, mean);
+        ES_RUN((k_bn_partials<true, false, MODE, OFF>), grid, dim3(kBlock), 0, s, x, ES_BN_GEOM_ARGS(g), grid.x, mean, part);
+        ES_RUN(k_bn_final, dim3(g.C), dim3(kBlock), 0, s, part, g.nblk, fM, var);
     }
+    return hipSuccess;
 }
 
 hipError_t launch_bn_batch_stats(hipStream_t s, const float* x, uint32_t B, uint32_t C, uint32_t HW,
@@ -2204,15 +2224,15 @@ hipError_t launch_bn_batch_stats_polls(hipStream_t s, const float* x, uint32_t B
     const bool small = (uint64_t)B * C * HW * sizeof(float) <= 0xFFFFFFFFull;
 #define ES_BN(MODE)                                                              \
     do {                                                                         \
-        if (small) launch_bn<MODE, uint32_t>(s, x, g, mean, var, part, polls);          \
-        else launch_bn<MODE, uint64_t>(s, x, g, mean, var, part, polls);                \
+        if (small) return launch_bn<MODE, uint32_t>(s, x, g, mean, var, part, polls);   \
+        return launch_bn<MODE, uint64_t>(s, x, g, mean, var, part, polls);              \
     } while (0)
     if (HW % 4 == 0) ES_BN(kBnVector);
     else if (HW >= (g.nblk > kBnWaves + kBnExtra ? kBnLongSharedHW : kBnLongHW)) ES_BN(kBnLong);
     else if (HW >= 4) ES_BN(kBnWrap);
     else ES_BN(kBnAny);
 #undef ES_BN
-    return hipGetLastError();
+    return hipSuccess;
 }
 
 }  // namespace es
