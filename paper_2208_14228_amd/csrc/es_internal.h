@@ -262,4 +262,12 @@ inline bool stream_captured(hipStream_t s)
     return true;
 }
 
+// What the runtime knows of a stream without enqueuing on it.  Set by the file that holds the kernels when the library is
+// loaded; null in a program that has the host side alone, whose streams are always handed over by events.
+struct StreamProbe {
+    bool (*idle)(hipStream_t);          // everything that was enqueued has finished: what follows on any stream sees it
+    bool (*done)(hipEvent_t);           // the event has been reached
+};
+extern StreamProbe stream_probe;
+
 }  // namespace es

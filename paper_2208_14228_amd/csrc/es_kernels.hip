@@ -2235,4 +2235,46 @@ hipError_t launch_bn_batch_stats_polls(hipStream_t s, const float* x, uint32_t B
     return hipSuccess;
 }
 
+// ---------------------------------------------------------------------------
+// What the runtime knows of a stream (StreamProbe).
+// ---------------------------------------------------------------------------
+namespace {
+
+// A query is not allowed while another thread captures in the global mode, unless this thread says that it does not mind.
+struct RelaxedCapture {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    bool set = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+    ~RelaxedCapture()
+    {
+        if (set) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    }
+};
+
+bool answered_yes(hipError_t e)
+{
+    if (e == hipSuccess) return true;
+    (void)hipGetLastError();
+    return false;
+}
+
+// Only of streams that are not ordered with the null stream: an idle one of the others may still have to wait for it.
+bool stream_idle(hipStream_t s)
+{
+    unsigned flags = 0;
+    if (reinterpret_cast<uintptr_t>(s) <= 2) return false;                    // the null stream and the named ones
+    if (!answered_yes(hipStreamGetFlags(s, &flags)) || !(flags & hipStreamNonBlocking) || stream_captured(s)) return false;
+    RelaxedCapture relaxed;
+    return relaxed.set && answered_yes(hipStreamQuery(s));
+}
+
+bool event_done(hipEvent_t e)
+{
+    RelaxedCapture relaxed;
+    return relaxed.set && answered_yes(hipEventQuery(e));
+}
+
+const bool g_probe_set = (stream_probe = StreamProbe{stream_idle, event_done}, true);
+
+}  // namespace
+
 }  // namespace es
