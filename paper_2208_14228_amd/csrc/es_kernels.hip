@@ -1732,8 +1732,8 @@ __device__ __forceinline__ float bn_block_sum(const f4 (&t)[4][4], uint32_t blk,
 // 0..63 of the tree, and its strides 128 and 64 only add +0.  With one block per channel a
 // workgroup takes one channel per wave instead and needs no LDS.
 // Bound by the launch and one round trip to memory for small layers, by HBM for large ones.
-// Measured against two passes of two launches each: 32x2048x7x7 27.2 -> 7.1 us, 32x512x28x28
-// 23.8 -> 11.0 us, 32x256x56x56 (25 blocks, parked) 46.7 -> 19.9 us = 5.2 TB/s.
+// Two passes of two launches each, and this as it is now: 32x2048x7x7 27.2 and 3.9 us, 32x512x28x28
+// 23.8 and 8.9, 32x256x56x56 (25 blocks, parked) 46.7 and 18.0 = 5.7 TB/s.
 constexpr uint32_t kBnWaves = 16;                       // 1024 lanes: the registers of a CU hold 16 blocks
 constexpr uint32_t kBnExtra = 9;                        // 16 KiB each: what fits in 160 KiB beside the partials
 constexpr uint32_t kBnSingles = 4;                      // channels per workgroup when a channel is one block
@@ -1813,10 +1813,10 @@ void k_bn_channel(const float* __restrict__ x, float* __restrict__ mean, float* 
 // back with every replay, has that.)  Nothing depends on all workgroups of a channel being resident at once: one that has
 // looked for the others' sums `polls` times computes them from memory and goes on.
 //
-// Bound by reading x, then by one exchange of sums (2 us) and the second pass over what is held (3 us of three
-// operations per value).  Against reading x twice in three launches: 32x64x112x112 37.6 -> 21.7 us (captured, with the
-// clearing launch, 38.7 -> 24.9), 144x51x53x53 30.3 -> 19.9, 64x512x56x56 (411 MB, several rounds of workgroups) 138
-// -> 74, 26x4x64x64 8.4 -> 6.6, 256x3x120x120 19.1 -> 13.4.
+// Bound by reading x (6.4 TB/s), then by the second pass over what is held (three operations per value: 1.9 of 20.7 us on
+// 32x64x112x112) and the exchange of sums (0.8 us of them).  Reading x twice in three launches, and this: 32x64x112x112 37.6 and
+// 20.6 us (captured, with the clearing launch, 38.7 and 24.5), 144x51x53x53 30.3 and 18.9, 64x512x56x56 (411 MB, several rounds of
+// workgroups) 138 and 72, 26x4x64x64 8.4 and 5.6, 256x3x120x120 19.1 and 12.9.
 constexpr uint32_t kBnPerWave = 3;
 constexpr uint32_t kBnHeld = kBnPerWave + 1;            // blocks per wave
 constexpr uint32_t kBnMostGroups = 64;                  // one per lane
@@ -2154,11 +2154,15 @@ static hipError_t launch_bn(hipStream_t s, const float* x, const BnGeom& g, floa
     // Few channels of many tiny images (a line of memory holds an image's few values of a channel, the rest
     // belongs to others): a channel's loads queue in the L1 of the one CU that has it, and most CUs have
     // none.  Three launches spread a channel over several workgroups instead.  16 blocks in one launch and in
-    // three: 16 channels of 1, 3, 4 and 5 positions 57 / 31, 64 / 30, 25 / 15.4 and 38 / 16.8 us, 64 channels 74 / 43,
-    // 78 / 37, 35 / 20 and 60 / 20.7; 64 channels of 8 and 12 positions 20 / 18 and 21 / 17.  With 160 channels
-    // one launch is ahead again (1 and 3 positions 90 / 127 and 83 / 101 us) except for vectors of one image each
-    // (4 positions 51 / 42), and from 16 positions on it is everywhere as fast as two launches per pass.
-    const bool spread = g.HW < 8 ? g.nblk >= 8 && g.C <= (g.HW == 4 ? 255 : 128) : g.HW < 16 && g.nblk > 12 && g.C <= 64;
+    // three: 16 channels of 1, 3, 5 and 7 positions 59 / 31, 64 / 30, 36 / 16 and 27 / 16 us, 64 channels 72 / 44, 63 / 38, 33 / 19 and
+    // 24 / 16; 160 channels take one launch.  Vectors of one image each (4 positions) need
+    // it least: 40 channels of 10, 12 and 16 blocks 16.0 / 13.3, 18.8 / 13.5 and 24.3 / 15.9 us, 64 channels of 8, 10, 14 and 16 blocks
+    // 6.3 / 12.9, 7.6 / 15.9, 16.2 / 18.4 and 21.9 / 19.6, 96 channels of 10 and 25 blocks 14.9 / 23.0 and 35 / 37, 160 of 16 24.9 / 43.4.  8 and 12
+    // positions: 16 blocks, 64 channels 13.8 / 17.3 and 13.0 / 16.1, but 24 blocks 21 / 17 and 18.5 / 13.9, 16 channels of 12
+    // positions 15 / 10; from 16 positions on one launch is everywhere as fast as two per pass.
+    const bool spread = g.HW == 4  ? (g.nblk > 14 ? g.C <= 64 : g.nblk > 9 && g.C <= 48)
+                        : g.HW < 8 ? g.nblk >= 8 && g.C <= 128
+                                   : g.HW < 16 && g.nblk > 12 && g.C <= 64;
     bool captured = false;
     if (g.nblk == 1) {                                  // at most 65,535 x 4096 values: 32-bit offsets always
         ES_RUN((k_bn_channel<MODE, uint32_t, kBnSingle>), dim3((g.C + kBnSingles - 1) / kBnSingles),

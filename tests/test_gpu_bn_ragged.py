@@ -27,3 +27,13 @@ def test_every_end_of_a_ragged_image(hw, images):
                 got_m, got_v = gpu_bn(x, shift)
                 assert np.array_equal(bits(got_m), bits(want_m)), ("mean", n, c, shift)
                 assert np.array_equal(bits(got_v), bits(want_v)), ("var", n, c, shift)
+
+
+@pytest.mark.parametrize("blocks,c", [(9, 48), (10, 48), (10, 49), (14, 48), (14, 49), (15, 64), (15, 65), (25, 64)])
+def test_images_of_one_vector_in_one_launch_and_in_three(blocks, c):
+    rng = np.random.default_rng(blocks + c)
+    for n in (1024 * blocks, 1024 * blocks - 7):
+        x = (rng.standard_normal((n, c, 4), dtype=np.float32) * 3 + 1).astype(np.float32)
+        want_m, want_v = oracle.bn_batch_stats(x)
+        got_m, got_v = gpu_bn(x)
+        assert np.array_equal(bits(got_m), bits(want_m)) and np.array_equal(bits(got_v), bits(want_v)), n
