@@ -709,6 +709,8 @@ int es_set_streams(es_handle* h, void* main, void* ctx, void* stage)
     h->s_main = (hipStream_t)main;
     h->s_ctx = (hipStream_t)ctx;
     h->s_stage = (hipStream_t)stage;
+    h->main_recorded = false;                   // what stage_after_main has learned is of the streams before
+    h->main_busy = h->main_skip = 0;
     return ES_OK;
 }
 

@@ -65,6 +65,14 @@ int main()
         g_capturing = 0;
         CHECK(hand_offs(j, 1) == 0 && g_asked_idle == 1 && g_asked_done == 0);
     }
+    // another main: what was learned of the one before says nothing, and its event is not asked
+    g_idle = false;
+    CHECK(hand_offs(j, 100) == 100);
+    CHECK(es_set_streams(j.h, (void*)48, (void*)48, (void*)32) == ES_OK);
+    g_idle = true;
+    g_asked_idle = g_asked_done = 0;
+    CHECK(hand_offs(j, 1) == 0 && g_asked_idle == 1 && g_asked_done == 0);
+    CHECK(hand_offs(j, 20) == 0 && g_asked_idle == 21);
     // one stream for both: neither
     CHECK(es_set_streams(j.h, (void*)16, (void*)16, (void*)16) == ES_OK);
     g_asked_idle = 0;
