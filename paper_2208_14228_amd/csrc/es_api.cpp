@@ -77,7 +77,7 @@ struct es_handle {
     hipStream_t s_main = nullptr, s_ctx = nullptr, s_stage = nullptr;
     hipEvent_t ev_main = nullptr, ev_ctx = nullptr, ev_stage = nullptr;
     bool stage_pending = false;                 // staging copies enqueued since the last fence
-    bool main_recorded = false;                 // stage_after_main has recorded ev_main, and not into a capture
+    bool main_recorded = false;                 // ev_main has been recorded on this main, and not into a capture
     uint32_t main_busy = 0, main_skip = 0;      // see stage_after_main
 
     // one pass per workgroup: 256 lanes x 2 vectors x 4 floats (measured best on MI355X)
@@ -396,6 +396,14 @@ int order_after(es_handle* h, hipStream_t to, hipStream_t from, hipEvent_t ev)
     return ES_OK;
 }
 
+// `to` behind what main has been given so far.
+int after_main(es_handle* h, hipStream_t to)
+{
+    if (to == h->s_main) return ES_OK;
+    h->main_recorded = stream_probe.idle && !stream_captured(h->s_main);   // no event of a capture is asked later
+    return order_after(h, to, h->s_main, h->ev_main);
+}
+
 // Staging behind what main has been given so far, which has produced the gradients.
 //
 // By an event that is 11 us of the host's time, launch of the copy included (the runtime waits for the event's signal to come
@@ -410,9 +418,7 @@ int stage_after_main(es_handle* h)
 {
     if (h->s_stage == h->s_main) return ES_OK;
     const StreamProbe& probe = stream_probe;
-    if (!probe.idle || stream_captured(h->s_main) || stream_captured(h->s_stage)) {
-        h->main_recorded = false;                // no event of a capture is asked
-    } else {
+    if (probe.idle && !stream_captured(h->s_main) && !stream_captured(h->s_stage)) {
         if (h->main_skip) {
             --h->main_skip;
         } else if (!h->main_recorded || probe.done(h->ev_main)) {
@@ -424,9 +430,8 @@ int stage_after_main(es_handle* h)
             h->main_busy = std::min(h->main_busy + 2, 6u);
             h->main_skip = (1u << h->main_busy) - 1;
         }
-        h->main_recorded = true;
     }
-    return order_after(h, h->s_stage, h->s_main, h->ev_main);
+    return after_main(h, h->s_stage);
 }
 
 int sync_all(es_handle* h)
@@ -569,7 +574,7 @@ int swap_reduce(es_handle* h, float* avg, float* p, float* v, float lr, float mu
     const size_t nb = h->buckets.size();
     // the copy queue starts after every staging copy of the step and after main (in-place sources)
     if ((rc = order_after(h, h->s_swap, h->s_stage, h->ev_stage)) != ES_OK) return rc;
-    if ((rc = order_after(h, h->s_swap, h->s_main, h->ev_main)) != ES_OK) return rc;
+    if ((rc = after_main(h, h->s_swap)) != ES_OK) return rc;
     h->stage_pending = false;
     std::vector<const float*> in_place(h->N, nullptr);
     for (size_t k = 0; k < h->in_place_rank.size(); ++k) in_place[h->in_place_rank[k]] = h->in_place_ptr[k];
@@ -856,7 +861,7 @@ int es_ctx_restore(es_handle* h, uint32_t est)
     DeviceGuard guard__(h);
     if (h->seg_bytes.empty()) return ES_OK;
     const Worker& w = h->workers[h->worker_of[est]];
-    if ((rc = order_after(h, h->s_ctx, h->s_main, h->ev_main)) != ES_OK) return rc;
+    if ((rc = after_main(h, h->s_ctx)) != ES_OK) return rc;
     ES_HIP(h, launch_ctx(h->s_ctx, w.d_pieces, w.n_pieces, ctx_base(h, est), nullptr, kRestore));
     return order_after(h, h->s_main, h->s_ctx, h->ev_ctx);
 }
@@ -868,7 +873,7 @@ int es_ctx_save(es_handle* h, uint32_t est)
     DeviceGuard guard__(h);
     if (h->seg_bytes.empty()) return ES_OK;
     const Worker& w = h->workers[h->worker_of[est]];
-    if ((rc = order_after(h, h->s_ctx, h->s_main, h->ev_main)) != ES_OK) return rc;
+    if ((rc = after_main(h, h->s_ctx)) != ES_OK) return rc;
     ES_HIP(h, launch_ctx(h->s_ctx, w.d_pieces, w.n_pieces, ctx_base(h, est), nullptr, kSave));
     return ES_OK;
 }
@@ -881,7 +886,7 @@ int es_ctx_switch(es_handle* h, uint32_t est_out, uint32_t est_in)
     if (h->seg_bytes.empty()) return ES_OK;
     const Worker& w = h->workers[h->worker_of[est_out]];
     if (!w.bound) return ES_ESTATE;
-    int rc = order_after(h, h->s_ctx, h->s_main, h->ev_main);
+    int rc = after_main(h, h->s_ctx);
     if (rc != ES_OK) return rc;
     ES_HIP(h, launch_ctx(h->s_ctx, w.d_pieces, w.n_pieces, ctx_base(h, est_out), ctx_base(h, est_in), kSwitch));
     return order_after(h, h->s_main, h->s_ctx, h->ev_ctx);
@@ -1114,7 +1119,7 @@ try {
         }
         mark_batch(h, est_out, n, buckets);
         if (n_pieces) {
-            if ((rc = order_after(h, h->s_ctx, h->s_main, h->ev_main)) != ES_OK) return rc;
+            if ((rc = after_main(h, h->s_ctx)) != ES_OK) return rc;
             ES_HIP(h, launch_ctx(h->s_ctx, w.d_pieces, n_pieces, ctx_base(h, est_out),
                                  has_in ? ctx_base(h, est_in) : nullptr, has_in ? kSwitch : kSave));
             if (has_in && (rc = order_after(h, h->s_main, h->s_ctx, h->ev_ctx)) != ES_OK) return rc;

@@ -29,6 +29,43 @@ static int hand_offs(Job& j, int n)
     return g_records - before;
 }
 
+// The calls beside staging record the same event on main: into a capture it is not asked afterwards, else it is.
+static int other_calls()
+{
+    const uint64_t seg = 16;
+    es_bucket b[2] = {{0, 64}, {64, 64}};
+    es_bucket_layout lay = {128, 2, b, 4, 1, &seg, dev_alloc, dev_free, nullptr};
+    es_handle* h = nullptr;
+    alignas(16) static uint64_t live[2];
+    alignas(16) static float g[128];
+    void* ptrs[1] = {live};
+    const uint32_t ids[2] = {0, 1};
+    const float* grads[2] = {g, g + 64};
+    CHECK(es_init(&h, 2, &lay) == ES_OK && es_bind_live_state(h, 0, ptrs) == ES_OK);
+    CHECK(es_set_streams(h, (void*)48, (void*)64, (void*)32) == ES_OK);
+    g_idle = false;
+    for (int call = 0; call < 4; ++call)
+        for (int c : {0, 1, -1}) {
+            // a record outside any capture, by staging, and the ladder back at its start
+            CHECK(es_set_streams(h, (void*)48, (void*)64, (void*)32) == ES_OK);
+            CHECK(es_accumulate(h, 0, 0, g) == ES_OK && es_accumulate(h, 0, 1, g + 64) == ES_OK);
+            for (int k = 0; k < 2; ++k) CHECK(es_accumulate(h, 1, k, g + 64 * k) == ES_OK);
+            CHECK(es_ring_order_reduce(h, g) == ES_OK);
+            g_capturing = c;
+            if (call == 0) CHECK(es_ctx_restore(h, 0) == ES_OK);
+            if (call == 1) CHECK(es_ctx_save(h, 0) == ES_OK);
+            if (call == 2) CHECK(es_ctx_switch(h, 0, 1) == ES_OK);
+            if (call == 3) CHECK(es_est_boundary(h, 0, 1, 0, nullptr, nullptr) == ES_OK);
+            g_capturing = 0;
+            g_asked_done = g_asked_idle = 0;
+            CHECK(es_accumulate_batch(h, 0, 2, ids, grads) == ES_OK);
+            CHECK(g_asked_done == (c == 0) && g_asked_idle == 1);
+            for (int k = 0; k < 2; ++k) CHECK(es_accumulate(h, 1, k, g + 64 * k) == ES_OK);
+            CHECK(es_ring_order_reduce(h, g) == ES_OK);
+        }
+    return es_destroy(h) == ES_OK ? 0 : 1;
+}
+
 int main()
 {
     Job j(1, 4096);
@@ -73,6 +110,7 @@ int main()
     g_asked_idle = g_asked_done = 0;
     CHECK(hand_offs(j, 1) == 0 && g_asked_idle == 1 && g_asked_done == 0);
     CHECK(hand_offs(j, 20) == 0 && g_asked_idle == 21);
+    if (other_calls() != 0) return 1;
     // one stream for both: neither
     CHECK(es_set_streams(j.h, (void*)16, (void*)16, (void*)16) == ES_OK);
     g_asked_idle = 0;
