@@ -2075,11 +2075,9 @@ static hipError_t launch_bn_shared(hipStream_t s, const float* x, const BnGeom& 
 // their way; three launches.  (A read that hits the Infinity Cache is no faster than one that does not.)
 // Beyond that: one partial per block, and a launch after each pass that combines them.
 template <bool SQDEV, bool WIDE, int MODE, typename OFF>
-__global__ __launch_bounds__(kBlock) void k_bn_partials(const float* __restrict__ x, ES_BN_GEOM_PARAMS, uint32_t groups,
-                                                        float* __restrict__ mean, float* __restrict__ part)
+__device__ __forceinline__ void bn_partials(const float* __restrict__ x, const BnGeom& g, uint32_t groups, float fM,
+                                            float* __restrict__ mean, float* __restrict__ part)
 {
-    const BnGeom g = ES_BN_GEOM;
-    const float fM = (float)M;
     const uint32_t h = threadIdx.x & 63;
     const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t bx = SQDEV ? groups - 1 - blockIdx.x : blockIdx.x;
@@ -2111,6 +2109,43 @@ __global__ __launch_bounds__(kBlock) void k_bn_partials(const float* __restrict_
         const float r = bn_block_sum<SQDEV>(t, blk, h, g.M, center);
         if (h == 0) part[(uint64_t)ch * g.nblk + blk] = r;
     }
+}
+
+template <bool SQDEV, bool WIDE, int MODE, typename OFF>
+__global__ __launch_bounds__(kBlock) void k_bn_partials(const float* __restrict__ x, ES_BN_GEOM_PARAMS, uint32_t groups,
+                                                        float* __restrict__ mean, float* __restrict__ part)
+{
+    bn_partials<SQDEV, WIDE, MODE, OFF>(x, ES_BN_GEOM, groups, (float)M, mean, part);
+}
+
+// The same for images of up to kBnFetchedHW positions that are no vector, whose lines of memory are shared by many waves that run
+// at about the same time, with its arguments in a structure: fetched by each wave, not in registers when it starts.  The wait
+// costs a launch 0.15 us, but without it the layers take longer; the fetch is the only difference in the code, so it is when
+// the waves reach their loads.  All launches of a layer, arguments in registers and so: 64 channels of 30 blocks of 1, 2, 3
+// positions 75.8 / 73.7, 63.2 / 59.9 and 67.6 / 66.5 us, 256 of them 430 / 396, 324 / 294 and 334 / 309, 256 of 64 blocks 758 / 677,
+// 672 / 572 and 587 / 536, of 64 blocks of 5 positions 275 / 266; 8 channels of 30 blocks 20.1 / 20.3.  7 and 9 positions: 25.0 / 25.4
+// and 24.9 / 25.3 (64 channels of 30 blocks), 190.4 / 190.1 and 176.5 / 176.4 (256 of 64), so those have them in registers.
+constexpr uint32_t kBnFetchedHW = 6;
+
+template <bool SQDEV, bool WIDE, int MODE, typename OFF>
+__global__ __launch_bounds__(kBlock) void k_bn_partials_fetched(const float* __restrict__ x, const BnGeom g, uint32_t groups,
+                                                               float fM, float* __restrict__ mean, float* __restrict__ part)
+{
+    bn_partials<SQDEV, WIDE, MODE, OFF>(x, g, groups, fM, mean, part);
+}
+
+template <bool SQDEV, bool WIDE, int MODE, typename OFF>
+static hipError_t launch_bn_partials(hipStream_t s, dim3 grid, const float* x, const BnGeom& g, float fM, float* mean, float* part)
+{
+    if constexpr (MODE == kBnWrap || MODE == kBnAny) {
+        if (g.HW <= kBnFetchedHW) {
+            ES_RUN((k_bn_partials_fetched<SQDEV, WIDE, MODE, OFF>), grid, dim3(kBlock), 0, s, x, g, grid.x, fM, mean, part);
+            return hipSuccess;
+        }
+    }
+    if constexpr (MODE != kBnAny)
+        ES_RUN((k_bn_partials<SQDEV, WIDE, MODE, OFF>), grid, dim3(kBlock), 0, s, x, ES_BN_GEOM_ARGS(g), grid.x, mean, part);
+    return hipSuccess;
 }
 
 // out[ch] = the tree over the last `n` <= 64 sums of channel ch / M; one wave per channel.
@@ -2164,6 +2199,7 @@ static hipError_t launch_bn(hipStream_t s, const float* x, const BnGeom& g, floa
                         : g.HW < 8 ? g.nblk >= 8 && g.C <= 128
                                    : g.HW < 16 && g.nblk > 12 && g.C <= 64;
     bool captured = false;
+    hipError_t e;
     if (g.nblk == 1) {                                  // at most 65,535 x 4096 values: 32-bit offsets always
         ES_RUN((k_bn_channel<MODE, uint32_t, kBnSingle>), dim3((g.C + kBnSingles - 1) / kBnSingles),
                            dim3(64 * kBnSingles), 0, s, x, mean, var, ES_BN_GEOM_ARGS(g));
@@ -2189,15 +2225,15 @@ static hipError_t launch_bn(hipStream_t s, const float* x, const BnGeom& g, floa
         uint32_t n = 4;                                 // sums per channel: a quarter of the blocks' power of two
         while (4 * n < g.nblk) n *= 2;
         const dim3 grid(n, g.C);
-        ES_RUN((k_bn_partials<false, true, MODE, OFF>), grid, dim3(kBlock), 0, s, x, ES_BN_GEOM_ARGS(g), grid.x, mean, part);
-        ES_RUN((k_bn_partials<true, true, MODE, OFF>), grid, dim3(kBlock), 0, s, x, ES_BN_GEOM_ARGS(g), grid.x, mean, part);
+        if ((e = launch_bn_partials<false, true, MODE, OFF>(s, grid, x, g, fM, mean, part)) != hipSuccess) return e;
+        if ((e = launch_bn_partials<true, true, MODE, OFF>(s, grid, x, g, fM, mean, part)) != hipSuccess) return e;
         ES_RUN(k_bn_final_wave, dim3((g.C + 3) / 4), dim3(kBlock), 0, s, part + (uint64_t)g.C * n, n, g.C,
                            fM, var);
     } else {
         const dim3 grid((g.nblk + 3) / 4, g.C);
-        ES_RUN((k_bn_partials<false, false, MODE, OFF>), grid, dim3(kBlock), 0, s, x, ES_BN_GEOM_ARGS(g), grid.x, mean, part);
+        if ((e = launch_bn_partials<false, false, MODE, OFF>(s, grid, x, g, fM, mean, part)) != hipSuccess) return e;
         ES_RUN(k_bn_final, dim3(g.C), dim3(kBlock), 0, s, part, g.nblk, fM, mean);
-        ES_RUN((k_bn_partials<true, false, MODE, OFF>), grid, dim3(kBlock), 0, s, x, ES_BN_GEOM_ARGS(g), grid.x, mean, part);
+        if ((e = launch_bn_partials<true, false, MODE, OFF>(s, grid, x, g, fM, mean, part)) != hipSuccess) return e;
         ES_RUN(k_bn_final, dim3(g.C), dim3(kBlock), 0, s, part, g.nblk, fM, var);
     }
     return hipSuccess;

@@ -74,6 +74,8 @@ def test_infinities_and_nan_stay_in_their_channel(HW):
     # short ragged images and images below four positions: up to 16 blocks, up to 25, up to 256, more
     (600, 40_000, 49), (1_700, 13_000, 49), (3_000, 7_400, 49), (25_000, 900, 49),
     (20_000, 20_000, 3), (30_000, 12_000, 3), (50_000, 7_200, 3), (400_000, 900, 3),
+    # short ragged images read in single loads
+    (9_000, 17_100, 7), (14_000, 11_000, 7), (40_000, 3_900, 7), (200_000, 780, 7), (50_000, 4_400, 5), (250_000, 880, 5),
     # long images and whole vectors in the forms not reached above
     (100, 12_000, 901), (1_200, 1_000, 901), (100, 12_000, 900), (1_200, 1_000, 900)])
 def test_offsets_beyond_32_bits(Bn, C, HW):
