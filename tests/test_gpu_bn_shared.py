@@ -77,8 +77,11 @@ def test_many_channels(shape):
     c.check()
 
 
-def test_launches_in_flight_together():
-    cases = [Case(26, 40 + k, 4096 + 4 * k, seed=k) for k in range(3)] + [Case(33, 30 + k, 4097, seed=k) for k in range(3)]
+# up to 1,500 blocks workgroups of eight waves, beyond of four; ragged long images are the second of each pair
+@pytest.mark.parametrize("whole,ragged", [(40, 30), (60, 50)])
+def test_launches_in_flight_together(whole, ragged):
+    cases = ([Case(26, whole + k, 4096 + 4 * k, seed=k) for k in range(3)]
+             + [Case(33, ragged + k, 4097, seed=k) for k in range(3)])
     streams = [torch.cuda.Stream(DEV) for _ in range(3)]
     for _ in range(3):
         for k, c in enumerate(cases):
@@ -101,8 +104,10 @@ def test_workgroups_that_do_not_wait(shape, polls):
         c.check(k)
 
 
-# little work (another form where it is captured) and more, on both sides of the lines between them
-@pytest.mark.parametrize("shape", [(26, 4, BLK), (26, 38, BLK), (26, 39, BLK), (130, 9, BLK + 1), (130, 10, BLK + 1)])
+# little work (another form where it is captured) and more (workgroups of eight waves, beyond 1,500 blocks of four), on both
+# sides of the lines between them, and much
+@pytest.mark.parametrize("shape", [(26, 4, BLK), (26, 38, BLK), (26, 39, BLK), (130, 9, BLK + 1), (130, 10, BLK + 1), (26, 57, BLK),
+                                   (26, 58, BLK), (130, 11, BLK + 1), (130, 12, BLK + 1), (32, 64, 12544)])
 def test_captured_launches_replayed(shape):
     c = Case(*shape)
     s = torch.cuda.Stream(DEV)
