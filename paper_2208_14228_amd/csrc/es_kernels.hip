@@ -2292,9 +2292,9 @@ struct RelaxedCapture {
 
 bool answered_yes(hipError_t e)
 {
-    if (e == hipSuccess) return true;
-    (void)hipGetLastError();
-    return false;
+    // "Not ready" is no error to the runtime: it leaves the thread's last one as it is, which may be another library's.
+    if (e != hipSuccess && e != hipErrorNotReady) (void)hipGetLastError();
+    return e == hipSuccess;
 }
 
 // Only of streams that are not ordered with the null stream: an idle one of the others may still have to wait for it.

@@ -166,3 +166,33 @@ def test_first_staging_call_asks_main(writer, entry, busy, answers):
     slot = job.memory.blocks[B.es_grad_slot(job.h, 0, 0)].view(torch.float32)[:P]
     assert torch.equal(slot, new) and torch.equal(job.avg, new)
     job.close()
+
+
+@pytest.mark.gpu
+def test_an_error_of_somebody_else_stays(answers):
+    """Main and the event on it are asked while they work, which is answered with a status that is no error: an error that
+    another library has left in this thread is still there afterwards."""
+    hip = ctypes.CDLL([line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line][0])
+    P = 1 << 16
+    job = ESTJob(6, P, [(0, P)], 4, use_streams="two")
+    g = torch.ones(P, device=DEV)
+    slow = torch.zeros(1 << 27, device=DEV)
+    for e in range(6):                                  # loads the kernels
+        B.check(B.es_accumulate(job.h, e, 0, g.data_ptr()), "es_accumulate", job.h)
+    job.ring_order_reduce()
+    B.check(B.es_set_streams(job.h, *(s.cuda_stream for s in (job.main, job.ctx, job.stage))), "es_set_streams", job.h)
+    torch.cuda.synchronize()
+    answers.clear()
+    with torch.cuda.stream(job.main):
+        keep_busy(slow)
+    left = hip.hipSetDevice(9999)
+    status = [B.es_accumulate(job.h, e, 0, g.data_ptr()) for e in range(6)]
+    still = hip.hipGetLastError()
+    assert status == [B.ES_OK] * 6 and left != 0
+    assert answers == [("idle", False), ("done", False), ("done", False)]
+    assert still == left
+    job.ring_order_reduce()
+    job.sync()
+    torch.cuda.synchronize()
+    assert bool((job.avg == 1.0).all())
+    job.close()
