@@ -131,8 +131,9 @@ int es_destroy(es_handle* h);
  * work already enqueued on main and is visible to work enqueued on main
  * afterwards; a save or an accumulate starts after the work already enqueued
  * on main; the reduce starts after every accumulate of the step.  If all three
- * are the same stream no events are used, nor for an accumulate when main (a
- * non-blocking stream) has nothing left to do.  Must not be called while work of
+ * are the same stream no events are used.  An accumulate may go without one
+ * where main, a non-blocking stream, is found to have nothing left to do; do not
+ * rely on either.  Must not be called while work of
  * this handle is in flight (call es_sync first).  The streams stay the
  * caller's; they must exist until es_destroy (which waits on them) or until
  * another es_set_streams replaces them.
