@@ -1662,8 +1662,8 @@ __device__ __forceinline__ void bn_load(const float* __restrict__ x, const BnGeo
             else if (__any(pos + 3 >= g.HW || m + 3 >= g.M)) singles();
             else e = *reinterpret_cast<const f4_dword_aligned*>(xb + off);
         } else {
-            // the whole wave is beyond M: no loads (four of them cost more than this branch: 8.0 -> 7.1 us
-            // on 32x2048x7x7; the one load of kBnVector does not: 10.8 -> 11.5 us on 32x512x28x28)
+            // the whole wave is beyond M: no loads (four of them can cost more than this branch: 500x256x3 4.9 -> 3.9 us,
+            // 1000x256x7 4.8 -> 4.5, but 1600x256x3 5.4 -> 5.7; the one load of kBnVector does not: 32x512x28x28 8.9 -> 9.8)
             if (blk * 4096u + 256u * i < g.M) singles();
             else e = f4{0.0f, 0.0f, 0.0f, 0.0f};
         }
@@ -1744,7 +1744,9 @@ enum { kBnSingle = 0, kBnRegs = 1, kBnParked = 2 };
 // workgroups run.  Channels that follow each other share lines of memory: always where an image's positions fill less
 // than a line, at both ends otherwise.  In the order of dispatch every die that has one of them fetches the line.  So, against
 // that: 900x2048x5 56.4 -> 16.2 us, 512x1024x9 17.4 -> 8.0, 256x2048x25 20.2 -> 15.7, 128x512x7x7 6.03 -> 5.56, 32x512x14x14 4.39 ->
-// 3.77; where images are whole lines (32x512x28x28 9.21 -> 8.93, 64x256x56x56) nothing is lost.
+// 3.77; where images are whole lines (32x512x28x28 9.21 -> 8.93, 64x256x56x56) nothing is lost.  Long channels of images of
+// one position lose, where they are many: 25 blocks, 160, 256, 300, 512 and 1,000 channels 140 -> 125, 221 -> 244, 320 -> 285,
+// 412 -> 417 and 674 -> 705.
 __device__ __forceinline__ uint32_t die_contiguous(uint32_t b, uint32_t n)
 {
     const uint32_t die = b & 7, each = n >> 3, more = n & 7;
@@ -2118,13 +2120,14 @@ __global__ __launch_bounds__(kBlock) void k_bn_partials(const float* __restrict_
     bn_partials<SQDEV, WIDE, MODE, OFF>(x, ES_BN_GEOM, groups, (float)M, mean, part);
 }
 
-// The same for images of up to kBnFetchedHW positions that are no vector, whose lines of memory are shared by many waves that run
-// at about the same time, with its arguments in a structure: fetched by each wave, not in registers when it starts.  The wait
-// costs a launch 0.15 us, but without it the layers take longer; the fetch is the only difference in the code, so it is when
-// the waves reach their loads.  All launches of a layer, arguments in registers and so: 64 channels of 30 blocks of 1, 2, 3
-// positions 75.8 / 73.7, 63.2 / 59.9 and 67.6 / 66.5 us, 256 of them 430 / 396, 324 / 294 and 334 / 309, 256 of 64 blocks 758 / 677,
-// 672 / 572 and 587 / 536, of 64 blocks of 5 positions 275 / 266; 8 channels of 30 blocks 20.1 / 20.3.  7 and 9 positions: 25.0 / 25.4
-// and 24.9 / 25.3 (64 channels of 30 blocks), 190.4 / 190.1 and 176.5 / 176.4 (256 of 64), so those have them in registers.
+// The same for images of up to kBnFetchedHW positions that are no vector, whose lines of memory are shared by many waves that
+// run at about the same time, with its arguments in a structure: fetched by each wave, not in registers when it starts.  The
+// wait costs a launch 0.15 us, but without it the layers take longer; the fetch is the only difference in the code, so it is
+// when the waves reach their loads.  All launches of a layer, arguments in registers and so: 64 channels of 30 blocks of 1,
+// 2, 3 positions 75.8 / 73.7, 63.2 / 59.9 and 67.6 / 66.5 us, 256 of them 430 / 396, 324 / 294 and 334 / 309, 256 of 64
+// blocks 758 / 677, 672 / 572 and 587 / 536, of 64 blocks of 5 positions 275 / 266; 8 channels of 30 blocks 20.1 / 20.3.  7
+// and 9 positions: 25.0 / 25.4 and 24.9 / 25.3 (64 channels of 30 blocks), 190.4 / 190.1 and 176.5 / 176.4 (256 of 64), so
+// those have them in registers.
 constexpr uint32_t kBnFetchedHW = 6;
 
 template <bool SQDEV, bool WIDE, int MODE, typename OFF>
@@ -2168,11 +2171,17 @@ __global__ __launch_bounds__(kBlock) void k_bn_final(const float* __restrict__ p
     if (threadIdx.x == 0) out[blockIdx.x] = s / fM;
 }
 
-// Whether several workgroups share a channel (k_bn_shared).  Up to 25 blocks one workgroup is 1.2-1.5 times as
-// fast, and images so short that they are read in single loads keep the forms below.  Captured, with the
-// clearing launch before it, little work takes longer so: 26 blocks 7.2 -> 10.4 us for 4 channels (0.4 MB each), 9.1
-// -> 9.6 for 20, 11.9 -> 10.7 for 40; 120 blocks 11.1 -> 11.3 for 8, 12.3 -> 12.2 for 10; 240 blocks 12.1 -> 12.7 for 5.
-// Enqueued, with no other launch than itself, it is ahead everywhere (1 to 8 channels of 26 to 1,000 blocks 1.2-1.5).
+// Whether several workgroups share a channel (k_bn_shared).  Up to 25 blocks one workgroup is 1.2-1.5 times as fast.  Images
+// of up to 127 positions that are no whole vectors keep the forms below because they were read in single loads when the line
+// was drawn.  It has not been moved since they are read as vectors (from 10 positions on), though three launches and a shared
+// channel now take, for 64 channels of 30 blocks of 17, 49 and 121 positions, 17.8 / 14.2, 15.5 / 12.4 and 14.9 / 10.9 us,
+// for 16 of 300 blocks 66 / 21, 42 / 19 and 36 / 19, for 200 of 26 blocks 42 / 41, 33 / 27 and 33 / 23. Captured, with the
+// clearing launch before it, little work takes longer so.  The line was drawn with workgroups of four waves (26 blocks: 4
+// channels 7.2 in three launches and 10.4 us so, 20 channels 9.1 / 9.6, 40 11.9 / 10.7; 120 blocks: 8 channels 11.1 / 11.3,
+// 10 12.3 / 12.2).  With those of eight, which work below it now has, the two meet earlier: 26 blocks: 3 channels 7.0 / 8.0,
+// 19 8.5 / 8.1, 34 10.7 / 9.2; 64 blocks: 4 channels 7.3 / 8.3, 7 8.4 / 8.3, 14 10.2 / 9.5; 120 blocks: 4 channels 8.4 / 8.4,
+// 8 10.3 / 9.9; 240 blocks: 4 channels 10.3 / 10.7, 5 11.6 / 10.8.  Enqueued, with no other launch than itself, it is ahead
+// everywhere (1 to 8 channels of 26 to 1,000 blocks 1.2-1.5).
 template <int MODE>
 static bool bn_shares(const BnGeom& g, hipStream_t s, bool& captured)
 {
@@ -2186,15 +2195,19 @@ template <int MODE, typename OFF>
 static hipError_t launch_bn(hipStream_t s, const float* x, const BnGeom& g, float* mean, float* var, float* part, uint32_t polls)
 {
     const float fM = (float)g.M;
-    // Few channels of many tiny images (a line of memory holds an image's few values of a channel, the rest
-    // belongs to others): a channel's loads queue in the L1 of the one CU that has it, and most CUs have
-    // none.  Three launches spread a channel over several workgroups instead.  16 blocks in one launch and in
-    // three: 16 channels of 1, 3, 5 and 7 positions 59 / 31, 64 / 30, 36 / 16 and 27 / 16 us, 64 channels 72 / 44, 63 / 38, 33 / 19 and
-    // 24 / 16; 160 channels take one launch.  Vectors of one image each (4 positions) need
-    // it least: 40 channels of 10, 12 and 16 blocks 16.0 / 13.3, 18.8 / 13.5 and 24.3 / 15.9 us, 64 channels of 8, 10, 14 and 16 blocks
-    // 6.3 / 12.9, 7.6 / 15.9, 16.2 / 18.4 and 21.9 / 19.6, 96 channels of 10 and 25 blocks 14.9 / 23.0 and 35 / 37, 160 of 16 24.9 / 43.4.  8 and 12
-    // positions: 16 blocks, 64 channels 13.8 / 17.3 and 13.0 / 16.1, but 24 blocks 21 / 17 and 18.5 / 13.9, 16 channels of 12
-    // positions 15 / 10; from 16 positions on one launch is everywhere as fast as two per pass.
+    // Few channels of many tiny images (a line of memory holds an image's few values of a channel, the rest belongs to
+    // others): a channel's loads queue in the L1 of the one CU that has it, and most CUs have none.  Three launches spread a
+    // channel over several workgroups instead.  16 blocks in one launch and in three: 16 channels of 1, 3, 5 and 7 positions
+    // 59 / 31, 64 / 30, 36 / 16 and 27 / 16 us, 64 channels 72 / 44, 63 / 38, 33 / 19 and 24 / 16; 160 channels take one
+    // launch.  Vectors of one image each (4 positions) need it least: 40 channels of 10, 12 and 16 blocks 16.0 / 13.3, 18.8 /
+    // 13.5 and 24.3 / 15.9 us, 64 channels of 8, 10, 14 and 16 blocks 6.3 / 12.9, 7.6 / 15.9, 16.2 / 18.4 and 21.9 / 19.6, 96
+    // channels of 10 and 25 blocks 14.9 / 23.0 and 35 / 37, 160 of 16 24.9 / 43.4. 8 to 15 positions, 16 and 64 channels: 10
+    // blocks of 9 positions 12.4 / 11.6 and 16.1 / 13.6, of 15 6.7 / 10.0 and 12.5 / 12.4, 14 blocks of 9 18.4 / 14.1 and
+    // 21.6 / 16.0, of 13 13.7 / 11.4 and 17.7 / 15.5, 25 of 11 27 / 11 and 33 / 19; 96 channels of 14 blocks of 9 and 13 26.3
+    // / 26.0 and 17.9 / 23.8.  The line is theirs.  Whole vectors share it, though they change sides with the number of
+    // channels: 16 blocks of 8 positions, 16, 32, 48 and 64 channels 6.5 / 11.9, 6.4 / 13.9, 15.2 / 13.2 and 13.5 / 17.1, of
+    // 12 15.2 / 9.8, 11.4 / 11.0, 15.6 / 12.6 and 13.1 / 16.0; 25 blocks of 8 22 / 11, 21 / 13, 22 / 17 and 24 / 19, of 12 23
+    // / 10, 17 / 11, 23 / 14 and 20 / 16.  From 16 positions on one launch is everywhere as fast as two per pass.
     const bool spread = g.HW == 4  ? (g.nblk > 14 ? g.C <= 64 : g.nblk > 9 && g.C <= 48)
                         : g.HW < 8 ? g.nblk >= 8 && g.C <= 128
                                    : g.HW < 16 && g.nblk > 12 && g.C <= 64;

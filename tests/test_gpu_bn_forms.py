@@ -43,7 +43,8 @@ def test_every_form_at_its_edges(Bn, HW):
             assert np.array_equal(bits(got_v), bits(want_v)), ("var", C, shift)
 
 
-@pytest.mark.parametrize("Bn,C,HW", [(7_373, 128, 5), (7_373, 129, 5), (9_300, 255, 4), (9_300, 256, 4), (4_800, 64, 12), (4_800, 65, 12)])
+@pytest.mark.parametrize("Bn,C,HW", [(7_373, 128, 5), (7_373, 129, 5), (9_300, 48, 4), (9_300, 49, 4),
+                                      (15_000, 64, 4), (15_000, 65, 4), (4_800, 64, 12), (4_800, 65, 12)])
 def test_both_sides_of_the_channel_lines_for_tiny_images(Bn, C, HW):
     rng = np.random.default_rng(C)
     x = (rng.standard_normal((Bn, C, HW), dtype=np.float32) * 3 + 1).astype(np.float32)
